@@ -304,42 +304,9 @@ __device__ __forceinline__ Ent comp_ent(const float4 *__restrict__ ents, int i)
     return ent_from(ents[EW * i], ents[EW * i + 1], ents[EW * i + 2], ents[EW * i + 3]);
 }
 
-// Cone of a wave's rays: unit centre direction (uniform over the wave) and the cosine of the
-// largest angle between it and a ray of the wave.
-struct TileCone {
-    float c0, c1, c2, ca;
-};
-
-__device__ __forceinline__ float wave_sum_f(float x)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
-}
-
-__device__ __forceinline__ TileCone comp_cone(float v0, float v1, float v2, bool valid)
-{
-    float c0 = wave_sum_f(valid ? v0 : 0.0f), c1 = wave_sum_f(valid ? v1 : 0.0f), c2 = wave_sum_f(valid ? v2 : 0.0f);
-    c0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c0)));
-    c1 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c1)));
-    c2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c2)));
-    const float inv = rsq_(fmaf(c0, c0, fmaf(c1, c1, fmaf(c2, c2, kEpsN))));
-    TileCone tc;
-    tc.c0 = c0 * inv;
-    tc.c1 = c1 * inv;
-    tc.c2 = c2 * inv;
-    float ca = valid ? fmaf(tc.c0, v0, fmaf(tc.c1, v1, tc.c2 * v2)) : 1.0f;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ca = fminf(ca, __shfl_xor(ca, off, 64));
-    // margins for the rounding of the directions and of the cone
-    tc.ca = fminf(ca, 1.0f) - 1e-5f;
-    return tc;
-}
-
-// Staged Gaussians [0, cnt) whose log2 density can exceed thr on some ray of the cone (the bound of
-// tile_bounds from the cone's centre ray and radius), as two 64-bit masks (lane j tests Gaussians
-// j and 64 + j).
-__device__ __forceinline__ void comp_cull(const float4 *__restrict__ ents, int ew, int cnt, const TileCone &tc,
+// Staged Gaussians [0, cnt) whose log2 density can exceed thr on some ray of the tile (tile_bounds on
+// its box), as two 64-bit masks (lane j tests Gaussians j and 64 + j).
+__device__ __forceinline__ void comp_cull(const float4 *__restrict__ ents, int ew, int cnt, const TileBox &tb,
                                           float thr, unsigned long long mask[2])
 {
     static_assert(kCompTG == 128, "two 64-bit masks per staged tile");
@@ -349,12 +316,8 @@ __device__ __forceinline__ void comp_cull(const float4 *__restrict__ ents, int e
         bool keep = false;
         if (i < cnt) {
             const Ent g = ent_from(ents[ew * i], ents[ew * i + 1], ents[ew * i + 2], ents[ew * i + 3]);
-            // the largest distance of a unit ray direction of the cone from its centre: |v - c|^2 = 2 - 2 cos
-            const float rho = sqrtf(fmaxf(0.0f, 2.0f - 2.0f * tc.ca)) * (1.0f + 1e-4f) + 1e-6f;
-            float d2_hi, z_hi;
-            tile_bounds(g, ents[ew * i + kCompEst], make_float4(tc.c0, tc.c1, tc.c2, rho), (float)(-0.5 * kLog2e),
-                        0.0f, 0.0f, d2_hi, z_hi);
-            keep = !(d2_hi <= thr);  // (a NaN bound keeps the Gaussian)
+            const PairBounds pb = tile_bounds(g, ents[ew * i + kCompEst], tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
+            keep = !(pb.d2_hi <= thr);  // (a NaN bound keeps the Gaussian)
         }
         mask[c] = wave_ballot(keep);
     }
@@ -369,7 +332,7 @@ __device__ __forceinline__ void comp_cull(const float4 *__restrict__ ents, int e
 template <int EW, class OnTie>
 __device__ __forceinline__ int comp_collect(const Params &P, const SceneRec &sr, const double o[3],
                                             float4 *__restrict__ ents, bool resident, float v0, float v1,
-                                            float v2, float hm, float sig2, const TileCone &tc, CompWin &w,
+                                            float v2, float hm, float sig2, const TileBox &tc, CompWin &w,
                                             CompList &L, int *__restrict__ slot_g, OnTie on_tie)
 {
     int ns = 0;
@@ -489,7 +452,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
             at = O.alpha_t[vr.ray_off + loc];
             dt = O.depth_t[vr.ray_off + loc];
         }
-        const TileCone tc = comp_cone(v0, v1, v2, valid);
+        const TileBox tc = wave_box(v0, v1, v2, valid, e);
         float M, S, T, N0, N1, N2, C0, C1, C2, D;
         auto reset = [&]() {
             M = -INFINITY;
@@ -664,7 +627,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
         CompWin w = w0;
         CompList L;
         CompZ zs;
-        const TileCone tc = comp_cone(v0, v1, v2, valid);
+        const TileBox tc = wave_box(v0, v1, v2, valid, e);
 
         // z_bar of the slots' own pairs (the lanes' significant intersections of the window)
         auto slots_z = [&](int ns) {
@@ -984,7 +947,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves)
         const float wskip = valid ? M2 - __builtin_amdgcn_logf(invS) + skip2 : INFINITY;
         CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
         CompList L;
-        const TileCone tc = comp_cone(v0, v1, v2, valid);
+        const TileBox tc = wave_box(v0, v1, v2, valid, e);
         const auto no_tie = [](const Ent &, const Geo &, float, int) {};
         for (bool first = true;; first = false) {
             const int ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, no_tie);

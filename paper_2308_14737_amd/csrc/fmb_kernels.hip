@@ -31,7 +31,7 @@ namespace fmb {
 // ------------------------------------------------------------------------------------
 
 template <int BLOCK, int RPT, int TG, int F>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void fwd_kernel(Params P, FwdOut O, const FwdItem *__restrict__ items,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 ? 3 : 4))) void fwd_kernel(Params P, FwdOut O, const FwdItem *__restrict__ items,
                                                    int n_items, const int *__restrict__ order,
                                                    int *__restrict__ counter)
 {
@@ -39,13 +39,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     constexpr bool COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int EW = COLOR ? 6 : 5;  // float4 per LDS entry: the entry, the m estimate terms, colour
     __shared__ float4 tile[TG * EW];
-    // the first sweep's weight bound of each (Gaussian, ray tile) for the second sweep (-inf where
-    // the first sweep took the pair): per wave, per group of 64 / RPT Gaussians, per lane
-    __shared__ float zsave[BLOCK / 64][TG * RPT];
-    // scenes beyond BLOCK Gaussians: the item's tile cones, the waves' least running maxima and
-    // counts of survivors, and a round's survivors
-    __shared__ float4 icones[BIG ? BLOCK / 64 * RPT : 1];
-    __shared__ float wmin[BIG ? BLOCK / 64 : 1];
+    // the upper bounds (log2 density, log2 weight) of each staged (Gaussian, ray tile): per wave, per
+    // group of 64 / RPT Gaussians, per lane
+    __shared__ float2 hisave[BLOCK / 64][TG * RPT];
+    __shared__ float4 tbox[BLOCK / 64 * RPT * 3];  // each ray tile's box (TileBox)
+    // scenes beyond BLOCK Gaussians: the waves' least running maxima and density sums, their counts
+    // of survivors, and a round's survivors
+    __shared__ float2 wmin[BIG ? BLOCK / 64 : 1];
     __shared__ int wcnt[BIG ? BLOCK / 64 : 1];
     __shared__ int slist[BIG ? BLOCK : 1];
     __shared__ int s_item;
@@ -92,81 +92,62 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                 dt[j] = O.depth_t[vr.ray_off + lc];
             }
         }
-        // The cone of each of the wave's ray tiles (unit centre direction, largest |v - c|), for the
-        // bound of tile_bounds: lane l bounds Gaussian l / RPT on ray tile l % RPT (cl: its cone).
+        // The box of each of the wave's ray tiles, for the bounds of tile_bounds: lane l bounds Gaussian
+        // l / RPT on ray tile l % RPT.
         const int jl = lane % RPT;
-        float4 cl = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-            const bool ok = loc[j] >= 0;
-            float c0 = ok ? v0[j] : 0.0f, c1 = ok ? v1[j] : 0.0f, c2 = ok ? v2[j] : 0.0f;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                c0 += __shfl_xor(c0, off, 64);
-                c1 += __shfl_xor(c1, off, 64);
-                c2 += __shfl_xor(c2, off, 64);
+            const TileBox b = wave_box(v0[j], v1[j], v2[j], loc[j] >= 0, e);
+            if (lane == 0) {
+                tbox[3 * (wave * RPT + j)] = b.c;
+                tbox[3 * (wave * RPT + j) + 1] = b.x;
+                tbox[3 * (wave * RPT + j) + 2] = b.y;
             }
-            const float inv = rsq_(fmaf(c0, c0, fmaf(c1, c1, fmaf(c2, c2, kEpsN))));
-            c0 *= inv;
-            c1 *= inv;
-            c2 *= inv;
-            const float e0 = v0[j] - c0, e1 = v1[j] - c1, e2 = v2[j] - c2;
-            float rho = ok ? sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2))) : 0.0f;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) rho = fmaxf(rho, __shfl_xor(rho, off, 64));
-            if (jl == j) cl = make_float4(c0, c1, c2, rho * (1.0f + 1e-4f) + 1e-6f);
         }
+        const float g2n = ceil_log2(sr.n), wskip = fminf(kFwdSkipLog2, -kDensRelLog2 - g2n);
+        // lower bounds over lane's tile jl, from the Gaussians bounded so far: log2 of the density sum
+        // and the running maximum
+        float dlow = -INFINITY, mlow = -INFINITY;
 
         // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
-        // round is first bounded on a cone around all the item's tiles, and only those whose
-        // density can reach 2^kDensSkipLog2 there, or whose weight can be above FP32's zero
+        // round is first bounded on a box around all the item's tiles, and only those whose
+        // density can reach the cutoff there, or whose weight can be above 2^kFwdSkipLog2
         // against the least running maximum of the item's rays so far, are staged, in scene order
-        // (slist).  The running maxima only grow, so a Gaussian left out is one whose every pair
-        // the tests below would skip when its turn came: the sums are those of the full order.
+        // (slist).  The running maxima and density sums only grow, so a Gaussian left out is one that
+        // the tests below would skip when its turn came.
         // Smaller scenes take one round of all their Gaussians (and launches without kBig, whose
         // scenes are all small, have no such rounds).
         const bool sparse = BIG && sr.n > BLOCK;
-        if (sparse && lane < RPT) icones[wave * RPT + lane] = cl;
         for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
           int total = sr.n;
           if (sparse) {
-            float mm = INFINITY;
+            float mm = INFINITY, dm = INFINITY;
 #pragma unroll
-            for (int j = 0; j < RPT; ++j) mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) mm = fminf(mm, __shfl_xor(mm, off, 64));
+            for (int j = 0; j < RPT; ++j) {
+                mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
+                dm = loc[j] >= 0 ? fminf(dm, D[j]) : dm;
+            }
+            mm = wave_min_u(mm);
+            dm = wave_min_u(dm);
             __syncthreads();  // the previous round's list and staged tile are consumed
-            if (lane == 0) wmin[wave] = mm;
-            __syncthreads();  // tile cones and least maxima visible
-            float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, imin = INFINITY;
-            for (int t = 0; t < NW * RPT; ++t) {
-                s0 += icones[t].x;  // (a tile without a ray in the view has centre 0)
-                s1 += icones[t].y;
-                s2 += icones[t].z;
+            if (lane == 0) wmin[wave] = make_float2(mm, dm);
+            __syncthreads();  // tile boxes and least maxima visible
+            const TileBox ibox = wave_box_of(tbox, NW * RPT, lane, e);
+            float imin = INFINITY, idm = INFINITY;
+            for (int w = 0; w < NW; ++w) {
+                imin = fminf(imin, wmin[w].x);
+                idm = fminf(idm, wmin[w].y);
             }
-            for (int w = 0; w < NW; ++w) imin = fminf(imin, wmin[w]);
-            const float si = rsq_(fmaf(s0, s0, fmaf(s1, s1, fmaf(s2, s2, kEpsN))));
-            s0 *= si;
-            s1 *= si;
-            s2 *= si;
-            float irho = 0.0f;  // |v - c| <= |v - c_t| + |c_t - c| for a ray v of tile t
-            for (int t = 0; t < NW * RPT; ++t) {
-                const float4 ct = icones[t];
-                if (fmaf(ct.x, ct.x, fmaf(ct.y, ct.y, ct.z * ct.z)) < 0.25f) continue;
-                const float d0 = ct.x - s0, d1 = ct.y - s1, d2 = ct.z - s2;
-                irho = fmaxf(irho, sqrtf(fmaf(d0, d0, fmaf(d1, d1, d2 * d2))) + ct.w);
-            }
-            const float4 icone = make_float4(s0, s1, s2, irho * (1.0f + 1e-4f) + 1e-6f);
+            const float dcut = fmaxf(kDensSkipLog2, __builtin_amdgcn_logf(idm) - kDensRelLog2 - g2n);
             const int gl = rb + (int)threadIdx.x;
             bool keep = false;
             if (gl < sr.n) {
                 const int gg = sr.gauss_off + gl;
                 float4 q[5];
                 make_entry_est(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
-                float d2_hi, z_hi;
-                tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], icone, bl.hm, bl.b1, bl.nc2, d2_hi, z_hi);
+                const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], ibox, bl.hm, bl.b1, bl.nc2);
                 // (written so that a NaN bound keeps the Gaussian)
-                keep = !(b1_pos && d2_hi < kDensSkipLog2 && z_hi - imin < kSkipLog2);
+                keep = !(b1_pos && pb.d2_hi < dcut && pb.z_hi - imin < wskip);
             }
             const unsigned long long bal = wave_ballot(keep);
             if (lane == 0) wcnt[wave] = __popcll(bal);
@@ -189,74 +170,75 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                 if (COLOR) tile[EW * q + 5] = colour_entry(P.colors + 3 * gi);
             }
             __syncthreads();
-            // Two sweeps over the staged Gaussians, GP at a time.  The first takes the (Gaussian, ray
-            // tile) pairs whose density can reach 2^kDensSkipLog2 on some ray of the tile -- these
-            // hold every ray's largest weights -- and the second the others, except where the tile's
-            // least running maximum then rules out a weight above FP32's zero (tile_bounds; a pair
-            // of neither sweep is one the per-pair test below would skip).  Without beta1 >= 0 the
-            // weight bound does not hold and the first sweep takes every pair.
+            // Every (Gaussian, ray tile) of the staged tile is bounded first, GP Gaussians at a time;
+            // the lower bounds give the least density sum and the least running maximum that the
+            // tile's rays end with.  A pair is taken if on some ray its density can reach the cutoff
+            // (2^kDensSkipLog2, or 2^-kDensRelLog2 / n of the least density sum) or its weight
+            // 2^kFwdSkipLog2 of the running maximum.  Without beta1 >= 0 the weight bounds do not
+            // hold and every pair is taken.
             constexpr int GP = 64 / RPT;
-            float mmin = -INFINITY;  // the least running maximum of lane's bound tile (second sweep)
-            for (int sweep = 0; sweep < 2; ++sweep) {
-              if (sweep == 1) {
+            const TileBox bj = TileBox{tbox[3 * (wave * RPT + jl)], tbox[3 * (wave * RPT + jl) + 1], tbox[3 * (wave * RPT + jl) + 2]};
+            for (int ib = 0; ib < cnt; ib += GP) {
+                const int il = ib + lane / RPT;
+                if (il < cnt) {
+                    const Ent gl = ent_from(tile[EW * il], tile[EW * il + 1], tile[EW * il + 2], tile[EW * il + 3]);
+                    const PairBounds pb = tile_bounds(gl, tile[EW * il + 4], bj, bl.hm, bl.b1, bl.nc2);
+                    hisave[wave][ib * RPT + lane] = make_float2(pb.d2_hi, pb.z_hi);
+                    dlow = fmaxf(dlow, pb.d2_lo);
+                    mlow = fmaxf(mlow, pb.z_lo);
+                }
+            }
+#pragma unroll
+            for (int off = RPT; off < 64; off <<= 1) {
+                dlow = fmaxf(dlow, __shfl_xor(dlow, off, 64));
+                mlow = fmaxf(mlow, __shfl_xor(mlow, off, 64));
+            }
+            if (rb > 0 || gb > 0) {  // the sums of the Gaussians taken so far bound too
 #pragma unroll
                 for (int j = 0; j < RPT; ++j) {
-                    float mm = loc[j] >= 0 ? M[j] : INFINITY;
-#pragma unroll
-                    for (int off = 32; off > 0; off >>= 1) mm = fminf(mm, __shfl_xor(mm, off, 64));
-                    if (jl == j) mmin = mm;
-                }
-              }
-              for (int ib = 0; ib < cnt; ib += GP) {
-                const int il = ib + lane / RPT;
-                float *const zs = &zsave[wave][ib * RPT + lane];
-                bool need = false;
-                if (il < cnt) {
-                    if (sweep == 0) {
-                        const Ent gl = ent_from(tile[EW * il], tile[EW * il + 1], tile[EW * il + 2], tile[EW * il + 3]);
-                        float d2h, zh;
-                        tile_bounds(gl, tile[EW * il + 4], cl, bl.hm, bl.b1, bl.nc2, d2h, zh);
-                        // (comparisons written so that a NaN bound keeps the pair)
-                        need = !(b1_pos && d2h < kDensSkipLog2);
-                        *zs = need ? -INFINITY : zh;
-                    } else {
-                        const float zh = *zs;
-                        need = zh != -INFINITY && !(zh - mmin < kSkipLog2);
+                    const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY), dm = wave_min_u(loc[j] >= 0 ? D[j] : INFINITY);
+                    if (jl == j) {
+                        mlow = fmaxf(mlow, mm);
+                        dlow = fmaxf(dlow, __builtin_amdgcn_logf(dm));
                     }
                 }
-                const unsigned long long nm = wave_ballot(need);
-                if (nm == 0ull) continue;
-                const int kn = min(GP, cnt - ib);
-#pragma unroll 2
-              for (int k = 0; k < kn; ++k) {
+            } else if (b1_pos) {
+                // the running maximum starts at its lower bound (a pair that reaches it is staged here),
+                // so that lesser weights are skipped from the start
+#pragma unroll
+                for (int j = 0; j < RPT; ++j)
+                    M[j] = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mlow), j)), 1e30f);
+            }
+            const float dcut = fmaxf(kDensSkipLog2, dlow - kDensRelLog2 - g2n), zcut = mlow + wskip;
+            for (int ib = 0; ib < cnt; ib += GP) {
+                const int il = ib + lane / RPT;
+                bool need = false;
+                if (il < cnt && bj.c.w >= 0.0f) {
+                    const float2 h = hisave[wave][ib * RPT + lane];
+                    // (written so that a NaN bound keeps the pair)
+                    need = !(b1_pos && h.x < dcut && h.y < zcut);
+                }
+                unsigned long long nm = wave_ballot(need);
+              while (nm != 0ull) {
+                const int k = __builtin_ctzll(nm) / RPT;
                 const unsigned bits = (unsigned)(nm >> (k * RPT)) & ((1u << RPT) - 1u);
-                if (bits == 0u) continue;
+                nm &= ~((unsigned long long)((1u << RPT) - 1u) << (k * RPT));
                 const int i = ib + k;
                 const Ent g = ent_from(tile[EW * i], tile[EW * i + 1], tile[EW * i + 2], tile[EW * i + 3]);
-                const float4 est = tile[EW * i + 4];
                 float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (COLOR) cc = tile[EW * i + 5];
 #pragma unroll
                 for (int j = 0; j < RPT; ++j) {
                     if (!((bits >> j) & 1u)) continue;  // no ray of tile j needs the pair
                     Geo q;
-                    const float vc = pair_geo_peak(g, v0[j], v1[j], v2[j], q);
-                    {
-                        // upper bounds of the log2 density and weight from a lower bound of m (one
-                        // FMA): a pair below both cutoffs adds a weight that is zero in FP32 and a
-                        // density below 2^kDensSkipLog2 to alpha's sum, and skips the residual
-                        const float d2_hi = fmaf(bl.hm, pair_m_low(est, vc, q.t), g.l2l);
-                        const float zr_hi = b1_pos ? fmaf(bl.b1, d2_hi, fmaf(bl.nc2, q.t, -M[j])) : INFINITY;
-                        if (zr_hi < kSkipLog2 && d2_hi < kDensSkipLog2) continue;
-                    }
-                    pair_geo_resid(g, v0[j], v1[j], v2[j], bl.hm, bl.b1, bl.nc2, q);
+                    pair_geo_coarse(g, v0[j], v1[j], v2[j], bl.hm, bl.b1, bl.nc2, q);
                     const float delta = exp2_(q.d2);
                     D[j] += delta;
                     // log2 of the weight relative to the running maximum, b1 d2 + (nc2 t - M)
                     float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -M[j]));
-                    // A weight below 2^-150 of the running maximum is zero in FP32: its terms are
-                    // skipped (the branch is uniform over a wave for most distant Gaussians).
-                    if (zr < kSkipLog2) continue;
+                    // A weight below 2^kFwdSkipLog2 of the running maximum does not change the sums:
+                    // its terms are skipped (the branch is uniform over a wave for most Gaussians).
+                    if (zr < wskip) continue;
                     pair_refine(q);
                     if (zr > 0.0f) {  // new running maximum: rescale the sums (rare)
                         const float sc = exp2_(M[j] - q.z2);
@@ -293,7 +275,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
                         C2[j] = fmaf(ew, cc.z, C2[j]);
                     }
                 }
-              }
               }
             }
         }
@@ -734,7 +715,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
     constexpr int REC = COLOR ? kPartialColor : kPartial;     // partial record per Gaussian
     // per ray: (v, M2 + log2 S), (tf_bar, D_bar, dc, t_f) [, (C_bar, C_bar . C)]
     __shared__ float4 rays[RW * RAYS];
-    __shared__ float4 tcone[T];               // per ray tile: unit centre direction, largest |v - c|
+    __shared__ float4 tbox[3 * T];            // per ray tile: its box (TileBox)
     __shared__ float tnorm[T];                // per ray tile: least M2 + log2 S over its rays
     __shared__ int tdb[T];                    // per ray tile: 1 if some ray has D_bar != 0, else 0
     __shared__ float4 ents[EW * TG];          // the Gaussian tile's entries (m estimate terms, colour)
@@ -769,11 +750,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
 
         __syncthreads();  // the previous item is done with the staged rays
         for (int q = tid; q < RAYS; q += BLOCK) {
-            int row, col;
+            int row = 0, col = 0;
             const int local = (q >> 6) < nt ? tile_local(vr, item.ray0 + (q >> 6), q & 63, row, col) : -1;
             float4 pr[4];
             ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local >= 0 ? local : 0, local >= 0, bl.b1, bl.nc2,
-                            pr);
+                            pr, local >= 0 ? row : 0, col);
             // the weight 2^(z2 - M2) / S as 2^(z2 - M2 - log2 S); a ray past the edge has M2 = inf, S = inf
             rays[RW * q] = make_float4(pr[0].x, pr[0].y, pr[0].z, pr[0].w - __builtin_amdgcn_logf(pr[1].x));
             rays[RW * q + 1] = make_float4(pr[1].y, pr[2].z, pr[3].w, pr[2].w);
@@ -788,38 +769,27 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
             }
         }
         __syncthreads();
-        // each ray tile's cone (centre direction and radius) and least normaliser, for the bound
-        // that lets a wave pass over the tiles on which a Gaussian can neither weigh above FP32's
-        // zero nor add a density above 2^kDensSkipLog2 (tile_bounds)
+        // each ray tile's box and least normaliser, for the bound that lets a wave pass over the tiles
+        // on which a Gaussian can neither weigh above FP32's zero nor add a density above
+        // 2^kDensSkipLog2 (tile_bounds)
         for (int tt = wave; tt < nt; tt += NW) {
             int row, col;
             const bool ok = tile_local(vr, item.ray0 + tt, lane, row, col) >= 0;
             const float4 x0 = rays[RW * (64 * tt + lane)];
             const int db_flag = wave_any(rays[RW * (64 * tt + lane) + 1].y != 0.0f) ? 1 : 0;
-            float c0 = wave_sum(ok ? x0.x : 0.0f), c1 = wave_sum(ok ? x0.y : 0.0f), c2 = wave_sum(ok ? x0.z : 0.0f);
-            const float inv = rsq_(fmaf(c0, c0, fmaf(c1, c1, fmaf(c2, c2, kEpsN))));
-            c0 *= inv;
-            c1 *= inv;
-            c2 *= inv;
-            const float e0 = x0.x - c0, e1 = x0.y - c1, e2 = x0.z - c2;
-            float rho = ok ? sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2))) : 0.0f;
-            float nmin = ok ? x0.w : INFINITY;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                rho = fmaxf(rho, __shfl_xor(rho, off, 64));
-                nmin = fminf(nmin, __shfl_xor(nmin, off, 64));
-            }
+            const TileBox b = wave_box(x0.x, x0.y, x0.z, ok, e);
+            const float nmin = wave_min_u(ok ? x0.w : INFINITY);
             if (lane == 0) {
-                tcone[tt] = make_float4(c0, c1, c2, rho * (1.0f + 1e-4f) + 1e-6f);
+                tbox[3 * tt] = b.c;
+                tbox[3 * tt + 1] = b.x;
+                tbox[3 * tt + 2] = b.y;
                 tnorm[tt] = nmin;
                 tdb[tt] = db_flag;
             }
         }
         float aB1 = 0.0f, aB2 = 0.0f;
-        unsigned db_any = 0;  // bit t: some ray of tile t has a density cotangent
-        bool db_set = false;
         // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
-        // round is first bounded on the whole item (tile_bounds on a cone around all its tiles,
+        // round is first bounded on the whole item (tile_bounds on a box around all its tiles,
         // against their least normaliser), and only those that can matter on some tile are staged,
         // TG at a time, in scene order (slist: their scene-local indices); the others' records are
         // zero, as the per-tile bounds would have left them.  Smaller scenes take one round of all
@@ -829,25 +799,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
         for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
           int total = sr.n;
           if (sparse) {
-            __syncthreads();  // cones visible; the previous round's list and entries are consumed
-            float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, inorm = INFINITY;
-            for (int t = 0; t < nt; ++t) {
-                s0 += tcone[t].x;
-                s1 += tcone[t].y;
-                s2 += tcone[t].z;
-                inorm = fminf(inorm, tnorm[t]);
-            }
-            const float si = rsq_(fmaf(s0, s0, fmaf(s1, s1, fmaf(s2, s2, kEpsN))));
-            s0 *= si;
-            s1 *= si;
-            s2 *= si;
-            float irho = 0.0f;  // |v - c| <= |v - c_t| + |c_t - c| for a ray v of tile t
-            for (int t = 0; t < nt; ++t) {
-                const float4 ct = tcone[t];
-                const float d0 = ct.x - s0, d1 = ct.y - s1, d2 = ct.z - s2;
-                irho = fmaxf(irho, sqrtf(fmaf(d0, d0, fmaf(d1, d1, d2 * d2))) + ct.w);
-            }
-            const float4 icone = make_float4(s0, s1, s2, irho * (1.0f + 1e-4f) + 1e-6f);
+            __syncthreads();  // boxes visible; the previous round's list and entries are consumed
+            float inorm = INFINITY;
+            for (int t = 0; t < nt; ++t) inorm = fminf(inorm, tnorm[t]);
+            const TileBox ibox = wave_box_of(tbox, nt, lane, e);
             // the round's records start as zeros, written contiguously by all threads (the
             // survivors' are overwritten after the barriers below)
             {
@@ -861,10 +816,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 const int gg = sr.gauss_off + gl;
                 float4 q[5];
                 make_entry_est(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
-                float d2_hi, z_hi;
-                tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], icone, bl.hm, bl.b1, bl.nc2, d2_hi, z_hi);
+                const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], ibox, bl.hm, bl.b1, bl.nc2);
                 // (written so that a NaN bound keeps the Gaussian)
-                keep = !(b1_pos && z_hi - inorm < kSkipLog2 && d2_hi < kDensSkipLog2);
+                keep = !(b1_pos && pb.z_hi - inorm < kSkipLog2 && pb.d2_hi < kDensSkipLog2);
             }
             const unsigned long long bal = wave_ballot(keep);
             if (lane == 0) wcnt[wave] = __popcll(bal);
@@ -887,10 +841,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 if (COLOR) ents[EW * q + 5] = colour_entry(P.colors + 3 * gi);
             }
             __syncthreads();
-            if (!db_set) {  // (uniform: the first batch of the item)
-                db_any = (unsigned)wave_ballot(lane < nt && tdb[lane] != 0);
-                db_set = true;
-            }
             // The wave takes Gaussians i0, i0 + NW, ... and bounds GPB of them on the item's tiles in
             // one pass (lane: tile lane % T of Gaussian i0 + (lane / T) NW), then walks them in order.
             constexpr int GPB = 64 / T;
@@ -901,10 +851,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 bool need = false;
                 if (tl < nt && ik < cnt) {
                     const Ent gk = ent_from(ents[EW * ik], ents[EW * ik + 1], ents[EW * ik + 2], ents[EW * ik + 3]);
-                    float d2_hi, z_hi;
-                    tile_bounds(gk, ents[EW * ik + 4], tcone[tl], bl.hm, bl.b1, bl.nc2, d2_hi, z_hi);
+                    const PairBounds pb = tile_bounds(gk, ents[EW * ik + 4], TileBox{tbox[3 * tl], tbox[3 * tl + 1], tbox[3 * tl + 2]},
+                                                      bl.hm, bl.b1, bl.nc2);
                     // (written so that a NaN bound keeps the tile)
-                    need = !(b1_pos && z_hi - tnorm[tl] < kSkipLog2 && d2_hi < kDensSkipLog2);
+                    need = !(b1_pos && pb.z_hi - tnorm[tl] < kSkipLog2 && (pb.d2_hi < kDensSkipLog2 || tdb[tl] == 0));
                 }
                 tmasks = wave_ballot(need);
               }
@@ -919,7 +869,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                     continue;
                 }
                 const Ent g = ent_from(ents[EW * i], ents[EW * i + 1], ents[EW * i + 2], ents[EW * i + 3]);
-                const float4 est = ents[EW * i + 4];
                 float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (COLOR) cc = ents[EW * i + 5];
                 OffsetAcc acc;
@@ -930,18 +879,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                     tmask &= tmask - 1;
                     const float4 x0 = rays[RW * (64 * t + lane)], x1 = rays[RW * (64 * t + lane) + 1];
                     Geo q;
-                    const float vc = pair_geo_peak(g, x0.x, x0.y, x0.z, q);
-                    {
-                        // upper bounds of the log2 density and of the log2 weight from a lower bound
-                        // of m (one FMA): a tile they put below both cutoffs everywhere is one the exact
-                        // test below would skip, and it skips the residual as well
-                        // (each vote on a single comparison; the tile's density-cotangent flag
-                        // loosens the second to rays without one, which the exact test excludes)
-                        const float d2_hi = fmaf(bl.hm, pair_m_low(est, vc, q.t), g.l2l);
-                        const bool w_hi = !b1_pos || wave_any(fmaf(bl.b1, d2_hi, fmaf(bl.nc2, q.t, -x0.w)) >= kSkipLog2);
-                        if (!w_hi && !(((db_any >> t) & 1u) && wave_any(d2_hi >= kDensSkipLog2))) continue;
-                    }
-                    pair_geo_resid(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
+                    pair_geo_coarse(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
                     // log2 of the normalised weight, and the density term D_bar delta
                     const float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w));
                     // a weight below 2^-150 rounds to zero in FP32, and a density below 2^kDensSkipLog2
@@ -1142,7 +1080,7 @@ __global__ __launch_bounds__(BLOCK) void statt_kernel(Params P, const float *__r
     constexpr int NW = BLOCK / 64, RAYS = 64 * T, GPB = 64 / T;
     __shared__ float4 rays[RAYS];   // per ray: (v, M2 + log2 S)
     __shared__ float lossv[RAYS];   // per ray: its loss value
-    __shared__ float4 tcone[T];     // per ray tile: unit centre direction, largest |v - c|
+    __shared__ float4 tbox[3 * T];  // per ray tile: its box (TileBox)
     __shared__ float tnorm[T];      // per ray tile: least M2 + log2 S over its rays
     __shared__ float4 ents[5 * TG];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1177,28 +1115,19 @@ __global__ __launch_bounds__(BLOCK) void statt_kernel(Params P, const float *__r
         int row, col;
         const bool ok = tile_local(vr, item.ray0 + tt, lane, row, col) >= 0;
         const float4 x0 = rays[64 * tt + lane];
-        float c0 = wave_sum(ok ? x0.x : 0.0f), c1 = wave_sum(ok ? x0.y : 0.0f), c2 = wave_sum(ok ? x0.z : 0.0f);
-        const float inv = rsq_(fmaf(c0, c0, fmaf(c1, c1, fmaf(c2, c2, kEpsN))));
-        c0 *= inv;
-        c1 *= inv;
-        c2 *= inv;
-        const float e0 = x0.x - c0, e1 = x0.y - c1, e2 = x0.z - c2;
-        float rho = ok ? sqrtf(fmaf(e0, e0, fmaf(e1, e1, e2 * e2))) : 0.0f;
-        float nmin = ok ? x0.w : INFINITY;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            rho = fmaxf(rho, __shfl_xor(rho, off, 64));
-            nmin = fminf(nmin, __shfl_xor(nmin, off, 64));
-        }
+        const TileBox b = wave_box(x0.x, x0.y, x0.z, ok, e);
+        const float nmin = wave_min_u(ok ? x0.w : INFINITY);
         if (lane == 0) {
-            tcone[tt] = make_float4(c0, c1, c2, rho * (1.0f + 1e-4f) + 1e-6f);
+            tbox[3 * tt] = b.c;
+            tbox[3 * tt + 1] = b.x;
+            tbox[3 * tt + 2] = b.y;
             tnorm[tt] = nmin;
         }
     }
     float *__restrict__ out = partial + item.poff;
     for (int gb = 0; gb < sr.n; gb += TG) {
         const int cnt = min(TG, sr.n - gb);
-        __syncthreads();  // staged rays and cones visible; the previous tile's entries are consumed
+        __syncthreads();  // staged rays and boxes visible; the previous tile's entries are consumed
         for (int q = tid; q < cnt; q += BLOCK) {
             const int gi = sr.gauss_off + gb + q;
             make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[5 * q]);
@@ -1211,10 +1140,10 @@ __global__ __launch_bounds__(BLOCK) void statt_kernel(Params P, const float *__r
                 bool need = false;
                 if (tl < nt && ik < cnt) {
                     const Ent gk = ent_from(ents[5 * ik], ents[5 * ik + 1], ents[5 * ik + 2], ents[5 * ik + 3]);
-                    float d2_hi, z_hi;
-                    tile_bounds(gk, ents[5 * ik + 4], tcone[tl], bl.hm, bl.b1, bl.nc2, d2_hi, z_hi);
+                    const PairBounds pb = tile_bounds(gk, ents[5 * ik + 4], TileBox{tbox[3 * tl], tbox[3 * tl + 1], tbox[3 * tl + 2]},
+                                                      bl.hm, bl.b1, bl.nc2);
                     // (written so that a NaN bound keeps the tile)
-                    need = !(b1_pos && z_hi - tnorm[tl] < kSkipLog2);
+                    need = !(b1_pos && pb.z_hi - tnorm[tl] < kSkipLog2);
                 }
                 tmasks = wave_ballot(need);
             }
