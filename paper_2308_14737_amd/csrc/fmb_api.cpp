@@ -45,15 +45,16 @@ hipError_t launch_loss(int p, const float *depth, const float *alpha, const floa
                        float w_depth, float w_flow, int flow_norm, int flow_cols, float w_color, float *g_depth,
                        float *g_alpha, float *g_flow, float *g_color, float *block_loss, hipStream_t st);
 hipError_t launch_validate(const Params &P, int n_total, int n_scenes, int *flags, hipStream_t st);
-hipError_t launch_fwdc(int flags, int n_items, hipStream_t st, const Params &P, const FwdOut &O,
-                       const BwdItem *items, const int *order);
+int comp_resident_max();
+hipError_t launch_fwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const FwdOut &O,
+                       const CompItem *items);
 hipError_t launch_stat(int n_items, int n_tasks, int max_gc, hipStream_t st, const Params &P, const float *loss,
                        const float *stash, const BwdItem *items, const StatTask *tasks, float *partial,
                        const int64_t *rays_per_scene, float *lbar);
-hipError_t launch_statc(int n_items, hipStream_t st, const Params &P, const float *loss, const float *stash,
-                        const BwdItem *items, float *partial);
-hipError_t launch_bwdc(int flags, int n_items, hipStream_t st, const Params &P, const BwdIn &I,
-                       const BwdItem *items, const int *order, float *partial, float *beta_partial, int max_n);
+hipError_t launch_statc(int n_small, int n_big, hipStream_t st, const Params &P, const float *loss, const float *stash,
+                        const BwdItem *items, const int *order, float *partial);
+hipError_t launch_bwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const BwdIn &I,
+                       const BwdItem *items, const int *order, float *partial, float *beta_partial);
 hipError_t occupancy_fwd(int variant, int flags, int *blocks_per_cu);
 hipError_t occupancy_bwd(int variant, int flags, int *blocks_per_cu);
 hipError_t scratch_base(void **out);
@@ -246,7 +247,12 @@ struct Job {
     int fwd_variant = 1, fwd_built = -1, n_fitems = 0;
     bool launch_fixed = false;  // variants set by the caller or the autotuner
     DevBuf d_fitems, d_forder;
+    // compositing forward work: items of scenes of at most comp_resident_max() Gaussians, then the others'
+    bool comp_fwd_built = false;
+    int n_cfitems[2] = {0, 0};
+    DevBuf d_cfitems;
     // backward work
+    int n_bitems_small = 0;  // compositing: how many of the items in order are small scenes'
     int bwd_variant = 8, bwd_built = -1, n_bitems = 0, n_tasks = 0, n_groups = 0;
     int fin_max_gc = 1, fin_max_nval = 1;  // largest chunk and first-stage record (finalize grid)
     DevBuf d_bitems, d_border, d_tasks, d_groups, d_partial, d_bpart, d_stage, d_stage_beta;
@@ -321,6 +327,64 @@ struct Job {
         return FMB_OK;
     }
 
+    // Ray tiles per item of the compositing forward: blocks of four waves share a small scene's staged
+    // entries over 16 tiles, or over fewer where that leaves less than two blocks per compute unit
+    // (20 views of 128 x 128: 4 tiles, 1280 blocks instead of 320); a larger scene's tiles stage their own
+    // survivors, one tile an item.
+    int build_comp_fwd()
+    {
+        if (comp_fwd_built) return FMB_OK;
+        drop_graphs();
+        std::vector<CompItem> items[2];
+        std::vector<double> cost[2];
+        int64_t small_tiles = 0;
+        for (int k = 0; k < V; ++k)
+            if (scenes[views[k].scene].n <= comp_resident_max()) small_tiles += views[k].tiles;
+        int span = kCompTiles;
+        while (span > 4 && small_tiles < 4LL * n_cu * span) span /= 2;
+        for (int k = 0; k < V; ++k) {
+            const int n = scenes[views[k].scene].n;
+            const int big = n > comp_resident_max() ? 1 : 0;
+            const int sp = big ? 1 : span;
+            for (int t0 = 0; t0 < views[k].tiles; t0 += sp) {
+                items[big].push_back({k, t0, sp});
+                cost[big].push_back((double)n * std::min(sp, views[k].tiles - t0));
+            }
+        }
+        std::vector<CompItem> all;
+        for (int b = 0; b < 2; ++b) {
+            std::vector<int> order(items[b].size());
+            std::iota(order.begin(), order.end(), 0);
+            std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[b][x] > cost[b][y]; });
+            for (int i : order) all.push_back(items[b][i]);
+            n_cfitems[b] = (int)items[b].size();
+        }
+        HIPCHK(d_cfitems.upload(all));
+        comp_fwd_built = true;
+        return FMB_OK;
+    }
+
+    // Ray tiles per item of the compositing backward of scene s, from that scene alone (its gradient
+    // is then the same in any batch).  Small scenes: 16, or 8 or 4 where the scene has too few
+    // tiles for 512 items.  Larger scenes, whose items are one wave each: as few as keep the partial
+    // records below 8 MiB.
+    int comp_bwd_span(int s, int rec) const
+    {
+        auto count = [&](int span) {
+            int64_t c = 0;
+            for (int k = scenes[s].view_off; k < scenes[s].view_off + scenes[s].n_views; ++k)
+                c += (views[k].tiles + span - 1) / span;
+            return c;
+        };
+        int span = kCompTiles;
+        if (scenes[s].n <= comp_resident_max()) {
+            while (span > 4 && count(span) < 512) span /= 2;
+        } else {
+            while (span > 1 && count(span / 2) * scenes[s].n * rec * (int64_t)sizeof(float) <= (8 << 20)) span /= 2;
+        }
+        return span;
+    }
+
     static void chunking(int n, int block, int &gc, int &slots)
     {
         if (n >= block) {
@@ -363,6 +427,7 @@ struct Job {
         std::vector<FinGroup> groups;
         size_t poff = 0, soff = 0;  // partial floats, first-stage doubles
         int max_gc = 1, max_nval = 1;
+        int n_small = 0;  // compositing: leading items of `order` that are small scenes'
     };
     BwdPlan na_plan;  // the plan of the last fmb_backward_noalloc call (host memory only)
 
@@ -387,6 +452,7 @@ struct Job {
         HIPCHK(d_bpart.ensure(std::max<size_t>(2 * pl.items.size(), 2) * sizeof(float)));
         partial_floats = pl.poff;
         n_bitems = (int)pl.items.size();
+        n_bitems_small = pl.n_small;
         n_tasks = (int)pl.tasks.size();
         bwd_built = key;
         return FMB_OK;
@@ -408,7 +474,7 @@ struct Job {
                 // tiled kernels: the whole scene per item, `tiles` ray tiles (ViewRec) per item
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
-                min_span[s] = spans[s] = tiles;
+                min_span[s] = spans[s] = comp ? comp_bwd_span(s, rec) : tiles;
             } else if (ray_tile > 0) {
                 // ray-lane kernel: the whole scene per item, two ray tiles per item to start
                 gcs[s] = scenes[s].n;
@@ -513,7 +579,14 @@ struct Job {
         }
         std::vector<int> order(items.size());
         std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+        if (comp) {  // (the compositing kernels have a form for small scenes and one for the others)
+            auto big = [&](int i) { return items[i].gc > comp_resident_max(); };
+            std::stable_sort(order.begin(), order.end(),
+                             [&](int a, int b) { return big(a) != big(b) ? big(b) : cost[a] > cost[b]; });
+            pl.n_small = (int)std::count_if(order.begin(), order.end(), [&](int i) { return !big(i); });
+        } else {
+            std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+        }
         pl.key = key;
         pl.max_gc = 1;
         pl.max_nval = 1;
@@ -530,8 +603,8 @@ struct Job {
 
     // split statistic: its own items (runs of ray tiles of one view against the whole scene, for
     // both models) and buffers, so captured graphs of the passes stay valid
-    int stat_built = -1, n_sitems = 0, n_stasks = 0, stat_max_gc = 0;
-    DevBuf d_sitems, d_stasks, d_spartial, d_srays;
+    int stat_built = -1, n_sitems = 0, n_sitems_small = 0, n_stasks = 0, stat_max_gc = 0;
+    DevBuf d_sitems, d_sorder, d_stasks, d_spartial, d_srays;
 
     int build_stat()
     {
@@ -545,7 +618,7 @@ struct Job {
         for (int s = 0; s < S; ++s) {
             const int n = scenes[s].n;
             const int gc = n, sl = 1;
-            const int span = comp ? kCompTiles : kStatTiles;  // ray tiles (ViewRec) per item
+            const int span = comp ? comp_bwd_span(s, 1) : kStatTiles;  // ray tiles (ViewRec) per item
             stat_max_gc = std::max(stat_max_gc, gc);
             for (int k = scenes[s].view_off; k < scenes[s].view_off + scenes[s].n_views; ++k)
                 rays[s] += (int64_t)views[k].h * views[k].w;
@@ -578,6 +651,11 @@ struct Job {
                 tasks.push_back(t);
             }
         }
+        std::vector<int> order(items.size());  // small scenes' items first
+        std::iota(order.begin(), order.end(), 0);
+        auto small = [&](int i) { return items[i].gc <= comp_resident_max(); };
+        n_sitems_small = (int)(std::stable_partition(order.begin(), order.end(), small) - order.begin());
+        HIPCHK(d_sorder.upload(order));
         HIPCHK(d_sitems.upload(items));
         HIPCHK(d_stasks.upload(tasks));
         HIPCHK(d_srays.upload(rays));
@@ -596,8 +674,8 @@ struct Job {
         int rc = build_stat();
         if (rc) return rc;
         if (model == FMB_MODEL_COMPOSITE) {
-            HIPCHK(launch_statc(n_sitems, st, prm, loss, stash, d_sitems.as<BwdItem>(),
-                                d_spartial.as<float>()));
+            HIPCHK(launch_statc(n_sitems_small, n_sitems - n_sitems_small, st, prm, loss, stash, d_sitems.as<BwdItem>(),
+                                d_sorder.as<int>(), d_spartial.as<float>()));
             HIPCHK(launch_stat(0, n_stasks, stat_max_gc, st, prm, loss, stash, d_sitems.as<BwdItem>(),
                                d_stasks.as<StatTask>(), d_spartial.as<float>(), d_srays.as<int64_t>(), lbar));
         } else {
@@ -674,11 +752,10 @@ struct Job {
         CHECK_ARG(!O.color || prm.colors, "colour output given but no colours were set");
         CHECK_ARG(!O.stash || aligned(O.stash, 16), "stash must be 16-byte aligned");
         if (model == FMB_MODEL_COMPOSITE) {
-            // items shared with the backward pass: keep whichever colour record is built
-            int rc = (bwd_built == 1 || bwd_built == 3) ? FMB_OK : build_bwd(bwd_variant, prm.colors != nullptr);
+            int rc = build_comp_fwd();
             if (rc) return rc;
             TimedSpan ts(st, 0);
-            HIPCHK(launch_fwdc(fwd_flags(O, false), n_bitems, st, prm, O, d_bitems.as<BwdItem>(), d_border.as<int>()));
+            HIPCHK(launch_fwdc(fwd_flags(O, false), n_cfitems[0], n_cfitems[1], st, prm, O, d_cfitems.as<CompItem>()));
             ts.stop();
             return FMB_OK;
         }
@@ -710,8 +787,8 @@ struct Job {
         if (rc) return rc;
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwdc(bwd_flags(I, false), n_bitems, st, prm, I, d_bitems.as<BwdItem>(), d_border.as<int>(),
-                               d_partial.as<float>(), d_bpart.as<float>(), max_scene_n()));
+            HIPCHK(launch_bwdc(bwd_flags(I, false), n_bitems_small, n_bitems - n_bitems_small, st, prm, I,
+                               d_bitems.as<BwdItem>(), d_border.as<int>(), d_partial.as<float>(), d_bpart.as<float>()));
             tb.stop();
         } else {
             const int flags = blend_bwd_flags(I, persist, bv);
@@ -760,6 +837,7 @@ struct Job {
             return at;
         };
         const size_t o_items = take(pl.items.size() * sizeof(BwdItem));
+        const size_t o_order = model == FMB_MODEL_COMPOSITE ? take(pl.order.size() * sizeof(int)) : 0;
         const size_t o_tasks = take(pl.tasks.size() * sizeof(FinTask));
         const size_t o_groups = take(pl.groups.size() * sizeof(FinGroup));
         const size_t o_part = take(std::max<size_t>(pl.poff, 1) * sizeof(float));
@@ -779,6 +857,8 @@ struct Job {
         HIPCHK(scratch_base(&base));
         char *b = static_cast<char *>(base);
         HIPCHK(hipMemcpyAsync(b + o_items, pl.items.data(), pl.items.size() * sizeof(BwdItem), hipMemcpyHostToDevice, st));
+        if (model == FMB_MODEL_COMPOSITE)
+            HIPCHK(hipMemcpyAsync(b + o_order, pl.order.data(), pl.order.size() * sizeof(int), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(b + o_tasks, pl.tasks.data(), pl.tasks.size() * sizeof(FinTask), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(b + o_groups, pl.groups.data(), pl.groups.size() * sizeof(FinGroup),
                               hipMemcpyHostToDevice, st));
@@ -788,7 +868,8 @@ struct Job {
         const int n_items = (int)pl.items.size();
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwdc(bwd_flags(I, false), n_items, st, prm, I, items, nullptr, part, bpart, max_scene_n()));
+            HIPCHK(launch_bwdc(bwd_flags(I, false), pl.n_small, n_items - pl.n_small, st, prm, I, items,
+                               reinterpret_cast<const int *>(b + o_order), part, bpart));
             tb.stop();
         } else {
             TimedSpan tb(st, 1);
@@ -926,6 +1007,7 @@ int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr
     j.prm.dirs = nullptr;
     j.has_flow = w2c_b != nullptr;
     j.fwd_built = j.bwd_built = j.stat_built = -1;
+    j.comp_fwd_built = false;
     j.cams_set = false;
     if ((rc = j.upload_descriptors())) return rc;
     j.cams_set = true;
@@ -968,6 +1050,7 @@ int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, c
     j.prm.dirs = dirs;
     j.has_flow = w2c_b != nullptr;
     j.fwd_built = j.bwd_built = j.stat_built = -1;
+    j.comp_fwd_built = false;
     j.cams_set = false;
     int rc = j.upload_descriptors();
     if (rc) return rc;
@@ -1186,6 +1269,7 @@ int fmb_batch_capture(fmb_batch *b, float *depth, float *alpha, float *normal, f
     const Grads G{g_means, g_prec, g_weights, g_colors, g_betas};
     // item lists and occupancy are prepared outside the capture (they use synchronous copies)
     int rc = j.build_bwd(j.bwd_run_variant(I), g_color != nullptr);
+    if (!rc && j.model == FMB_MODEL_COMPOSITE) rc = j.build_comp_fwd();
     if (j.model == FMB_MODEL_BLEND) {
         int gdummy = 0;
         if (!rc) rc = j.build_fwd(j.fwd_variant);
@@ -1300,7 +1384,7 @@ int fmb_get_config(const fmb_scene *s, const fmb_batch *b, int32_t *out)
     const bool comp = j.model == FMB_MODEL_COMPOSITE;
     const bool bwd_cur = comp ? (j.bwd_built == 1 || j.bwd_built == 3)
                               : (j.bwd_built >= 0 && j.bwd_built % 2 == 0 && j.bwd_built / 4 == j.bwd_variant);
-    out[6] = comp ? (bwd_cur ? j.n_bitems : 0) : (j.fwd_built == j.fwd_variant ? j.n_fitems : 0);
+    out[6] = comp ? (j.comp_fwd_built ? j.n_cfitems[0] + j.n_cfitems[1] : 0) : (j.fwd_built == j.fwd_variant ? j.n_fitems : 0);
     out[7] = bwd_cur ? j.n_bitems : 0;
     return FMB_OK;
 }

@@ -9,13 +9,17 @@
 // Gaussian keep finite weights.  The strict inequality is taken literally: intersections at
 // equal depth do not attenuate one another.
 //
-// Layout: one ray per lane, one 8 x 8 pixel tile (ViewRec's ray tiles) per wave, one wave per
-// block; an item is a run of consecutive tiles of one view, and the Gaussians are staged through
-// LDS in tiles of kCompTG entries (once per item when the scene fits one tile).
+// Layout: one ray per lane, one 8 x 8 pixel tile (ViewRec's ray tiles) per wave; an item is a run of
+// consecutive tiles of one view.  A scene of at most kCompTG Gaussians is staged in LDS once per item
+// and block for four waves, which take the item's tiles in turn (one wave per block staged it for itself
+// and left a 20-view 128 x 128 job at 320 waves: 980 -> 197 us for its step).  Of a larger scene each
+// wave first bounds every Gaussian on its tile and stages those that can matter there (about 10 of 1000 on
+// a clustered 480 x 270 view, 9.4 -> 0.9 ms); only a tile with more than kCompTG of them takes the
+// scene in staged tiles.
 //
 // Front sums without a sort: F_i only needs the densities in front of t_i, and of those only the
-// significant ones (density above 2^sig, comp_sig_log2: the rest total below 2^-24, FP32's
-// rounding of T_i).  A lane keeps its ray's significant intersections, with their depths, in
+// significant ones (density above 2^sig: the rest total below 2^-27 in the forward,
+// comp_front_log2, and 2^-36 in the adjoint, comp_sig_log2, below FP32's rounding of T_i).  A lane keeps its ray's significant intersections, with their depths, in
 // registers and forms F_i as a sum of exact 0/1 steps over them: per pair the cost is the count of
 // significant intersections around the tile (about ten on the benchmark scenes), not N.  Slots are
 // filled in Gaussian order at positions uniform over the wave -- a lane for which the slot's
@@ -46,13 +50,14 @@
 
 namespace fmb {
 
-constexpr int kCompSlots = 48;  // significant intersections a lane holds per depth window
+// Significant intersections a lane holds per depth window: in the backward (and the split statistic),
+// and in the forward, whose cutoff is higher (on the 16 benchmark scenes 2 % of the tiles have more than
+// 32 above it, 3.6 % above the backward's).
+constexpr int kCompSlots = 48, kFwdcSlots = 32;
 constexpr int kCompTG = 128;    // Gaussians staged per LDS tile
-// Waves per SIMD the kernels are compiled for: the slots take 2 kCompSlots VGPRs (3 kCompSlots
-// in the backward).  With 48 slots rather than 32 the dense tiles of the benchmark scenes take one
-// window instead of several, which costs less than the lost occupancy.  The forward is held to
-// three waves (168 VGPRs, with about 48 values spilled to scratch), which
-// is faster than two waves without spills; the backward (and the split statistic) keep two.
+// Waves per SIMD the kernels are compiled for: the slots take 2 (forward) or 3 VGPRs each.  The
+// forward is held to three waves (168 VGPRs, some values spilled to scratch); the backward and the split
+// statistic, with 48 slots so that their dense tiles take one window instead of several, keep two.
 constexpr int kFwdcWaves = 3, kBwdcWaves = 2, kStatcWaves = 2;
 
 // log2(1 - exp(-delta)) with log2(delta) = d2.
@@ -87,6 +92,11 @@ __device__ __forceinline__ float comp_sig_log2(int n)
     return fminf(-30.0f, -36.0f - (float)lg);
 }
 
+// The forward's cutoff of the log2 density: densities below 2^this (n of them) total less than 2^-27, of
+// a front sum, or, added to the log2 of a ray's density sum (at most 0), of its sum of weights, which
+// is at least 0.63 of that sum.
+__device__ __forceinline__ float comp_front_log2(int n) { return -27.0f - ceil_log2(n); }
+
 // A ray whose largest base-2 log weight is at least this takes only its significant pairs: the
 // others weigh less than n 2^sig <= 2^-36 together, below 2^-24 of its sum of weights.
 constexpr float kCompHitLog2 = -12.0f;
@@ -101,18 +111,20 @@ __device__ __forceinline__ float comp_skip_log2(int n)
     return fminf(-40.0f, -26.0f - (float)lg);
 }
 
-// A lane's slots: scaled depth and density of the significant intersection of the slot's
-// Gaussian (density 0 where that Gaussian is not significant for the lane, or not in its window).
-// They are register vectors (slots 0..31 in the first, 32..47 in the second), read at
+// A lane's NS slots (32 or 48): scaled depth and density of the significant intersection of the
+// slot's Gaussian (density 0 where that Gaussian is not significant for the lane, or not in its
+// window).  They are register vectors (slots 0..31 in the first, 32..47 in the second), read at
 // compile-time positions and written at the wave-uniform fill position by one indirect register
 // move; slot k holds the window's k-th Gaussian in staging order, and the slots from ns on hold
 // zeros.
 typedef float CompV32 __attribute__((ext_vector_type(32)));
 typedef float CompV16 __attribute__((ext_vector_type(16)));
-static_assert(kCompSlots == 48, "the slot vectors hold 32 + 16 slots");
+template <int NS>
 struct CompList {
+    static_assert(NS == 32 || NS == 48, "the slot vectors hold 32 + 16 slots");
+    static constexpr int N = NS;
     CompV32 t0, d0;
-    CompV16 t1, d1;
+    CompV16 t1, d1;  // (unused with 32 slots)
 };
 // a value per slot (the backward's z_bar of the slots' pairs)
 struct CompZ {
@@ -120,21 +132,25 @@ struct CompZ {
     CompV16 z1;
 };
 
-__device__ __forceinline__ float slot_t(const CompList &L, int k) { return k < 32 ? L.t0[k] : L.t1[k - 32]; }
-__device__ __forceinline__ float slot_d(const CompList &L, int k) { return k < 32 ? L.d0[k] : L.d1[k - 32]; }
+template <int NS>
+__device__ __forceinline__ float slot_t(const CompList<NS> &L, int k) { return NS == 32 || k < 32 ? L.t0[k] : L.t1[k - 32]; }
+template <int NS>
+__device__ __forceinline__ float slot_d(const CompList<NS> &L, int k) { return NS == 32 || k < 32 ? L.d0[k] : L.d1[k - 32]; }
 __device__ __forceinline__ float slot_z(const CompZ &z, int k) { return k < 32 ? z.z0[k] : z.z1[k - 32]; }
 
-__device__ __forceinline__ void slot_set_d(CompList &L, int k, float d)
+template <int NS>
+__device__ __forceinline__ void slot_set_d(CompList<NS> &L, int k, float d)
 {
-    if (k < 32)
+    if (NS == 32 || k < 32)
         L.d0[k] = d;
     else
         L.d1[k - 32] = d;
 }
 
-__device__ __forceinline__ void slot_set(CompList &L, int k, float t, float d)
+template <int NS>
+__device__ __forceinline__ void slot_set(CompList<NS> &L, int k, float t, float d)
 {
-    if (k < 32) {
+    if (NS == 32 || k < 32) {
         L.t0[k] = t;
         L.d0[k] = d;
     } else {
@@ -157,66 +173,70 @@ struct CompWin {
     float lo, hi, base, tie;
 };
 
-__device__ __forceinline__ void comp_clear(CompList &L)
+template <int NS>
+__device__ __forceinline__ void comp_clear(CompList<NS> &L)
 {
     L.t0 = (CompV32)(0.0f);
     L.d0 = (CompV32)(0.0f);
-    L.t1 = (CompV16)(0.0f);
-    L.d1 = (CompV16)(0.0f);
+    if (NS > 32) {
+        L.t1 = (CompV16)(0.0f);
+        L.d1 = (CompV16)(0.0f);
+    }
 }
 
-// Step sums over the slots in use, eight slots at a time (template recursion, so that every slot
+// Step sums over the slots in use, four slots at a time (template recursion, so that every slot
 // index is a compile-time register index); ns is uniform, so the early exits are scalar branches,
 // and the unused slots of a group add zeros.  The even and the odd slots go to two sums (two
 // independent chains).
-constexpr int kSlotGroup = 8;
-template <int K>
+constexpr int kSlotGroup = 4;
+template <int K, int NS>
 struct SlotSums {
     // sum of the densities of the slots in front of ts
-    __device__ static __forceinline__ void front(const CompList &L, int ns, float ts, float &f, float &g)
+    __device__ static __forceinline__ void front(const CompList<NS> &L, int ns, float ts, float &f, float &g)
     {
-        if (K >= ns) return;
+        if constexpr (K < NS) {
+            if (K >= ns) return;
 #pragma unroll
-        for (int k = K; k < K + kSlotGroup; k += 2) {
-            f = fmaf(before(slot_t(L, k), ts), slot_d(L, k), f);
-            g = fmaf(before(slot_t(L, k + 1), ts), slot_d(L, k + 1), g);
+            for (int k = K; k < K + kSlotGroup; k += 2) {
+                f = fmaf(before(slot_t(L, k), ts), slot_d(L, k), f);
+                g = fmaf(before(slot_t(L, k + 1), ts), slot_d(L, k + 1), g);
+            }
+            SlotSums<K + kSlotGroup, NS>::front(L, ns, ts, f, g);
         }
-        SlotSums<K + kSlotGroup>::front(L, ns, ts, f, g);
     }
     // sum of z over the slots behind ts
-    __device__ static __forceinline__ void behind(const CompList &L, const CompZ &z, int ns, float ts, float &b,
+    __device__ static __forceinline__ void behind(const CompList<NS> &L, const CompZ &z, int ns, float ts, float &b,
                                                   float &c)
     {
-        if (K >= ns) return;
+        if constexpr (K < NS) {
+            if (K >= ns) return;
 #pragma unroll
-        for (int k = K; k < K + kSlotGroup; k += 2) {
-            b = fmaf(before(ts, slot_t(L, k)), slot_z(z, k), b);
-            c = fmaf(before(ts, slot_t(L, k + 1)), slot_z(z, k + 1), c);
+            for (int k = K; k < K + kSlotGroup; k += 2) {
+                b = fmaf(before(ts, slot_t(L, k)), slot_z(z, k), b);
+                c = fmaf(before(ts, slot_t(L, k + 1)), slot_z(z, k + 1), c);
+            }
+            SlotSums<K + kSlotGroup, NS>::behind(L, z, ns, ts, b, c);
         }
-        SlotSums<K + kSlotGroup>::behind(L, z, ns, ts, b, c);
     }
 };
-template <>
-struct SlotSums<kCompSlots> {
-    __device__ static __forceinline__ void front(const CompList &, int, float, float &, float &) {}
-    __device__ static __forceinline__ void behind(const CompList &, const CompZ &, int, float, float &, float &) {}
-};
-static_assert(kCompSlots % kSlotGroup == 0 && kSlotGroup % 2 == 0, "whole slot groups, of pairs");
+static_assert(32 % kSlotGroup == 0 && 48 % kSlotGroup == 0 && kSlotGroup % 2 == 0, "whole slot groups, of pairs");
 
 // F at scaled depth ts inside window w: base, the densities at lo (if ts > lo), and the slots
 // in front of ts.
-__device__ __forceinline__ float comp_front(const CompList &L, int ns, const CompWin &w, float ts)
+template <int NS>
+__device__ __forceinline__ float comp_front(const CompList<NS> &L, int ns, const CompWin &w, float ts)
 {
     float f = ts > w.lo ? w.base + w.tie : w.base, g = 0.0f;
-    SlotSums<0>::front(L, ns, ts, f, g);
+    SlotSums<0, NS>::front(L, ns, ts, f, g);
     return f + g;
 }
 
 // Sum of z over the slots behind ts.
-__device__ __forceinline__ float comp_behind(const CompList &L, const CompZ &z, int ns, float ts)
+template <int NS>
+__device__ __forceinline__ float comp_behind(const CompList<NS> &L, const CompZ &z, int ns, float ts)
 {
     float b = 0.0f, c = 0.0f;
-    SlotSums<0>::behind(L, z, ns, ts, b, c);
+    SlotSums<0, NS>::behind(L, z, ns, ts, b, c);
     return b + c;
 }
 
@@ -228,14 +248,16 @@ __device__ __forceinline__ float comp_behind(const CompList &L, const CompZ &z, 
 // kernel's 118 KB of code (same speed on the benchmark scenes).
 __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, float invS, float tfb, float kap);
 
-__device__ __forceinline__ float slot_z_plain(const CompList &L, int ns, const CompWin &w, float M2, float invS,
+template <int NS>
+__device__ __forceinline__ float slot_z_plain(const CompList<NS> &L, int ns, const CompWin &w, float M2, float invS,
                                               float tfb, float kap, float dl, float ts)
 {
     if (!(dl > 0.0f)) return 0.0f;
     return slot_zf(comp_front(L, ns, w, ts), dl, ts, M2, invS, tfb, kap);
 }
 
-__device__ __forceinline__ void slots_z_plain(const CompList &L, CompZ &zs, int ns, const CompWin &w, float M2,
+template <int NS>
+__device__ __forceinline__ void slots_z_plain(const CompList<NS> &L, CompZ &zs, int ns, const CompWin &w, float M2,
                                               float invS, float tfb, float kap)
 {
     // (one loop per register vector, so that each writes a single vector in place)
@@ -261,7 +283,8 @@ __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, 
 // behind it from the density registers: the slots' densities are needed only for the front sums,
 // and a second front sum per pair is saved.  The values are those slots_z_plain and comp_front
 // form, bit for bit.
-__device__ __forceinline__ void slots_fz_plain(CompList &L, CompZ &zs, int ns, const CompWin &w, float M2,
+template <int NS>
+__device__ __forceinline__ void slots_fz_plain(CompList<NS> &L, CompZ &zs, int ns, const CompWin &w, float M2,
                                                float invS, float tfb, float kap)
 {
 #pragma unroll 1
@@ -279,23 +302,19 @@ __device__ __forceinline__ void slots_fz_plain(CompList &L, CompZ &zs, int ns, c
 // of the m estimate (make_entry_est) and, with EW = 6, the colour.
 constexpr int kCompEst = 4, kCompCol = 5;  // float4 offsets within an LDS entry
 template <int EW>
+__device__ __forceinline__ void comp_entry(const Params &P, int gi, const double o[3], float4 *__restrict__ dst)
+{
+    make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, dst);
+    if (EW == 6) dst[kCompCol] = colour_entry(P.colors + 3 * gi);
+}
+
+template <int EW, int THREADS>
 __device__ __forceinline__ void comp_stage(const Params &P, const SceneRec &sr, int gb, int cnt, const double o[3],
                                            float4 *__restrict__ ents)
 {
     __syncthreads();  // the previous tile is consumed
-    for (int q = threadIdx.x; q < cnt; q += 64) {
-        const int gi = sr.gauss_off + gb + q;
-        make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[EW * q]);
-        if (EW == 6) ents[EW * q + kCompCol] = colour_entry(P.colors + 3 * gi);
-    }
+    for (int q = threadIdx.x; q < cnt; q += THREADS) comp_entry<EW>(P, sr.gauss_off + gb + q, o, &ents[EW * q]);
     __syncthreads();
-}
-
-// Upper bound of the pair's log2 density from the one-FMA lower bound of m (pair_m_low), with the
-// peak already formed (pair_geo_peak returned vc).
-__device__ __forceinline__ float comp_d2_hi(const Ent &g, const float4 &est, float vc, float t, float hm)
-{
-    return fmaf(hm, pair_m_low(est, vc, t), g.l2l);
 }
 
 template <int EW>
@@ -304,101 +323,160 @@ __device__ __forceinline__ Ent comp_ent(const float4 *__restrict__ ents, int i)
     return ent_from(ents[EW * i], ents[EW * i + 1], ents[EW * i + 2], ents[EW * i + 3]);
 }
 
-// Staged Gaussians [0, cnt) whose log2 density can exceed thr on some ray of the tile (tile_bounds on
-// its box), as two 64-bit masks (lane j tests Gaussians j and 64 + j).
-__device__ __forceinline__ void comp_cull(const float4 *__restrict__ ents, int ew, int cnt, const TileBox &tb,
-                                          float thr, unsigned long long mask[2])
+// The staged Gaussians [0, cnt) of a ray tile: lane j's upper bounds of the log2 densities of
+// Gaussians j and 64 + j over the tile (tile_bounds on its box; -inf past cnt) and the least, over the
+// tile's rays, of the largest log2 density, from below.
+struct CompBounds {
+    float hi[2];
+    float low;
+};
+
+template <int EW>
+__device__ __forceinline__ CompBounds comp_bounds(const float4 *__restrict__ ents, int cnt, const TileBox &tb, int lane)
 {
-    static_assert(kCompTG == 128, "two 64-bit masks per staged tile");
+    static_assert(kCompTG == 128, "two bounds per lane");
+    CompBounds cb{{-INFINITY, -INFINITY}, -INFINITY};
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const int i = 64 * c + (int)threadIdx.x;
-        bool keep = false;
+        const int i = 64 * c + lane;
         if (i < cnt) {
-            const Ent g = ent_from(ents[ew * i], ents[ew * i + 1], ents[ew * i + 2], ents[ew * i + 3]);
-            const PairBounds pb = tile_bounds(g, ents[ew * i + kCompEst], tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
-            keep = !(pb.d2_hi <= thr);  // (a NaN bound keeps the Gaussian)
+            const PairBounds pb = tile_bounds(comp_ent<EW>(ents, i), ents[EW * i + kCompEst], tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
+            cb.hi[c] = pb.d2_hi;
+            cb.low = fmaxf(cb.low, pb.d2_lo);
         }
-        mask[c] = wave_ballot(keep);
+    }
+    cb.low = wave_max_u(cb.low);
+    return cb;
+}
+
+// Those whose log2 density can reach thr, as 64-bit masks (a NaN bound keeps the Gaussian).
+__device__ __forceinline__ void comp_masks(const CompBounds &cb, int cnt, int lane, float thr, unsigned long long mask[2])
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) mask[c] = wave_ballot(64 * c + lane < cnt && !(cb.hi[c] < thr));
+}
+
+// A scene of more than kCompTG Gaussians: those whose log2 density can reach the cutoff on a ray of the
+// tile, staged in scene order with their scene-local indices in gid.  The cutoff is `thr`, or with REL
+// (the forward) rel + min(0, the largest lower bound of the tile's log2 densities), bounded by the
+// Gaussians seen so far (a superset of the final cutoff's, which is returned in `low`).  Returns their
+// count, which may exceed kCompTG: then the first kCompTG are staged, and the tile takes the scene in
+// staged tiles.  One wave.
+template <int EW, bool REL>
+__device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &sr, const double o[3], float4 *__restrict__ ents,
+                                              int *__restrict__ gid, const TileBox &tb, float thr, int lane, float &low)
+{
+    int ne = 0;
+    low = -INFINITY;
+    __syncthreads();  // the previous tile's entries are consumed
+    for (int gb = 0; gb < sr.n; gb += 64) {
+        const int gl = gb + lane;
+        const bool in = gl < sr.n;
+        const int gi = sr.gauss_off + (in ? gl : 0);
+        float4 q[5];
+        make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, q);
+        const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
+        if (REL) low = fmaxf(low, wave_max_u(in ? pb.d2_lo : -INFINITY));
+        const bool keep = in && !(pb.d2_hi < (REL ? fminf(low, 0.0f) + thr : thr));
+        const unsigned long long bal = wave_ballot(keep);
+        const int at = ne + __popcll(bal & ((1ull << lane) - 1ull));
+        if (keep && at < kCompTG) {
+#pragma unroll
+            for (int k = 0; k < 5; ++k) ents[EW * at + k] = q[k];
+            if (EW == 6) ents[EW * at + kCompCol] = colour_entry(P.colors + 3 * gi);
+            gid[at] = gl;
+        }
+        ne += __popcll(bal);
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(ne);
+}
+
+// The slots of window w: every staged Gaussian of `mask` significant for some lane of the wave (log2
+// density above sig2), with a depth behind lo for that lane, takes the next slot; the densities at lo
+// go to w.tie (and each such pair, whose front sum is w.base, to on_tie(g, q, density, staged index)); a
+// lane that meets one more than the slots hold lowers w.hi to its depth.  gb: the scene-local index of
+// the first staged Gaussian; slot_g receives gb + the slots' staged indices.
+template <int EW, int NS, class OnTie>
+__device__ __forceinline__ void comp_collect_tile(const float4 *__restrict__ ents, int gb, const unsigned long long mask[2],
+                                                  float v0, float v1, float v2, float hm, float sig2, int lane, CompWin &w,
+                                                  CompList<NS> &L, int &ns, bool &t_inf, int *__restrict__ slot_g, OnTie on_tie)
+{
+    // the pair's share of the window: tie, slot or (a full list) the end of the window
+    auto take = [&](const Ent &g, const Geo &q, int i) {
+        const bool sig = q.d2 > sig2;
+        const float ts = q.t * kDepthScale;
+        const float dl = exp2_(q.d2);
+        const bool tie = sig && ts == w.lo;
+        if (wave_any(tie)) {
+            if (tie) {
+                w.tie += dl;
+                on_tie(g, q, dl, i);
+            }
+        }
+        const bool cand = sig && ts > w.lo;
+        if (!wave_any(cand)) return;
+        if (ns < NS) {
+            slot_set(L, ns, ts, cand ? dl : 0.0f);
+            t_inf = t_inf || (cand && ts == INFINITY);
+            if (lane == 0) slot_g[ns] = gb + i;
+            ns = __builtin_amdgcn_readfirstlane(ns + 1);
+        } else if (cand) {
+            w.hi = fminf(w.hi, ts);
+        }
+    };
+    // two candidates a step, their geometry computed together (two independent chains)
+#pragma unroll 1
+    for (int c = 0; c < 2; ++c) {
+        unsigned long long mk = mask[c];
+        while (mk) {
+            const int ia = 64 * c + __builtin_ctzll(mk);
+            mk &= mk - 1;
+            const bool two = mk != 0;
+            const int ib = two ? 64 * c + __builtin_ctzll(mk) : ia;
+            if (two) mk &= mk - 1;
+            const Ent ga = comp_ent<EW>(ents, ia), gb2 = comp_ent<EW>(ents, ib);
+            Geo qa, qb;
+            pair_geo_coarse(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
+            pair_geo_coarse(gb2, v0, v1, v2, hm, 0.0f, 0.0f, qb);
+            take(ga, qa, ia);
+            if (two) take(gb2, qb, ib);
+        }
     }
 }
 
-// The slots of window w: every Gaussian significant for some lane of the wave, with a depth behind
-// lo for that lane, takes the next slot; the densities at lo go to w.tie (and each such pair, whose
-// front sum is w.base, to on_tie(g, q, density, staged index)); a lane that meets one more than the
-// slots hold lowers w.hi to its depth, and its slots at or behind w.hi are cleared (they belong to a
-// later window).  Returns the slot count (uniform); slot_g (if given) receives the slots'
-// scene-local Gaussian indices.
-template <int EW, class OnTie>
+// All slots of window w, from the staged Gaussians of `mask` (resident) or the scene's staged tiles;
+// slots at or behind w.hi are cleared (they belong to a later window).  Returns the slot count
+// (uniform).
+template <int EW, int NS, class OnTie>
 __device__ __forceinline__ int comp_collect(const Params &P, const SceneRec &sr, const double o[3],
-                                            float4 *__restrict__ ents, bool resident, float v0, float v1,
-                                            float v2, float hm, float sig2, const TileBox &tc, CompWin &w,
-                                            CompList &L, int *__restrict__ slot_g, OnTie on_tie)
+                                            float4 *__restrict__ ents, bool resident, const unsigned long long rmask[2],
+                                            float v0, float v1, float v2, float hm, float sig2, const TileBox &tb, int lane,
+                                            CompWin &w, CompList<NS> &L, int *__restrict__ slot_g, OnTie on_tie)
 {
     int ns = 0;
     bool t_inf = false;  // a slot of this lane holds an infinite scaled depth
     comp_clear(L);
-    for (int gb = 0; gb < sr.n; gb += kCompTG) {
-        const int cnt = min(kCompTG, sr.n - gb);
-        if (!resident) comp_stage<EW>(P, sr, gb, cnt, o, ents);
-        // only the Gaussians that can be significant on some ray of the wave
-        unsigned long long mask[2];
-        comp_cull(ents, EW, cnt, tc, sig2, mask);
-        // the pair's share of the window: tie, slot or (a full list) the end of the window
-        auto take = [&](const Ent &g, const Geo &q, int i) {
-            const bool sig = q.d2 > sig2;
-            if (!wave_any(sig)) return;
-            const float ts = q.t * kDepthScale;
-            const float dl = exp2_(q.d2);
-            if (sig && ts == w.lo) {
-                w.tie += dl;
-                on_tie(g, q, dl, i);
-            }
-            const bool cand = sig && ts > w.lo;
-            if (!wave_any(cand)) return;
-            if (ns < kCompSlots) {
-                slot_set(L, ns, ts, cand ? dl : 0.0f);
-                t_inf = t_inf || (cand && ts == INFINITY);
-                if (threadIdx.x == 0) slot_g[ns] = gb + i;
-                ns = __builtin_amdgcn_readfirstlane(ns + 1);
-            } else if (cand) {
-                w.hi = fminf(w.hi, ts);
-            }
-        };
-        // two candidates a step, their geometry computed together (two independent chains)
-        for (int c = 0; c < 2; ++c) {
-            unsigned long long mk = mask[c];
-            while (mk) {
-                const int ia = 64 * c + __builtin_ctzll(mk);
-                mk &= mk - 1;
-                const bool two = mk != 0;
-                const int ib = two ? 64 * c + __builtin_ctzll(mk) : ia;
-                if (two) mk &= mk - 1;
-                const Ent ga = comp_ent<EW>(ents, ia), gb2 = comp_ent<EW>(ents, ib);
-                Geo qa, qb;
-                const float vca = pair_geo_peak(ga, v0, v1, v2, qa), vcb = pair_geo_peak(gb2, v0, v1, v2, qb);
-                // the residual only where the density bound allows a significant pair
-                if (wave_any(comp_d2_hi(ga, ents[EW * ia + kCompEst], vca, qa.t, hm) > sig2)) {
-                    pair_geo_resid(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
-                    take(ga, qa, ia);
-                }
-                if (two && wave_any(comp_d2_hi(gb2, ents[EW * ib + kCompEst], vcb, qb.t, hm) > sig2)) {
-                    pair_geo_resid(gb2, v0, v1, v2, hm, 0.0f, 0.0f, qb);
-                    take(gb2, qb, ib);
-                }
-            }
+    for (int gb = 0; gb < (resident ? 1 : sr.n); gb += kCompTG) {
+        unsigned long long mask[2] = {rmask[0], rmask[1]};
+        if (!resident) {
+            const int cnt = min(kCompTG, sr.n - gb);
+            comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
+            comp_masks(comp_bounds<EW>(ents, cnt, tb, lane), cnt, lane, sig2, mask);
         }
+        comp_collect_tile<EW>(ents, gb, mask, v0, v1, v2, hm, sig2, lane, w, L, ns, t_inf, slot_g, on_tie);
     }
     // (where no lane's window was cut, only a slot at an infinite scaled depth can be at or behind hi)
     if (wave_any(w.hi != INFINITY || t_inf)) {
 #pragma unroll
-        for (int k = 0; k < kCompSlots; ++k) slot_set_d(L, k, slot_t(L, k) >= w.hi ? 0.0f : slot_d(L, k));
+        for (int k = 0; k < NS; ++k) slot_set_d(L, k, slot_t(L, k) >= w.hi ? 0.0f : slot_d(L, k));
     }
     return ns;
 }
 
 // Moves window w past hi (or marks the lane done); returns true while the lane has depths left.
-__device__ __forceinline__ bool comp_next(CompWin &w, const CompList &L, int ns)
+template <int NS>
+__device__ __forceinline__ bool comp_next(CompWin &w, const CompList<NS> &L, int ns)
 {
     if (w.hi == INFINITY) {
         w.lo = INFINITY;
@@ -406,7 +484,7 @@ __device__ __forceinline__ bool comp_next(CompWin &w, const CompList &L, int ns)
     }
     float s = w.tie;
 #pragma unroll
-    for (int k = 0; k < kCompSlots; ++k) s += slot_d(L, k);
+    for (int k = 0; k < NS; ++k) s += slot_d(L, k);
     w.base += s;
     w.lo = w.hi;
     w.hi = INFINITY;
@@ -418,16 +496,31 @@ __device__ __forceinline__ bool comp_next(CompWin &w, const CompList &L, int ns)
 // Forward
 // ------------------------------------------------------------------------------------
 
-template <int F>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))) void fwdc_kernel(Params P, FwdOut O, const BwdItem *__restrict__ items,
-                                                                                                      const int *__restrict__ order)
+// 1 - exp(-delta), relatively exact: the series below 1/4 (its next term is 5e-8 of it).
+__device__ __forceinline__ float opacity(float delta)
+{
+    float p = fmaf(delta, -1.0f / 720.0f, 1.0f / 120.0f);
+    p = fmaf(delta, p, -1.0f / 24.0f);
+    p = fmaf(delta, p, 1.0f / 6.0f);
+    p = fmaf(delta, p, -0.5f);
+    p = fmaf(delta, p, 1.0f);
+    return delta < 0.25f ? delta * p : 1.0f - exp2_(-(float)kLog2e * delta);
+}
+
+// NW waves per block: 4 for scenes of at most kCompTG Gaussians (staged once per item for all four, each
+// wave taking every fourth tile of it), 1 for larger ones (each wave stages its own tile's survivors).
+template <int F, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))) void fwdc_kernel(
+    Params P, FwdOut O, const CompItem *__restrict__ items)
 {
     constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     constexpr int EW = COLOR ? 6 : 5;
     __shared__ float4 ents[kCompTG * EW];
-    __shared__ int slot_g[kCompSlots];
-    const int lane = threadIdx.x;
-    const BwdItem item = ld_uniform(items + (order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x));
+    __shared__ int slot_gs[NW][kFwdcSlots];
+    __shared__ int gid[NW == 1 ? kCompTG : 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int *const slot_g = slot_gs[wave];
+    const CompItem item = ld_uniform(items + blockIdx.x);
     const ViewRec vr = ld_uniform(P.views + item.view);
     const SceneRec sr = ld_uniform(P.scenes + vr.scene);
     const CamRec cam = cam_of(P, item.view);
@@ -436,14 +529,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
     cam_centre(e, o);
     const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
     const float hm = (float)(-0.5 * kLog2e);
-    const float sig2 = comp_sig_log2(sr.n), skip2 = comp_skip_log2(sr.n);
-    const bool resident = sr.n <= kCompTG;
-    if (resident) comp_stage<EW>(P, sr, 0, sr.n, o, ents);
-    const int nt = min(item.span, vr.tiles - item.ray0);  // ray0: the item's first tile
+    const float front2 = comp_front_log2(sr.n);
+    if (NW > 1) comp_stage<EW, 64 * NW>(P, sr, 0, sr.n, o, ents);
+    const int nt = min(item.span, vr.tiles - item.tile0);
 
-    for (int tt = 0; tt < nt; ++tt) {
+    for (int tt = wave; tt < nt; tt += NW) {
         int row, col;
-        const int loc = tile_local(vr, item.ray0 + tt, lane, row, col);
+        const int loc = tile_local(vr, item.tile0 + tt, lane, row, col);
         const bool valid = loc >= 0;
         float v0, v1, v2;
         tile_ray_dir(P, vr, e, kk, valid ? loc : 0, valid ? row : 0, valid ? col : 0, v0, v1, v2);
@@ -453,32 +545,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
             dt = O.depth_t[vr.ray_off + loc];
         }
         const TileBox tc = wave_box(v0, v1, v2, valid, e);
+        // the tile's Gaussians: the whole scene, or its survivors, staged (ne of them)
+        int ne = sr.n;
+        float low = -INFINITY;
+        if (NW == 1) ne = comp_survivors<EW, true>(P, sr, o, ents, gid, tc, front2, lane, low);
+        const bool resident = NW > 1 || ne <= kCompTG;
+        // Cutoffs of the log2 density: a tile whose every ray has a density sum of at least 2^low blends
+        // the pairs that can reach rel (the others total below 2^-26 of the ray's sum of weights); of
+        // the rest only those above front2 matter to a front sum.  On a tile with low above
+        // kCompHitLog2 every pair blended has a slot.
+        CompBounds cb{{0.0f, 0.0f}, low};
+        if (resident) cb = comp_bounds<EW>(ents, ne, tc, lane);
+        const float rel = fminf(cb.low, 0.0f) + front2;
+        const bool hit = resident && cb.low >= kCompHitLog2;
+        const float sig2 = hit ? rel : front2;
+        unsigned long long smask[2] = {0, 0};
+        if (resident) comp_masks(cb, ne, lane, sig2, smask);
         float M, S, T, N0, N1, N2, C0, C1, C2, D;
-        auto reset = [&]() {
-            M = -INFINITY;
+        auto reset = [&](float m) {
+            M = m;
             S = T = N0 = N1 = N2 = C0 = C1 = C2 = D = 0.0f;
         };
-        reset();
-        CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
-        CompList L;
-        // blends pair (g, q) of this lane at front sum fs; ci: the staged index of its colour
-        auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
-            const float delta = exp2_(q.d2);
-            D += delta;
-            const float lw = fmaf(-(float)kLog2e, fs, log2_opacity(delta, q.d2));
-            if (lw > M) {  // new running maximum: rescale the sums
-                const float sc = exp2_(M - lw);
-                S *= sc;
-                T *= sc;
-                N0 *= sc;
-                N1 *= sc;
-                N2 *= sc;
-                C0 *= sc;
-                C1 *= sc;
-                C2 *= sc;
-                M = lw;
-            }
-            const float ew = exp2_(lw - M);
+        // adds weight ew of pair (g, q); ci: the staged index of its colour
+        auto add = [&](const Ent &g, Geo &q, float ew, int ci) {
             S += ew;
             T = fmaf(ew, q.t, T);
             if (NORMALS) {
@@ -495,17 +584,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
                 C2 = fmaf(ew, cc.z, C2);
             }
         };
+        // scales the sums, e.g. to a new largest weight
+        auto rescale = [&](float sc) {
+            S *= sc;
+            T *= sc;
+            N0 *= sc;
+            N1 *= sc;
+            N2 *= sc;
+            C0 *= sc;
+            C1 *= sc;
+            C2 *= sc;
+        };
+        CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
+        CompList<kFwdcSlots> L;
         const auto no_tie = [](const Ent &, const Geo &, float, int) {};
-        int ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, no_tie);
+        int ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
 
-        // A tile of one window whose rays all weigh at least 2^kCompHitLog2 somewhere blends only the
-        // significant pairs (the slots' Gaussians), each ray its own.
-        bool done = false;
-        // (a ray without a significant intersection cannot qualify)
-        float own = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kCompSlots; ++k) own += slot_d(L, k);
-        if (resident && ns > 0 && !wave_any(w.hi != INFINITY) && wave_all(!valid || own > 0.0f)) {
+        if (hit && !wave_any(w.hi != INFINITY)) {
+            // One window of a tile that every ray meets: the slots' pairs, with their weights themselves
+            // (the largest is far above FP32's smallest, so no logarithm is needed until the end).
+            reset(0.0f);
+            auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
+                const float delta = exp2_(q.d2);
+                D += delta;
+                const float ew = exp2_(-(float)kLog2e * fs) * opacity(delta);
+                M = fmaxf(M, ew);
+                add(g, q, ew, ci);
+            };
             for (int s = 0; s < ns; s += 2) {  // two slots a step (two independent chains)
                 const bool two = s + 1 < ns;
                 const int ia = slot_g[s], ib = two ? slot_g[s + 1] : ia;
@@ -516,40 +621,58 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
                 if (valid && qa.d2 > sig2) blend(ga, qa, comp_front(L, ns, w, qa.t * kDepthScale), ia);
                 if (two && valid && qb.d2 > sig2) blend(gb, qb, comp_front(L, ns, w, qb.t * kDepthScale), ib);
             }
-            done = wave_all(!valid || M >= kCompHitLog2);
-            if (!done) reset();
-        }
-        // Otherwise every pair of every window (a tile that sees background or several windows).
-        while (!done) {
-            for (int gb = 0; gb < sr.n; gb += kCompTG) {
-                const int cnt = min(kCompTG, sr.n - gb);
-                if (!resident) comp_stage<EW>(P, sr, gb, cnt, o, ents);
-                for (int i = 0; i < cnt; i += 2) {  // two Gaussians a step (two independent chains)
-                    const bool two = i + 1 < cnt;
-                    const int ib = two ? i + 1 : i;
-                    const Ent ga = comp_ent<EW>(ents, i), gb = comp_ent<EW>(ents, ib);
-                    Geo qa, qb;
-                    const float vca = pair_geo_peak(ga, v0, v1, v2, qa), vcb = pair_geo_peak(gb, v0, v1, v2, qb);
-                    // a pair of this window whose weight (at most its density) is not below
-                    // 2^skip2 of the running maximum (nor is its density below 2^skip2, as M <= 0);
-                    // the density bound rules most pairs out before the residual
-                    const float tsa = qa.t * kDepthScale, tsb = qb.t * kDepthScale;
-                    const bool ina = tsa >= w.lo && tsa < w.hi, inb = two && tsb >= w.lo && tsb < w.hi;
-                    if (wave_any(ina && comp_d2_hi(ga, ents[EW * i + kCompEst], vca, qa.t, hm) - M >= skip2)) {
-                        pair_geo_resid(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
-                        const bool la = ina && qa.d2 - M >= skip2;
-                        if (wave_any(la) && la) blend(ga, qa, comp_front(L, ns, w, tsa), i);
+            rescale(1.0f / M);
+            M = __builtin_amdgcn_logf(M);
+        } else {
+            // A tile that sees background, or of several windows: every pair that can reach rel, with
+            // logarithms of the weights.
+            reset(-INFINITY);
+            auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
+                const float delta = exp2_(q.d2);
+                D += delta;
+                const float lw = fmaf(-(float)kLog2e, fs, log2_opacity(delta, q.d2));
+                if (lw > M) {  // new running maximum: rescale the sums
+                    rescale(exp2_(M - lw));
+                    M = lw;
+                }
+                add(g, q, exp2_(lw - M), ci);
+            };
+            for (;;) {
+                for (int gb = 0; gb < (resident ? 1 : sr.n); gb += kCompTG) {
+                    const int cnt = resident ? ne : min(kCompTG, sr.n - gb);
+                    if (!resident) {
+                        comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
+                        cb = comp_bounds<EW>(ents, cnt, tc, lane);
                     }
-                    if (wave_any(inb && comp_d2_hi(gb, ents[EW * ib + kCompEst], vcb, qb.t, hm) - M >= skip2)) {
-                        pair_geo_resid(gb, v0, v1, v2, hm, 0.0f, 0.0f, qb);
-                        const bool lb = inb && qb.d2 - M >= skip2;
-                        if (wave_any(lb) && lb) blend(gb, qb, comp_front(L, ns, w, tsb), ib);
+                    unsigned long long mask[2];
+                    comp_masks(cb, cnt, lane, rel, mask);
+#pragma unroll 1
+                    for (int c = 0; c < 2; ++c) {
+                        unsigned long long mk = mask[c];
+                        while (mk) {  // two Gaussians a step (two independent chains)
+                            const int ia = 64 * c + __builtin_ctzll(mk);
+                            mk &= mk - 1;
+                            const bool two = mk != 0;
+                            const int ib = two ? 64 * c + __builtin_ctzll(mk) : ia;
+                            if (two) mk &= mk - 1;
+                            const Ent ga = comp_ent<EW>(ents, ia), gb2 = comp_ent<EW>(ents, ib);
+                            Geo qa, qb;
+                            pair_geo_coarse(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
+                            pair_geo_coarse(gb2, v0, v1, v2, hm, 0.0f, 0.0f, qb);
+                            // a pair of this window whose weight (at most its density) is not below
+                            // 2^front2 of the running maximum
+                            const float tsa = qa.t * kDepthScale, tsb = qb.t * kDepthScale;
+                            const bool la = tsa >= w.lo && tsa < w.hi && qa.d2 - M >= front2;
+                            if (wave_any(la) && la) blend(ga, qa, comp_front(L, ns, w, tsa), ia);
+                            const bool lb = two && tsb >= w.lo && tsb < w.hi && qb.d2 - M >= front2;
+                            if (wave_any(lb) && lb) blend(gb2, qb, comp_front(L, ns, w, tsb), ib);
+                        }
                     }
                 }
+                const bool more = comp_next(w, L, ns);
+                if (!wave_any(more)) break;
+                ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
             }
-            const bool more = comp_next(w, L, ns);
-            if (!wave_any(more)) break;
-            ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, no_tie);
         }
         if (valid)
             write_ray<F>(P, O, item.view, vr.ray_off + loc, e, kk, o0, o1, o2, v0, v1, v2, M, S, T, N0, N1, N2, C0,
@@ -561,10 +684,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))
 // Backward
 // ------------------------------------------------------------------------------------
 
-template <int F>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))) void bwdc_kernel(Params P, BwdIn I, const BwdItem *__restrict__ items,
-                                                  const int *__restrict__ order, float *__restrict__ partial,
-                                                  float *__restrict__ beta_partial)
+// NW waves per block as in the forward: with 4, the waves share the staged scene and each sums its
+// tiles' terms into its own record, added in wave order at the end of the item.
+template <int F, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))) void bwdc_kernel(
+    Params P, BwdIn I, const BwdItem *__restrict__ items, const int *__restrict__ order, float *__restrict__ partial,
+    float *__restrict__ beta_partial)
 {
     constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     // without a normal cotangent the pairs take the offset form of the adjoint
@@ -576,14 +701,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
     constexpr int LREC = (PLAIN ? kOffsetAcc : kPartial) + (COLOR ? 3 : 0);
     static_assert(LREC <= 16, "one 16-value wave sum per pair");
     __shared__ float4 ents[kCompTG * EW];
-    // the slots' entries, for scenes beyond one LDS tile (dynamic: launched without it when every
-    // scene is resident, so that more blocks share a compute unit)
+    // the slots' entries, for scenes beyond one LDS tile (dynamic: the four-wave form, whose scenes are
+    // all resident, is launched without it)
     extern __shared__ float4 sents[];
-    __shared__ float rec[kCompTG * LREC];      // the item's sums of the staged Gaussians
-    __shared__ int slot_g[kCompSlots];
-    __shared__ int touched[kCompTG];
-    const int lane = threadIdx.x;
-    const BwdItem item = ld_uniform(items + (order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x));
+    __shared__ float recs[NW][kCompTG * LREC];  // each wave's sums of the staged Gaussians
+    __shared__ int slot_gs[NW][kCompSlots];
+    __shared__ int touched[NW == 1 ? kCompTG : 1];
+    __shared__ int gid[NW == 1 ? kCompTG : 1];  // scene-local indices of a tile's survivors
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int *const slot_g = slot_gs[wave];
+    float *const rec = recs[wave];
+    const BwdItem item = ld_uniform(items + ld_uniform(order + blockIdx.x));
     const ViewRec vr = ld_uniform(P.views + item.view);
     const SceneRec sr = ld_uniform(P.scenes + vr.scene);
     const CamRec cam = cam_of(P, item.view);
@@ -594,24 +722,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
     const float hm = (float)(-0.5 * kLog2e);
     const float sig2 = comp_sig_log2(sr.n), skip2 = comp_skip_log2(sr.n);
     const int n = sr.n;
-    const bool resident = n <= kCompTG;
     float *__restrict__ prec_out = partial + item.poff;
-    if (resident) {
-        comp_stage<EW>(P, sr, 0, n, o, ents);
+    if (NW > 1) {
         for (int q = lane; q < n * LREC; q += 64) rec[q] = 0.0f;
+        comp_stage<EW, 64 * NW>(P, sr, 0, n, o, ents);
     } else {
         // the record is summed in place over the item's tiles and windows, one staged tile at a time
         for (int q = lane; q < n * REC; q += 64) prec_out[q] = 0.0f;
+        __syncthreads();
     }
-    __syncthreads();
     const int nt = min(item.span, vr.tiles - item.ray0);
 
-    for (int tt = 0; tt < nt; ++tt) {
+    for (int tt = wave; tt < nt; tt += NW) {
         int row, col;
         const int loc = tile_local(vr, item.ray0 + tt, lane, row, col);
         const bool valid = loc >= 0;
         float4 pr[4];
-        ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, valid ? loc : 0, valid, 0.0f, 0.0f, pr);
+        ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, valid ? loc : 0, valid, 0.0f, 0.0f, pr, valid ? row : 0,
+                        valid ? col : 0);
         const float v0 = pr[0].x, v1 = pr[0].y, v2 = pr[0].z, M2 = pr[0].w;
         const float invS = pr[1].x, tfb = pr[1].y, nb0 = pr[1].z, nb1 = pr[1].w;
         const float nb2 = pr[2].x, kap = pr[2].y, Db = pr[2].z;
@@ -620,14 +748,29 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
         // and lw is at most the log2 density
         const float wskip = valid ? M2 - __builtin_amdgcn_logf(invS) + skip2 : INFINITY;
         // the least cutoff of the wave's rays (pairs below a ray's cutoff are not taken)
-        float lim_min = valid ? fminf(skip2, wskip) : INFINITY;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) lim_min = fminf(lim_min, __shfl_xor(lim_min, off, 64));
+        const float lim = fminf(skip2, wskip), lim_min = wave_min_u(valid ? lim : INFINITY);
         const CompWin w0{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
         CompWin w = w0;
-        CompList L;
+        CompList<kCompSlots> L;
         CompZ zs;
         const TileBox tc = wave_box(v0, v1, v2, valid, e);
+        // the tile's Gaussians: the whole scene, or its survivors, staged (ne of them)
+        int ne = n;
+        float low;
+        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), lane, low);
+        const bool resident = NW > 1 || ne <= kCompTG;
+        const bool mapped = NW == 1 && resident;  // the staged Gaussians' records are flushed per tile
+        unsigned long long smask[2] = {0, 0}, fmask[2] = {0, 0};
+        if (resident) {
+            const CompBounds cb = comp_bounds<EW>(ents, ne, tc, lane);
+            comp_masks(cb, ne, lane, sig2, smask);
+            comp_masks(cb, ne, lane, lim_min, fmask);
+        }
+        if (mapped) {
+            for (int q = lane; q < ne * LREC; q += 64) rec[q] = 0.0f;
+            for (int q = lane; q < ne; q += 64) touched[q] = 0;
+            __syncthreads();
+        }
 
         // z_bar of the slots' own pairs (the lanes' significant intersections of the window)
         auto slots_z = [&](int ns) {
@@ -711,7 +854,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
 
         // First sweep, for tiles that take several windows: the sum of z_bar over all significant
         // intersections of each ray, so that a window knows the z_bar of the windows behind it.
-        int ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, on_tie);
+        int ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, on_tie);
         float zall = 0.0f;
         if (wave_any(w.hi != INFINITY)) {
             bool more = true;
@@ -721,11 +864,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
                 more = comp_next(w, L, ns);
                 if (!wave_any(more)) break;
                 ztie = 0.0f;
-                ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, on_tie);
+                ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, on_tie);
             }
             w = w0;
             ztie = 0.0f;
-            ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, on_tie);
+            ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, on_tie);
         }
 
         // A tile of one window whose rays all weigh at least 2^kCompHitLog2 somewhere (the forward's
@@ -788,6 +931,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
             if ((lane & 3) == 0 && idx < LREC) rec[LREC * r + idx] += tot;
         };
 
+        // adds the sums of the staged Gaussians that took a term to the item's record (gb: the first one's
+        // scene-local index, or -1 for a tile's survivors)
+        auto flush = [&](int cnt, int gb) {
+            for (int qq = lane; qq < cnt; qq += 64) {
+                if (!touched[qq]) continue;
+                const int gl = gb >= 0 ? gb + qq : gid[qq];
+                const int gg = sr.gauss_off + gl;
+                float r[kPartialColor];
+                if (PLAIN)
+                    write_partial_offset(r, rec + LREC * qq, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
+                else
+                    write_partial(r, rec + LREC * qq, REC, P.means + 3 * gg, o);
+                float *dst = prec_out + REC * gl;
+                for (int c = 0; c < REC; ++c) dst[c] += r[c];
+            }
+        };
         float zthrough = 0.0f;
         for (;;) {
             // (a tile of one window whose pairs are all slots': the slots keep F and z_bar)
@@ -810,89 +969,73 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
                     // the pair of slot s is the slot's own (its front sum is F of the slot)
                     const float fa = fz ? slot_z(zs, s) : 0.0f;
                     pair_terms(ga, qa, qa.t * kDepthScale, valid && qa.d2 > sig2, ia, ia, zafter, fz, fa);
+                    if (mapped && lane == 0) touched[ia] = 1;
                 }
             } else {
-                for (int gb = 0; gb < n; gb += kCompTG) {
+                for (int gb = 0; gb < (resident ? 1 : n); gb += kCompTG) {
                     const int cnt = min(kCompTG, n - gb);
+                    unsigned long long fm[2] = {fmask[0], fmask[1]};
                     if (!resident) {
-                        comp_stage<EW>(P, sr, gb, cnt, o, ents);
+                        comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
                         for (int q = lane; q < cnt * LREC; q += 64) rec[q] = 0.0f;
                         for (int q = lane; q < cnt; q += 64) touched[q] = 0;
                         __syncthreads();
+                        // only the Gaussians whose density can reach some lane's cutoff on the tile
+                        comp_masks(comp_bounds<EW>(ents, cnt, tc, lane), cnt, lane, lim_min, fm);
                     }
-                    // only the Gaussians whose density can reach some lane's cutoff on the tile
-                    // (the tile bound of comp_cull), two a step (two independent chains)
-                    unsigned long long fm[2];
-                    comp_cull(ents, EW, cnt, tc, lim_min, fm);
+#pragma unroll 1
                     for (int c = 0; c < 2; ++c) {
                       unsigned long long mk = fm[c];
                       while (mk) {
                         const int i = 64 * c + __builtin_ctzll(mk);
                         mk &= mk - 1;
-                        const bool two = mk != 0;
-                        const int ib = two ? 64 * c + __builtin_ctzll(mk) : i;
-                        if (two) mk &= mk - 1;
-                        const Ent ga = comp_ent<EW>(ents, i), gb = comp_ent<EW>(ents, ib);
-                        Geo qa, qb;
-                        const float vca = pair_geo_peak(ga, v0, v1, v2, qa), vcb = pair_geo_peak(gb, v0, v1, v2, qb);
-                        // a pair of this window with a normalised weight or a density not below
-                        // 2^skip2 (the density bound rules most pairs out before the residual)
-                        const float tsa = qa.t * kDepthScale, tsb = qb.t * kDepthScale;
-                        const float lim = fminf(skip2, wskip);
-                        const bool ina = tsa >= w.lo && tsa < w.hi, inb = two && tsb >= w.lo && tsb < w.hi;
-                        if (wave_any(ina && comp_d2_hi(ga, ents[EW * i + kCompEst], vca, qa.t, hm) >= lim)) {
-                            pair_geo_resid(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
-                            const bool la = ina && qa.d2 >= lim;
-                            if (wave_any(la)) {
-                                pair_terms(ga, qa, tsa, la, i, i, zafter, false, 0.0f);
-                                if (!resident && lane == 0) touched[i] = 1;
-                            }
-                        }
-                        if (wave_any(inb && comp_d2_hi(gb, ents[EW * ib + kCompEst], vcb, qb.t, hm) >= lim)) {
-                            pair_geo_resid(gb, v0, v1, v2, hm, 0.0f, 0.0f, qb);
-                            const bool lb = inb && qb.d2 >= lim;
-                            if (wave_any(lb)) {
-                                pair_terms(gb, qb, tsb, lb, ib, ib, zafter, false, 0.0f);
-                                if (!resident && lane == 0) touched[ib] = 1;
-                            }
+                        const Ent ga = comp_ent<EW>(ents, i);
+                        Geo qa;
+                        pair_geo_coarse(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
+                        // a pair of this window with a normalised weight or a density not below 2^skip2
+                        const float tsa = qa.t * kDepthScale;
+                        const bool la = tsa >= w.lo && tsa < w.hi && qa.d2 >= lim;
+                        if (wave_any(la)) {
+                            pair_terms(ga, qa, tsa, la, i, i, zafter, false, 0.0f);
+                            if (NW == 1 && lane == 0) touched[i] = 1;
                         }
                       }
                     }
                     if (!resident) {
-                        // add the tile's sums of this window to the item's record
                         __syncthreads();
-                        for (int qq = lane; qq < cnt; qq += 64) {
-                            if (!touched[qq]) continue;
-                            const int gg = sr.gauss_off + gb + qq;
-                            float r[kPartialColor];
-                            if (PLAIN)
-                                write_partial_offset(r, rec + LREC * qq, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
-                            else
-                                write_partial(r, rec + LREC * qq, REC, P.means + 3 * gg, o);
-                            float *dst = prec_out + REC * (gb + qq);
-                            for (int c = 0; c < REC; ++c) dst[c] += r[c];
-                        }
+                        flush(cnt, gb);
                     }
                 }
             }
             const bool more = comp_next(w, L, ns);
             if (!wave_any(more)) break;
             ztie = 0.0f;
-            ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, on_tie);
+            ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, on_tie);
+        }
+        if (mapped) {
+            __syncthreads();
+            flush(ne, -1);
         }
     }
 
-    if (resident) {
+    if (NW > 1) {
         __syncthreads();
-        for (int q = lane; q < n; q += 64) {
+        for (int q = threadIdx.x; q < n; q += 64 * NW) {
             const int gg = sr.gauss_off + q;
+            float sum[LREC];
+#pragma unroll
+            for (int c = 0; c < LREC; ++c) sum[c] = recs[0][LREC * q + c];
+#pragma unroll
+            for (int k = 1; k < NW; ++k)
+#pragma unroll
+                for (int c = 0; c < LREC; ++c) sum[c] += recs[k][LREC * q + c];
             if (PLAIN)
-                write_partial_offset(prec_out + REC * q, rec + LREC * q, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
+                write_partial_offset(prec_out + REC * q, sum, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
             else
-                write_partial(prec_out + REC * q, rec + LREC * q, REC, P.means + 3 * gg, o);
+                write_partial(prec_out + REC * q, sum, REC, P.means + 3 * gg, o);
         }
     }
-    if (lane < 2) beta_partial[2 * item.seq + lane] = 0.0f;  // the model has no blend parameters
+    if (threadIdx.x < 2) beta_partial[2 * item.seq + threadIdx.x] = 0.0f;  // the model has no blend parameters
 }
 
 // ------------------------------------------------------------------------------------
@@ -900,17 +1043,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kBwdcWaves))
 // here per item and Gaussian; the running maximum and 1/S come from the forward's stash.
 // ------------------------------------------------------------------------------------
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves))) void statc_kernel(Params P, const float *__restrict__ loss,
-                                                   const float *__restrict__ stash,
-                                                   const BwdItem *__restrict__ items, float *__restrict__ partial)
+// (waves and staging as in the backward)
+template <int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kStatcWaves))) void statc_kernel(
+    Params P, const float *__restrict__ loss, const float *__restrict__ stash, const BwdItem *__restrict__ items,
+    const int *__restrict__ order, float *__restrict__ partial)
 {
     constexpr int EW = 5;
-    const int *order = nullptr;
     __shared__ float4 ents[kCompTG * EW];
-    __shared__ float rec[kCompTG];
-    __shared__ int slot_g[kCompSlots];
-    const int lane = threadIdx.x;
-    const BwdItem item = ld_uniform(items + (order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x));
+    __shared__ float recs[NW][kCompTG];
+    __shared__ int slot_gs[NW][kCompSlots];
+    __shared__ int gid[NW == 1 ? kCompTG : 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int *const slot_g = slot_gs[wave];
+    float *const rec = recs[wave];
+    const BwdItem item = ld_uniform(items + ld_uniform(order + blockIdx.x));
     const ViewRec vr = ld_uniform(P.views + item.view);
     const SceneRec sr = ld_uniform(P.scenes + vr.scene);
     const CamRec cam = cam_of(P, item.view);
@@ -920,17 +1067,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves)
     const float hm = (float)(-0.5 * kLog2e);
     const float sig2 = comp_sig_log2(sr.n), skip2 = comp_skip_log2(sr.n);
     const int n = sr.n;
-    const bool resident = n <= kCompTG;
     float *__restrict__ out = partial + item.poff;
-    if (resident) {
-        comp_stage<EW>(P, sr, 0, n, o, ents);
+    if (NW > 1) {
         for (int q = lane; q < n; q += 64) rec[q] = 0.0f;
+        comp_stage<EW, 64 * NW>(P, sr, 0, n, o, ents);
     } else {
         for (int q = lane; q < n; q += 64) out[q] = 0.0f;
+        __syncthreads();
     }
-    __syncthreads();
     const int nt = min(item.span, vr.tiles - item.ray0);
-    for (int tt = 0; tt < nt; ++tt) {
+    for (int tt = wave; tt < nt; tt += NW) {
         int row, col;
         const int loc = tile_local(vr, item.ray0 + tt, lane, row, col);
         const bool valid = loc >= 0;
@@ -945,55 +1091,70 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves)
             lr = loss[r];
         }
         const float wskip = valid ? M2 - __builtin_amdgcn_logf(invS) + skip2 : INFINITY;
+        const float lim_min = wave_min_u(wskip);
         CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
-        CompList L;
+        CompList<kCompSlots> L;
         const TileBox tc = wave_box(v0, v1, v2, valid, e);
+        int ne = n;
+        float low;
+        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), lane, low);
+        const bool resident = NW > 1 || ne <= kCompTG;
+        const bool mapped = NW == 1 && resident;
+        unsigned long long smask[2] = {0, 0}, fmask[2] = {0, 0};
+        if (resident) {
+            const CompBounds cb = comp_bounds<EW>(ents, ne, tc, lane);
+            comp_masks(cb, ne, lane, sig2, smask);
+            comp_masks(cb, ne, lane, lim_min, fmask);
+        }
+        if (mapped) {
+            for (int q = lane; q < ne; q += 64) rec[q] = 0.0f;
+            __syncthreads();
+        }
         const auto no_tie = [](const Ent &, const Geo &, float, int) {};
+        // loss times the normalised weight of the lane's pair, summed over the wave into rec[i]
+        auto term = [&](const Geo &q, bool live, float ts, int ns, int i) {
+            float x = 0.0f;
+            if (live) {
+                const float lw = fmaf(-(float)kLog2e, comp_front(L, ns, w, ts), log2_opacity(exp2_(q.d2), q.d2));
+                x = lr * (exp2_(lw - M2) * invS);
+            }
+            x = wave_sum_u(x);
+            if (lane == 0) rec[i] += x;
+        };
         for (bool first = true;; first = false) {
-            const int ns = comp_collect<EW>(P, sr, o, ents, resident, v0, v1, v2, hm, sig2, tc, w, L, slot_g, no_tie);
-            // as in the forward: a tile of one window whose rays all weigh at least 2^kCompHitLog2
+            const int ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
+            // as in the backward: a tile of one window whose rays all weigh at least 2^kCompHitLog2
             // somewhere takes only the slots' Gaussians
             if (first && resident && ns > 0 && !wave_any(w.hi != INFINITY) && wave_all(!valid || M2 >= kCompHitLog2)) {
                 for (int s = 0; s < ns; ++s) {
                     const int gi = slot_g[s];
-                    const Ent g = comp_ent<EW>(ents, gi);
                     Geo q;
-                    pair_geo_coarse(g, v0, v1, v2, hm, 0.0f, 0.0f, q);
-                    const float ts = q.t * kDepthScale;
-                    float x = 0.0f;
-                    if (valid && q.d2 > sig2) {
-                        const float lw = fmaf(-(float)kLog2e, comp_front(L, ns, w, ts), log2_opacity(exp2_(q.d2), q.d2));
-                        x = lr * (exp2_(lw - M2) * invS);
-                    }
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-                    if (lane == 0) rec[gi] += x;
+                    pair_geo_coarse(comp_ent<EW>(ents, gi), v0, v1, v2, hm, 0.0f, 0.0f, q);
+                    term(q, valid && q.d2 > sig2, q.t * kDepthScale, ns, gi);
                 }
                 break;
             }
-            for (int gb = 0; gb < n; gb += kCompTG) {
+            for (int gb = 0; gb < (resident ? 1 : n); gb += kCompTG) {
                 const int cnt = min(kCompTG, n - gb);
+                unsigned long long fm[2] = {fmask[0], fmask[1]};
                 if (!resident) {
-                    comp_stage<EW>(P, sr, gb, cnt, o, ents);
+                    comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
                     for (int q = lane; q < cnt; q += 64) rec[q] = 0.0f;
                     __syncthreads();
+                    comp_masks(comp_bounds<EW>(ents, cnt, tc, lane), cnt, lane, lim_min, fm);
                 }
-                for (int i = 0; i < cnt; ++i) {
-                    const Ent g = comp_ent<EW>(ents, i);
-                    Geo q;
-                    pair_geo_coarse(g, v0, v1, v2, hm, 0.0f, 0.0f, q);
-                    const float ts = q.t * kDepthScale;
-                    const bool live = ts >= w.lo && ts < w.hi && q.d2 >= wskip;
-                    if (!wave_any(live)) continue;
-                    float x = 0.0f;
-                    if (live) {
-                        const float lw = fmaf(-(float)kLog2e, comp_front(L, ns, w, ts), log2_opacity(exp2_(q.d2), q.d2));
-                        x = lr * (exp2_(lw - M2) * invS);
+#pragma unroll 1
+                for (int c = 0; c < 2; ++c) {
+                    unsigned long long mk = fm[c];
+                    while (mk) {
+                        const int i = 64 * c + __builtin_ctzll(mk);
+                        mk &= mk - 1;
+                        Geo q;
+                        pair_geo_coarse(comp_ent<EW>(ents, i), v0, v1, v2, hm, 0.0f, 0.0f, q);
+                        const float ts = q.t * kDepthScale;
+                        const bool live = ts >= w.lo && ts < w.hi && q.d2 >= wskip;
+                        if (wave_any(live)) term(q, live, ts, ns, i);
                     }
-                    // sum over the wave in a fixed order
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-                    if (lane == 0) rec[i] += x;
                 }
                 if (!resident) {
                     __syncthreads();
@@ -1003,10 +1164,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves)
             const bool more = comp_next(w, L, ns);
             if (!wave_any(more)) break;
         }
+        if (mapped) {
+            __syncthreads();
+            for (int q = lane; q < ne; q += 64) out[gid[q]] += rec[q];
+        }
     }
-    if (resident) {
+    if (NW > 1) {
         __syncthreads();
-        for (int q = lane; q < n; q += 64) out[q] = rec[q];
+        for (int q = threadIdx.x; q < n; q += 64 * NW) {
+            float sum = recs[0][q];
+#pragma unroll
+            for (int k = 1; k < NW; ++k) sum += recs[k][q];
+            out[q] = sum;
+        }
     }
 }
 
@@ -1027,37 +1197,44 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kStatcWaves)
     default: return hipErrorInvalidValue;                                                                 \
     }
 
-#define FMB_FWDC_CALL(F_) hipLaunchKernelGGL((fwdc_kernel<F_>), dim3(n_items), dim3(64), 0, st, P, O, items, order)
-#define FMB_BWDC_CALL(F_)                                                                                 \
-    hipLaunchKernelGGL((bwdc_kernel<F_>), dim3(n_items), dim3(64), dyn, st, P, I, items, order, partial,    \
-                       beta_partial)
+#define FMB_FWDC_SMALL(F_) hipLaunchKernelGGL((fwdc_kernel<F_, 4>), dim3(n_small), dim3(256), 0, st, P, O, items)
+#define FMB_FWDC_BIG(F_) hipLaunchKernelGGL((fwdc_kernel<F_, 1>), dim3(n_big), dim3(64), 0, st, P, O, items + n_small)
+#define FMB_BWDC_SMALL(F_)                                                                                \
+    hipLaunchKernelGGL((bwdc_kernel<F_, 4>), dim3(n_small), dim3(256), 0, st, P, I, items, order, partial, beta_partial)
+#define FMB_BWDC_BIG(F_)                                                                                  \
+    hipLaunchKernelGGL((bwdc_kernel<F_, 1>), dim3(n_big), dim3(64), dyn, st, P, I, items, order + n_small, partial, beta_partial)
 
-// Blocks take the items in `order` (longest first) where given, else in item order.
-hipError_t launch_fwdc(int flags, int n_items, hipStream_t st, const Params &P, const FwdOut &O,
-                       const BwdItem *items, const int *order)
+int comp_resident_max() { return kCompTG; }
+
+// Blocks take the items in order: first the n_small items of scenes of at most kCompTG Gaussians (four
+// waves per block), then the n_big of larger ones (one wave per block).
+hipError_t launch_fwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const FwdOut &O,
+                       const CompItem *items)
 {
     flags &= ~kPer;
-    if (n_items < 1) return hipSuccess;
-    FMB_COMP_DISPATCH(flags, FMB_FWDC_CALL)
+    if (n_small > 0) FMB_COMP_DISPATCH(flags, FMB_FWDC_SMALL)
+    if (n_big > 0) FMB_COMP_DISPATCH(flags, FMB_FWDC_BIG)
     return hipGetLastError();
 }
 
-// max_n: the largest scene of the batch (the slots' entries are staged only beyond one LDS tile).
-hipError_t launch_bwdc(int flags, int n_items, hipStream_t st, const Params &P, const BwdIn &I,
-                       const BwdItem *items, const int *order, float *partial, float *beta_partial, int max_n)
+// order: the items' indices, the n_small of small scenes first.
+hipError_t launch_bwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const BwdIn &I,
+                       const BwdItem *items, const int *order, float *partial, float *beta_partial)
 {
     flags &= ~kPer;
-    if (n_items < 1) return hipSuccess;
-    const size_t dyn = max_n > kCompTG ? (size_t)kCompSlots * 6 * sizeof(float4) : 0;
-    FMB_COMP_DISPATCH(flags, FMB_BWDC_CALL)
+    const size_t dyn = (size_t)kCompSlots * 6 * sizeof(float4);
+    if (n_small > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_SMALL)
+    if (n_big > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_BIG)
     return hipGetLastError();
 }
 
-hipError_t launch_statc(int n_items, hipStream_t st, const Params &P, const float *loss, const float *stash,
-                        const BwdItem *items, float *partial)
+hipError_t launch_statc(int n_small, int n_big, hipStream_t st, const Params &P, const float *loss, const float *stash,
+                        const BwdItem *items, const int *order, float *partial)
 {
-    if (n_items < 1) return hipSuccess;
-    hipLaunchKernelGGL(statc_kernel, dim3(n_items), dim3(64), 0, st, P, loss, stash, items, partial);
+    if (n_small > 0)
+        hipLaunchKernelGGL((statc_kernel<4>), dim3(n_small), dim3(256), 0, st, P, loss, stash, items, order, partial);
+    if (n_big > 0)
+        hipLaunchKernelGGL((statc_kernel<1>), dim3(n_big), dim3(64), 0, st, P, loss, stash, items, order + n_small, partial);
     return hipGetLastError();
 }
 

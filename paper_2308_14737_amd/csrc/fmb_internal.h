@@ -56,6 +56,11 @@ struct FwdItem {       // 8 bytes
     int32_t tile0;     // first ray tile (see ViewRec) of the view
 };
 
+struct CompItem {      // compositing forward: a run of ray tiles of one view
+    int32_t view;
+    int32_t tile0, span;
+};
+
 struct BwdItem {       // 32 bytes
     int32_t view;
     int32_t ray0;      // first local ray of the span
@@ -101,8 +106,7 @@ struct StatTask {
 constexpr int kPartial = 10;       // per-Gaussian partial: dU (6), sum rho (3), dlog(lambda) (1)
 constexpr int kPartialColor = 13;  // ... and dL/d(colour) (3)
 
-// Zero-parameter (alpha-compositing) renderer: ray tiles (ViewRec) per work item, one wave per
-// item.
+// Zero-parameter (alpha-compositing) renderer: the most ray tiles (ViewRec) per work item.
 constexpr int kCompTiles = 16;
 constexpr int kStatTiles = 16;  // ray tiles (ViewRec) per item of the blend model's split statistic
 
