@@ -29,6 +29,7 @@ int num_bwd_variants();
 int bwd_variant_rt(int v);
 int bwd_variant_ray_tile(int v);
 int bwd_variant_tiles(int v);
+int bwd_normal_variant();
 int block_size();
 hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const FwdOut &O,
                       const FwdItem *items, int n, const int *order, int *counter);
@@ -458,6 +459,57 @@ struct Job {
         return FMB_OK;
     }
 
+    // Items of scene s whose view rays (or ray tiles) are cut in spans of `span`, for one Gaussian chunk.
+    int64_t scene_items(int s, int span, bool tiled) const
+    {
+        int64_t c = 0;
+        for (int k = scenes[s].view_off; k < scenes[s].view_off + scenes[s].n_views; ++k) {
+            const int64_t lim = tiled ? views[k].tiles : (int64_t)views[k].h * views[k].w;
+            c += (lim + span - 1) / span;
+        }
+        return c;
+    }
+
+    // Span of rays per item, chosen per scene only (so a scene is cut the same way alone
+    // and inside a batch): `span` to start, at most 16384 items and, where the scene is small, at
+    // least 2048, of at least `least` rays.
+    int ray_span(int s, int gc, int span, int least) const
+    {
+        const int64_t chunks = (scenes[s].n + gc - 1) / gc;
+        while (chunks * scene_items(s, span, false) > 16384 && span < (1 << 22)) span *= 2;
+        while (chunks * scene_items(s, span, false) < 2048 && span > least) span /= 2;
+        return span;
+    }
+
+    // Whether calls with a normal cotangent run the tiled form: its items hold a record of every Gaussian
+    // of the scene, those of the Gaussian-lane variant 2 of a chunk.  Every scene's records have to
+    // stay within what variant 2 takes, or within 16 MiB (which leaves the fixed workspace of
+    // fmb_backward_noalloc its slack), or, of a scene whose variant 2 records that workspace cannot hold
+    // anyway, within 2 GiB.
+    int normals_form[2] = {-1, -1};  // by colour: the answer, -1 until asked for these cameras
+    bool normals_tiled(bool colour)
+    {
+        if (normals_form[colour] < 0) normals_form[colour] = normals_fit(colour) ? 1 : 0;
+        return normals_form[colour] == 1;
+    }
+    bool normals_fit(bool colour) const
+    {
+        const int64_t rec = (colour ? kPartialColor : kPartial) * (int64_t)sizeof(float);
+        int64_t all = 0;
+        for (int s = 0; s < S; ++s) {
+            const int n = scenes[s].n;
+            const int64_t tiled = scene_items(s, bwd_variant_tiles(bwd_normal_variant()), true) * n * rec;
+            int gc, sl;
+            chunking(n, block_size(), gc, sl);
+            const int RT = bwd_variant_rt(2);
+            const int span = ray_span(s, gc, std::max(RT, ((256 * sl + RT - 1) / RT) * RT), RT);
+            const int64_t gauss = scene_items(s, span, false) * ((n + gc - 1) / gc) * gc * rec;
+            if (tiled > std::max<int64_t>(gauss, 16 << 20) && !(gauss > (32 << 20) && tiled <= (2LL << 30))) return false;
+            all += tiled;
+        }
+        return all <= (8LL << 30) - (1 << 20);  // offsets of the records are 32-bit floats
+    }
+
     int plan_bwd(int variant, bool colour, BwdPlan &pl)
     {
         const int key = bwd_key(variant, colour);
@@ -468,40 +520,22 @@ struct Job {
         // ray tiles per item of the tiled kernels (the compositing kernels are tiled too)
         const int tiles = comp ? kCompTiles : bwd_variant_tiles(variant);
         const int B = block_size();
-        std::vector<int> gcs(S), sls(S), spans(S), min_span(S);
+        std::vector<int> gcs(S), sls(S), spans(S);
         for (int s = 0; s < S; ++s) {
             if (tiles > 0) {
                 // tiled kernels: the whole scene per item, `tiles` ray tiles (ViewRec) per item
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
-                min_span[s] = spans[s] = comp ? comp_bwd_span(s, rec) : tiles;
+                spans[s] = comp ? comp_bwd_span(s, rec) : tiles;
             } else if (ray_tile > 0) {
                 // ray-lane kernel: the whole scene per item, two ray tiles per item to start
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
-                min_span[s] = ray_tile;
-                spans[s] = 2 * ray_tile;
+                spans[s] = ray_span(s, gcs[s], 2 * ray_tile, ray_tile);
             } else {
                 chunking(scenes[s].n, B, gcs[s], sls[s]);
-                min_span[s] = RT;
-                spans[s] = std::max(RT, ((256 * sls[s] + RT - 1) / RT) * RT);
+                spans[s] = ray_span(s, gcs[s], std::max(RT, ((256 * sls[s] + RT - 1) / RT) * RT), RT);
             }
-        }
-        // Span of rays per item, chosen per scene only (so a scene is cut the same way alone
-        // and inside a batch): about 256 rays per lane, at most 16384 and, where the scene is
-        // small, at least 2048 items.
-        for (int s = 0; s < S && tiles == 0; ++s) {
-            const int chunks = (scenes[s].n + gcs[s] - 1) / gcs[s];
-            auto count_items = [&](int span) {
-                int64_t c = 0;
-                for (int k = scenes[s].view_off; k < scenes[s].view_off + scenes[s].n_views; ++k) {
-                    const int hw = views[k].h * views[k].w;
-                    c += (int64_t)chunks * ((hw + span - 1) / span);
-                }
-                return c;
-            };
-            while (count_items(spans[s]) > 16384 && spans[s] < (1 << 22)) spans[s] *= 2;
-            while (count_items(spans[s]) < 2048 && spans[s] > min_span[s]) spans[s] /= 2;
         }
         std::vector<BwdItem> items;
         std::vector<FinTask> tasks;
@@ -690,7 +724,7 @@ struct Job {
 
     int grid_fwd(int flags, int &grid)
     {
-        const int key = fwd_variant * 16 + (flags | kFlagPer);
+        const int key = fwd_variant * 32 + (flags | kFlagPer);
         auto it = occ_f.find(key);
         if (it == occ_f.end()) {
             int o = 0;
@@ -703,7 +737,7 @@ struct Job {
 
     int grid_bwd(int variant, int flags, int &grid)
     {
-        const int key = variant * 16 + (flags | kFlagPer);
+        const int key = variant * 32 + (flags | kFlagPer);
         auto it = occ_b.find(key);
         if (it == occ_b.end()) {
             int o = 0;
@@ -714,11 +748,12 @@ struct Job {
         return FMB_OK;
     }
 
-    // The backward variant a call runs: the tiled variants take no normal cotangent, so such calls
-    // run the Gaussian-lane variant 2 instead.
-    int bwd_run_variant(const BwdIn &I) const
+    // The backward variant a call runs: with a normal cotangent the tiled variants run their form for it.
+    // (where its records are not too large, else the Gaussian-lane variant 2)
+    int bwd_run_variant(const BwdIn &I)
     {
-        return bwd_variant_tiles(bwd_variant) > 0 && I.g_normal ? 2 : bwd_variant;
+        if (bwd_variant_tiles(bwd_variant) == 0 || !I.g_normal || model == FMB_MODEL_COMPOSITE) return bwd_variant;
+        return normals_tiled(I.g_color != nullptr) ? bwd_normal_variant() : 2;
     }
 
     static int fwd_flags(const FwdOut &O, bool persist)
@@ -1008,6 +1043,7 @@ int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr
     j.has_flow = w2c_b != nullptr;
     j.fwd_built = j.bwd_built = j.stat_built = -1;
     j.comp_fwd_built = false;
+    j.normals_form[0] = j.normals_form[1] = -1;
     j.cams_set = false;
     if ((rc = j.upload_descriptors())) return rc;
     j.cams_set = true;
@@ -1051,6 +1087,7 @@ int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, c
     j.has_flow = w2c_b != nullptr;
     j.fwd_built = j.bwd_built = j.stat_built = -1;
     j.comp_fwd_built = false;
+    j.normals_form[0] = j.normals_form[1] = -1;
     j.cams_set = false;
     int rc = j.upload_descriptors();
     if (rc) return rc;

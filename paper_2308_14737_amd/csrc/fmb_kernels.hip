@@ -689,7 +689,7 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
 }
 
 // ------------------------------------------------------------------------------------
-// Backward, tiled ray-lane layout (no normal cotangent): an item is T ray tiles of
+// Backward, tiled ray-lane layout: an item is T ray tiles of
 // one view (8 x 8 pixels, see ViewRec) against every Gaussian of its scene.  The item's rays
 // are staged in LDS with their adjoint prologue; each wave takes every NW-th Gaussian and walks
 // the T tiles with a lane per ray, so a lane sums that Gaussian's terms over T rays before one
@@ -699,19 +699,21 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
 // 34 % of (tile, Gaussian) pairs).
 // ------------------------------------------------------------------------------------
 
+// With a normal cotangent the staged ray is the prologue as ray_prologue writes it (64 bytes) and the
+// pair takes the general adjoint of bwd_kernel; items are then 8 tiles.
+
 template <int BLOCK, int T, int TG, int F>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void bwdt_kernel(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm) ? 4 : 6))) void bwdt_kernel(
     Params P, BwdIn I, const BwdItem *__restrict__ items, int n_items, const int *__restrict__ order,
     int *__restrict__ counter, float *__restrict__ partial, float *__restrict__ beta_partial)
 {
-    static_assert((F & kNrm) == 0, "the tiled backward takes no normal cotangent");
-    constexpr bool PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
+    constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int NW = BLOCK / 64;
     constexpr int RAYS = 64 * T;
     static_assert(T <= 32 && 64 % T == 0, "a 32-bit mask of the item's ray tiles, whole tile sets per wave");
-    constexpr int RW = COLOR ? 3 : 2;                         // float4 per staged ray
+    constexpr int RW = NORMALS ? 4 : COLOR ? 3 : 2;           // float4 per staged ray
     constexpr int EW = COLOR ? 6 : 5;                         // float4 per staged Gaussian
-    constexpr int LREC = kOffsetAcc + (COLOR ? 3 : 0);        // sums per Gaussian
+    constexpr int LREC = (NORMALS ? kPartial : kOffsetAcc) + (COLOR ? 3 : 0);  // sums per Gaussian
     constexpr int REC = COLOR ? kPartialColor : kPartial;     // partial record per Gaussian
     // per ray: (v, M2 + log2 S), (tf_bar, D_bar, dc, t_f) [, (C_bar, C_bar . C)]
     __shared__ float4 rays[RW * RAYS];
@@ -755,6 +757,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
             float4 pr[4];
             ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local >= 0 ? local : 0, local >= 0, bl.b1, bl.nc2,
                             pr, local >= 0 ? row : 0, col);
+            if (NORMALS) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) rays[RW * q + k] = pr[k];
+                continue;
+            }
             // the weight 2^(z2 - M2) / S as 2^(z2 - M2 - log2 S); a ray past the edge has M2 = inf, S = inf
             rays[RW * q] = make_float4(pr[0].x, pr[0].y, pr[0].z, pr[0].w - __builtin_amdgcn_logf(pr[1].x));
             rays[RW * q + 1] = make_float4(pr[1].y, pr[2].z, pr[3].w, pr[2].w);
@@ -776,9 +783,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
             int row, col;
             const bool ok = tile_local(vr, item.ray0 + tt, lane, row, col) >= 0;
             const float4 x0 = rays[RW * (64 * tt + lane)];
-            const int db_flag = wave_any(rays[RW * (64 * tt + lane) + 1].y != 0.0f) ? 1 : 0;
+            const float dbar = NORMALS ? rays[RW * (64 * tt + lane) + 2].z : rays[RW * (64 * tt + lane) + 1].y;
+            const int db_flag = wave_any(dbar != 0.0f) ? 1 : 0;
             const TileBox b = wave_box(x0.x, x0.y, x0.z, ok, e);
-            const float nmin = wave_min_u(ok ? x0.w : INFINITY);
+            const float norm = NORMALS ? x0.w - __builtin_amdgcn_logf(rays[RW * (64 * tt + lane) + 1].x) : x0.w;
+            const float nmin = wave_min_u(ok ? norm : INFINITY);
             if (lane == 0) {
                 tbox[3 * tt] = b.c;
                 tbox[3 * tt + 1] = b.x;
@@ -872,6 +881,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                 float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 if (COLOR) cc = ents[EW * i + 5];
                 OffsetAcc acc;
+                PairAcc nacc;
                 float aC0 = 0.0f, aC1 = 0.0f, aC2 = 0.0f;  // colour sums: wt C_bar
 #pragma unroll 1
                 while (tmask) {
@@ -879,6 +889,36 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                     tmask &= tmask - 1;
                     const float4 x0 = rays[RW * (64 * t + lane)], x1 = rays[RW * (64 * t + lane) + 1];
                     Geo q;
+                    if (NORMALS) {
+                        pair_geo(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
+                        const float4 x2 = rays[RW * (64 * t + lane) + 2];
+                        const float delta = exp2_(q.d2), dd = x2.z * delta;
+                        const float zr = q.z2 - x0.w;
+                        if (wave_any(zr >= kSkipLog2)) {
+                            const float4 x3 = rays[RW * (64 * t + lane) + 3];
+                            const float wt = exp2_(zr) * x1.x;  // normalised blend weight
+                            const float tfb = x1.y;
+                            const PairNormal pn = pair_normal(g, q, x1.z, x1.w, x2.x);
+                            // z_bar = wt (tf_bar t + Nb.n + Cb.c - kappa)
+                            float lin = fmaf(tfb, q.t, pn.nN);
+                            if (COLOR) {
+                                lin = fmaf(x3.x, cc.x, fmaf(x3.y, cc.y, fmaf(x3.z, cc.z, lin)));
+                                aC0 = fmaf(wt, x3.x, aC0);
+                                aC1 = fmaf(wt, x3.y, aC1);
+                                aC2 = fmaf(wt, x3.z, aC2);
+                            }
+                            const float zb = wt * (lin - x2.y);
+                            const float tb = fmaf(-bl.cb, zb, wt * tfb);
+                            const float db = fmaf(bl.b1, zb, dd);
+                            aB1 = fmaf(zb, q.d2 - x3.w, aB1);
+                            aB2 = fmaf(zb, q.t - x2.w, aB2);
+                            pair_adjoint<true>(g, q, x0.x, x0.y, x0.z, wt, pn, x1.z, x1.w, x2.x, tb, db, nacc);
+                        } else {
+                            const PairNormal pn{0, 0, 0, 0, 0};
+                            pair_adjoint<false>(g, q, x0.x, x0.y, x0.z, 0.0f, pn, 0.0f, 0.0f, 0.0f, 0.0f, dd, nacc);
+                        }
+                        continue;
+                    }
                     pair_geo_coarse(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
                     // log2 of the normalised weight, and the density term D_bar delta
                     const float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w));
@@ -915,11 +955,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
                     }
                 }
                 float v[16];
-                offset_acc_store(acc, v);
-                v[13] = aC0;
-                v[14] = aC1;
-                v[15] = aC2;
+                constexpr int C0 = NORMALS ? kPartial : kOffsetAcc;
                 static_assert(kOffsetAcc + 3 <= 16, "one 16-value wave sum per Gaussian");
+                if (NORMALS) {
+                    v[0] = nacc.u0; v[1] = nacc.u1; v[2] = nacc.u2; v[3] = nacc.u3; v[4] = nacc.u4; v[5] = nacc.u5;
+                    v[6] = nacc.p0; v[7] = nacc.p1; v[8] = nacc.p2; v[9] = nacc.l;
+                    v[13] = v[14] = v[15] = 0.0f;
+                } else {
+                    offset_acc_store(acc, v);
+                }
+                v[C0] = aC0;
+                v[C0 + 1] = aC1;
+                v[C0 + 2] = aC2;
                 const float tot = wave_sum16(v, lane);
                 const int idx = wave16_index(lane);
                 if ((lane & 3) == 0 && idx < LREC) rec[LREC * i + idx] = tot;
@@ -929,8 +976,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
             for (int q = tid; q < cnt; q += BLOCK) {
                 const int gl = sparse ? slist[gb + q] : gb + q;
                 const int gg = sr.gauss_off + gl;
-                write_partial_offset(partial + item.poff + REC * gl, rec + LREC * q, REC,
-                                     P.prec + 6 * gg, P.means + 3 * gg, o);
+                if (NORMALS)
+                    write_partial(partial + item.poff + REC * gl, rec + LREC * q, REC, P.means + 3 * gg, o);
+                else
+                    write_partial_offset(partial + item.poff + REC * gl, rec + LREC * q, REC,
+                                         P.prec + 6 * gg, P.means + 3 * gg, o);
             }
           }
         }
@@ -1332,12 +1382,15 @@ struct BwdRayVariant {
 static const BwdRayVariant kBwdRay[] = {{2, 64}, {4, 64}, {4, 128}};
 constexpr int kNumBwdGauss = (int)(sizeof kBwdRT / sizeof kBwdRT[0]);
 constexpr int kNumBwdRay = (int)(sizeof kBwdRay / sizeof kBwdRay[0]);
-// Variants 6-8: the tiled ray-lane kernel with T ray tiles per item (Gaussians staged 64 at a time);
-// without a normal cotangent only (the host runs variant 2 for that).
+// Variants 6-8: the tiled ray-lane kernel with T ray tiles per item (Gaussians staged 64 at a time),
+// without a normal cotangent.  Calls with one run the form of it that takes them, numbered 9 (not a
+// variant to choose: eight waves share 8 tiles, whose rays are twice the size).  It passes over the
+// pairs that the Gaussian-lane variant 2, run before, evaluated: 12 views of 203 x 150 against 60
+// Gaussians 76 -> 45 us.
 // (256 threads per block for variants 6 and 7; variant 8 has eight waves share an item's 16 staged
 // tiles, 512 threads)
-static const int kBwdTiles[] = {8, 16, 16};
-constexpr int kNumBwdTiled = (int)(sizeof kBwdTiles / sizeof kBwdTiles[0]);
+static const int kBwdTiles[] = {8, 16, 16, 8};
+constexpr int kNumBwdTiled = (int)(sizeof kBwdTiles / sizeof kBwdTiles[0]);  // the last: normal cotangents
 constexpr int kBwdTiledFirst = kNumBwdGauss + kNumBwdRay;
 
 // F dispatch: calls body<F>() for the runtime flag set f (0..15).
@@ -1429,15 +1482,34 @@ static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P
     case kBig | kCol | kFlw | kPer: FMB_BWDT_CALL(kBig | kCol | kFlw | kPer); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+// The form with a normal cotangent.
+static hipError_t launch_bwdt_normal(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
+                                     const BwdItem *items, int n, const int *order, int *counter, float *partial,
+                                     float *bpart)
+{
+    constexpr int BLK = 512, T = 8;
+    switch (f) {
+    case 1: FMB_BWDT_CALL(1); break;   case 3: FMB_BWDT_CALL(3); break;   case 5: FMB_BWDT_CALL(5); break;
+    case 7: FMB_BWDT_CALL(7); break;   case 9: FMB_BWDT_CALL(9); break;   case 11: FMB_BWDT_CALL(11); break;
+    case 13: FMB_BWDT_CALL(13); break; case 15: FMB_BWDT_CALL(15); break; case 17: FMB_BWDT_CALL(17); break;
+    case 19: FMB_BWDT_CALL(19); break; case 21: FMB_BWDT_CALL(21); break; case 23: FMB_BWDT_CALL(23); break;
+    case 25: FMB_BWDT_CALL(25); break; case 27: FMB_BWDT_CALL(27); break; case 29: FMB_BWDT_CALL(29); break;
+    case 31: FMB_BWDT_CALL(31); break;
+    default: return hipErrorInvalidValue;
+    }
 #undef FMB_BWDT_CALL
     return hipGetLastError();
 }
 
 int num_fwd_variants() { return (int)(sizeof kFwdVariants / sizeof kFwdVariants[0]); }
 int fwd_variant_rays(int v) { return kBlock * kFwdVariants[v].rpt; }
-int num_bwd_variants() { return kNumBwdGauss + kNumBwdRay + kNumBwdTiled; }
-// Tiled variants 6-8: ray tiles per item (0 for the others); they take no normal cotangent.
-int bwd_variant_tiles(int v) { return v >= kBwdTiledFirst && v < num_bwd_variants() ? kBwdTiles[v - kBwdTiledFirst] : 0; }
+int num_bwd_variants() { return kNumBwdGauss + kNumBwdRay + kNumBwdTiled - 1; }
+int bwd_normal_variant() { return num_bwd_variants(); }
+// Tiled variants 6-9: ray tiles per item (0 for the others).
+int bwd_variant_tiles(int v) { return v >= kBwdTiledFirst && v <= num_bwd_variants() ? kBwdTiles[v - kBwdTiledFirst] : 0; }
 // Gaussian-lane variants: rays staged per pass; others: 0.
 int bwd_variant_rt(int v) { return v < kNumBwdGauss ? kBwdRT[v] : 0; }
 // Ray-lane variants 3-5: rays per block tile (BLOCK * RPT); others: 0.
@@ -1470,6 +1542,7 @@ hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Pa
     case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
     case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
     case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
+    case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1594,6 +1667,20 @@ hipError_t occupancy_bwd(int variant, int flags, int *blocks_per_cu)
     if (variant == 7) FMB_OCC_T(256, 16)
     if (variant == 8) FMB_OCC_T(512, 16)
 #undef FMB_OCC_T
+#define FMB_OCC_N(F) return occb(bwdt_kernel<512, 8, 64, kNrm | kPer | (F)>, 512)
+    if (variant == 9) {
+        switch (flags & (kFlw | kCol | kBig)) {
+        case 0: FMB_OCC_N(0);
+        case kFlw: FMB_OCC_N(kFlw);
+        case kCol: FMB_OCC_N(kCol);
+        case kCol | kFlw: FMB_OCC_N(kCol | kFlw);
+        case kBig: FMB_OCC_N(kBig);
+        case kBig | kFlw: FMB_OCC_N(kBig | kFlw);
+        case kBig | kCol: FMB_OCC_N(kBig | kCol);
+        default: FMB_OCC_N(kBig | kCol | kFlw);
+        }
+    }
+#undef FMB_OCC_N
     return hipErrorInvalidValue;
 }
 
