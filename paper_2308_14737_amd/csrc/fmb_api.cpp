@@ -34,11 +34,12 @@ int block_size();
 hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const FwdOut &O,
                       const FwdItem *items, int n, const int *order, int *counter);
 hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart);
+                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart,
+                      unsigned long long *masks);
 hipError_t launch_fin(int n_tasks, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks,
-                      const FinGroup *groups, const float *partial, const float *bpart, double *stage,
-                      double *stage_beta, float *g_means, float *g_prec, float *g_weights, float *g_colors,
+                      const FinGroup *groups, const float *partial, const float *bpart, const unsigned long long *masks,
+                      int rec, double *stage, double *stage_beta, float *g_means, float *g_prec, float *g_weights, float *g_colors,
                       float *g_betas);
 hipError_t launch_fill(int *p, int n, int value, hipStream_t st);
 hipError_t launch_loss(int p, const float *depth, const float *alpha, const float *flow, const float *color,
@@ -256,8 +257,10 @@ struct Job {
     int n_bitems_small = 0;  // compositing: how many of the items in order are small scenes'
     int bwd_variant = 8, bwd_built = -1, n_bitems = 0, n_tasks = 0, n_groups = 0;
     int fin_max_gc = 1, fin_max_nval = 1;  // largest chunk and first-stage record (finalize grid)
-    DevBuf d_bitems, d_border, d_tasks, d_groups, d_partial, d_bpart, d_stage, d_stage_beta;
+    DevBuf d_bitems, d_border, d_tasks, d_groups, d_partial, d_bpart, d_stage, d_stage_beta, d_masks;
+    int bwd_rec = kPartial;      // floats per partial record
     size_t partial_floats = 0;
+    size_t mask_words = 0;       // 64-bit words of the items' record masks (0: every record is written)
 
     hipGraphExec_t gexec[2] = {nullptr, nullptr};  // captured forward, backward
 
@@ -428,6 +431,8 @@ struct Job {
         std::vector<FinGroup> groups;
         size_t poff = 0, soff = 0;  // partial floats, first-stage doubles
         int max_gc = 1, max_nval = 1;
+        int rec = kPartial;
+        size_t mask_words = 0;
         int n_small = 0;  // compositing: leading items of `order` that are small scenes'
     };
     BwdPlan na_plan;  // the plan of the last fmb_backward_noalloc call (host memory only)
@@ -451,6 +456,9 @@ struct Job {
         fin_max_nval = pl.max_nval;
         HIPCHK(d_partial.ensure(std::max<size_t>(pl.poff, 1) * sizeof(float)));
         HIPCHK(d_bpart.ensure(std::max<size_t>(2 * pl.items.size(), 2) * sizeof(float)));
+        if (pl.mask_words) HIPCHK(d_masks.ensure(pl.mask_words * sizeof(unsigned long long)));
+        mask_words = pl.mask_words;
+        bwd_rec = pl.rec;
         partial_floats = pl.poff;
         n_bitems = (int)pl.items.size();
         n_bitems_small = pl.n_small;
@@ -541,7 +549,9 @@ struct Job {
         std::vector<FinTask> tasks;
         std::vector<int> tasks_item_begin, tasks_item_end;
         std::vector<double> cost;
-        size_t poff = 0;
+        size_t poff = 0, moff = 0;
+        // the tiled kernels' form for large scenes writes only the records that an item touched
+        const bool masked = !comp && tiles > 0 && max_scene_n() > block_size();
         for (int s = 0; s < S; ++s) {
             const int gc = gcs[s], sl = sls[s], span = spans[s];
             const int n = scenes[s].n;
@@ -568,6 +578,10 @@ struct Job {
                         it.poff = (int)poff;
                         it.seq = (int)items.size();
                         poff += (size_t)gc * rec;
+                        if (masked) {
+                            it.moff = (int)moff;  // (less than poff)
+                            moff += (size_t)(gc + 63) / 64;
+                        }
                         items.push_back(it);
                         cost.push_back((double)t.gc * (tiles > 0 ? std::min<int64_t>(64LL * span, hw - 64LL * r0)
                                                                  : std::min(span, hw - r0)));
@@ -590,14 +604,22 @@ struct Job {
             }
             const int ib = tasks_item_begin[&t - &tasks[0]], ie = tasks_item_end[&t - &tasks[0]];
             t.group_begin = (int)groups.size();
-            // about sqrt(items) items per group so both stages sum similar counts
-            const int gsz = std::max(kGroupItems, (int)std::ceil(std::sqrt((double)(ie - ib))));
+            // About sqrt(items) items per group so both stages sum similar counts; more of a large scene
+            // whose records fit the fixed workspace of fmb_backward_noalloc, so that the items' masks
+            // take no more room than the groups saved.
+            const double root = std::sqrt((double)(ie - ib));
+            int gsz = std::max(kGroupItems, (int)std::ceil(root));
+            if (!comp && tiles > 0 && t.gc > block_size() &&
+                (double)(ie - ib) * t.gc * rec * sizeof(float) <= (double)FMB_NOALLOC_SCRATCH_BYTES)
+                gsz = std::max(48, (int)std::ceil(1.5 * root));
             for (int a = ib; a < ie; a += gsz) {
                 FinGroup g{};
                 g.item_begin = a;
                 g.item_end = std::min(ie, a + gsz);
                 g.poff = items[a].poff;
                 g.nval = items[a].gc * rec;
+                g.moff = items[a].moff;
+                g.words = masked ? (items[a].gc + 63) / 64 : 0;
                 g.soff = (int)soff;
                 soff += (size_t)g.nval;
                 groups.push_back(g);
@@ -632,6 +654,8 @@ struct Job {
         pl.groups = std::move(groups);
         pl.poff = poff;
         pl.soff = soff;
+        pl.rec = rec;
+        pl.mask_words = moff;
         return FMB_OK;
     }
 
@@ -835,12 +859,14 @@ struct Job {
             TimedSpan tb(st, 1);
             HIPCHK(launch_bwd(bv, flags, grid, st, prm, I, d_bitems.as<BwdItem>(), n_bitems,
                               persist ? d_border.as<int>() : nullptr, persist ? d_counter.as<int>() + 1 : nullptr,
-                              d_partial.as<float>(), d_bpart.as<float>()));
+                              d_partial.as<float>(), d_bpart.as<float>(),
+                              mask_words ? d_masks.as<unsigned long long>() : nullptr));
             tb.stop();
         }
         TimedSpan tf(st, 2);
         HIPCHK(launch_fin(n_tasks, n_groups, fin_max_gc, fin_max_nval, st, prm, d_tasks.as<FinTask>(), d_groups.as<FinGroup>(),
-                          d_partial.as<float>(), d_bpart.as<float>(), d_stage.as<double>(),
+                          d_partial.as<float>(), d_bpart.as<float>(),
+                          mask_words ? d_masks.as<unsigned long long>() : nullptr, bwd_rec, d_stage.as<double>(),
                           d_stage_beta.as<double>(), G.means, G.prec, G.weights, G.colors, G.betas));
         tf.stop();
         return FMB_OK;
@@ -875,6 +901,7 @@ struct Job {
         const size_t o_order = model == FMB_MODEL_COMPOSITE ? take(pl.order.size() * sizeof(int)) : 0;
         const size_t o_tasks = take(pl.tasks.size() * sizeof(FinTask));
         const size_t o_groups = take(pl.groups.size() * sizeof(FinGroup));
+        const size_t o_masks = pl.mask_words ? take(pl.mask_words * sizeof(unsigned long long)) : 0;
         const size_t o_part = take(std::max<size_t>(pl.poff, 1) * sizeof(float));
         const size_t o_bpart = take(std::max<size_t>(2 * pl.items.size(), 2) * sizeof(float));
         const size_t o_stage = take(std::max<size_t>(pl.soff, 1) * sizeof(double));
@@ -900,6 +927,7 @@ struct Job {
         const BwdItem *items = reinterpret_cast<const BwdItem *>(b + o_items);
         float *part = reinterpret_cast<float *>(b + o_part);
         float *bpart = reinterpret_cast<float *>(b + o_bpart);
+        unsigned long long *masks = pl.mask_words ? reinterpret_cast<unsigned long long *>(b + o_masks) : nullptr;
         const int n_items = (int)pl.items.size();
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
@@ -909,13 +937,13 @@ struct Job {
         } else {
             TimedSpan tb(st, 1);
             HIPCHK(launch_bwd(bv, blend_bwd_flags(I, false, bv), n_items, st, prm, I, items, n_items, nullptr, nullptr,
-                              part, bpart));
+                              part, bpart, masks));
             tb.stop();
         }
         TimedSpan tf(st, 2);
         HIPCHK(launch_fin((int)pl.tasks.size(), (int)pl.groups.size(), pl.max_gc, pl.max_nval, st, prm,
                           reinterpret_cast<const FinTask *>(b + o_tasks), reinterpret_cast<const FinGroup *>(b + o_groups),
-                          part, bpart, reinterpret_cast<double *>(b + o_stage), reinterpret_cast<double *>(b + o_sbeta),
+                          part, bpart, masks, pl.rec, reinterpret_cast<double *>(b + o_stage), reinterpret_cast<double *>(b + o_sbeta),
                           G.means, G.prec, G.weights, G.colors, G.betas));
         tf.stop();
         return FMB_OK;

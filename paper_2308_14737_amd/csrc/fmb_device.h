@@ -143,9 +143,9 @@ __device__ __forceinline__ void make_entry(const float *__restrict__ mu, const f
     out[3] = make_float4((float)c0, (float)c1, (float)c2, log2f(lam));
 }
 
-// The entry and, as a fifth float4, (|U mu'|^2, |Sigma^-1 mu'|_1, 0, 0): the terms of the one-FMA
-// estimate of the squared Mahalanobis distance m = |U mu'|^2 - (v.c) t and of its error bound
-// (pair_m_low).
+// The entry and, as a fifth float4, (|U mu'|^2, |Sigma^-1 mu'|_1, |U mu'|^2, 0): the terms of the
+// one-FMA estimate of the squared Mahalanobis distance m = |U mu'|^2 - (v.c) t and of its error bound
+// (pair_m_low, tile_bounds).
 __device__ __forceinline__ void make_entry_est(const float *__restrict__ mu, const float *__restrict__ u,
                                                float lam, const double o[3], float4 out[5])
 {
@@ -156,8 +156,30 @@ __device__ __forceinline__ void make_entry_est(const float *__restrict__ mu, con
     const double b1 = U11 * m1 + U12 * m2;
     const double b2 = U22 * m2;
     const double c0 = U00 * b0, c1 = U01 * b0 + U11 * b1, c2 = U02 * b0 + U12 * b1 + U22 * b2;
-    out[4] = make_float4((float)(b0 * b0 + b1 * b1 + b2 * b2), (float)(fabs(c0) + fabs(c1) + fabs(c2)), 0.0f,
-                         0.0f);
+    const float bb = (float)(b0 * b0 + b1 * b1 + b2 * b2);
+    out[4] = make_float4(bb, (float)(fabs(c0) + fabs(c1) + fabs(c2)), bb, 0.0f);
+}
+
+// The entry for the bounds alone, formed in FP32 (mu' from FP64): U, c, log2 lambda and the estimate
+// terms, with the error terms formed from absolute values, so that they bound the rounding of the
+// FP32 sums too: c and |U mu'|^2 err by a few 2^-24 of |U|^T |U| |mu'| and of its square, against 2^-17 of
+// them in the bounds.  A third of the FP64 entry's instructions, which run at half rate: bounding each of
+// 10 000 Gaussians on every item was a third of the time of such a scene.
+__device__ __forceinline__ void make_bound_entry(const float *__restrict__ mu, const float *__restrict__ u, float lam,
+                                                 const double o[3], Ent &g, float4 &est)
+{
+    const float m0 = (float)((double)mu[0] - o[0]), m1 = (float)((double)mu[1] - o[1]), m2 = (float)((double)mu[2] - o[2]);
+    g.u00 = u[0]; g.u01 = u[1]; g.u02 = u[2]; g.u11 = u[3]; g.u12 = u[4]; g.u22 = u[5];
+    const float b0 = fmaf(g.u00, m0, fmaf(g.u01, m1, g.u02 * m2)), b1 = fmaf(g.u11, m1, g.u12 * m2), b2 = g.u22 * m2;
+    const float n0 = fabsf(m0), n1 = fabsf(m1), n2 = fabsf(m2);
+    const float a0 = fmaf(fabsf(g.u00), n0, fmaf(fabsf(g.u01), n1, fabsf(g.u02) * n2));
+    const float a1 = fmaf(fabsf(g.u11), n1, fabsf(g.u12) * n2), a2 = fabsf(b2);
+    g.c0 = g.u00 * b0;
+    g.c1 = fmaf(g.u01, b0, g.u11 * b1);
+    g.c2 = fmaf(g.u02, b0, fmaf(g.u12, b1, g.u22 * b2));
+    g.l2l = log2f(lam);
+    const float ca = fmaf(fabsf(g.u00) + fabsf(g.u01) + fabsf(g.u02), a0, fmaf(fabsf(g.u11) + fabsf(g.u12), a1, fabsf(g.u22) * a2));
+    est = make_float4(fmaf(b0, b0, fmaf(b1, b1, b2 * b2)), ca, fmaf(a0, a0, fmaf(a1, a1, a2 * a2)), 0.0f);
 }
 
 // Unit direction of the ray through the centre of pixel (row, col).
@@ -398,19 +420,21 @@ __device__ __forceinline__ PairBounds tile_bounds(const Ent &g, const float4 &es
     const float f = fmaf(tb.c.w, na, sqrt_(f2)) * kUp;
     // (selects, not fmin / fmax, which would drop a NaN: a bound of NaN keeps the pair)
     const float s0 = f * ra, s = s0 > 1.0f ? 1.0f : s0, co = sqrt_(fmaf(-s, s, 1.0f));
-    const float at = fabsf(qc.t);
-    const float mid = fmaf(-vc, qc.t, est.x), err = kErr * fmaf(est.y, at, est.x);
+    // the centre ray's |t| from both sides (v.c errs by a few 2^-24 of est.y)
+    const float terr = kErr * est.y * qc.raa, at = fabsf(qc.t) + terr, atl = fabsf(qc.t) - terr;
+    const float mid = fmaf(-vc, qc.t, est.x), err = kErr * fmaf(est.y, at, est.z);
     const float ml = mid - err, mh = mid + err;
-    const float sl = sqrt_(ml < 0.0f ? 0.0f : ml), sh = sqrt_(mh < 0.0f ? 0.0f : mh), nb = sqrt_(est.x);
-    const float gs = at * fminf(f, na), gc = at * na * co;  // |U mu'| cos(theta_c) sin(psi), cos(psi)
+    const float sl = sqrt_(ml < 0.0f ? 0.0f : ml), sh = sqrt_(mh < 0.0f ? 0.0f : mh), nb = sqrt_(fmaf(kErr, est.z, est.x));
+    // |U mu'| cos(theta_c) sin(psi) from above, cos(psi) from above and below
+    const float gs = at * fminf(f, na), gc = at * na * co, gl = atl * na * co;
     const float l0 = fmaf(sl * co, kDown, -gs * kUp), lo = l0 < 0.0f ? 0.0f : l0;
-    const float hi = (sh * s < gc && s < 0.999f ? fmaf(sh, co, gs) : nb) * kUp;
+    const float hi = (sh * s < gl && s < 0.999f ? fmaf(sh, co, gs) : nb) * kUp;
     PairBounds r;
     r.d2_hi = fmaf(hm, lo * lo, g.l2l) + 1e-3f;
     r.d2_lo = fmaf(hm, hi * hi, g.l2l) - 1e-3f;
     // |t| in [(gc - sh s) / (|U c| + F), (gc + sh s) / (|U c| - F)], of the centre ray's sign unless the
     // lower end is negative; the upper numerator is |U mu'| where some ray's theta can be 0
-    const float nlo = fmaf(-sh, s, gc), rm = rcp_(na - f);
+    const float nlo = fmaf(-sh, s, gl), rm = rcp_(na - f);
     const float tlo = (nlo >= 0.0f ? nlo * rcp_(na + f) : nlo * rm) * (nlo >= 0.0f ? 1.0f - 1e-4f : 1.0f + 1e-4f);
     const float thi = (lo > 0.0f ? fmaf(sh, s, gc) : nb) * rm * (1.0f + 1e-4f);
     const bool open = s >= 0.999f;  // the depth is not bounded (a Gaussian of weight 0 weighs 0 all the same)

@@ -61,7 +61,7 @@ struct CompItem {      // compositing forward: a run of ray tiles of one view
     int32_t tile0, span;
 };
 
-struct BwdItem {       // 32 bytes
+struct BwdItem {       // 36 bytes
     int32_t view;
     int32_t ray0;      // first local ray of the span
     int32_t span;      // rays in the span (clipped to the view by the kernel)
@@ -70,6 +70,7 @@ struct BwdItem {       // 32 bytes
     int32_t slots;     // ray slots: thread t works on Gaussian t % gc, rays t / gc mod slots
     int32_t poff;      // offset (floats) of this item's partial record [gc][kPartial]
     int32_t seq;       // canonical item index (beta partials)
+    int32_t moff;      // tiled kernels with a large scene: first 64-bit word of the item's mask of records
 };
 
 struct FinTask {       // one per (scene, Gaussian chunk)
@@ -90,7 +91,8 @@ struct FinGroup {
     int32_t poff;      // partial offset (floats) of item_begin; items of a chunk are contiguous
     int32_t nval;      // gc * kPartial values per item (gc = item chunk size)
     int32_t soff;      // offset (doubles) of the group's sums in the stage buffer
-    int32_t pad[3];
+    int32_t moff, words;  // the first item's mask and the words of each (items of a chunk are contiguous)
+    int32_t pad;
 };
 constexpr int kGroupItems = 32;  // minimum items per first-stage group
 

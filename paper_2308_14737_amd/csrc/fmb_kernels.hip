@@ -118,6 +118,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
         // Smaller scenes take one round of all their Gaussians (and launches without kBig, whose
         // scenes are all small, have no such rounds).
         const bool sparse = BIG && sr.n > BLOCK;
+        TileBox ibox;
         for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
           int total = sr.n;
           if (sparse) {
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             __syncthreads();  // the previous round's list and staged tile are consumed
             if (lane == 0) wmin[wave] = make_float2(mm, dm);
             __syncthreads();  // tile boxes and least maxima visible
-            const TileBox ibox = wave_box_of(tbox, NW * RPT, lane, e);
+            if (rb == 0) ibox = wave_box_of(tbox, NW * RPT, lane, e);
             float imin = INFINITY, idm = INFINITY;
             for (int w = 0; w < NW; ++w) {
                 imin = fminf(imin, wmin[w].x);
@@ -143,9 +144,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             bool keep = false;
             if (gl < sr.n) {
                 const int gg = sr.gauss_off + gl;
-                float4 q[5];
-                make_entry_est(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
-                const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], ibox, bl.hm, bl.b1, bl.nc2);
+                Ent ge;
+                float4 ee;
+                make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
+                const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
                 // (written so that a NaN bound keeps the Gaussian)
                 keep = !(b1_pos && pb.d2_hi < dcut && pb.z_hi - imin < wskip);
             }
@@ -705,7 +707,8 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
 template <int BLOCK, int T, int TG, int F>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm) ? 4 : 6))) void bwdt_kernel(
     Params P, BwdIn I, const BwdItem *__restrict__ items, int n_items, const int *__restrict__ order,
-    int *__restrict__ counter, float *__restrict__ partial, float *__restrict__ beta_partial)
+    int *__restrict__ counter, float *__restrict__ partial, float *__restrict__ beta_partial,
+    unsigned long long *__restrict__ masks)
 {
     constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int NW = BLOCK / 64;
@@ -800,37 +803,37 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
         // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
         // round is first bounded on the whole item (tile_bounds on a box around all its tiles,
         // against their least normaliser), and only those that can matter on some tile are staged,
-        // TG at a time, in scene order (slist: their scene-local indices); the others' records are
-        // zero, as the per-tile bounds would have left them.  Smaller scenes take one round of all
+        // TG at a time, in scene order (slist: their scene-local indices); the others' records would be
+        // zero, as the per-tile bounds would have left them, and are not written: a bit per
+        // Gaussian (masks) tells the finalize which of the item's records are.  Smaller scenes take one round of all
         // their Gaussians in order (and launches without kBig, whose scenes are all small, have no
         // such rounds).
         const bool sparse = BIG && sr.n > BLOCK;
+        TileBox ibox;
+        if (BIG && !sparse && 64 * tid < sr.n) masks[item.moff + tid] = ~0ull;  // every record is written
         for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
           int total = sr.n;
           if (sparse) {
             __syncthreads();  // boxes visible; the previous round's list and entries are consumed
             float inorm = INFINITY;
             for (int t = 0; t < nt; ++t) inorm = fminf(inorm, tnorm[t]);
-            const TileBox ibox = wave_box_of(tbox, nt, lane, e);
-            // the round's records start as zeros, written contiguously by all threads (the
-            // survivors' are overwritten after the barriers below)
-            {
-                float *dst = partial + item.poff + REC * rb;
-                const int nz = REC * min(BLOCK, sr.n - rb);
-                for (int c = tid; c < nz; c += BLOCK) dst[c] = 0.0f;
-            }
+            if (rb == 0) ibox = wave_box_of(tbox, nt, lane, e);
             const int gl = rb + tid;
             bool keep = false;
             if (gl < sr.n) {
                 const int gg = sr.gauss_off + gl;
-                float4 q[5];
-                make_entry_est(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
-                const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], ibox, bl.hm, bl.b1, bl.nc2);
+                Ent ge;
+                float4 ee;
+                make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
+                const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
                 // (written so that a NaN bound keeps the Gaussian)
                 keep = !(b1_pos && pb.z_hi - inorm < kSkipLog2 && pb.d2_hi < kDensSkipLog2);
             }
             const unsigned long long bal = wave_ballot(keep);
-            if (lane == 0) wcnt[wave] = __popcll(bal);
+            if (lane == 0) {
+                wcnt[wave] = __popcll(bal);
+                if (rb + 64 * wave < sr.n) masks[item.moff + rb / 64 + wave] = bal;
+            }
             __syncthreads();
             int off = 0;
             total = 0;
@@ -1044,6 +1047,75 @@ __global__ __launch_bounds__(BLOCK) void fin1_kernel(const FinGroup *__restrict_
         stage[gr.soff + v] = ordered_sum(partial + gr.poff + v, n, gr.nval);
     if (blockIdx.y == 0 && tid < 2)
         stage_beta[2 * blockIdx.x + tid] = ordered_sum(beta_partial + 2 * gr.item_begin + tid, n, 2);
+}
+
+// First stage of large scenes' items (FinGroup::words: 64-bit words of the items' masks): a lane per
+// Gaussian sums, in item order, the records that the items wrote.  An item of 16 tiles touches a few
+// per cent of 10 000 clustered Gaussians, so the stage reads the masks and little else: 197 -> 42 us for
+// one 1920 x 1080 view, whose 0.8 GB of records were all written and read before.
+template <int BLOCK, int REC>
+__device__ __forceinline__ void fin1_sparse(const FinGroup &gr, const unsigned long long *__restrict__ masks,
+                                            const float *__restrict__ partial, double *__restrict__ stage, double *sums)
+{
+    const int lane = threadIdx.x & 63, gc = gr.nval / REC;
+    for (int base = blockIdx.y * BLOCK + (threadIdx.x & ~63); base < gc; base += BLOCK * gridDim.y) {
+        const unsigned long long *mw = masks + gr.moff + base / 64;
+        const float *rp = partial + gr.poff + REC * (base + lane);
+        const int n = gr.item_end - gr.item_begin;
+        double s[REC];
+#pragma unroll
+        for (int c = 0; c < REC; ++c) s[c] = 0.0;
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            // lane l holds the word of item i0 + l
+            const unsigned long long own = i0 + lane < n ? mw[(size_t)(i0 + lane) * gr.words] : 0ull;
+            unsigned long long any = wave_ballot(own != 0ull);
+            // Four items' records in flight, added in item order.  A lane whose record was not written
+            // loads the buffer's first one instead (one cache line for all of them) and adds zero, so
+            // that the loads take no branch.
+            while (any) {
+                float x[4][REC];
+                bool mine[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = any ? __builtin_ctzll(any) : 0;
+                    const unsigned lo = __builtin_amdgcn_readlane((unsigned)own, k), hi = __builtin_amdgcn_readlane((unsigned)(own >> 32), k);
+                    mine[u] = any && base + lane < gc && ((((unsigned long long)hi << 32) | lo) >> lane & 1ull);
+                    any &= any - 1;
+                    const float *r = mine[u] ? rp + (size_t)(i0 + k) * gr.nval : partial;
+#pragma unroll
+                    for (int c = 0; c < REC; ++c) x[u][c] = r[c];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int c = 0; c < REC; ++c) s[c] += mine[u] ? (double)x[u][c] : 0.0;
+            }
+        }
+        // through LDS, so that the wave writes its sums in one contiguous run
+#pragma unroll
+        for (int c = 0; c < REC; ++c) sums[REC * lane + c] = s[c];
+        __builtin_amdgcn_wave_barrier();
+        const int nv = REC * min(64, gc - base);
+        for (int v = lane; v < nv; v += 64) stage[gr.soff + REC * base + v] = sums[v];
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void fin1s_kernel(const FinGroup *__restrict__ groups, const float *__restrict__ partial,
+                                                     const float *__restrict__ beta_partial,
+                                                     const unsigned long long *__restrict__ masks, int rec,
+                                                     double *__restrict__ stage, double *__restrict__ stage_beta)
+{
+    __shared__ double sums[BLOCK / 64][64 * kPartialColor];
+    const FinGroup gr = groups[blockIdx.x];
+    if (rec == kPartial)
+        fin1_sparse<BLOCK, kPartial>(gr, masks, partial, stage, sums[threadIdx.x >> 6]);
+    else
+        fin1_sparse<BLOCK, kPartialColor>(gr, masks, partial, stage, sums[threadIdx.x >> 6]);
+    if (blockIdx.y == 0 && threadIdx.x < 2)
+        stage_beta[2 * blockIdx.x + threadIdx.x] =
+            ordered_sum(beta_partial + 2 * gr.item_begin + threadIdx.x, gr.item_end - gr.item_begin, 2);
 }
 
 // Second stage: block (task, slice) finishes kFinSlice Gaussians of a chunk.
@@ -1458,11 +1530,11 @@ static hipError_t launch_bwd_v(int f, int grid, hipStream_t st, const Params &P,
 template <int BLK, int T>
 static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
                                 const BwdItem *items, int n, const int *order, int *counter, float *partial,
-                                float *bpart)
+                                float *bpart, unsigned long long *masks)
 {
 #define FMB_BWDT_CALL(F)                                                                                   \
     hipLaunchKernelGGL((bwdt_kernel<BLK, T, 64, F>), dim3(grid), dim3(BLK), 0, st, P, I, items, n, order,   \
-                       counter, partial, bpart)
+                       counter, partial, bpart, masks)
     switch (f) {
     case 0: FMB_BWDT_CALL(0); break;
     case kFlw: FMB_BWDT_CALL(kFlw); break;
@@ -1488,7 +1560,7 @@ static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P
 // The form with a normal cotangent.
 static hipError_t launch_bwdt_normal(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
                                      const BwdItem *items, int n, const int *order, int *counter, float *partial,
-                                     float *bpart)
+                                     float *bpart, unsigned long long *masks)
 {
     constexpr int BLK = 512, T = 8;
     switch (f) {
@@ -1530,7 +1602,8 @@ hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Pa
 }
 
 hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart)
+                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart,
+                      unsigned long long *masks)
 {
     switch (variant) {
     case 0: return launch_bwd_v<64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
@@ -1539,25 +1612,30 @@ hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Pa
     case 3: return launch_bwdr_v<2, 64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
     case 4: return launch_bwdr_v<4, 64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
     case 5: return launch_bwdr_v<4, 128>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
+    case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
+    case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
+    case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
+    case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
     default: return hipErrorInvalidValue;
     }
 }
 
+// masks: the items' record masks (or NULL: every record is written), rec: floats per record.
 // max_gc: the largest chunk of any task (a whole scene for the ray-lane backward); max_nval: the
 // largest first-stage record of any group.
 hipError_t launch_fin(int n_tasks, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks, const FinGroup *groups, const float *partial, const float *bpart,
-                      double *stage, double *stage_beta, float *g_means, float *g_prec, float *g_weights,
+                      const unsigned long long *masks, int rec, double *stage, double *stage_beta, float *g_means, float *g_prec, float *g_weights,
                       float *g_colors, float *g_betas)
 {
     if (max_gc < 1 || max_nval < 1) return hipErrorInvalidValue;
     const int slices = (max_nval + 255) / 256 < 65535 ? (max_nval + 255) / 256 : 65535;
-    hipLaunchKernelGGL((fin1_kernel<256>), dim3(n_groups, slices), dim3(256), 0, st, groups, partial, bpart, stage,
-                       stage_beta);
+    if (masks)
+        hipLaunchKernelGGL((fin1s_kernel<256>), dim3(n_groups, (max_gc + 255) / 256 < 65535 ? (max_gc + 255) / 256 : 65535),
+                           dim3(256), 0, st, groups, partial, bpart, masks, rec, stage, stage_beta);
+    else
+        hipLaunchKernelGGL((fin1_kernel<256>), dim3(n_groups, slices), dim3(256), 0, st, groups, partial, bpart, stage,
+                           stage_beta);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int gslices = (max_gc + kFinSlice - 1) / kFinSlice;

@@ -93,3 +93,72 @@ def test_alpha_is_relatively_exact(n):
     err = np.abs(a[at] / r[at] - 1.0).max()
     print(f"[alpha] N={n}: {at.sum()} rays, relative error {err:.2e}", flush=True)
     assert err <= 8e-5 + n * 2.0 ** -48 / 1e-9 + 1e-6, err
+
+
+def _f32_bounds(u, mu, lam, box, hm):
+    """tile_bounds' log2 density bounds in FP32, from the FP32 entry that the pre-culls use
+    (make_bound_entry): u the packed factor, mu the mean relative to the camera, box (c, Z, ex, X, ey, Y)."""
+    f = np.float32
+    u00, u01, u02, u11, u12, u22 = (f(x) for x in u)
+    m = mu.astype(f)
+    c, Z, ex, X, ey, Y = [np.asarray(k, dtype=f) for k in box]
+
+    def mul(a):
+        return np.array([u00 * a[0] + u01 * a[1] + u02 * a[2], u11 * a[1] + u12 * a[2], u22 * a[2]], f)
+
+    b, n = mul(m), np.abs(m)
+    a0 = abs(u00) * n[0] + abs(u01) * n[1] + abs(u02) * n[2]
+    ab = np.array([a0, abs(u11) * n[1] + abs(u12) * n[2], abs(b[2])], f)
+    cc = np.array([u00 * b[0], u01 * b[0] + u11 * b[1], u02 * b[0] + u12 * b[1] + u22 * b[2]], f)
+    est_x, est_z = (b * b).sum(dtype=f), (ab * ab).sum(dtype=f)
+    est_y = (abs(u00) + abs(u01) + abs(u02)) * ab[0] + (abs(u11) + abs(u12)) * ab[1] + abs(u22) * ab[2]
+    err, up, down = f(2.0 ** -17), f(1 + 2e-5), f(1 - 2e-5)
+    a = mul(c)
+    aa, vc = (a * a).sum(dtype=f), (c * cc).sum(dtype=f)
+    t = vc / aa
+    na = np.sqrt(aa)
+    p, q = mul(ex), mul(ey)
+    fr = (Z * na + np.sqrt(X * X * (p @ p) + Y * Y * (q @ q) + f(2) * X * Y * abs(p @ q))) * up
+    s = min(fr / na, f(1))
+    co = np.sqrt(f(1) - s * s)
+    terr = err * est_y / aa
+    at, atl = abs(t) + terr, abs(t) - terr
+    mid, e = est_x - vc * t, err * (est_y * at + est_z)
+    sl, sh, nb = np.sqrt(max(mid - e, f(0))), np.sqrt(max(mid + e, f(0))), np.sqrt(est_x + err * est_z)
+    gs, gl = at * min(fr, na), atl * na * co
+    lo = max(sl * co * down - gs * up, f(0))
+    hi = (sh * co + gs if sh * s < gl and s < 0.999 else nb) * up
+    l2l = f(np.log2(lam))
+    return float(hm * lo * lo + l2l) + 1e-3, float(hm * hi * hi + l2l) - 1e-3
+
+
+def test_single_precision_bounds_hold():
+    """The FP32 entry and bounds with their slack terms, needles and discs seen edge on included."""
+    g = np.random.Generator(np.random.PCG64(23))
+    hm = -0.5 * np.log2(np.e)
+    near = 0
+    for k in range(500):
+        s = np.exp(g.uniform(np.log(0.003), np.log(0.6), 3))
+        r = _rotation(g)
+        U = np.linalg.cholesky(r @ np.diag(s ** -2.0) @ r.T).T
+        u = np.array([U[0, 0], U[0, 1], U[0, 2], U[1, 1], U[1, 2], U[2, 2]]).astype(np.float32)
+        U = np.array([[u[0], u[1], u[2]], [0, u[3], u[4]], [0, 0, u[5]]], dtype=np.float64)
+        c = g.standard_normal(3)
+        c /= np.linalg.norm(c)
+        ex = _rotation(g)[0]
+        ex -= (ex @ c) * c
+        ex /= np.linalg.norm(ex)
+        ey = np.cross(c, ex)
+        mu = g.uniform(0.3, 8.0) * c + s.max() * g.uniform(0, 6) * g.standard_normal(3)
+        h = np.exp(g.uniform(np.log(2e-4), np.log(0.05)))
+        v = c + g.uniform(-h, h, (64, 1)) * ex + g.uniform(-h, h, (64, 1)) * ey
+        v /= np.linalg.norm(v, axis=1, keepdims=True)
+        X, Y, Z = (np.abs((v - c) @ d).max() * (1 + 1e-5) + 5e-7 for d in (ex, ey, c))
+        lam = g.uniform(0.1, 2.0)
+        hi, lo = _f32_bounds(u, mu, lam, (c, Z, ex, X, ey, Y), hm)
+        a, b = v @ U.T, U @ mu
+        t = (a @ b) / (a * a).sum(1)
+        d2 = np.log2(lam) + hm * ((t[:, None] * a - b) ** 2).sum(1)
+        assert d2.max() <= hi and d2.min() >= lo, (k, lo, d2.min(), d2.max(), hi)
+        near += hi < d2.max() + 5
+    assert near > 200, near
