@@ -217,7 +217,7 @@ int fmb_backward_noalloc(fmb_scene *scene, const float *g_depth, const float *g_
 /* Batch of independent scenes (uneven Gaussian counts, view counts, resolutions) */
 /* ------------------------------------------------------------------------------ */
 
-/* Create a batch of s >= 1 scenes rendered together by persistent kernels.
+/* Create a batch of s >= 1 scenes rendered together, one launch per pass.
  *   n_host   host [s]: Gaussians per scene (>= 1); their parameters are concatenated
  *            scene after scene in means [sum n,3], prec [sum n,6], weights [sum n]
  *            (device); betas device [s,2]; eta host [s] (> 0).
@@ -240,8 +240,8 @@ int64_t fmb_batch_num_rays(const fmb_batch *batch);
 int64_t fmb_batch_ray_offset(const fmb_batch *batch, int32_t i);
 int64_t fmb_batch_gauss_offset(const fmb_batch *batch, int32_t i);
 
-/* Forward / backward over the whole batch with one persistent kernel each (work items
- * of (scene, view, ray tile) pulled from a device queue, largest first).  Arguments as
+/* Forward / backward over the whole batch with one kernel each (a block per work item of
+ * (scene, view, ray tiles), largest first).  Arguments as
  * fmb_render / fmb_backward with concatenated arrays; g_betas is [s,2]. */
 int fmb_batch_forward(fmb_batch *batch, float *depth, float *alpha, float *normal, float *flow,
                       float *color, float *stash, void *stream);
@@ -270,7 +270,7 @@ int fmb_batch_backward(fmb_batch *batch, const float *g_depth, const float *g_al
  * replays are seen (a loss can fill the cotangents between the two replays).
  * fmb_batch_graph_launch replays the forward (which = 0), the backward (1) or both (2)
  * on `stream`; FMB_ERR_STATE if nothing was captured.  Replays of one batch must not
- * overlap (they share the batch's work counters and partial-gradient workspace).
+ * overlap (they share the batch's partial-gradient workspace).
  * The graphs are dropped (the next fmb_batch_graph_launch returns FMB_ERR_STATE until the
  * batch is captured again) by every call that changes what they launch: fmb_autotune,
  * fmb_set_config, fmb_set_model, fmb_set_colors and fmb_set_flow_pose2 with a changed
@@ -362,10 +362,10 @@ int fmb_split_gaussians(int32_t n, const float *means, const float *prec, const 
 
 /* Pin the launch configuration of a scene or batch (exactly one non-NULL) instead of
  * autotuning it: forward variant in [0, 4), backward variant in [0, 9) (see
- * fmb_get_config), persistent-grid multipliers 1 or 2.  Every variant computes the same
- * results to rounding; captured graphs are dropped.  Until this call or fmb_autotune, a job
- * takes forward variant 1 (512 rays per item), or 0 (256) when it has fewer rays than two
- * 512-ray items per compute unit, and backward variant 8.  Errors: FMB_ERR_INVALID_ARG. */
+ * fmb_get_config), grid multipliers 1 or 2 (accepted and reported, without effect: a
+ * block takes one item).  Every variant computes the same results to rounding; captured graphs are dropped.  Until this call or fmb_autotune, a job
+ * takes forward variant 0 (256 rays per item), 1 (512) or 3 (1024) by its number of rays, and
+ * backward variant 8.  Errors: FMB_ERR_INVALID_ARG. */
 int fmb_set_config(fmb_scene *scene, fmb_batch *batch, int32_t fwd_variant, int32_t bwd_variant,
                    int32_t fwd_grid_mult, int32_t bwd_grid_mult);
 
@@ -376,7 +376,7 @@ int fmb_set_config(fmb_scene *scene, fmb_batch *batch, int32_t fwd_variant, int3
  * does and sum each Gaussian's terms over the wave per tile; the rays of an item, 8 or 16 tiles
  * of 8 x 8 pixels, for variants 6-8 (8: blocks of 512 threads), which give each lane a ray of
  * a tile and each wave a Gaussian at a time -- calls with a normal cotangent run a form of
- * theirs with 8 tiles per item), forward and backward persistent-grid multipliers, and the
+ * theirs with 8 tiles per item), forward and backward grid multipliers, and the
  * forward and backward work-item counts (0 until the first call built them). */
 int fmb_get_config(const fmb_scene *scene, const fmb_batch *batch, int32_t *out);
 

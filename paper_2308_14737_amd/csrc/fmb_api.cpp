@@ -32,9 +32,9 @@ int bwd_variant_tiles(int v);
 int bwd_normal_variant();
 int block_size();
 hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const FwdOut &O,
-                      const FwdItem *items, int n, const int *order, int *counter);
+                      const FwdItem *items, const int *order);
 hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart,
+                      const BwdItem *items, const int *order, float *partial, float *bpart,
                       unsigned long long *masks);
 hipError_t launch_fin(int n_tasks, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks,
@@ -57,8 +57,6 @@ hipError_t launch_statc(int n_small, int n_big, hipStream_t st, const Params &P,
                         const BwdItem *items, const int *order, float *partial);
 hipError_t launch_bwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const BwdIn &I,
                        const BwdItem *items, const int *order, float *partial, float *beta_partial);
-hipError_t occupancy_fwd(int variant, int flags, int *blocks_per_cu);
-hipError_t occupancy_bwd(int variant, int flags, int *blocks_per_cu);
 hipError_t scratch_base(void **out);
 size_t scratch_bytes();
 }  // namespace fmb
@@ -66,7 +64,7 @@ size_t scratch_bytes();
 using namespace fmb;
 
 namespace {
-constexpr int kFlagNrm = 1, kFlagFlw = 2, kFlagPer = 4, kFlagCol = 8, kFlagBig = 16;
+constexpr int kFlagNrm = 1, kFlagFlw = 2, kFlagCol = 4, kFlagBig = 8;
 
 // Gradient outputs of a backward call.
 struct Grads {
@@ -300,9 +298,16 @@ struct Job {
         prm.scenes = d_scenes.as<SceneRec>();
         prm.views = d_views.as<ViewRec>();
         prm.eta = d_eta.as<float>();
-        // untuned default: 512 rays per forward item, or 256 where that leaves fewer than two
-        // items per compute unit (a 64 x 64 view: 16 items instead of 8)
-        if (!launch_fixed) fwd_variant = P < 2LL * n_cu * fwd_variant_rays(1) ? 0 : 1;
+        // Untuned default of the forward: more rays per item amortise its staging and bounds, fewer fill
+        // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 59 / 71 / 75,
+        // 330 000 rays 59.6 / 61.8 / 64.4, 1.1e6 103 / 103 / 105, 2.4e6 146 / 142 / 143, 12.6e6 832 / 808 / 786;
+        // with 10 000 Gaussians, whose items also pre-cull them, 2.1e6 rays 1909 / 1648 / 1554 and (4000)
+        // 0.5e6 rays 471 / 460 / 549.
+        if (!launch_fixed) {
+            const int64_t r = 256LL * n_cu;
+            const int64_t wide = max_scene_n() > block_size() ? 28 : 64;
+            fwd_variant = P < 6 * r ? 0 : P < wide * r ? 1 : 3;
+        }
         return FMB_OK;
     }
 
@@ -743,34 +748,7 @@ struct Job {
         return FMB_OK;
     }
 
-    std::map<int, int> occ_f, occ_b;  // blocks per CU of the persistent kernels
-    int persist_mult[2] = {1, 1};     // persistent grid = mult x occupancy x CUs (fwd, bwd)
-
-    int grid_fwd(int flags, int &grid)
-    {
-        const int key = fwd_variant * 32 + (flags | kFlagPer);
-        auto it = occ_f.find(key);
-        if (it == occ_f.end()) {
-            int o = 0;
-            HIPCHK(occupancy_fwd(fwd_variant, flags | kFlagPer, &o));
-            it = occ_f.emplace(key, std::max(1, o)).first;
-        }
-        grid = std::max(1, std::min(n_fitems, persist_mult[0] * it->second * n_cu));
-        return FMB_OK;
-    }
-
-    int grid_bwd(int variant, int flags, int &grid)
-    {
-        const int key = variant * 32 + (flags | kFlagPer);
-        auto it = occ_b.find(key);
-        if (it == occ_b.end()) {
-            int o = 0;
-            HIPCHK(occupancy_bwd(variant, flags | kFlagPer, &o));
-            it = occ_b.emplace(key, std::max(1, o)).first;
-        }
-        grid = std::max(1, std::min(n_bitems, persist_mult[1] * it->second * n_cu));
-        return FMB_OK;
-    }
+    int grid_mult[2] = {1, 1};  // kept for fmb_set_config and its readers; a block takes one item
 
     // The backward variant a call runs: with a normal cotangent the tiled variants run their form for it.
     // (where its records are not too large, else the Gaussian-lane variant 2)
@@ -780,30 +758,30 @@ struct Job {
         return normals_tiled(I.g_color != nullptr) ? bwd_normal_variant() : 2;
     }
 
-    static int fwd_flags(const FwdOut &O, bool persist)
+    static int fwd_flags(const FwdOut &O)
     {
-        return (O.normal ? kFlagNrm : 0) | (O.flow ? kFlagFlw : 0) | (persist ? kFlagPer : 0) |
+        return (O.normal ? kFlagNrm : 0) | (O.flow ? kFlagFlw : 0) |
                (O.color ? kFlagCol : 0);
     }
     // The blend forward's flags: with a scene of more than a block's count of Gaussians, the kernel
     // form that takes such scenes in pre-culled rounds.
-    int blend_fwd_flags(const FwdOut &O, bool persist) const
+    int blend_fwd_flags(const FwdOut &O) const
     {
-        return fwd_flags(O, persist) | (max_scene_n() > block_size() ? kFlagBig : 0);
+        return fwd_flags(O) | (max_scene_n() > block_size() ? kFlagBig : 0);
     }
     // The blend backward's flags for variant v: for the tiled variants with a scene of more than a
     // block's count of Gaussians, the kernel form that takes such scenes in pre-culled rounds.
-    int blend_bwd_flags(const BwdIn &I, bool persist, int v) const
+    int blend_bwd_flags(const BwdIn &I, int v) const
     {
-        return bwd_flags(I, persist) | (bwd_variant_tiles(v) > 0 && max_scene_n() > block_size() ? kFlagBig : 0);
+        return bwd_flags(I) | (bwd_variant_tiles(v) > 0 && max_scene_n() > block_size() ? kFlagBig : 0);
     }
-    static int bwd_flags(const BwdIn &I, bool persist)
+    static int bwd_flags(const BwdIn &I)
     {
-        return (I.g_normal ? kFlagNrm : 0) | (I.g_flow ? kFlagFlw : 0) | (persist ? kFlagPer : 0) |
+        return (I.g_normal ? kFlagNrm : 0) | (I.g_flow ? kFlagFlw : 0) |
                (I.g_color ? kFlagCol : 0);
     }
 
-    int forward(const FwdOut &O, bool persist, hipStream_t st)
+    int forward(const FwdOut &O, bool ordered, hipStream_t st)
     {
         if (!cams_set) return fail(FMB_ERR_STATE, "render before cameras were set");
         CHECK_ARG(O.depth && O.alpha, "depth and alpha outputs are required");
@@ -814,26 +792,20 @@ struct Job {
             int rc = build_comp_fwd();
             if (rc) return rc;
             TimedSpan ts(st, 0);
-            HIPCHK(launch_fwdc(fwd_flags(O, false), n_cfitems[0], n_cfitems[1], st, prm, O, d_cfitems.as<CompItem>()));
+            HIPCHK(launch_fwdc(fwd_flags(O), n_cfitems[0], n_cfitems[1], st, prm, O, d_cfitems.as<CompItem>()));
             ts.stop();
             return FMB_OK;
         }
         int rc = build_fwd(fwd_variant);
         if (rc) return rc;
-        const int flags = blend_fwd_flags(O, persist);
-        int grid = n_fitems;
-        if (persist) {
-            if ((rc = grid_fwd(flags, grid))) return rc;
-            HIPCHK(launch_fill(d_counter.as<int>(), 1, 0, st));
-        }
         TimedSpan ts(st, 0);
-        HIPCHK(launch_fwd(fwd_variant, flags, grid, st, prm, O, d_fitems.as<FwdItem>(), n_fitems,
-                          persist ? d_forder.as<int>() : nullptr, persist ? d_counter.as<int>() : nullptr));
+        HIPCHK(launch_fwd(fwd_variant, blend_fwd_flags(O), n_fitems, st, prm, O, d_fitems.as<FwdItem>(),
+                          ordered ? d_forder.as<int>() : nullptr));
         ts.stop();
         return FMB_OK;
     }
 
-    int backward(const BwdIn &I, const Grads &G, bool persist, hipStream_t st)
+    int backward(const BwdIn &I, const Grads &G, bool ordered, hipStream_t st)
     {
         if (!cams_set) return fail(FMB_ERR_STATE, "backward before cameras were set");
         CHECK_ARG(I.depth && I.stash, "depth and stash from the forward pass are required");
@@ -846,20 +818,13 @@ struct Job {
         if (rc) return rc;
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwdc(bwd_flags(I, false), n_bitems_small, n_bitems - n_bitems_small, st, prm, I,
+            HIPCHK(launch_bwdc(bwd_flags(I), n_bitems_small, n_bitems - n_bitems_small, st, prm, I,
                                d_bitems.as<BwdItem>(), d_border.as<int>(), d_partial.as<float>(), d_bpart.as<float>()));
             tb.stop();
         } else {
-            const int flags = blend_bwd_flags(I, persist, bv);
-            int grid = n_bitems;
-            if (persist) {
-                if ((rc = grid_bwd(bv, flags, grid))) return rc;
-                HIPCHK(launch_fill(d_counter.as<int>() + 1, 1, 0, st));
-            }
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwd(bv, flags, grid, st, prm, I, d_bitems.as<BwdItem>(), n_bitems,
-                              persist ? d_border.as<int>() : nullptr, persist ? d_counter.as<int>() + 1 : nullptr,
-                              d_partial.as<float>(), d_bpart.as<float>(),
+            HIPCHK(launch_bwd(bv, blend_bwd_flags(I, bv), n_bitems, st, prm, I, d_bitems.as<BwdItem>(),
+                              ordered ? d_border.as<int>() : nullptr, d_partial.as<float>(), d_bpart.as<float>(),
                               mask_words ? d_masks.as<unsigned long long>() : nullptr));
             tb.stop();
         }
@@ -931,13 +896,12 @@ struct Job {
         const int n_items = (int)pl.items.size();
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwdc(bwd_flags(I, false), pl.n_small, n_items - pl.n_small, st, prm, I, items,
+            HIPCHK(launch_bwdc(bwd_flags(I), pl.n_small, n_items - pl.n_small, st, prm, I, items,
                                reinterpret_cast<const int *>(b + o_order), part, bpart));
             tb.stop();
         } else {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwd(bv, blend_bwd_flags(I, false, bv), n_items, st, prm, I, items, n_items, nullptr, nullptr,
-                              part, bpart, masks));
+            HIPCHK(launch_bwd(bv, blend_bwd_flags(I, bv), n_items, st, prm, I, items, nullptr, part, bpart, masks));
             tb.stop();
         }
         TimedSpan tf(st, 2);
@@ -1332,15 +1296,10 @@ int fmb_batch_capture(fmb_batch *b, float *depth, float *alpha, float *normal, f
     const FwdOut O{depth, alpha, normal, flow, color, stash};
     const BwdIn I{g_depth, g_alpha, g_normal, g_flow, g_color, depth, color, stash};
     const Grads G{g_means, g_prec, g_weights, g_colors, g_betas};
-    // item lists and occupancy are prepared outside the capture (they use synchronous copies)
+    // item lists are prepared outside the capture (they use synchronous copies)
     int rc = j.build_bwd(j.bwd_run_variant(I), g_color != nullptr);
     if (!rc && j.model == FMB_MODEL_COMPOSITE) rc = j.build_comp_fwd();
-    if (j.model == FMB_MODEL_BLEND) {
-        int gdummy = 0;
-        if (!rc) rc = j.build_fwd(j.fwd_variant);
-        if (!rc) rc = j.grid_fwd(j.blend_fwd_flags(O, true), gdummy);
-        if (!rc) rc = j.grid_bwd(j.bwd_run_variant(I), j.blend_bwd_flags(I, true, j.bwd_run_variant(I)), gdummy);
-    }
+    if (!rc && j.model == FMB_MODEL_BLEND) rc = j.build_fwd(j.fwd_variant);
     if (rc) return rc;
     j.drop_graphs();
     for (int which = 0; which < 2; ++which) {
@@ -1425,8 +1384,8 @@ int fmb_set_config(fmb_scene *s, fmb_batch *b, int32_t fwd_variant, int32_t bwd_
     j.fwd_variant = fwd_variant;
     j.bwd_variant = bwd_variant;
     j.launch_fixed = true;
-    j.persist_mult[0] = fwd_grid_mult;
-    j.persist_mult[1] = bwd_grid_mult;
+    j.grid_mult[0] = fwd_grid_mult;
+    j.grid_mult[1] = bwd_grid_mult;
     j.drop_graphs();
     return FMB_OK;
 }
@@ -1443,8 +1402,8 @@ int fmb_get_config(const fmb_scene *s, const fmb_batch *b, int32_t *out)
     out[3] = bwd_variant_rt(j.bwd_variant) > 0 ? bwd_variant_rt(j.bwd_variant)
              : bwd_variant_tiles(j.bwd_variant) > 0 ? 64 * bwd_variant_tiles(j.bwd_variant)
                                                     : bwd_variant_ray_tile(j.bwd_variant);
-    out[4] = j.persist_mult[0];
-    out[5] = j.persist_mult[1];
+    out[4] = j.grid_mult[0];
+    out[5] = j.grid_mult[1];
     // item counts of the lists built for the configuration in use (0 until built)
     const bool comp = j.model == FMB_MODEL_COMPOSITE;
     const bool bwd_cur = comp ? (j.bwd_built == 1 || j.bwd_built == 3)
@@ -1489,7 +1448,7 @@ static std::string tune_key(const Job &j, int fflags, int unused, int cot_mask)
     hipDeviceProp_t prop{};
     (void)hipGetDeviceProperties(&prop, j.device);
     std::ostringstream k;
-    k << prop.gcnArchName << ":cu" << j.n_cu << ":v5:S" << j.S << ":V" << j.V << ":P" << j.P << ":N" << j.n_total
+    k << prop.gcnArchName << ":cu" << j.n_cu << ":v6:S" << j.S << ":V" << j.V << ":P" << j.P << ":N" << j.n_total
       << ":out" << fflags << ":cot" << cot_mask;
     (void)unused;
     return k.str();
@@ -1504,7 +1463,7 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
     CHECK_ARG((s != nullptr) != (b != nullptr), "exactly one of scene and batch must be given");
     CHECK_ARG(depth && alpha && stash && g_means && g_prec && g_weights && g_betas, "buffers are required");
     Job &j = s ? s->job : b->job;
-    const bool persist = b != nullptr;
+    const bool ordered = b != nullptr;
     hipStream_t st = (hipStream_t)stream;
     if (!j.cams_set) return fail(FMB_ERR_STATE, "autotune before cameras were set");
     if (j.model == FMB_MODEL_COMPOSITE) return FMB_OK;  // one launch configuration
@@ -1514,7 +1473,7 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
     const Grads G{g_means, g_prec, g_weights, g_colors, g_betas};
     const int cot_mask = (g_depth ? 1 : 0) | (g_alpha ? 2 : 0) | (g_normal ? 4 : 0) | (g_flow ? 8 : 0) |
                          (g_color ? 16 : 0);
-    const std::string key = tune_key(j, Job::fwd_flags(O, false), 0, cot_mask);
+    const std::string key = tune_key(j, Job::fwd_flags(O), 0, cot_mask);
     if (cache_path) {
         std::ifstream in(cache_path);
         std::string line;
@@ -1526,8 +1485,8 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
                 bv < num_bwd_variants() && mf >= 1 && mf <= 2 && mb >= 1 && mb <= 2) {
                 j.fwd_variant = fv;
                 j.bwd_variant = bv;
-                j.persist_mult[0] = mf;
-                j.persist_mult[1] = mb;
+                j.grid_mult[0] = mf;
+                j.grid_mult[1] = mb;
                 j.launch_fixed = true;
                 return FMB_OK;
             }
@@ -1552,44 +1511,35 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
     int rc = FMB_OK;
     float best_f = 1e30f, best_b = 1e30f;
     int bf = j.fwd_variant, bb = j.bwd_variant;
-    const int n_mult = persist ? 2 : 1;
-    int bmf = 1, bmb = 1;
-    for (int v = 0; v < num_fwd_variants() && !rc; ++v)
-        for (int m = 1; m <= n_mult && !rc; ++m) {
-            j.fwd_variant = v;
-            j.persist_mult[0] = m;
-            float ms = 0.0f;
-            rc = time_it([&]() { return j.forward(O, persist, st); }, ms);
-            if (!rc && ms < best_f) {
-                best_f = ms;
-                bf = v;
-                bmf = m;
-            }
+    for (int v = 0; v < num_fwd_variants() && !rc; ++v) {
+        j.fwd_variant = v;
+        float ms = 0.0f;
+        rc = time_it([&]() { return j.forward(O, ordered, st); }, ms);
+        if (!rc && ms < best_f) {
+            best_f = ms;
+            bf = v;
         }
+    }
     j.fwd_variant = bf;
-    j.persist_mult[0] = bmf;
-    if (!rc) rc = j.forward(O, persist, st);
-    for (int v = 0; v < num_bwd_variants() && !rc; ++v)
-        for (int m = 1; m <= n_mult && !rc; ++m) {
-            j.bwd_variant = v;
-            j.persist_mult[1] = m;
-            float ms = 0.0f;
-            rc = time_it([&]() { return j.backward(I, G, persist, st); }, ms);
-            if (!rc && ms < best_b) {
-                best_b = ms;
-                bb = v;
-                bmb = m;
-            }
+    if (!rc) rc = j.forward(O, ordered, st);
+    for (int v = 0; v < num_bwd_variants() && !rc; ++v) {
+        j.bwd_variant = v;
+        float ms = 0.0f;
+        rc = time_it([&]() { return j.backward(I, G, ordered, st); }, ms);
+        if (!rc && ms < best_b) {
+            best_b = ms;
+            bb = v;
         }
+    }
     j.bwd_variant = bb;
-    j.persist_mult[1] = bmb;
+    j.grid_mult[0] = j.grid_mult[1] = 1;
     j.launch_fixed = true;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
     if (cache_path) {
         std::ofstream outf(cache_path, std::ios::app);
-        if (outf) outf << key << " " << bf << " " << bb << " " << bmf << " " << bmb << "\n";
+        if (outf) outf << key << " " << bf << " " << bb << " 1 1\n";
     }
     return FMB_OK;
 }

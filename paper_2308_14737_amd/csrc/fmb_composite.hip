@@ -1190,10 +1190,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kStatcW
     case 1: CALL(1); break;                                                                               \
     case 2: CALL(2); break;                                                                               \
     case 3: CALL(3); break;                                                                               \
-    case 8: CALL(8); break;                                                                               \
-    case 9: CALL(9); break;                                                                               \
-    case 10: CALL(10); break;                                                                             \
-    case 11: CALL(11); break;                                                                             \
+    case 4: CALL(4); break;                                                                               \
+    case 5: CALL(5); break;                                                                               \
+    case 6: CALL(6); break;                                                                             \
+    case 7: CALL(7); break;                                                                             \
     default: return hipErrorInvalidValue;                                                                 \
     }
 
@@ -1211,7 +1211,6 @@ int comp_resident_max() { return kCompTG; }
 hipError_t launch_fwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const FwdOut &O,
                        const CompItem *items)
 {
-    flags &= ~kPer;
     if (n_small > 0) FMB_COMP_DISPATCH(flags, FMB_FWDC_SMALL)
     if (n_big > 0) FMB_COMP_DISPATCH(flags, FMB_FWDC_BIG)
     return hipGetLastError();
@@ -1221,7 +1220,6 @@ hipError_t launch_fwdc(int flags, int n_small, int n_big, hipStream_t st, const 
 hipError_t launch_bwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const BwdIn &I,
                        const BwdItem *items, const int *order, float *partial, float *beta_partial)
 {
-    flags &= ~kPer;
     const size_t dyn = (size_t)kCompSlots * 6 * sizeof(float4);
     if (n_small > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_SMALL)
     if (n_big > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_BIG)

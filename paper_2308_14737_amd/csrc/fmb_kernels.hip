@@ -13,8 +13,8 @@
 //     reduction and no P x N storage (without a normal cotangent in the offset form of
 //     pair_adjoint_offset).  Partial gradients per item are reduced deterministically by
 //     the finalize kernel.
-//   * persistent variants pull items from a device counter (reset by a fill kernel)
-//     in the order given by the host (largest item first).
+//   * a block takes one item; of a batch, whose items are uneven, in the order given by the host
+//     (largest item first), so that the last blocks to start are the shortest.
 //
 // Per pair (ray o + t v with |v| = 1, Gaussian mu, U, lambda; mu' = mu - o):
 //   a = U v, t = v.c / a.a (peak of the density along the ray, Sec. 3.1),
@@ -32,10 +32,9 @@ namespace fmb {
 
 template <int BLOCK, int RPT, int TG, int F>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 ? 3 : 4))) void fwd_kernel(Params P, FwdOut O, const FwdItem *__restrict__ items,
-                                                   int n_items, const int *__restrict__ order,
-                                                   int *__restrict__ counter)
+                                                   const int *__restrict__ order)
 {
-    constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0;
+    constexpr bool NORMALS = (F & kNrm) != 0;
     constexpr bool COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int EW = COLOR ? 6 : 5;  // float4 per LDS entry: the entry, the m estimate terms, colour
     __shared__ float4 tile[TG * EW];
@@ -48,248 +47,236 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
     __shared__ float2 wmin[BIG ? BLOCK / 64 : 1];
     __shared__ int wcnt[BIG ? BLOCK / 64 : 1];
     __shared__ int slist[BIG ? BLOCK : 1];
-    __shared__ int s_item;
-    int pos = blockIdx.x;
-    for (;;) {
-        if (PERSIST) {
-            __syncthreads();  // everyone is done with s_item and the tile of the last item
-            if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
-            __syncthreads();
-            pos = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep the item in SGPRs
-        }
-        if (pos >= n_items) break;
-        const int it = order ? ld_uniform(order + pos) : pos;
-        const FwdItem item = ld_uniform(items + it);
-        const ViewRec vr = ld_uniform(P.views + item.view);
-        const SceneRec sr = ld_uniform(P.scenes + vr.scene);
-        const CamRec cam = cam_of(P, item.view);
-        const float *e = cam.e, *kk = cam.k;
-        double o[3];
-        cam_centre(e, o);
-        const Blend bl = blend_of(P, vr.scene);
-        const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
-        // ray j of a lane: lane `lane` of tile tile0 + j * NW + wave (8 x 8 pixels where the view is
-        // wide enough: a wave's rays stay close together, so the exact skip of zero weights below
-        // is uniform over the wave more often)
-        constexpr int NW = BLOCK / 64;
-        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
+    const FwdItem item = ld_uniform(items + it);
+    const ViewRec vr = ld_uniform(P.views + item.view);
+    const SceneRec sr = ld_uniform(P.scenes + vr.scene);
+    const CamRec cam = cam_of(P, item.view);
+    const float *e = cam.e, *kk = cam.k;
+    double o[3];
+    cam_centre(e, o);
+    const Blend bl = blend_of(P, vr.scene);
+    const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
+    // ray j of a lane: lane `lane` of tile tile0 + j * NW + wave (8 x 8 pixels where the view is
+    // wide enough: a wave's rays stay close together, so the exact skip of zero weights below
+    // is uniform over the wave more often)
+    constexpr int NW = BLOCK / 64;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
 
-        float v0[RPT], v1[RPT], v2[RPT];
-        float M[RPT], S[RPT], T[RPT], N0[RPT], N1[RPT], N2[RPT], D[RPT], C0[RPT], C1[RPT], C2[RPT];
-        float at[RPT], dt[RPT];  // loss targets, loaded now so that the epilogue does not wait
-        int loc[RPT];
+    float v0[RPT], v1[RPT], v2[RPT];
+    float M[RPT], S[RPT], T[RPT], N0[RPT], N1[RPT], N2[RPT], D[RPT], C0[RPT], C1[RPT], C2[RPT];
+    float at[RPT], dt[RPT];  // loss targets, loaded now so that the epilogue does not wait
+    int loc[RPT];
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        int row, col;
+        loc[j] = tile_local(vr, item.tile0 + j * NW + wave, lane, row, col);
+        const int lc = loc[j] >= 0 ? loc[j] : 0;  // a lane past the edge takes ray 0 (not written)
+        tile_ray_dir(P, vr, e, kk, lc, loc[j] >= 0 ? row : 0, loc[j] >= 0 ? col : 0, v0[j], v1[j], v2[j]);
+        M[j] = -INFINITY;
+        S[j] = T[j] = N0[j] = N1[j] = N2[j] = D[j] = C0[j] = C1[j] = C2[j] = 0.0f;
+        at[j] = dt[j] = 0.0f;
+        if (O.g_depth) {
+            at[j] = O.alpha_t[vr.ray_off + lc];
+            dt[j] = O.depth_t[vr.ray_off + lc];
+        }
+    }
+    // The box of each of the wave's ray tiles, for the bounds of tile_bounds: lane l bounds Gaussian
+    // l / RPT on ray tile l % RPT.
+    const int jl = lane % RPT;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const TileBox b = wave_box(v0[j], v1[j], v2[j], loc[j] >= 0, e);
+        if (lane == 0) {
+            tbox[3 * (wave * RPT + j)] = b.c;
+            tbox[3 * (wave * RPT + j) + 1] = b.x;
+            tbox[3 * (wave * RPT + j) + 2] = b.y;
+        }
+    }
+    const float g2n = ceil_log2(sr.n), wskip = fminf(kFwdSkipLog2, -kDensRelLog2 - g2n);
+    // lower bounds over lane's tile jl, from the Gaussians bounded so far: log2 of the density sum
+    // and the running maximum
+    float dlow = -INFINITY, mlow = -INFINITY;
+
+    // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
+    // round is first bounded on a box around all the item's tiles, and only those whose
+    // density can reach the cutoff there, or whose weight can be above 2^kFwdSkipLog2
+    // against the least running maximum of the item's rays so far, are staged, in scene order
+    // (slist).  The running maxima and density sums only grow, so a Gaussian left out is one that
+    // the tests below would skip when its turn came.
+    // Smaller scenes take one round of all their Gaussians (and launches without kBig, whose
+    // scenes are all small, have no such rounds).
+    const bool sparse = BIG && sr.n > BLOCK;
+    TileBox ibox;
+    for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
+      int total = sr.n;
+      if (sparse) {
+        float mm = INFINITY, dm = INFINITY;
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-            int row, col;
-            loc[j] = tile_local(vr, item.tile0 + j * NW + wave, lane, row, col);
-            const int lc = loc[j] >= 0 ? loc[j] : 0;  // a lane past the edge takes ray 0 (not written)
-            tile_ray_dir(P, vr, e, kk, lc, loc[j] >= 0 ? row : 0, loc[j] >= 0 ? col : 0, v0[j], v1[j], v2[j]);
-            M[j] = -INFINITY;
-            S[j] = T[j] = N0[j] = N1[j] = N2[j] = D[j] = C0[j] = C1[j] = C2[j] = 0.0f;
-            at[j] = dt[j] = 0.0f;
-            if (O.g_depth) {
-                at[j] = O.alpha_t[vr.ray_off + lc];
-                dt[j] = O.depth_t[vr.ray_off + lc];
+            mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
+            dm = loc[j] >= 0 ? fminf(dm, D[j]) : dm;
+        }
+        mm = wave_min_u(mm);
+        dm = wave_min_u(dm);
+        __syncthreads();  // the previous round's list and staged tile are consumed
+        if (lane == 0) wmin[wave] = make_float2(mm, dm);
+        __syncthreads();  // tile boxes and least maxima visible
+        if (rb == 0) ibox = wave_box_of(tbox, NW * RPT, lane, e);
+        float imin = INFINITY, idm = INFINITY;
+        for (int w = 0; w < NW; ++w) {
+            imin = fminf(imin, wmin[w].x);
+            idm = fminf(idm, wmin[w].y);
+        }
+        const float dcut = fmaxf(kDensSkipLog2, __builtin_amdgcn_logf(idm) - kDensRelLog2 - g2n);
+        const int gl = rb + (int)threadIdx.x;
+        bool keep = false;
+        if (gl < sr.n) {
+            const int gg = sr.gauss_off + gl;
+            Ent ge;
+            float4 ee;
+            make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
+            const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
+            // (written so that a NaN bound keeps the Gaussian)
+            keep = !(b1_pos && pb.d2_hi < dcut && pb.z_hi - imin < wskip);
+        }
+        const unsigned long long bal = wave_ballot(keep);
+        if (lane == 0) wcnt[wave] = __popcll(bal);
+        __syncthreads();
+        int off = 0;
+        total = 0;
+        for (int w = 0; w < NW; ++w) {
+            const int c = wcnt[w];
+            off += w < wave ? c : 0;
+            total += c;
+        }
+        if (keep) slist[off + __popcll(bal & ((1ull << lane) - 1ull))] = gl;
+      }
+    for (int gb = 0; gb < total; gb += TG) {
+        const int cnt = min(TG, total - gb);
+        if (gb > 0 || sparse) __syncthreads();
+        for (int q = threadIdx.x; q < cnt; q += BLOCK) {
+            const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
+            make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &tile[EW * q]);
+            if (COLOR) tile[EW * q + 5] = colour_entry(P.colors + 3 * gi);
+        }
+        __syncthreads();
+        // Every (Gaussian, ray tile) of the staged tile is bounded first, GP Gaussians at a time;
+        // the lower bounds give the least density sum and the least running maximum that the
+        // tile's rays end with.  A pair is taken if on some ray its density can reach the cutoff
+        // (2^kDensSkipLog2, or 2^-kDensRelLog2 / n of the least density sum) or its weight
+        // 2^kFwdSkipLog2 of the running maximum.  Without beta1 >= 0 the weight bounds do not
+        // hold and every pair is taken.
+        constexpr int GP = 64 / RPT;
+        const TileBox bj = TileBox{tbox[3 * (wave * RPT + jl)], tbox[3 * (wave * RPT + jl) + 1], tbox[3 * (wave * RPT + jl) + 2]};
+        for (int ib = 0; ib < cnt; ib += GP) {
+            const int il = ib + lane / RPT;
+            if (il < cnt) {
+                const Ent gl = ent_from(tile[EW * il], tile[EW * il + 1], tile[EW * il + 2], tile[EW * il + 3]);
+                const PairBounds pb = tile_bounds(gl, tile[EW * il + 4], bj, bl.hm, bl.b1, bl.nc2);
+                hisave[wave][ib * RPT + lane] = make_float2(pb.d2_hi, pb.z_hi);
+                dlow = fmaxf(dlow, pb.d2_lo);
+                mlow = fmaxf(mlow, pb.z_lo);
             }
         }
-        // The box of each of the wave's ray tiles, for the bounds of tile_bounds: lane l bounds Gaussian
-        // l / RPT on ray tile l % RPT.
-        const int jl = lane % RPT;
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            const TileBox b = wave_box(v0[j], v1[j], v2[j], loc[j] >= 0, e);
-            if (lane == 0) {
-                tbox[3 * (wave * RPT + j)] = b.c;
-                tbox[3 * (wave * RPT + j) + 1] = b.x;
-                tbox[3 * (wave * RPT + j) + 2] = b.y;
-            }
+        for (int off = RPT; off < 64; off <<= 1) {
+            dlow = fmaxf(dlow, __shfl_xor(dlow, off, 64));
+            mlow = fmaxf(mlow, __shfl_xor(mlow, off, 64));
         }
-        const float g2n = ceil_log2(sr.n), wskip = fminf(kFwdSkipLog2, -kDensRelLog2 - g2n);
-        // lower bounds over lane's tile jl, from the Gaussians bounded so far: log2 of the density sum
-        // and the running maximum
-        float dlow = -INFINITY, mlow = -INFINITY;
-
-        // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
-        // round is first bounded on a box around all the item's tiles, and only those whose
-        // density can reach the cutoff there, or whose weight can be above 2^kFwdSkipLog2
-        // against the least running maximum of the item's rays so far, are staged, in scene order
-        // (slist).  The running maxima and density sums only grow, so a Gaussian left out is one that
-        // the tests below would skip when its turn came.
-        // Smaller scenes take one round of all their Gaussians (and launches without kBig, whose
-        // scenes are all small, have no such rounds).
-        const bool sparse = BIG && sr.n > BLOCK;
-        TileBox ibox;
-        for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
-          int total = sr.n;
-          if (sparse) {
-            float mm = INFINITY, dm = INFINITY;
+        if (rb > 0 || gb > 0) {  // the sums of the Gaussians taken so far bound too
 #pragma unroll
             for (int j = 0; j < RPT; ++j) {
-                mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
-                dm = loc[j] >= 0 ? fminf(dm, D[j]) : dm;
-            }
-            mm = wave_min_u(mm);
-            dm = wave_min_u(dm);
-            __syncthreads();  // the previous round's list and staged tile are consumed
-            if (lane == 0) wmin[wave] = make_float2(mm, dm);
-            __syncthreads();  // tile boxes and least maxima visible
-            if (rb == 0) ibox = wave_box_of(tbox, NW * RPT, lane, e);
-            float imin = INFINITY, idm = INFINITY;
-            for (int w = 0; w < NW; ++w) {
-                imin = fminf(imin, wmin[w].x);
-                idm = fminf(idm, wmin[w].y);
-            }
-            const float dcut = fmaxf(kDensSkipLog2, __builtin_amdgcn_logf(idm) - kDensRelLog2 - g2n);
-            const int gl = rb + (int)threadIdx.x;
-            bool keep = false;
-            if (gl < sr.n) {
-                const int gg = sr.gauss_off + gl;
-                Ent ge;
-                float4 ee;
-                make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
-                const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
-                // (written so that a NaN bound keeps the Gaussian)
-                keep = !(b1_pos && pb.d2_hi < dcut && pb.z_hi - imin < wskip);
-            }
-            const unsigned long long bal = wave_ballot(keep);
-            if (lane == 0) wcnt[wave] = __popcll(bal);
-            __syncthreads();
-            int off = 0;
-            total = 0;
-            for (int w = 0; w < NW; ++w) {
-                const int c = wcnt[w];
-                off += w < wave ? c : 0;
-                total += c;
-            }
-            if (keep) slist[off + __popcll(bal & ((1ull << lane) - 1ull))] = gl;
-          }
-        for (int gb = 0; gb < total; gb += TG) {
-            const int cnt = min(TG, total - gb);
-            if (gb > 0 || !PERSIST || sparse) __syncthreads();
-            for (int q = threadIdx.x; q < cnt; q += BLOCK) {
-                const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
-                make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &tile[EW * q]);
-                if (COLOR) tile[EW * q + 5] = colour_entry(P.colors + 3 * gi);
-            }
-            __syncthreads();
-            // Every (Gaussian, ray tile) of the staged tile is bounded first, GP Gaussians at a time;
-            // the lower bounds give the least density sum and the least running maximum that the
-            // tile's rays end with.  A pair is taken if on some ray its density can reach the cutoff
-            // (2^kDensSkipLog2, or 2^-kDensRelLog2 / n of the least density sum) or its weight
-            // 2^kFwdSkipLog2 of the running maximum.  Without beta1 >= 0 the weight bounds do not
-            // hold and every pair is taken.
-            constexpr int GP = 64 / RPT;
-            const TileBox bj = TileBox{tbox[3 * (wave * RPT + jl)], tbox[3 * (wave * RPT + jl) + 1], tbox[3 * (wave * RPT + jl) + 2]};
-            for (int ib = 0; ib < cnt; ib += GP) {
-                const int il = ib + lane / RPT;
-                if (il < cnt) {
-                    const Ent gl = ent_from(tile[EW * il], tile[EW * il + 1], tile[EW * il + 2], tile[EW * il + 3]);
-                    const PairBounds pb = tile_bounds(gl, tile[EW * il + 4], bj, bl.hm, bl.b1, bl.nc2);
-                    hisave[wave][ib * RPT + lane] = make_float2(pb.d2_hi, pb.z_hi);
-                    dlow = fmaxf(dlow, pb.d2_lo);
-                    mlow = fmaxf(mlow, pb.z_lo);
+                const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY), dm = wave_min_u(loc[j] >= 0 ? D[j] : INFINITY);
+                if (jl == j) {
+                    mlow = fmaxf(mlow, mm);
+                    dlow = fmaxf(dlow, __builtin_amdgcn_logf(dm));
                 }
             }
+        } else if (b1_pos) {
+            // the running maximum starts at its lower bound (a pair that reaches it is staged here),
+            // so that lesser weights are skipped from the start
 #pragma unroll
-            for (int off = RPT; off < 64; off <<= 1) {
-                dlow = fmaxf(dlow, __shfl_xor(dlow, off, 64));
-                mlow = fmaxf(mlow, __shfl_xor(mlow, off, 64));
+            for (int j = 0; j < RPT; ++j)
+                M[j] = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mlow), j)), 1e30f);
+        }
+        const float dcut = fmaxf(kDensSkipLog2, dlow - kDensRelLog2 - g2n), zcut = mlow + wskip;
+        for (int ib = 0; ib < cnt; ib += GP) {
+            const int il = ib + lane / RPT;
+            bool need = false;
+            if (il < cnt && bj.c.w >= 0.0f) {
+                const float2 h = hisave[wave][ib * RPT + lane];
+                // (written so that a NaN bound keeps the pair)
+                need = !(b1_pos && h.x < dcut && h.y < zcut);
             }
-            if (rb > 0 || gb > 0) {  // the sums of the Gaussians taken so far bound too
+            unsigned long long nm = wave_ballot(need);
+          while (nm != 0ull) {
+            const int k = __builtin_ctzll(nm) / RPT;
+            const unsigned bits = (unsigned)(nm >> (k * RPT)) & ((1u << RPT) - 1u);
+            nm &= ~((unsigned long long)((1u << RPT) - 1u) << (k * RPT));
+            const int i = ib + k;
+            const Ent g = ent_from(tile[EW * i], tile[EW * i + 1], tile[EW * i + 2], tile[EW * i + 3]);
+            float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (COLOR) cc = tile[EW * i + 5];
 #pragma unroll
-                for (int j = 0; j < RPT; ++j) {
-                    const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY), dm = wave_min_u(loc[j] >= 0 ? D[j] : INFINITY);
-                    if (jl == j) {
-                        mlow = fmaxf(mlow, mm);
-                        dlow = fmaxf(dlow, __builtin_amdgcn_logf(dm));
-                    }
-                }
-            } else if (b1_pos) {
-                // the running maximum starts at its lower bound (a pair that reaches it is staged here),
-                // so that lesser weights are skipped from the start
-#pragma unroll
-                for (int j = 0; j < RPT; ++j)
-                    M[j] = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mlow), j)), 1e30f);
-            }
-            const float dcut = fmaxf(kDensSkipLog2, dlow - kDensRelLog2 - g2n), zcut = mlow + wskip;
-            for (int ib = 0; ib < cnt; ib += GP) {
-                const int il = ib + lane / RPT;
-                bool need = false;
-                if (il < cnt && bj.c.w >= 0.0f) {
-                    const float2 h = hisave[wave][ib * RPT + lane];
-                    // (written so that a NaN bound keeps the pair)
-                    need = !(b1_pos && h.x < dcut && h.y < zcut);
-                }
-                unsigned long long nm = wave_ballot(need);
-              while (nm != 0ull) {
-                const int k = __builtin_ctzll(nm) / RPT;
-                const unsigned bits = (unsigned)(nm >> (k * RPT)) & ((1u << RPT) - 1u);
-                nm &= ~((unsigned long long)((1u << RPT) - 1u) << (k * RPT));
-                const int i = ib + k;
-                const Ent g = ent_from(tile[EW * i], tile[EW * i + 1], tile[EW * i + 2], tile[EW * i + 3]);
-                float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (COLOR) cc = tile[EW * i + 5];
-#pragma unroll
-                for (int j = 0; j < RPT; ++j) {
-                    if (!((bits >> j) & 1u)) continue;  // no ray of tile j needs the pair
-                    Geo q;
-                    pair_geo_coarse(g, v0[j], v1[j], v2[j], bl.hm, bl.b1, bl.nc2, q);
-                    const float delta = exp2_(q.d2);
-                    D[j] += delta;
-                    // log2 of the weight relative to the running maximum, b1 d2 + (nc2 t - M)
-                    float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -M[j]));
-                    // A weight below 2^kFwdSkipLog2 of the running maximum does not change the sums:
-                    // its terms are skipped (the branch is uniform over a wave for most Gaussians).
-                    if (zr < wskip) continue;
-                    pair_refine(q);
-                    if (zr > 0.0f) {  // new running maximum: rescale the sums (rare)
-                        const float sc = exp2_(M[j] - q.z2);
-                        S[j] *= sc;
-                        T[j] *= sc;
-                        if (NORMALS) {
-                            N0[j] *= sc;
-                            N1[j] *= sc;
-                            N2[j] *= sc;
-                        }
-                        if (COLOR) {
-                            C0[j] *= sc;
-                            C1[j] *= sc;
-                            C2[j] *= sc;
-                        }
-                        M[j] = q.z2;
-                        zr = 0.0f;
-                    }
-                    const float ew = exp2_(zr);
-                    S[j] += ew;
-                    T[j] = fmaf(ew, q.t, T[j]);
+            for (int j = 0; j < RPT; ++j) {
+                if (!((bits >> j) & 1u)) continue;  // no ray of tile j needs the pair
+                Geo q;
+                pair_geo_coarse(g, v0[j], v1[j], v2[j], bl.hm, bl.b1, bl.nc2, q);
+                const float delta = exp2_(q.d2);
+                D[j] += delta;
+                // log2 of the weight relative to the running maximum, b1 d2 + (nc2 t - M)
+                float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -M[j]));
+                // A weight below 2^kFwdSkipLog2 of the running maximum does not change the sums:
+                // its terms are skipped (the branch is uniform over a wave for most Gaussians).
+                if (zr < wskip) continue;
+                pair_refine(q);
+                if (zr > 0.0f) {  // new running maximum: rescale the sums (rare)
+                    const float sc = exp2_(M[j] - q.z2);
+                    S[j] *= sc;
+                    T[j] *= sc;
                     if (NORMALS) {
-                        const float g0 = g.u00 * q.r0;
-                        const float g1 = fmaf(g.u01, q.r0, g.u11 * q.r1);
-                        const float g2 = fmaf(g.u02, q.r0, fmaf(g.u12, q.r1, g.u22 * q.r2));
-                        const float es = ew * rsq_(fmaf(g0, g0, fmaf(g1, g1, fmaf(g2, g2, kEpsN))));
-                        N0[j] = fmaf(es, g0, N0[j]);
-                        N1[j] = fmaf(es, g1, N1[j]);
-                        N2[j] = fmaf(es, g2, N2[j]);
+                        N0[j] *= sc;
+                        N1[j] *= sc;
+                        N2[j] *= sc;
                     }
                     if (COLOR) {
-                        C0[j] = fmaf(ew, cc.x, C0[j]);
-                        C1[j] = fmaf(ew, cc.y, C1[j]);
-                        C2[j] = fmaf(ew, cc.z, C2[j]);
+                        C0[j] *= sc;
+                        C1[j] *= sc;
+                        C2[j] *= sc;
                     }
+                    M[j] = q.z2;
+                    zr = 0.0f;
                 }
-              }
+                const float ew = exp2_(zr);
+                S[j] += ew;
+                T[j] = fmaf(ew, q.t, T[j]);
+                if (NORMALS) {
+                    const float g0 = g.u00 * q.r0;
+                    const float g1 = fmaf(g.u01, q.r0, g.u11 * q.r1);
+                    const float g2 = fmaf(g.u02, q.r0, fmaf(g.u12, q.r1, g.u22 * q.r2));
+                    const float es = ew * rsq_(fmaf(g0, g0, fmaf(g1, g1, fmaf(g2, g2, kEpsN))));
+                    N0[j] = fmaf(es, g0, N0[j]);
+                    N1[j] = fmaf(es, g1, N1[j]);
+                    N2[j] = fmaf(es, g2, N2[j]);
+                }
+                if (COLOR) {
+                    C0[j] = fmaf(ew, cc.x, C0[j]);
+                    C1[j] = fmaf(ew, cc.y, C1[j]);
+                    C2[j] = fmaf(ew, cc.z, C2[j]);
+                }
             }
+          }
         }
-        }
+    }
+    }
 
-        const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
+    const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            if (loc[j] < 0) continue;
-            write_ray<F>(P, O, item.view, vr.ray_off + loc[j], e, kk, o0, o1, o2, v0[j], v1[j], v2[j], M[j], S[j],
-                         T[j], N0[j], N1[j], N2[j], C0[j], C1[j], C2[j], D[j], at[j], dt[j]);
-        }
-        if (!PERSIST) break;
+    for (int j = 0; j < RPT; ++j) {
+        if (loc[j] < 0) continue;
+        write_ray<F>(P, O, item.view, vr.ray_off + loc[j], e, kk, o0, o1, o2, v0[j], v1[j], v2[j], M[j], S[j],
+                     T[j], N0[j], N1[j], N2[j], C0[j], C1[j], C2[j], D[j], at[j], dt[j]);
     }
 }
 
@@ -302,16 +289,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
 // variant fits without spilling, else what its registers give.
 constexpr int bwd_min_waves(int F)
 {
-    return ((F & kCol) ? F == kCol : !((F & kFlw) && (F & kPer))) ? 6 : 1;
+    return (F & kCol) && F != kCol ? 1 : 6;
 }
 
 template <int BLOCK, int RT, int F>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(bwd_min_waves(F)))) void bwd_kernel(Params P, BwdIn I, const BwdItem *__restrict__ items,
-                                                   int n_items, const int *__restrict__ order,
-                                                   int *__restrict__ counter, float *__restrict__ partial,
+                                                   const int *__restrict__ order, float *__restrict__ partial,
                                                    float *__restrict__ beta_partial)
 {
-    constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0;
+    constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     // Without a normal cotangent the pairs take pair_adjoint_offset: the staged ray is
     // (v, M2) (invS, tf_bar, kappa, D_bar) (t_f, dc, 0, 0) [(Cb, 0)]; with one it is the prologue
     // as written by ray_prologue (four float4).
@@ -326,172 +312,160 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(bwd_min_w
     __shared__ float4 smem[SM4];
     float4 *rays = smem;
     float *red = reinterpret_cast<float *>(smem);
-    __shared__ int s_item;
-    int pos = blockIdx.x;
     const int tid = threadIdx.x;
-    for (;;) {
-        if (PERSIST) {
-            __syncthreads();
-            if (tid == 0) s_item = atomicAdd(counter, 1);
-            __syncthreads();
-            pos = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep the item in SGPRs
-        }
-        if (pos >= n_items) break;
-        const int it = order ? ld_uniform(order + pos) : pos;
-        const BwdItem item = ld_uniform(items + it);
-        const ViewRec vr = ld_uniform(P.views + item.view);
-        const SceneRec sr = ld_uniform(P.scenes + vr.scene);
-        const CamRec cam = cam_of(P, item.view);
-        const float *e = cam.e, *kk = cam.k;
-        double o[3];
-        cam_centre(e, o);
-        const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
-        const Blend bl = blend_of(P, vr.scene);
-        const int hw = vr.h * vr.w;
-        const int end = min(item.ray0 + item.span, hw);
+    const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
+    const BwdItem item = ld_uniform(items + it);
+    const ViewRec vr = ld_uniform(P.views + item.view);
+    const SceneRec sr = ld_uniform(P.scenes + vr.scene);
+    const CamRec cam = cam_of(P, item.view);
+    const float *e = cam.e, *kk = cam.k;
+    double o[3];
+    cam_centre(e, o);
+    const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
+    const Blend bl = blend_of(P, vr.scene);
+    const int hw = vr.h * vr.w;
+    const int end = min(item.ray0 + item.span, hw);
 
-        const int gi = tid % item.gc;
-        const int slot = tid / item.gc;
-        const bool active = slot < item.slots && item.g0 + gi < sr.n;
-        Ent g;
-        float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (active) {
-            const int gg = sr.gauss_off + item.g0 + gi;
-            float4 q[4];
-            make_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
-            g = ent_from(q[0], q[1], q[2], q[3]);
-            if (COLOR) cc = colour_entry(P.colors + 3 * gg);
-        }
-        float aB1 = 0, aB2 = 0;
-        float aC0 = 0, aC1 = 0, aC2 = 0;
-        // The item's rays RT at a time: staged with their prologue, then `pair` runs over this lane's
-        // rays slot, slot + slots, ... (walked by address: one induction variable).
-        auto passes = [&](auto &&pair) {
-            for (int r0 = item.ray0; r0 < end; r0 += RT) {
-                const int cnt = min(RT, end - r0);
-                __syncthreads();
-                for (int q = tid; q < RT; q += BLOCK) {
-                    float4 pr[4];
-                    ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, r0 + q, q < cnt, bl.b1, bl.nc2, pr);
-                    if (PLAIN) {
-                        rays[RW * q] = pr[0];
-                        rays[RW * q + 1] = make_float4(pr[1].x, pr[1].y, pr[2].y, pr[2].z);
-                        rays[RW * q + 2] = make_float4(pr[2].w, pr[3].w, 0.0f, 0.0f);
-                        if (COLOR) rays[RW * q + 3] = pr[3];
-                    } else {
+    const int gi = tid % item.gc;
+    const int slot = tid / item.gc;
+    const bool active = slot < item.slots && item.g0 + gi < sr.n;
+    Ent g;
+    float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (active) {
+        const int gg = sr.gauss_off + item.g0 + gi;
+        float4 q[4];
+        make_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, q);
+        g = ent_from(q[0], q[1], q[2], q[3]);
+        if (COLOR) cc = colour_entry(P.colors + 3 * gg);
+    }
+    float aB1 = 0, aB2 = 0;
+    float aC0 = 0, aC1 = 0, aC2 = 0;
+    // The item's rays RT at a time: staged with their prologue, then `pair` runs over this lane's
+    // rays slot, slot + slots, ... (walked by address: one induction variable).
+    auto passes = [&](auto &&pair) {
+        for (int r0 = item.ray0; r0 < end; r0 += RT) {
+            const int cnt = min(RT, end - r0);
+            __syncthreads();
+            for (int q = tid; q < RT; q += BLOCK) {
+                float4 pr[4];
+                ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, r0 + q, q < cnt, bl.b1, bl.nc2, pr);
+                if (PLAIN) {
+                    rays[RW * q] = pr[0];
+                    rays[RW * q + 1] = make_float4(pr[1].x, pr[1].y, pr[2].y, pr[2].z);
+                    rays[RW * q + 2] = make_float4(pr[2].w, pr[3].w, 0.0f, 0.0f);
+                    if (COLOR) rays[RW * q + 3] = pr[3];
+                } else {
 #pragma unroll
-                        for (int k = 0; k < RW; ++k) rays[RW * q + k] = pr[k];
-                    }
-                }
-                __syncthreads();
-                if (active) {
-                    const float4 *const rend = rays + RW * cnt;
-                    for (const float4 *rp = rays + RW * slot; rp < rend; rp += RW * item.slots) pair(rp);
+                    for (int k = 0; k < RW; ++k) rays[RW * q + k] = pr[k];
                 }
             }
-            __syncthreads();  // every lane is done with the staged rays (the LDS is reused below)
-        };
-        // One pair without a normal cotangent, accumulated in the offset form.
-        auto plain_pair = [&](const float4 *rp, OffsetAcc &acc) {
-            const float4 x0 = rp[0], x1 = rp[1], x2 = rp[2];
-            float4 x4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (COLOR) x4 = rp[3];
+            __syncthreads();
+            if (active) {
+                const float4 *const rend = rays + RW * cnt;
+                for (const float4 *rp = rays + RW * slot; rp < rend; rp += RW * item.slots) pair(rp);
+            }
+        }
+        __syncthreads();  // every lane is done with the staged rays (the LDS is reused below)
+    };
+    // One pair without a normal cotangent, accumulated in the offset form.
+    auto plain_pair = [&](const float4 *rp, OffsetAcc &acc) {
+        const float4 x0 = rp[0], x1 = rp[1], x2 = rp[2];
+        float4 x4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (COLOR) x4 = rp[3];
+        const float v0 = x0.x, v1 = x0.y, v2 = x0.z;
+        Geo q;
+        pair_geo_coarse(g, v0, v1, v2, bl.hm, bl.b1, bl.nc2, q);
+        const float delta = exp2_(q.d2);
+        // normalised blend weight 2^(z2 - M) / S, with z2 - M = b1 d2 + (nc2 t - M)
+        const float wt = exp2_(fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w))) * x1.x;
+        const float tfb = x1.y;
+        float lin = tfb * q.t;
+        if (COLOR) {
+            lin = fmaf(x4.x, cc.x, fmaf(x4.y, cc.y, fmaf(x4.z, cc.z, lin)));
+            aC0 = fmaf(wt, x4.x, aC0);
+            aC1 = fmaf(wt, x4.y, aC1);
+            aC2 = fmaf(wt, x4.z, aC2);
+        }
+        const float zb = wt * (lin - x1.z);
+        const float tb = fmaf(-bl.cb, zb, wt * tfb);
+        const float db = fmaf(bl.b1, zb, x1.w * delta);
+        aB1 = fmaf(zb, q.d2 - x2.y, aB1);
+        aB2 = fmaf(zb, q.t - x2.x, aB2);
+        pair_adjoint_offset(q, v0, v1, v2, tb, db, acc);
+    };
+    float *my = red + RS * tid;
+    if (!PLAIN) {
+        PairAcc acc;
+        passes([&](const float4 *rp) {
+            const float4 x0 = rp[0], x1 = rp[1], x2 = rp[2], x3 = rp[3];
             const float v0 = x0.x, v1 = x0.y, v2 = x0.z;
             Geo q;
-            pair_geo_coarse(g, v0, v1, v2, bl.hm, bl.b1, bl.nc2, q);
+            pair_geo(g, v0, v1, v2, bl.hm, bl.b1, bl.nc2, q);
             const float delta = exp2_(q.d2);
-            // normalised blend weight 2^(z2 - M) / S, with z2 - M = b1 d2 + (nc2 t - M)
-            const float wt = exp2_(fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w))) * x1.x;
+            const float wt = exp2_(q.z2 - x0.w) * x1.x;   // normalised blend weight
             const float tfb = x1.y;
-            float lin = tfb * q.t;
+            PairNormal pn{0, 0, 0, 0, 0};
+            if (NORMALS) pn = pair_normal(g, q, x1.z, x1.w, x2.x);
+            // softmax adjoint: z_bar = wt (tf_bar t + Nb.n + Cb.c - kappa)
+            float lin = fmaf(tfb, q.t, pn.nN);
             if (COLOR) {
-                lin = fmaf(x4.x, cc.x, fmaf(x4.y, cc.y, fmaf(x4.z, cc.z, lin)));
-                aC0 = fmaf(wt, x4.x, aC0);
-                aC1 = fmaf(wt, x4.y, aC1);
-                aC2 = fmaf(wt, x4.z, aC2);
+                lin = fmaf(x3.x, cc.x, fmaf(x3.y, cc.y, fmaf(x3.z, cc.z, lin)));
+                aC0 = fmaf(wt, x3.x, aC0);
+                aC1 = fmaf(wt, x3.y, aC1);
+                aC2 = fmaf(wt, x3.z, aC2);
             }
-            const float zb = wt * (lin - x1.z);
+            const float zb = wt * (lin - x2.y);
+            // z = beta1 d - (beta2/eta) t
             const float tb = fmaf(-bl.cb, zb, wt * tfb);
-            const float db = fmaf(bl.b1, zb, x1.w * delta);
-            aB1 = fmaf(zb, q.d2 - x2.y, aB1);
-            aB2 = fmaf(zb, q.t - x2.x, aB2);
-            pair_adjoint_offset(q, v0, v1, v2, tb, db, acc);
-        };
-        float *my = red + RS * tid;
-        if (!PLAIN) {
-            PairAcc acc;
-            passes([&](const float4 *rp) {
-                const float4 x0 = rp[0], x1 = rp[1], x2 = rp[2], x3 = rp[3];
-                const float v0 = x0.x, v1 = x0.y, v2 = x0.z;
-                Geo q;
-                pair_geo(g, v0, v1, v2, bl.hm, bl.b1, bl.nc2, q);
-                const float delta = exp2_(q.d2);
-                const float wt = exp2_(q.z2 - x0.w) * x1.x;   // normalised blend weight
-                const float tfb = x1.y;
-                PairNormal pn{0, 0, 0, 0, 0};
-                if (NORMALS) pn = pair_normal(g, q, x1.z, x1.w, x2.x);
-                // softmax adjoint: z_bar = wt (tf_bar t + Nb.n + Cb.c - kappa)
-                float lin = fmaf(tfb, q.t, pn.nN);
-                if (COLOR) {
-                    lin = fmaf(x3.x, cc.x, fmaf(x3.y, cc.y, fmaf(x3.z, cc.z, lin)));
-                    aC0 = fmaf(wt, x3.x, aC0);
-                    aC1 = fmaf(wt, x3.y, aC1);
-                    aC2 = fmaf(wt, x3.z, aC2);
-                }
-                const float zb = wt * (lin - x2.y);
-                // z = beta1 d - (beta2/eta) t
-                const float tb = fmaf(-bl.cb, zb, wt * tfb);
-                const float db = fmaf(bl.b1, zb, x2.z * delta);
-                aB1 = fmaf(zb, q.d2 - x3.w, aB1);
-                aB2 = fmaf(zb, q.t - x2.w, aB2);
-                pair_adjoint<NORMALS>(g, q, v0, v1, v2, wt, pn, x1.z, x1.w, x2.x, tb, db, acc);
-            });
-            my[0] = acc.u0; my[1] = acc.u1; my[2] = acc.u2; my[3] = acc.u3; my[4] = acc.u4; my[5] = acc.u5;
-            my[6] = acc.p0; my[7] = acc.p1; my[8] = acc.p2; my[9] = acc.l;
-        } else {
-            OffsetAcc acc;
-            passes([&](const float4 *rp) { plain_pair(rp, acc); });
-            offset_acc_store(acc, my);
-        }
+            const float db = fmaf(bl.b1, zb, x2.z * delta);
+            aB1 = fmaf(zb, q.d2 - x3.w, aB1);
+            aB2 = fmaf(zb, q.t - x2.w, aB2);
+            pair_adjoint<NORMALS>(g, q, v0, v1, v2, wt, pn, x1.z, x1.w, x2.x, tb, db, acc);
+        });
+        my[0] = acc.u0; my[1] = acc.u1; my[2] = acc.u2; my[3] = acc.u3; my[4] = acc.u4; my[5] = acc.u5;
+        my[6] = acc.p0; my[7] = acc.p1; my[8] = acc.p2; my[9] = acc.l;
+    } else {
+        OffsetAcc acc;
+        passes([&](const float4 *rp) { plain_pair(rp, acc); });
+        offset_acc_store(acc, my);
+    }
 
-        // deterministic block reduction: Gaussian partials over the slots, betas over all lanes
-        if (COLOR) {
-            my[LREC - 3] = aC0; my[LREC - 2] = aC1; my[LREC - 1] = aC2;
-        }
-        my[LREC] = aB1; my[LREC + 1] = aB2;
-        __syncthreads();
-        if (slot == 0 && gi < item.gc && item.g0 + gi < sr.n) {
-            float sum[LREC];
+    // deterministic block reduction: Gaussian partials over the slots, betas over all lanes
+    if (COLOR) {
+        my[LREC - 3] = aC0; my[LREC - 2] = aC1; my[LREC - 1] = aC2;
+    }
+    my[LREC] = aB1; my[LREC + 1] = aB2;
+    __syncthreads();
+    if (slot == 0 && gi < item.gc && item.g0 + gi < sr.n) {
+        float sum[LREC];
 #pragma unroll
-            for (int c = 0; c < LREC; ++c) sum[c] = red[RS * gi + c];
-            for (int s = 1; s < item.slots; ++s) {
+        for (int c = 0; c < LREC; ++c) sum[c] = red[RS * gi + c];
+        for (int s = 1; s < item.slots; ++s) {
 #pragma unroll
-                for (int c = 0; c < LREC; ++c) sum[c] += red[RS * (s * item.gc + gi) + c];
-            }
-            const int gg = sr.gauss_off + item.g0 + gi;
-            if (PLAIN)
-                write_partial_offset(partial + item.poff + REC * gi, sum, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
-            else
-                write_partial(partial + item.poff + REC * gi, sum, REC, P.means + 3 * gg, o);
+            for (int c = 0; c < LREC; ++c) sum[c] += red[RS * (s * item.gc + gi) + c];
         }
-        if (tid < 64) {
-            // lane l sums lanes l, l+64, ... in order, then a fixed butterfly over the wave
-            float s1 = 0.0f, s2 = 0.0f;
-            for (int k = tid; k < BLOCK; k += 64) {
-                s1 += red[RS * k + LREC];
-                s2 += red[RS * k + LREC + 1];
-            }
+        const int gg = sr.gauss_off + item.g0 + gi;
+        if (PLAIN)
+            write_partial_offset(partial + item.poff + REC * gi, sum, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
+        else
+            write_partial(partial + item.poff + REC * gi, sum, REC, P.means + 3 * gg, o);
+    }
+    if (tid < 64) {
+        // lane l sums lanes l, l+64, ... in order, then a fixed butterfly over the wave
+        float s1 = 0.0f, s2 = 0.0f;
+        for (int k = tid; k < BLOCK; k += 64) {
+            s1 += red[RS * k + LREC];
+            s2 += red[RS * k + LREC + 1];
+        }
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                s1 += __shfl_xor(s1, off, 64);
-                s2 += __shfl_xor(s2, off, 64);
-            }
-            if (tid == 0) {
-                beta_partial[2 * item.seq] = s1;
-                beta_partial[2 * item.seq + 1] = s2;
-            }
+        for (int off = 32; off > 0; off >>= 1) {
+            s1 += __shfl_xor(s1, off, 64);
+            s2 += __shfl_xor(s2, off, 64);
         }
-        if (!PERSIST) break;
+        if (tid == 0) {
+            beta_partial[2 * item.seq] = s1;
+            beta_partial[2 * item.seq + 1] = s2;
+        }
     }
 }
 
@@ -513,11 +487,10 @@ __device__ __forceinline__ float wave_sum(float x)
 
 template <int BLOCK, int RPT, int TG, int F>
 __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const BwdItem *__restrict__ items,
-                                                    int n_items, const int *__restrict__ order,
-                                                    int *__restrict__ counter, float *__restrict__ partial,
+                                                    const int *__restrict__ order, float *__restrict__ partial,
                                                     float *__restrict__ beta_partial)
 {
-    constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0;
+    constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     // without a normal cotangent the pairs take the offset form (pair_adjoint_offset)
     constexpr bool PLAIN = !NORMALS;
     constexpr int EW = COLOR ? 5 : 4;                       // float4 per LDS entry
@@ -528,165 +501,153 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
     __shared__ float4 tile[TG * EW];
     __shared__ float wsum[NW * TG * LREC];  // per wave, per Gaussian of the tile
     __shared__ float bsum[NW * 2];
-    __shared__ int s_item;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int pos = blockIdx.x;
-    for (;;) {
-        if (PERSIST) {
-            __syncthreads();
-            if (tid == 0) s_item = atomicAdd(counter, 1);
-            __syncthreads();
-            pos = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep the item in SGPRs
-        }
-        if (pos >= n_items) break;
-        const int it = order ? ld_uniform(order + pos) : pos;
-        const BwdItem item = ld_uniform(items + it);
-        const ViewRec vr = ld_uniform(P.views + item.view);
-        const SceneRec sr = ld_uniform(P.scenes + vr.scene);
-        const CamRec cam = cam_of(P, item.view);
-        const float *e = cam.e, *kk = cam.k;
-        double o[3];
-        cam_centre(e, o);
-        const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
-        const Blend bl = blend_of(P, vr.scene);
-        const int hw = vr.h * vr.w;
-        const int end = min(item.ray0 + item.span, hw);
-        float aB1 = 0.0f, aB2 = 0.0f;
+    const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
+    const BwdItem item = ld_uniform(items + it);
+    const ViewRec vr = ld_uniform(P.views + item.view);
+    const SceneRec sr = ld_uniform(P.scenes + vr.scene);
+    const CamRec cam = cam_of(P, item.view);
+    const float *e = cam.e, *kk = cam.k;
+    double o[3];
+    cam_centre(e, o);
+    const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
+    const Blend bl = blend_of(P, vr.scene);
+    const int hw = vr.h * vr.w;
+    const int end = min(item.ray0 + item.span, hw);
+    float aB1 = 0.0f, aB2 = 0.0f;
 
-        for (int gb = 0; gb < sr.n; gb += TG) {
-            const int cnt = min(TG, sr.n - gb);
-            __syncthreads();  // the previous tile's entries and sums are no longer read
-            for (int q = tid; q < cnt; q += BLOCK) {
-                const int gi = sr.gauss_off + gb + q;
-                make_entry(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &tile[EW * q]);
-                if (COLOR) tile[EW * q + 4] = colour_entry(P.colors + 3 * gi);
+    for (int gb = 0; gb < sr.n; gb += TG) {
+        const int cnt = min(TG, sr.n - gb);
+        __syncthreads();  // the previous tile's entries and sums are no longer read
+        for (int q = tid; q < cnt; q += BLOCK) {
+            const int gi = sr.gauss_off + gb + q;
+            make_entry(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &tile[EW * q]);
+            if (COLOR) tile[EW * q + 4] = colour_entry(P.colors + 3 * gi);
+        }
+        for (int q = tid; q < NW * TG * LREC; q += BLOCK) wsum[q] = 0.0f;
+        __syncthreads();
+        for (int rb = item.ray0; rb < end; rb += BLOCK * RPT) {
+            float4 x0[RPT], x1[RPT], x2[RPT], x3[RPT];
+#pragma unroll
+            for (int j = 0; j < RPT; ++j) {
+                const int local = rb + tid + j * BLOCK;
+                float4 pr[4];
+                ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local, local < end, bl.b1, bl.nc2, pr);
+                x0[j] = pr[0];
+                x1[j] = pr[1];
+                x2[j] = pr[2];
+                x3[j] = pr[3];
             }
-            for (int q = tid; q < NW * TG * LREC; q += BLOCK) wsum[q] = 0.0f;
-            __syncthreads();
-            for (int rb = item.ray0; rb < end; rb += BLOCK * RPT) {
-                float4 x0[RPT], x1[RPT], x2[RPT], x3[RPT];
+            for (int i = 0; i < cnt; ++i) {
+                const Ent g = ent_from(tile[EW * i], tile[EW * i + 1], tile[EW * i + 2], tile[EW * i + 3]);
+                float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (COLOR) cc = tile[EW * i + 4];
+                Geo q[RPT];
+                float delta[RPT], wt[RPT];
+                bool need_w = false, need_d = false;
 #pragma unroll
                 for (int j = 0; j < RPT; ++j) {
-                    const int local = rb + tid + j * BLOCK;
-                    float4 pr[4];
-                    ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local, local < end, bl.b1, bl.nc2, pr);
-                    x0[j] = pr[0];
-                    x1[j] = pr[1];
-                    x2[j] = pr[2];
-                    x3[j] = pr[3];
+                    if (PLAIN)
+                        pair_geo_coarse(g, x0[j].x, x0[j].y, x0[j].z, bl.hm, bl.b1, bl.nc2, q[j]);
+                    else
+                        pair_geo(g, x0[j].x, x0[j].y, x0[j].z, bl.hm, bl.b1, bl.nc2, q[j]);
+                    delta[j] = exp2_(q[j].d2);
+                    const bool w_on = q[j].z2 - x0[j].w >= kSkipLog2;
+                    wt[j] = w_on ? exp2_(q[j].z2 - x0[j].w) * x1[j].x : 0.0f;
+                    need_w |= w_on;
+                    need_d |= x2[j].z * delta[j] != 0.0f;
                 }
-                for (int i = 0; i < cnt; ++i) {
-                    const Ent g = ent_from(tile[EW * i], tile[EW * i + 1], tile[EW * i + 2], tile[EW * i + 3]);
-                    float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (COLOR) cc = tile[EW * i + 4];
-                    Geo q[RPT];
-                    float delta[RPT], wt[RPT];
-                    bool need_w = false, need_d = false;
+                PairAcc a;
+                OffsetAcc pa;
+                float aC0 = 0.0f, aC1 = 0.0f, aC2 = 0.0f;
+                if (wave_any(need_w)) {
 #pragma unroll
                     for (int j = 0; j < RPT; ++j) {
-                        if (PLAIN)
-                            pair_geo_coarse(g, x0[j].x, x0[j].y, x0[j].z, bl.hm, bl.b1, bl.nc2, q[j]);
-                        else
-                            pair_geo(g, x0[j].x, x0[j].y, x0[j].z, bl.hm, bl.b1, bl.nc2, q[j]);
-                        delta[j] = exp2_(q[j].d2);
-                        const bool w_on = q[j].z2 - x0[j].w >= kSkipLog2;
-                        wt[j] = w_on ? exp2_(q[j].z2 - x0[j].w) * x1[j].x : 0.0f;
-                        need_w |= w_on;
-                        need_d |= x2[j].z * delta[j] != 0.0f;
-                    }
-                    PairAcc a;
-                    OffsetAcc pa;
-                    float aC0 = 0.0f, aC1 = 0.0f, aC2 = 0.0f;
-                    if (wave_any(need_w)) {
-#pragma unroll
-                        for (int j = 0; j < RPT; ++j) {
-                            const float tfb = x1[j].y;
-                            PairNormal pn{0, 0, 0, 0, 0};
-                            if (NORMALS) pn = pair_normal(g, q[j], x1[j].z, x1[j].w, x2[j].x);
-                            float lin = fmaf(tfb, q[j].t, pn.nN);
-                            if (COLOR) {
-                                lin = fmaf(x3[j].x, cc.x, fmaf(x3[j].y, cc.y, fmaf(x3[j].z, cc.z, lin)));
-                                aC0 = fmaf(wt[j], x3[j].x, aC0);
-                                aC1 = fmaf(wt[j], x3[j].y, aC1);
-                                aC2 = fmaf(wt[j], x3[j].z, aC2);
-                            }
-                            const float zb = wt[j] * (lin - x2[j].y);
-                            const float tb = fmaf(-bl.cb, zb, wt[j] * tfb);
-                            const float db = fmaf(bl.b1, zb, x2[j].z * delta[j]);
-                            aB1 = fmaf(zb, q[j].d2 - x3[j].w, aB1);
-                            aB2 = fmaf(zb, q[j].t - x2[j].w, aB2);
-                            if (PLAIN) {
-                                pair_adjoint_offset(q[j], x0[j].x, x0[j].y, x0[j].z, tb, db, pa);
-                            } else {
-                                pair_adjoint<NORMALS>(g, q[j], x0[j].x, x0[j].y, x0[j].z, wt[j], pn, x1[j].z,
-                                                      x1[j].w, x2[j].x, tb, db, a);
-                            }
+                        const float tfb = x1[j].y;
+                        PairNormal pn{0, 0, 0, 0, 0};
+                        if (NORMALS) pn = pair_normal(g, q[j], x1[j].z, x1[j].w, x2[j].x);
+                        float lin = fmaf(tfb, q[j].t, pn.nN);
+                        if (COLOR) {
+                            lin = fmaf(x3[j].x, cc.x, fmaf(x3[j].y, cc.y, fmaf(x3[j].z, cc.z, lin)));
+                            aC0 = fmaf(wt[j], x3[j].x, aC0);
+                            aC1 = fmaf(wt[j], x3[j].y, aC1);
+                            aC2 = fmaf(wt[j], x3[j].z, aC2);
                         }
-                    } else if (wave_any(need_d)) {
-                        // zero weight on every ray of the wave: only d(alpha)/d(delta) remains
-#pragma unroll
-                        for (int j = 0; j < RPT; ++j) {
-                            if (PLAIN) {
-                                pair_adjoint_offset(q[j], x0[j].x, x0[j].y, x0[j].z, 0.0f, x2[j].z * delta[j], pa);
-                            } else {
-                                const PairNormal pn{0, 0, 0, 0, 0};
-                                pair_adjoint<false>(g, q[j], x0[j].x, x0[j].y, x0[j].z, 0.0f, pn, 0.0f, 0.0f, 0.0f,
-                                                    0.0f, x2[j].z * delta[j], a);
-                            }
+                        const float zb = wt[j] * (lin - x2[j].y);
+                        const float tb = fmaf(-bl.cb, zb, wt[j] * tfb);
+                        const float db = fmaf(bl.b1, zb, x2[j].z * delta[j]);
+                        aB1 = fmaf(zb, q[j].d2 - x3[j].w, aB1);
+                        aB2 = fmaf(zb, q[j].t - x2[j].w, aB2);
+                        if (PLAIN) {
+                            pair_adjoint_offset(q[j], x0[j].x, x0[j].y, x0[j].z, tb, db, pa);
+                        } else {
+                            pair_adjoint<NORMALS>(g, q[j], x0[j].x, x0[j].y, x0[j].z, wt[j], pn, x1[j].z,
+                                                  x1[j].w, x2[j].x, tb, db, a);
                         }
-                    } else {
-                        continue;  // no term of this Gaussian on this wave's rays
                     }
-                    float v[LREC];
-                    if (PLAIN) {
-                        offset_acc_store(pa, v);
-                    } else {
-                        v[0] = a.u0; v[1] = a.u1; v[2] = a.u2; v[3] = a.u3; v[4] = a.u4; v[5] = a.u5;
-                        v[6] = a.p0; v[7] = a.p1; v[8] = a.p2; v[9] = a.l;
-                    }
-                    if (COLOR) {
-                        v[LREC - 3] = aC0; v[LREC - 2] = aC1; v[LREC - 1] = aC2;
-                    }
+                } else if (wave_any(need_d)) {
+                    // zero weight on every ray of the wave: only d(alpha)/d(delta) remains
 #pragma unroll
-                    for (int c = 0; c < LREC; ++c) v[c] = wave_sum(v[c]);
-                    if (lane == 0) {
-                        float *dst = wsum + (wave * TG + i) * LREC;
-#pragma unroll
-                        for (int c = 0; c < LREC; ++c) dst[c] += v[c];
+                    for (int j = 0; j < RPT; ++j) {
+                        if (PLAIN) {
+                            pair_adjoint_offset(q[j], x0[j].x, x0[j].y, x0[j].z, 0.0f, x2[j].z * delta[j], pa);
+                        } else {
+                            const PairNormal pn{0, 0, 0, 0, 0};
+                            pair_adjoint<false>(g, q[j], x0[j].x, x0[j].y, x0[j].z, 0.0f, pn, 0.0f, 0.0f, 0.0f,
+                                                0.0f, x2[j].z * delta[j], a);
+                        }
                     }
+                } else {
+                    continue;  // no term of this Gaussian on this wave's rays
+                }
+                float v[LREC];
+                if (PLAIN) {
+                    offset_acc_store(pa, v);
+                } else {
+                    v[0] = a.u0; v[1] = a.u1; v[2] = a.u2; v[3] = a.u3; v[4] = a.u4; v[5] = a.u5;
+                    v[6] = a.p0; v[7] = a.p1; v[8] = a.p2; v[9] = a.l;
+                }
+                if (COLOR) {
+                    v[LREC - 3] = aC0; v[LREC - 2] = aC1; v[LREC - 1] = aC2;
+                }
+#pragma unroll
+                for (int c = 0; c < LREC; ++c) v[c] = wave_sum(v[c]);
+                if (lane == 0) {
+                    float *dst = wsum + (wave * TG + i) * LREC;
+#pragma unroll
+                    for (int c = 0; c < LREC; ++c) dst[c] += v[c];
                 }
             }
-            __syncthreads();
-            // the tile's partial records: waves summed in order, -(sum rho) mu'^T applied in double
-            for (int q = tid; q < cnt; q += BLOCK) {
-                float sum[LREC];
-#pragma unroll
-                for (int c = 0; c < LREC; ++c) sum[c] = wsum[q * LREC + c];
-                for (int w = 1; w < NW; ++w) {
-#pragma unroll
-                    for (int c = 0; c < LREC; ++c) sum[c] += wsum[(w * TG + q) * LREC + c];
-                }
-                const int gg = sr.gauss_off + gb + q;
-                if (PLAIN)
-                    write_partial_offset(partial + item.poff + REC * (gb + q), sum, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
-                else
-                    write_partial(partial + item.poff + REC * (gb + q), sum, REC, P.means + 3 * gg, o);
-            }
-        }
-        // betas: lanes summed over the wave, then the waves in order
-        aB1 = wave_sum(aB1);
-        aB2 = wave_sum(aB2);
-        if (lane == 0) {
-            bsum[2 * wave] = aB1;
-            bsum[2 * wave + 1] = aB2;
         }
         __syncthreads();
-        if (tid < 2) {
-            float sb = 0.0f;
-            for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
-            beta_partial[2 * item.seq + tid] = sb;
+        // the tile's partial records: waves summed in order, -(sum rho) mu'^T applied in double
+        for (int q = tid; q < cnt; q += BLOCK) {
+            float sum[LREC];
+#pragma unroll
+            for (int c = 0; c < LREC; ++c) sum[c] = wsum[q * LREC + c];
+            for (int w = 1; w < NW; ++w) {
+#pragma unroll
+                for (int c = 0; c < LREC; ++c) sum[c] += wsum[(w * TG + q) * LREC + c];
+            }
+            const int gg = sr.gauss_off + gb + q;
+            if (PLAIN)
+                write_partial_offset(partial + item.poff + REC * (gb + q), sum, REC, P.prec + 6 * gg, P.means + 3 * gg, o);
+            else
+                write_partial(partial + item.poff + REC * (gb + q), sum, REC, P.means + 3 * gg, o);
         }
-        if (!PERSIST) break;
+    }
+    // betas: lanes summed over the wave, then the waves in order
+    aB1 = wave_sum(aB1);
+    aB2 = wave_sum(aB2);
+    if (lane == 0) {
+        bsum[2 * wave] = aB1;
+        bsum[2 * wave + 1] = aB2;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        float sb = 0.0f;
+        for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
+        beta_partial[2 * item.seq + tid] = sb;
     }
 }
 
@@ -706,11 +667,11 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
 
 template <int BLOCK, int T, int TG, int F>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm) ? 4 : 6))) void bwdt_kernel(
-    Params P, BwdIn I, const BwdItem *__restrict__ items, int n_items, const int *__restrict__ order,
-    int *__restrict__ counter, float *__restrict__ partial, float *__restrict__ beta_partial,
+    Params P, BwdIn I, const BwdItem *__restrict__ items, const int *__restrict__ order, float *__restrict__ partial,
+    float *__restrict__ beta_partial,
     unsigned long long *__restrict__ masks)
 {
-    constexpr bool NORMALS = (F & kNrm) != 0, PERSIST = (F & kPer) != 0, COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
+    constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int NW = BLOCK / 64;
     constexpr int RAYS = 64 * T;
     static_assert(T <= 32 && 64 % T == 0, "a 32-bit mask of the item's ray tiles, whole tile sets per wave");
@@ -728,279 +689,267 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     __shared__ float bsum[2 * NW];
     __shared__ int slist[BIG ? BLOCK : 1];    // scenes beyond BLOCK Gaussians: a round's survivors
     __shared__ int wcnt[BIG ? NW : 1];
-    __shared__ int s_item;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int pos = blockIdx.x;
-    for (;;) {
-        if (PERSIST) {
-            __syncthreads();
-            if (tid == 0) s_item = atomicAdd(counter, 1);
-            __syncthreads();
-            pos = __builtin_amdgcn_readfirstlane(s_item);  // block-uniform: keep the item in SGPRs
-        }
-        if (pos >= n_items) break;
-        const int it = order ? ld_uniform(order + pos) : pos;
-        const BwdItem item = ld_uniform(items + it);
-        const ViewRec vr = ld_uniform(P.views + item.view);
-        const SceneRec sr = ld_uniform(P.scenes + vr.scene);
-        const CamRec cam = cam_of(P, item.view);
-        const float *e = cam.e, *kk = cam.k;
-        double o[3];
-        cam_centre(e, o);
-        const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
-        const Blend bl = blend_of(P, vr.scene);
-        const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
-        const int nt = min(T, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
+    const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
+    const BwdItem item = ld_uniform(items + it);
+    const ViewRec vr = ld_uniform(P.views + item.view);
+    const SceneRec sr = ld_uniform(P.scenes + vr.scene);
+    const CamRec cam = cam_of(P, item.view);
+    const float *e = cam.e, *kk = cam.k;
+    double o[3];
+    cam_centre(e, o);
+    const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
+    const Blend bl = blend_of(P, vr.scene);
+    const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
+    const int nt = min(T, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
 
-        __syncthreads();  // the previous item is done with the staged rays
-        for (int q = tid; q < RAYS; q += BLOCK) {
-            int row = 0, col = 0;
-            const int local = (q >> 6) < nt ? tile_local(vr, item.ray0 + (q >> 6), q & 63, row, col) : -1;
-            float4 pr[4];
-            ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local >= 0 ? local : 0, local >= 0, bl.b1, bl.nc2,
-                            pr, local >= 0 ? row : 0, col);
-            if (NORMALS) {
+    __syncthreads();  // the previous item is done with the staged rays
+    for (int q = tid; q < RAYS; q += BLOCK) {
+        int row = 0, col = 0;
+        const int local = (q >> 6) < nt ? tile_local(vr, item.ray0 + (q >> 6), q & 63, row, col) : -1;
+        float4 pr[4];
+        ray_prologue<F>(P, I, item.view, vr, e, kk, o0, o1, o2, local >= 0 ? local : 0, local >= 0, bl.b1, bl.nc2,
+                        pr, local >= 0 ? row : 0, col);
+        if (NORMALS) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) rays[RW * q + k] = pr[k];
+            for (int k = 0; k < 4; ++k) rays[RW * q + k] = pr[k];
+            continue;
+        }
+        // the weight 2^(z2 - M2) / S as 2^(z2 - M2 - log2 S); a ray past the edge has M2 = inf, S = inf
+        rays[RW * q] = make_float4(pr[0].x, pr[0].y, pr[0].z, pr[0].w - __builtin_amdgcn_logf(pr[1].x));
+        rays[RW * q + 1] = make_float4(pr[1].y, pr[2].z, pr[3].w, pr[2].w);
+        if (COLOR) {
+            // the colour cotangent and its product with the blended colour (kappa's colour part)
+            float kc = 0.0f;
+            if (local >= 0) {
+                const size_t r3 = 3 * ((size_t)vr.ray_off + local);
+                kc = fmaf(pr[3].x, I.color[r3], fmaf(pr[3].y, I.color[r3 + 1], pr[3].z * I.color[r3 + 2]));
+            }
+            rays[RW * q + 2] = make_float4(pr[3].x, pr[3].y, pr[3].z, kc);
+        }
+    }
+    __syncthreads();
+    // each ray tile's box and least normaliser, for the bound that lets a wave pass over the tiles
+    // on which a Gaussian can neither weigh above FP32's zero nor add a density above
+    // 2^kDensSkipLog2 (tile_bounds)
+    for (int tt = wave; tt < nt; tt += NW) {
+        int row, col;
+        const bool ok = tile_local(vr, item.ray0 + tt, lane, row, col) >= 0;
+        const float4 x0 = rays[RW * (64 * tt + lane)];
+        const float dbar = NORMALS ? rays[RW * (64 * tt + lane) + 2].z : rays[RW * (64 * tt + lane) + 1].y;
+        const int db_flag = wave_any(dbar != 0.0f) ? 1 : 0;
+        const TileBox b = wave_box(x0.x, x0.y, x0.z, ok, e);
+        const float norm = NORMALS ? x0.w - __builtin_amdgcn_logf(rays[RW * (64 * tt + lane) + 1].x) : x0.w;
+        const float nmin = wave_min_u(ok ? norm : INFINITY);
+        if (lane == 0) {
+            tbox[3 * tt] = b.c;
+            tbox[3 * tt + 1] = b.x;
+            tbox[3 * tt + 2] = b.y;
+            tnorm[tt] = nmin;
+            tdb[tt] = db_flag;
+        }
+    }
+    float aB1 = 0.0f, aB2 = 0.0f;
+    // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
+    // round is first bounded on the whole item (tile_bounds on a box around all its tiles,
+    // against their least normaliser), and only those that can matter on some tile are staged,
+    // TG at a time, in scene order (slist: their scene-local indices); the others' records would be
+    // zero, as the per-tile bounds would have left them, and are not written: a bit per
+    // Gaussian (masks) tells the finalize which of the item's records are.  Smaller scenes take one round of all
+    // their Gaussians in order (and launches without kBig, whose scenes are all small, have no
+    // such rounds).
+    const bool sparse = BIG && sr.n > BLOCK;
+    TileBox ibox;
+    if (BIG && !sparse && 64 * tid < sr.n) masks[item.moff + tid] = ~0ull;  // every record is written
+    for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
+      int total = sr.n;
+      if (sparse) {
+        __syncthreads();  // boxes visible; the previous round's list and entries are consumed
+        float inorm = INFINITY;
+        for (int t = 0; t < nt; ++t) inorm = fminf(inorm, tnorm[t]);
+        if (rb == 0) ibox = wave_box_of(tbox, nt, lane, e);
+        const int gl = rb + tid;
+        bool keep = false;
+        if (gl < sr.n) {
+            const int gg = sr.gauss_off + gl;
+            Ent ge;
+            float4 ee;
+            make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
+            const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
+            // (written so that a NaN bound keeps the Gaussian)
+            keep = !(b1_pos && pb.z_hi - inorm < kSkipLog2 && pb.d2_hi < kDensSkipLog2);
+        }
+        const unsigned long long bal = wave_ballot(keep);
+        if (lane == 0) {
+            wcnt[wave] = __popcll(bal);
+            if (rb + 64 * wave < sr.n) masks[item.moff + rb / 64 + wave] = bal;
+        }
+        __syncthreads();
+        int off = 0;
+        total = 0;
+        for (int w = 0; w < NW; ++w) {
+            const int c = wcnt[w];
+            off += w < wave ? c : 0;
+            total += c;
+        }
+        if (keep) slist[off + __popcll(bal & ((1ull << lane) - 1ull))] = gl;
+      }
+      for (int gb = 0; gb < total; gb += TG) {
+        const int cnt = min(TG, total - gb);
+        __syncthreads();  // staged rays (and the list) visible; the previous tile's entries and sums are consumed
+        for (int q = tid; q < cnt; q += BLOCK) {
+            const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
+            make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[EW * q]);
+            if (COLOR) ents[EW * q + 5] = colour_entry(P.colors + 3 * gi);
+        }
+        __syncthreads();
+        // The wave takes Gaussians i0, i0 + NW, ... and bounds GPB of them on the item's tiles in
+        // one pass (lane: tile lane % T of Gaussian i0 + (lane / T) NW), then walks them in order.
+        constexpr int GPB = 64 / T;
+        for (int i0 = wave; i0 < cnt; i0 += GPB * NW) {
+          unsigned long long tmasks;  // bits [T k, T k + T): the tiles Gaussian i0 + k NW can matter on
+          {
+            const int ik = i0 + (lane / T) * NW, tl = lane % T;
+            bool need = false;
+            if (tl < nt && ik < cnt) {
+                const Ent gk = ent_from(ents[EW * ik], ents[EW * ik + 1], ents[EW * ik + 2], ents[EW * ik + 3]);
+                const PairBounds pb = tile_bounds(gk, ents[EW * ik + 4], TileBox{tbox[3 * tl], tbox[3 * tl + 1], tbox[3 * tl + 2]},
+                                                  bl.hm, bl.b1, bl.nc2);
+                // (written so that a NaN bound keeps the tile)
+                need = !(b1_pos && pb.z_hi - tnorm[tl] < kSkipLog2 && (pb.d2_hi < kDensSkipLog2 || tdb[tl] == 0));
+            }
+            tmasks = wave_ballot(need);
+          }
+          for (int k = 0; k < GPB; ++k) {
+            const int i = i0 + k * NW;
+            if (i >= cnt) break;
+            unsigned tmask = (unsigned)(tmasks >> (T * k));
+            if (T < 32) tmask &= (1u << (T % 32)) - 1u;
+            if (tmask == 0u) {
+                // no tile of the item takes a term of this Gaussian: its sums are zero
+                if (lane < LREC) rec[LREC * i + lane] = 0.0f;
                 continue;
             }
-            // the weight 2^(z2 - M2) / S as 2^(z2 - M2 - log2 S); a ray past the edge has M2 = inf, S = inf
-            rays[RW * q] = make_float4(pr[0].x, pr[0].y, pr[0].z, pr[0].w - __builtin_amdgcn_logf(pr[1].x));
-            rays[RW * q + 1] = make_float4(pr[1].y, pr[2].z, pr[3].w, pr[2].w);
-            if (COLOR) {
-                // the colour cotangent and its product with the blended colour (kappa's colour part)
-                float kc = 0.0f;
-                if (local >= 0) {
-                    const size_t r3 = 3 * ((size_t)vr.ray_off + local);
-                    kc = fmaf(pr[3].x, I.color[r3], fmaf(pr[3].y, I.color[r3 + 1], pr[3].z * I.color[r3 + 2]));
-                }
-                rays[RW * q + 2] = make_float4(pr[3].x, pr[3].y, pr[3].z, kc);
-            }
-        }
-        __syncthreads();
-        // each ray tile's box and least normaliser, for the bound that lets a wave pass over the tiles
-        // on which a Gaussian can neither weigh above FP32's zero nor add a density above
-        // 2^kDensSkipLog2 (tile_bounds)
-        for (int tt = wave; tt < nt; tt += NW) {
-            int row, col;
-            const bool ok = tile_local(vr, item.ray0 + tt, lane, row, col) >= 0;
-            const float4 x0 = rays[RW * (64 * tt + lane)];
-            const float dbar = NORMALS ? rays[RW * (64 * tt + lane) + 2].z : rays[RW * (64 * tt + lane) + 1].y;
-            const int db_flag = wave_any(dbar != 0.0f) ? 1 : 0;
-            const TileBox b = wave_box(x0.x, x0.y, x0.z, ok, e);
-            const float norm = NORMALS ? x0.w - __builtin_amdgcn_logf(rays[RW * (64 * tt + lane) + 1].x) : x0.w;
-            const float nmin = wave_min_u(ok ? norm : INFINITY);
-            if (lane == 0) {
-                tbox[3 * tt] = b.c;
-                tbox[3 * tt + 1] = b.x;
-                tbox[3 * tt + 2] = b.y;
-                tnorm[tt] = nmin;
-                tdb[tt] = db_flag;
-            }
-        }
-        float aB1 = 0.0f, aB2 = 0.0f;
-        // A scene of more than BLOCK Gaussians is taken in rounds of BLOCK: each Gaussian of the
-        // round is first bounded on the whole item (tile_bounds on a box around all its tiles,
-        // against their least normaliser), and only those that can matter on some tile are staged,
-        // TG at a time, in scene order (slist: their scene-local indices); the others' records would be
-        // zero, as the per-tile bounds would have left them, and are not written: a bit per
-        // Gaussian (masks) tells the finalize which of the item's records are.  Smaller scenes take one round of all
-        // their Gaussians in order (and launches without kBig, whose scenes are all small, have no
-        // such rounds).
-        const bool sparse = BIG && sr.n > BLOCK;
-        TileBox ibox;
-        if (BIG && !sparse && 64 * tid < sr.n) masks[item.moff + tid] = ~0ull;  // every record is written
-        for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
-          int total = sr.n;
-          if (sparse) {
-            __syncthreads();  // boxes visible; the previous round's list and entries are consumed
-            float inorm = INFINITY;
-            for (int t = 0; t < nt; ++t) inorm = fminf(inorm, tnorm[t]);
-            if (rb == 0) ibox = wave_box_of(tbox, nt, lane, e);
-            const int gl = rb + tid;
-            bool keep = false;
-            if (gl < sr.n) {
-                const int gg = sr.gauss_off + gl;
-                Ent ge;
-                float4 ee;
-                make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
-                const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
-                // (written so that a NaN bound keeps the Gaussian)
-                keep = !(b1_pos && pb.z_hi - inorm < kSkipLog2 && pb.d2_hi < kDensSkipLog2);
-            }
-            const unsigned long long bal = wave_ballot(keep);
-            if (lane == 0) {
-                wcnt[wave] = __popcll(bal);
-                if (rb + 64 * wave < sr.n) masks[item.moff + rb / 64 + wave] = bal;
-            }
-            __syncthreads();
-            int off = 0;
-            total = 0;
-            for (int w = 0; w < NW; ++w) {
-                const int c = wcnt[w];
-                off += w < wave ? c : 0;
-                total += c;
-            }
-            if (keep) slist[off + __popcll(bal & ((1ull << lane) - 1ull))] = gl;
-          }
-          for (int gb = 0; gb < total; gb += TG) {
-            const int cnt = min(TG, total - gb);
-            __syncthreads();  // staged rays (and the list) visible; the previous tile's entries and sums are consumed
-            for (int q = tid; q < cnt; q += BLOCK) {
-                const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
-                make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[EW * q]);
-                if (COLOR) ents[EW * q + 5] = colour_entry(P.colors + 3 * gi);
-            }
-            __syncthreads();
-            // The wave takes Gaussians i0, i0 + NW, ... and bounds GPB of them on the item's tiles in
-            // one pass (lane: tile lane % T of Gaussian i0 + (lane / T) NW), then walks them in order.
-            constexpr int GPB = 64 / T;
-            for (int i0 = wave; i0 < cnt; i0 += GPB * NW) {
-              unsigned long long tmasks;  // bits [T k, T k + T): the tiles Gaussian i0 + k NW can matter on
-              {
-                const int ik = i0 + (lane / T) * NW, tl = lane % T;
-                bool need = false;
-                if (tl < nt && ik < cnt) {
-                    const Ent gk = ent_from(ents[EW * ik], ents[EW * ik + 1], ents[EW * ik + 2], ents[EW * ik + 3]);
-                    const PairBounds pb = tile_bounds(gk, ents[EW * ik + 4], TileBox{tbox[3 * tl], tbox[3 * tl + 1], tbox[3 * tl + 2]},
-                                                      bl.hm, bl.b1, bl.nc2);
-                    // (written so that a NaN bound keeps the tile)
-                    need = !(b1_pos && pb.z_hi - tnorm[tl] < kSkipLog2 && (pb.d2_hi < kDensSkipLog2 || tdb[tl] == 0));
-                }
-                tmasks = wave_ballot(need);
-              }
-              for (int k = 0; k < GPB; ++k) {
-                const int i = i0 + k * NW;
-                if (i >= cnt) break;
-                unsigned tmask = (unsigned)(tmasks >> (T * k));
-                if (T < 32) tmask &= (1u << (T % 32)) - 1u;
-                if (tmask == 0u) {
-                    // no tile of the item takes a term of this Gaussian: its sums are zero
-                    if (lane < LREC) rec[LREC * i + lane] = 0.0f;
+            const Ent g = ent_from(ents[EW * i], ents[EW * i + 1], ents[EW * i + 2], ents[EW * i + 3]);
+            float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (COLOR) cc = ents[EW * i + 5];
+            OffsetAcc acc;
+            PairAcc nacc;
+            float aC0 = 0.0f, aC1 = 0.0f, aC2 = 0.0f;  // colour sums: wt C_bar
+#pragma unroll 1
+            while (tmask) {
+                const int t = __builtin_ctz(tmask);
+                tmask &= tmask - 1;
+                const float4 x0 = rays[RW * (64 * t + lane)], x1 = rays[RW * (64 * t + lane) + 1];
+                Geo q;
+                if (NORMALS) {
+                    pair_geo(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
+                    const float4 x2 = rays[RW * (64 * t + lane) + 2];
+                    const float delta = exp2_(q.d2), dd = x2.z * delta;
+                    const float zr = q.z2 - x0.w;
+                    if (wave_any(zr >= kSkipLog2)) {
+                        const float4 x3 = rays[RW * (64 * t + lane) + 3];
+                        const float wt = exp2_(zr) * x1.x;  // normalised blend weight
+                        const float tfb = x1.y;
+                        const PairNormal pn = pair_normal(g, q, x1.z, x1.w, x2.x);
+                        // z_bar = wt (tf_bar t + Nb.n + Cb.c - kappa)
+                        float lin = fmaf(tfb, q.t, pn.nN);
+                        if (COLOR) {
+                            lin = fmaf(x3.x, cc.x, fmaf(x3.y, cc.y, fmaf(x3.z, cc.z, lin)));
+                            aC0 = fmaf(wt, x3.x, aC0);
+                            aC1 = fmaf(wt, x3.y, aC1);
+                            aC2 = fmaf(wt, x3.z, aC2);
+                        }
+                        const float zb = wt * (lin - x2.y);
+                        const float tb = fmaf(-bl.cb, zb, wt * tfb);
+                        const float db = fmaf(bl.b1, zb, dd);
+                        aB1 = fmaf(zb, q.d2 - x3.w, aB1);
+                        aB2 = fmaf(zb, q.t - x2.w, aB2);
+                        pair_adjoint<true>(g, q, x0.x, x0.y, x0.z, wt, pn, x1.z, x1.w, x2.x, tb, db, nacc);
+                    } else {
+                        const PairNormal pn{0, 0, 0, 0, 0};
+                        pair_adjoint<false>(g, q, x0.x, x0.y, x0.z, 0.0f, pn, 0.0f, 0.0f, 0.0f, 0.0f, dd, nacc);
+                    }
                     continue;
                 }
-                const Ent g = ent_from(ents[EW * i], ents[EW * i + 1], ents[EW * i + 2], ents[EW * i + 3]);
-                float4 cc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (COLOR) cc = ents[EW * i + 5];
-                OffsetAcc acc;
-                PairAcc nacc;
-                float aC0 = 0.0f, aC1 = 0.0f, aC2 = 0.0f;  // colour sums: wt C_bar
-#pragma unroll 1
-                while (tmask) {
-                    const int t = __builtin_ctz(tmask);
-                    tmask &= tmask - 1;
-                    const float4 x0 = rays[RW * (64 * t + lane)], x1 = rays[RW * (64 * t + lane) + 1];
-                    Geo q;
-                    if (NORMALS) {
-                        pair_geo(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
-                        const float4 x2 = rays[RW * (64 * t + lane) + 2];
-                        const float delta = exp2_(q.d2), dd = x2.z * delta;
-                        const float zr = q.z2 - x0.w;
-                        if (wave_any(zr >= kSkipLog2)) {
-                            const float4 x3 = rays[RW * (64 * t + lane) + 3];
-                            const float wt = exp2_(zr) * x1.x;  // normalised blend weight
-                            const float tfb = x1.y;
-                            const PairNormal pn = pair_normal(g, q, x1.z, x1.w, x2.x);
-                            // z_bar = wt (tf_bar t + Nb.n + Cb.c - kappa)
-                            float lin = fmaf(tfb, q.t, pn.nN);
-                            if (COLOR) {
-                                lin = fmaf(x3.x, cc.x, fmaf(x3.y, cc.y, fmaf(x3.z, cc.z, lin)));
-                                aC0 = fmaf(wt, x3.x, aC0);
-                                aC1 = fmaf(wt, x3.y, aC1);
-                                aC2 = fmaf(wt, x3.z, aC2);
-                            }
-                            const float zb = wt * (lin - x2.y);
-                            const float tb = fmaf(-bl.cb, zb, wt * tfb);
-                            const float db = fmaf(bl.b1, zb, dd);
-                            aB1 = fmaf(zb, q.d2 - x3.w, aB1);
-                            aB2 = fmaf(zb, q.t - x2.w, aB2);
-                            pair_adjoint<true>(g, q, x0.x, x0.y, x0.z, wt, pn, x1.z, x1.w, x2.x, tb, db, nacc);
-                        } else {
-                            const PairNormal pn{0, 0, 0, 0, 0};
-                            pair_adjoint<false>(g, q, x0.x, x0.y, x0.z, 0.0f, pn, 0.0f, 0.0f, 0.0f, 0.0f, dd, nacc);
+                pair_geo_coarse(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
+                // log2 of the normalised weight, and the density term D_bar delta
+                const float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w));
+                // a weight below 2^-150 rounds to zero in FP32, and a density below 2^kDensSkipLog2
+                // adds nothing measurable: such a tile skips the exponential and the adjoint
+                // (the density test only where no weight is left)
+                const bool any_w = wave_any(zr >= kSkipLog2);
+                if (any_w || wave_any(q.d2 >= kDensSkipLog2 && x1.y != 0.0f)) {
+                    const float dd = x1.y * exp2_(q.d2);
+                    // with zero weights on every ray of the tile only the density term remains:
+                    // t_bar = 0, d_bar = D_bar delta (the offset form then adds exactly that)
+                    float tb = 0.0f, db = dd;
+                    if (any_w) {
+                        // z_bar = wt (tf_bar t - kappa) with kappa = tf_bar t_f [+ C_bar . C, and
+                        // C_bar . c added to the pair's share]
+                        const float x = q.t - x1.w;
+                        const float wt = exp2_(zr);
+                        const float wtf = wt * x1.x;
+                        float zb = wtf * x;
+                        if (COLOR) {
+                            const float4 x2 = rays[RW * (64 * t + lane) + 2];
+                            zb = fmaf(wt, fmaf(x2.x, cc.x, fmaf(x2.y, cc.y, fmaf(x2.z, cc.z, -x2.w))), zb);
+                            aC0 = fmaf(wt, x2.x, aC0);
+                            aC1 = fmaf(wt, x2.y, aC1);
+                            aC2 = fmaf(wt, x2.z, aC2);
                         }
-                        continue;
+                        tb = fmaf(-bl.cb, zb, wtf);
+                        db = fmaf(bl.b1, zb, dd);
+                        aB1 = fmaf(zb, q.d2 - x1.z, aB1);
+                        aB2 = fmaf(zb, x, aB2);
                     }
-                    pair_geo_coarse(g, x0.x, x0.y, x0.z, bl.hm, bl.b1, bl.nc2, q);
-                    // log2 of the normalised weight, and the density term D_bar delta
-                    const float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -x0.w));
-                    // a weight below 2^-150 rounds to zero in FP32, and a density below 2^kDensSkipLog2
-                    // adds nothing measurable: such a tile skips the exponential and the adjoint
-                    // (the density test only where no weight is left)
-                    const bool any_w = wave_any(zr >= kSkipLog2);
-                    if (any_w || wave_any(q.d2 >= kDensSkipLog2 && x1.y != 0.0f)) {
-                        const float dd = x1.y * exp2_(q.d2);
-                        // with zero weights on every ray of the tile only the density term remains:
-                        // t_bar = 0, d_bar = D_bar delta (the offset form then adds exactly that)
-                        float tb = 0.0f, db = dd;
-                        if (any_w) {
-                            // z_bar = wt (tf_bar t - kappa) with kappa = tf_bar t_f [+ C_bar . C, and
-                            // C_bar . c added to the pair's share]
-                            const float x = q.t - x1.w;
-                            const float wt = exp2_(zr);
-                            const float wtf = wt * x1.x;
-                            float zb = wtf * x;
-                            if (COLOR) {
-                                const float4 x2 = rays[RW * (64 * t + lane) + 2];
-                                zb = fmaf(wt, fmaf(x2.x, cc.x, fmaf(x2.y, cc.y, fmaf(x2.z, cc.z, -x2.w))), zb);
-                                aC0 = fmaf(wt, x2.x, aC0);
-                                aC1 = fmaf(wt, x2.y, aC1);
-                                aC2 = fmaf(wt, x2.z, aC2);
-                            }
-                            tb = fmaf(-bl.cb, zb, wtf);
-                            db = fmaf(bl.b1, zb, dd);
-                            aB1 = fmaf(zb, q.d2 - x1.z, aB1);
-                            aB2 = fmaf(zb, x, aB2);
-                        }
-                        // one accumulation for both cases, so the sums stay in their registers
-                        pair_adjoint_offset(q, x0.x, x0.y, x0.z, tb, db, acc);
-                    }
+                    // one accumulation for both cases, so the sums stay in their registers
+                    pair_adjoint_offset(q, x0.x, x0.y, x0.z, tb, db, acc);
                 }
-                float v[16];
-                constexpr int C0 = NORMALS ? kPartial : kOffsetAcc;
-                static_assert(kOffsetAcc + 3 <= 16, "one 16-value wave sum per Gaussian");
-                if (NORMALS) {
-                    v[0] = nacc.u0; v[1] = nacc.u1; v[2] = nacc.u2; v[3] = nacc.u3; v[4] = nacc.u4; v[5] = nacc.u5;
-                    v[6] = nacc.p0; v[7] = nacc.p1; v[8] = nacc.p2; v[9] = nacc.l;
-                    v[13] = v[14] = v[15] = 0.0f;
-                } else {
-                    offset_acc_store(acc, v);
-                }
-                v[C0] = aC0;
-                v[C0 + 1] = aC1;
-                v[C0 + 2] = aC2;
-                const float tot = wave_sum16(v, lane);
-                const int idx = wave16_index(lane);
-                if ((lane & 3) == 0 && idx < LREC) rec[LREC * i + idx] = tot;
-              }
             }
-            __syncthreads();
-            for (int q = tid; q < cnt; q += BLOCK) {
-                const int gl = sparse ? slist[gb + q] : gb + q;
-                const int gg = sr.gauss_off + gl;
-                if (NORMALS)
-                    write_partial(partial + item.poff + REC * gl, rec + LREC * q, REC, P.means + 3 * gg, o);
-                else
-                    write_partial_offset(partial + item.poff + REC * gl, rec + LREC * q, REC,
-                                         P.prec + 6 * gg, P.means + 3 * gg, o);
+            float v[16];
+            constexpr int C0 = NORMALS ? kPartial : kOffsetAcc;
+            static_assert(kOffsetAcc + 3 <= 16, "one 16-value wave sum per Gaussian");
+            if (NORMALS) {
+                v[0] = nacc.u0; v[1] = nacc.u1; v[2] = nacc.u2; v[3] = nacc.u3; v[4] = nacc.u4; v[5] = nacc.u5;
+                v[6] = nacc.p0; v[7] = nacc.p1; v[8] = nacc.p2; v[9] = nacc.l;
+                v[13] = v[14] = v[15] = 0.0f;
+            } else {
+                offset_acc_store(acc, v);
             }
+            v[C0] = aC0;
+            v[C0 + 1] = aC1;
+            v[C0 + 2] = aC2;
+            const float tot = wave_sum16(v, lane);
+            const int idx = wave16_index(lane);
+            if ((lane & 3) == 0 && idx < LREC) rec[LREC * i + idx] = tot;
           }
         }
-        // betas: lanes summed over the wave, then the waves in order
-        aB1 = wave_sum(aB1);
-        aB2 = wave_sum(aB2);
-        if (lane == 0) {
-            bsum[2 * wave] = aB1;
-            bsum[2 * wave + 1] = aB2;
-        }
         __syncthreads();
-        if (tid < 2) {
-            float sb = 0.0f;
-            for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
-            beta_partial[2 * item.seq + tid] = sb;
+        for (int q = tid; q < cnt; q += BLOCK) {
+            const int gl = sparse ? slist[gb + q] : gb + q;
+            const int gg = sr.gauss_off + gl;
+            if (NORMALS)
+                write_partial(partial + item.poff + REC * gl, rec + LREC * q, REC, P.means + 3 * gg, o);
+            else
+                write_partial_offset(partial + item.poff + REC * gl, rec + LREC * q, REC,
+                                     P.prec + 6 * gg, P.means + 3 * gg, o);
         }
-        if (!PERSIST) break;
+      }
+    }
+    // betas: lanes summed over the wave, then the waves in order
+    aB1 = wave_sum(aB1);
+    aB2 = wave_sum(aB2);
+    if (lane == 0) {
+        bsum[2 * wave] = aB1;
+        bsum[2 * wave + 1] = aB2;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        float sb = 0.0f;
+        for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
+        beta_partial[2 * item.seq + tid] = sb;
     }
 }
 
@@ -1465,50 +1414,45 @@ static const int kBwdTiles[] = {8, 16, 16, 8};
 constexpr int kNumBwdTiled = (int)(sizeof kBwdTiles / sizeof kBwdTiles[0]);  // the last: normal cotangents
 constexpr int kBwdTiledFirst = kNumBwdGauss + kNumBwdRay;
 
-// F dispatch: calls body<F>() for the runtime flag set f (0..15).
+// F dispatch: calls body<F>() for the runtime flag set f (0..7).
 #define FMB_DISPATCH_F(f, CALL)                                                                            \
     switch (f) {                                                                                           \
     case 0: CALL(0); break;   case 1: CALL(1); break;   case 2: CALL(2); break;   case 3: CALL(3); break;   \
     case 4: CALL(4); break;   case 5: CALL(5); break;   case 6: CALL(6); break;   case 7: CALL(7); break;   \
-    case 8: CALL(8); break;   case 9: CALL(9); break;   case 10: CALL(10); break; case 11: CALL(11); break; \
-    case 12: CALL(12); break; case 13: CALL(13); break; case 14: CALL(14); break; case 15: CALL(15); break; \
     default: return hipErrorInvalidValue;                                                                  \
     }
 
-// ... and over the forward's flag sets with kBig (16..31).
-#define FMB_DISPATCH_F32(f, CALL)                                                                          \
-    if ((f) < 16) {                                                                                        \
+// ... and over the forward's flag sets with kBig (8..15).
+#define FMB_DISPATCH_F16(f, CALL)                                                                          \
+    if ((f) < 8) {                                                                                         \
         FMB_DISPATCH_F(f, CALL)                                                                            \
     } else {                                                                                               \
         switch (f) {                                                                                       \
-        case 16: CALL(16); break; case 17: CALL(17); break; case 18: CALL(18); break; case 19: CALL(19); break; \
-        case 20: CALL(20); break; case 21: CALL(21); break; case 22: CALL(22); break; case 23: CALL(23); break; \
-        case 24: CALL(24); break; case 25: CALL(25); break; case 26: CALL(26); break; case 27: CALL(27); break; \
-        case 28: CALL(28); break; case 29: CALL(29); break; case 30: CALL(30); break; case 31: CALL(31); break; \
+        case 8: CALL(8); break;   case 9: CALL(9); break;   case 10: CALL(10); break; case 11: CALL(11); break; \
+        case 12: CALL(12); break; case 13: CALL(13); break; case 14: CALL(14); break; case 15: CALL(15); break; \
         default: return hipErrorInvalidValue;                                                              \
         }                                                                                                  \
     }
 
 template <int RPT, int TG>
 static hipError_t launch_fwd_v(int f, int grid, hipStream_t st, const Params &P, const FwdOut &O,
-                               const FwdItem *items, int n, const int *order, int *counter)
+                               const FwdItem *items, const int *order)
 {
 #define FMB_FWD_CALL(F)                                                                                    \
-    hipLaunchKernelGGL((fwd_kernel<kBlock, RPT, TG, F>), dim3(grid), dim3(kBlock), 0, st, P, O, items, n, order, \
-                       counter)
-    FMB_DISPATCH_F32(f, FMB_FWD_CALL)
+    hipLaunchKernelGGL((fwd_kernel<kBlock, RPT, TG, F>), dim3(grid), dim3(kBlock), 0, st, P, O, items, order)
+    FMB_DISPATCH_F16(f, FMB_FWD_CALL)
 #undef FMB_FWD_CALL
     return hipGetLastError();
 }
 
 template <int RPT, int TG>
 static hipError_t launch_bwdr_v(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                                const BwdItem *items, int n, const int *order, int *counter, float *partial,
+                                const BwdItem *items, const int *order, float *partial,
                                 float *bpart)
 {
 #define FMB_BWDR_CALL(F)                                                                                   \
-    hipLaunchKernelGGL((bwdr_kernel<kBlock, RPT, TG, F>), dim3(grid), dim3(kBlock), 0, st, P, I, items, n,      \
-                       order, counter, partial, bpart)
+    hipLaunchKernelGGL((bwdr_kernel<kBlock, RPT, TG, F>), dim3(grid), dim3(kBlock), 0, st, P, I, items, order, \
+                       partial, bpart)
     FMB_DISPATCH_F(f, FMB_BWDR_CALL)
 #undef FMB_BWDR_CALL
     return hipGetLastError();
@@ -1516,12 +1460,12 @@ static hipError_t launch_bwdr_v(int f, int grid, hipStream_t st, const Params &P
 
 template <int RT>
 static hipError_t launch_bwd_v(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                               const BwdItem *items, int n, const int *order, int *counter, float *partial,
+                               const BwdItem *items, const int *order, float *partial,
                                float *bpart)
 {
 #define FMB_BWD_CALL(F)                                                                                    \
-    hipLaunchKernelGGL((bwd_kernel<kBlock, RT, F>), dim3(grid), dim3(kBlock), 0, st, P, I, items, n, order,     \
-                       counter, partial, bpart)
+    hipLaunchKernelGGL((bwd_kernel<kBlock, RT, F>), dim3(grid), dim3(kBlock), 0, st, P, I, items, order, \
+                       partial, bpart)
     FMB_DISPATCH_F(f, FMB_BWD_CALL)
 #undef FMB_BWD_CALL
     return hipGetLastError();
@@ -1529,29 +1473,21 @@ static hipError_t launch_bwd_v(int f, int grid, hipStream_t st, const Params &P,
 
 template <int BLK, int T>
 static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                                const BwdItem *items, int n, const int *order, int *counter, float *partial,
+                                const BwdItem *items, const int *order, float *partial,
                                 float *bpart, unsigned long long *masks)
 {
 #define FMB_BWDT_CALL(F)                                                                                   \
-    hipLaunchKernelGGL((bwdt_kernel<BLK, T, 64, F>), dim3(grid), dim3(BLK), 0, st, P, I, items, n, order,   \
-                       counter, partial, bpart, masks)
-    switch (f) {
+    hipLaunchKernelGGL((bwdt_kernel<BLK, T, 64, F>), dim3(grid), dim3(BLK), 0, st, P, I, items, order,   \
+                       partial, bpart, masks)
+    switch (f) {  // (no normal cotangent)
     case 0: FMB_BWDT_CALL(0); break;
     case kFlw: FMB_BWDT_CALL(kFlw); break;
-    case kPer: FMB_BWDT_CALL(kPer); break;
-    case kFlw | kPer: FMB_BWDT_CALL(kFlw | kPer); break;
     case kCol: FMB_BWDT_CALL(kCol); break;
     case kCol | kFlw: FMB_BWDT_CALL(kCol | kFlw); break;
-    case kCol | kPer: FMB_BWDT_CALL(kCol | kPer); break;
-    case kCol | kFlw | kPer: FMB_BWDT_CALL(kCol | kFlw | kPer); break;
     case kBig: FMB_BWDT_CALL(kBig); break;
     case kBig | kFlw: FMB_BWDT_CALL(kBig | kFlw); break;
-    case kBig | kPer: FMB_BWDT_CALL(kBig | kPer); break;
-    case kBig | kFlw | kPer: FMB_BWDT_CALL(kBig | kFlw | kPer); break;
     case kBig | kCol: FMB_BWDT_CALL(kBig | kCol); break;
     case kBig | kCol | kFlw: FMB_BWDT_CALL(kBig | kCol | kFlw); break;
-    case kBig | kCol | kPer: FMB_BWDT_CALL(kBig | kCol | kPer); break;
-    case kBig | kCol | kFlw | kPer: FMB_BWDT_CALL(kBig | kCol | kFlw | kPer); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1559,17 +1495,14 @@ static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P
 
 // The form with a normal cotangent.
 static hipError_t launch_bwdt_normal(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                                     const BwdItem *items, int n, const int *order, int *counter, float *partial,
+                                     const BwdItem *items, const int *order, float *partial,
                                      float *bpart, unsigned long long *masks)
 {
     constexpr int BLK = 512, T = 8;
     switch (f) {
     case 1: FMB_BWDT_CALL(1); break;   case 3: FMB_BWDT_CALL(3); break;   case 5: FMB_BWDT_CALL(5); break;
     case 7: FMB_BWDT_CALL(7); break;   case 9: FMB_BWDT_CALL(9); break;   case 11: FMB_BWDT_CALL(11); break;
-    case 13: FMB_BWDT_CALL(13); break; case 15: FMB_BWDT_CALL(15); break; case 17: FMB_BWDT_CALL(17); break;
-    case 19: FMB_BWDT_CALL(19); break; case 21: FMB_BWDT_CALL(21); break; case 23: FMB_BWDT_CALL(23); break;
-    case 25: FMB_BWDT_CALL(25); break; case 27: FMB_BWDT_CALL(27); break; case 29: FMB_BWDT_CALL(29); break;
-    case 31: FMB_BWDT_CALL(31); break;
+    case 13: FMB_BWDT_CALL(13); break; case 15: FMB_BWDT_CALL(15); break;
     default: return hipErrorInvalidValue;
     }
 #undef FMB_BWDT_CALL
@@ -1588,34 +1521,34 @@ int bwd_variant_rt(int v) { return v < kNumBwdGauss ? kBwdRT[v] : 0; }
 int bwd_variant_ray_tile(int v) { return v >= kNumBwdGauss ? kBlock * kBwdRay[v - kNumBwdGauss].rpt : 0; }
 int block_size() { return kBlock; }
 
-// flags: bit 0 normals, 1 flow, 2 persistent, 3 colour
+// flags: bit 0 normals, 1 flow, 2 colour, 3 a scene beyond a block's count of Gaussians
 hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const FwdOut &O,
-                      const FwdItem *items, int n, const int *order, int *counter)
+                      const FwdItem *items, const int *order)
 {
     switch (variant) {
-    case 0: return launch_fwd_v<1, 128>(flags, grid, st, P, O, items, n, order, counter);
-    case 1: return launch_fwd_v<2, 128>(flags, grid, st, P, O, items, n, order, counter);
-    case 2: return launch_fwd_v<2, 256>(flags, grid, st, P, O, items, n, order, counter);
-    case 3: return launch_fwd_v<4, 128>(flags, grid, st, P, O, items, n, order, counter);
+    case 0: return launch_fwd_v<1, 128>(flags, grid, st, P, O, items, order);
+    case 1: return launch_fwd_v<2, 128>(flags, grid, st, P, O, items, order);
+    case 2: return launch_fwd_v<2, 256>(flags, grid, st, P, O, items, order);
+    case 3: return launch_fwd_v<4, 128>(flags, grid, st, P, O, items, order);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, int n, const int *order, int *counter, float *partial, float *bpart,
+                      const BwdItem *items, const int *order, float *partial, float *bpart,
                       unsigned long long *masks)
 {
     switch (variant) {
-    case 0: return launch_bwd_v<64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 1: return launch_bwd_v<128>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 2: return launch_bwd_v<256>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 3: return launch_bwdr_v<2, 64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 4: return launch_bwdr_v<4, 64>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 5: return launch_bwdr_v<4, 128>(flags, grid, st, P, I, items, n, order, counter, partial, bpart);
-    case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
-    case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
-    case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
-    case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, n, order, counter, partial, bpart, masks);
+    case 0: return launch_bwd_v<64>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 1: return launch_bwd_v<128>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 2: return launch_bwd_v<256>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 3: return launch_bwdr_v<2, 64>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 4: return launch_bwdr_v<4, 64>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 5: return launch_bwdr_v<4, 128>(flags, grid, st, P, I, items, order, partial, bpart);
+    case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, order, partial, bpart, masks);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1669,97 +1602,6 @@ hipError_t launch_validate(const Params &P, int n_total, int n_scenes, int *flag
     const int n = n_total > n_scenes ? n_total : n_scenes;
     hipLaunchKernelGGL(validate_kernel, dim3((n + 255) / 256), dim3(256), 0, st, P, n_total, n_scenes, flags);
     return hipGetLastError();
-}
-
-template <typename K>
-static hipError_t occ(K kernel, int *blocks)
-{
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, kernel, kBlock, 0);
-}
-
-// Occupancy of the persistent kernels (flags include kPer).
-hipError_t occupancy_fwd(int variant, int flags, int *blocks_per_cu)
-{
-#define FMB_OCC_F(F) return occ(fwd_kernel<kBlock, RPT, TG, F>, blocks_per_cu)
-#define FMB_OCC_V(RPT_, TG_)                                                                               \
-    {                                                                                                      \
-        constexpr int RPT = RPT_, TG = TG_;                                                                \
-        FMB_DISPATCH_F32(flags, FMB_OCC_F)                                                                 \
-    }
-    switch (variant) {
-    case 0: FMB_OCC_V(1, 128)
-    case 1: FMB_OCC_V(2, 128)
-    case 2: FMB_OCC_V(2, 256)
-    case 3: FMB_OCC_V(4, 128)
-    default: return hipErrorInvalidValue;
-    }
-#undef FMB_OCC_V
-#undef FMB_OCC_F
-    return hipErrorInvalidValue;
-}
-
-hipError_t occupancy_bwd(int variant, int flags, int *blocks_per_cu)
-{
-#define FMB_OCC_F(F) return occ(bwd_kernel<kBlock, RT, F>, blocks_per_cu)
-#define FMB_OCC_V(RT_)                                                                                     \
-    {                                                                                                      \
-        constexpr int RT = RT_;                                                                            \
-        FMB_DISPATCH_F(flags, FMB_OCC_F)                                                                   \
-    }
-    switch (variant) {
-    case 0: FMB_OCC_V(64)
-    case 1: FMB_OCC_V(128)
-    case 2: FMB_OCC_V(256)
-    default: break;
-    }
-#undef FMB_OCC_V
-#undef FMB_OCC_F
-#define FMB_OCC_F(F) return occ(bwdr_kernel<kBlock, RPT, TG, F>, blocks_per_cu)
-#define FMB_OCC_V(RPT_, TG_)                                                                               \
-    {                                                                                                      \
-        constexpr int RPT = RPT_, TG = TG_;                                                                \
-        FMB_DISPATCH_F(flags, FMB_OCC_F)                                                                   \
-    }
-    switch (variant) {
-    case 3: FMB_OCC_V(2, 64)
-    case 4: FMB_OCC_V(4, 64)
-    case 5: FMB_OCC_V(4, 128)
-    default: break;
-    }
-#undef FMB_OCC_V
-#undef FMB_OCC_F
-    auto occb = [&](auto kernel, int blk) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, kernel, blk, 0); };
-    // the persistent forms the batch launches (flow, colour and the large-scene form as given)
-#define FMB_OCC_T(BLK, T)                                                                                  \
-    switch (flags & (kFlw | kCol | kBig)) {                                                                \
-    case 0: return occb(bwdt_kernel<BLK, T, 64, kPer>, BLK);                                              \
-    case kFlw: return occb(bwdt_kernel<BLK, T, 64, kFlw | kPer>, BLK);                                    \
-    case kCol: return occb(bwdt_kernel<BLK, T, 64, kCol | kPer>, BLK);                                    \
-    case kCol | kFlw: return occb(bwdt_kernel<BLK, T, 64, kCol | kFlw | kPer>, BLK);                      \
-    case kBig: return occb(bwdt_kernel<BLK, T, 64, kBig | kPer>, BLK);                                    \
-    case kBig | kFlw: return occb(bwdt_kernel<BLK, T, 64, kBig | kFlw | kPer>, BLK);                      \
-    case kBig | kCol: return occb(bwdt_kernel<BLK, T, 64, kBig | kCol | kPer>, BLK);                      \
-    default: return occb(bwdt_kernel<BLK, T, 64, kBig | kCol | kFlw | kPer>, BLK);                        \
-    }
-    if (variant == 6) FMB_OCC_T(256, 8)
-    if (variant == 7) FMB_OCC_T(256, 16)
-    if (variant == 8) FMB_OCC_T(512, 16)
-#undef FMB_OCC_T
-#define FMB_OCC_N(F) return occb(bwdt_kernel<512, 8, 64, kNrm | kPer | (F)>, 512)
-    if (variant == 9) {
-        switch (flags & (kFlw | kCol | kBig)) {
-        case 0: FMB_OCC_N(0);
-        case kFlw: FMB_OCC_N(kFlw);
-        case kCol: FMB_OCC_N(kCol);
-        case kCol | kFlw: FMB_OCC_N(kCol | kFlw);
-        case kBig: FMB_OCC_N(kBig);
-        case kBig | kFlw: FMB_OCC_N(kBig | kFlw);
-        case kBig | kCol: FMB_OCC_N(kBig | kCol);
-        default: FMB_OCC_N(kBig | kCol | kFlw);
-        }
-    }
-#undef FMB_OCC_N
-    return hipErrorInvalidValue;
 }
 
 }  // namespace fmb

@@ -301,7 +301,7 @@ def _tune_args(outs, cot, grads):
 
 
 class Batch:
-    """Many scenes rendered by the persistent batched kernels (one launch per pass)."""
+    """Many scenes rendered together (one launch per pass, a block per work item)."""
 
     def __init__(self, means, prec, weights, betas, eta: Sequence[float], n_per_scene: Sequence[int],
                  cams: List[Cameras]):
@@ -435,14 +435,14 @@ class Batch:
 
 def set_launch_config(scene: Optional["Scene"] = None, batch: Optional["Batch"] = None, fwd_variant: int = 3,
                       bwd_variant: int = 8, fwd_grid_mult: int = 1, bwd_grid_mult: int = 1):
-    """Pin the tile variants and persistent-grid multipliers (see launch_config)."""
+    """Pin the tile variants (the grid multipliers are accepted without effect; see launch_config)."""
     _lib.call("fmb_set_config", scene.handle if scene is not None else None,
               batch._h if batch is not None else None, int(fwd_variant), int(bwd_variant), int(fwd_grid_mult),
               int(bwd_grid_mult))
 
 
 def launch_config(scene: Optional["Scene"] = None, batch: Optional["Batch"] = None) -> dict:
-    """Tile variants, persistent-grid multipliers and work-item counts in use."""
+    """Tile variants, grid multipliers and work-item counts in use."""
     out = (ctypes.c_int32 * 8)()
     _lib.call("fmb_get_config", scene.handle if scene is not None else None,
               batch._h if batch is not None else None, out)
