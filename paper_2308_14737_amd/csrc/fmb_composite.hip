@@ -50,15 +50,20 @@
 
 namespace fmb {
 
-// Significant intersections a lane holds per depth window: in the backward (and the split statistic),
+// Significant intersections a lane holds per depth window: in the backward and the split statistic,
 // and in the forward, whose cutoff is higher (on the 16 benchmark scenes 2 % of the tiles have more than
-// 32 above it, 3.6 % above the backward's).
-constexpr int kCompSlots = 48, kFwdcSlots = 32;
+// 32 above it, 3.6 % above the backward's; larger scenes' tiles are denser, and one of 100 takes
+// a third of a millisecond in windows of 32).
+constexpr int kCompSlots = 48;
+__host__ __device__ constexpr int fwdc_slots(int nw) { return nw > 1 ? 32 : 48; }
 constexpr int kCompTG = 128;    // Gaussians staged per LDS tile
 // Waves per SIMD the kernels are compiled for: the slots take 2 (forward) or 3 VGPRs each.  The
-// forward is held to three waves (168 VGPRs, some values spilled to scratch); the backward and the split
-// statistic, with 48 slots so that their dense tiles take one window instead of several, keep two.
-constexpr int kFwdcWaves = 3, kBwdcWaves = 2, kStatcWaves = 2;
+// forward of small scenes is held to three waves (168 VGPRs, some values spilled to scratch, within
+// what the runtime keeps allocated); the others, with 48 slots so that their dense tiles take one window
+// instead of several, keep two and do not spill: spills above 267 bytes a lane make the runtime
+// allocate scratch for every launch, which cost 0.5 ms.
+constexpr int kBwdcWaves = 2, kStatcWaves = 2;
+__host__ __device__ constexpr int fwdc_waves(int nw) { return nw > 1 ? 3 : 2; }
 
 // log2(1 - exp(-delta)) with log2(delta) = d2.
 __device__ __forceinline__ float log2_opacity(float delta, float d2)
@@ -359,7 +364,8 @@ __device__ __forceinline__ void comp_masks(const CompBounds &cb, int cnt, int la
 // A scene of more than kCompTG Gaussians: those whose log2 density can reach the cutoff on a ray of the
 // tile, staged in scene order with their scene-local indices in gid.  The cutoff is `thr`, or with REL
 // (the forward) rel + min(0, the largest lower bound of the tile's log2 densities), bounded by the
-// Gaussians seen so far (a superset of the final cutoff's, which is returned in `low`).  Returns their
+// Gaussians seen so far (a superset of the final cutoff's, which is returned in `low`).  The bounds are
+// taken on FP32 entries (make_bound_entry); only the survivors' are formed in FP64.  Returns their
 // count, which may exceed kCompTG: then the first kCompTG are staged, and the tile takes the scene in
 // staged tiles.  One wave.
 template <int EW, bool REL>
@@ -373,21 +379,19 @@ __device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &s
         const int gl = gb + lane;
         const bool in = gl < sr.n;
         const int gi = sr.gauss_off + (in ? gl : 0);
-        float4 q[5];
-        make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, q);
-        const PairBounds pb = tile_bounds(ent_from(q[0], q[1], q[2], q[3]), q[4], tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
+        Ent g;
+        float4 est;
+        make_bound_entry(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, g, est);
+        const PairBounds pb = tile_bounds(g, est, tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
         if (REL) low = fmaxf(low, wave_max_u(in ? pb.d2_lo : -INFINITY));
         const bool keep = in && !(pb.d2_hi < (REL ? fminf(low, 0.0f) + thr : thr));
         const unsigned long long bal = wave_ballot(keep);
         const int at = ne + __popcll(bal & ((1ull << lane) - 1ull));
-        if (keep && at < kCompTG) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) ents[EW * at + k] = q[k];
-            if (EW == 6) ents[EW * at + kCompCol] = colour_entry(P.colors + 3 * gi);
-            gid[at] = gl;
-        }
+        if (keep && at < kCompTG) gid[at] = gl;
         ne += __popcll(bal);
     }
+    __syncthreads();
+    for (int q = lane; q < min(ne, kCompTG); q += 64) comp_entry<EW>(P, sr.gauss_off + gid[q], o, &ents[EW * q]);
     __syncthreads();
     return __builtin_amdgcn_readfirstlane(ne);
 }
@@ -510,13 +514,13 @@ __device__ __forceinline__ float opacity(float delta)
 // NW waves per block: 4 for scenes of at most kCompTG Gaussians (staged once per item for all four, each
 // wave taking every fourth tile of it), 1 for larger ones (each wave stages its own tile's survivors).
 template <int F, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kFwdcWaves))) void fwdc_kernel(
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_waves(NW)))) void fwdc_kernel(
     Params P, FwdOut O, const CompItem *__restrict__ items)
 {
     constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     constexpr int EW = COLOR ? 6 : 5;
     __shared__ float4 ents[kCompTG * EW];
-    __shared__ int slot_gs[NW][kFwdcSlots];
+    __shared__ int slot_gs[NW][fwdc_slots(NW)];
     __shared__ int gid[NW == 1 ? kCompTG : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int *const slot_g = slot_gs[wave];
@@ -596,7 +600,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kFwdcWa
             C2 *= sc;
         };
         CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
-        CompList<kFwdcSlots> L;
+        CompList<fwdc_slots(NW)> L;
         const auto no_tie = [](const Ent &, const Geo &, float, int) {};
         int ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
 
