@@ -36,7 +36,7 @@ hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Pa
 hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
                       const BwdItem *items, const int *order, float *partial, float *bpart,
                       unsigned long long *masks);
-hipError_t launch_fin(int n_tasks, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
+hipError_t launch_fin(int n_tasks, int n_one, int one_gc, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks,
                       const FinGroup *groups, const float *partial, const float *bpart, const unsigned long long *masks,
                       int rec, double *stage, double *stage_beta, float *g_means, float *g_prec, float *g_weights, float *g_colors,
@@ -254,6 +254,7 @@ struct Job {
     // backward work
     int n_bitems_small = 0;  // compositing: how many of the items in order are small scenes'
     int bwd_variant = 8, bwd_built = -1, n_bitems = 0, n_tasks = 0, n_groups = 0;
+    int n_one = 0, fin_one_gc = 1;         // leading tasks reduced in one stage, their largest chunk
     int fin_max_gc = 1, fin_max_nval = 1;  // largest chunk and first-stage record (finalize grid)
     DevBuf d_bitems, d_border, d_tasks, d_groups, d_partial, d_bpart, d_stage, d_stage_beta, d_masks;
     int bwd_rec = kPartial;      // floats per partial record
@@ -436,6 +437,7 @@ struct Job {
         std::vector<FinGroup> groups;
         size_t poff = 0, soff = 0;  // partial floats, first-stage doubles
         int max_gc = 1, max_nval = 1;
+        int n_one = 0, one_gc = 1;
         int rec = kPartial;
         size_t mask_words = 0;
         int n_small = 0;  // compositing: leading items of `order` that are small scenes'
@@ -459,6 +461,8 @@ struct Job {
         n_groups = (int)pl.groups.size();
         fin_max_gc = pl.max_gc;
         fin_max_nval = pl.max_nval;
+        n_one = pl.n_one;
+        fin_one_gc = pl.one_gc;
         HIPCHK(d_partial.ensure(std::max<size_t>(pl.poff, 1) * sizeof(float)));
         HIPCHK(d_bpart.ensure(std::max<size_t>(2 * pl.items.size(), 2) * sizeof(float)));
         if (pl.mask_words) HIPCHK(d_masks.ensure(pl.mask_words * sizeof(unsigned long long)));
@@ -600,14 +604,23 @@ struct Job {
         }
         // first-stage reduction groups: runs of kGroupItems items inside each chunk
         std::vector<FinGroup> groups;
+        // (a task that holds its whole scene, of few items whose records are all written, needs none)
+        auto one_stage = [&](const FinTask &t) {
+            return !masked && t.gc == scenes[t.scene].n && t.item_end - t.item_begin <= kOneStageItems;
+        };
         size_t soff = 0;
         int scene_first_group = 0, cur_scene = -1;
         for (auto &t : tasks) {
+            const size_t ti = &t - &tasks[0];
+            t.item_begin = tasks_item_begin[ti];
+            t.item_end = tasks_item_end[ti];
+            t.poff = items[t.item_begin].poff;
+            if (one_stage(t)) continue;
             if (t.scene != cur_scene) {
                 cur_scene = t.scene;
                 scene_first_group = (int)groups.size();
             }
-            const int ib = tasks_item_begin[&t - &tasks[0]], ie = tasks_item_end[&t - &tasks[0]];
+            const int ib = t.item_begin, ie = t.item_end;
             t.group_begin = (int)groups.size();
             // About sqrt(items) items per group so both stages sum similar counts; more of a large scene
             // whose records fit the fixed workspace of fmb_backward_noalloc, so that the items' masks
@@ -632,12 +645,12 @@ struct Job {
             t.group_end = (int)groups.size();
             t.sgroup_begin = scene_first_group;
         }
-        for (auto &t : tasks) {
-            int e = 0;
-            for (auto &u : tasks)
-                if (u.scene == t.scene) e = std::max(e, u.group_end);
-            t.sgroup_end = e;
-        }
+        std::vector<int> scene_end(S, 0);
+        for (const auto &t : tasks) scene_end[t.scene] = std::max(scene_end[t.scene], (int)t.group_end);
+        for (auto &t : tasks) t.sgroup_end = scene_end[t.scene];
+        pl.n_one = (int)(std::stable_partition(tasks.begin(), tasks.end(), one_stage) - tasks.begin());
+        pl.one_gc = 1;
+        for (int i = 0; i < pl.n_one; ++i) pl.one_gc = std::max(pl.one_gc, (int)tasks[i].gc);
         std::vector<int> order(items.size());
         std::iota(order.begin(), order.end(), 0);
         if (comp) {  // (the compositing kernels have a form for small scenes and one for the others)
@@ -829,7 +842,7 @@ struct Job {
             tb.stop();
         }
         TimedSpan tf(st, 2);
-        HIPCHK(launch_fin(n_tasks, n_groups, fin_max_gc, fin_max_nval, st, prm, d_tasks.as<FinTask>(), d_groups.as<FinGroup>(),
+        HIPCHK(launch_fin(n_tasks, n_one, fin_one_gc, n_groups, fin_max_gc, fin_max_nval, st, prm, d_tasks.as<FinTask>(), d_groups.as<FinGroup>(),
                           d_partial.as<float>(), d_bpart.as<float>(),
                           mask_words ? d_masks.as<unsigned long long>() : nullptr, bwd_rec, d_stage.as<double>(),
                           d_stage_beta.as<double>(), G.means, G.prec, G.weights, G.colors, G.betas));
@@ -905,7 +918,7 @@ struct Job {
             tb.stop();
         }
         TimedSpan tf(st, 2);
-        HIPCHK(launch_fin((int)pl.tasks.size(), (int)pl.groups.size(), pl.max_gc, pl.max_nval, st, prm,
+        HIPCHK(launch_fin((int)pl.tasks.size(), pl.n_one, pl.one_gc, (int)pl.groups.size(), pl.max_gc, pl.max_nval, st, prm,
                           reinterpret_cast<const FinTask *>(b + o_tasks), reinterpret_cast<const FinGroup *>(b + o_groups),
                           part, bpart, masks, pl.rec, reinterpret_cast<double *>(b + o_stage), reinterpret_cast<double *>(b + o_sbeta),
                           G.means, G.prec, G.weights, G.colors, G.betas));

@@ -81,7 +81,8 @@ struct FinTask {       // one per (scene, Gaussian chunk)
     int32_t beta;      // 1 if this task also reduces the scene's beta partials
     int32_t sgroup_begin, sgroup_end;  // all groups of the scene (beta partials)
     int32_t rec;       // floats per Gaussian in the partial records (kPartial or kPartialColor)
-    int32_t pad[3];
+    int32_t item_begin, item_end;  // one-stage tasks: the chunk's items (all of the scene's) ...
+    int32_t poff;      // ... and the partial offset of the first
 };
 
 // First stage of the deterministic gradient reduction: a group of consecutive
@@ -94,6 +95,8 @@ struct FinGroup {
     int32_t moff, words;  // the first item's mask and the words of each (items of a chunk are contiguous)
     int32_t pad;
 };
+// A chunk of at most this many items that holds its whole scene is reduced in one stage.
+constexpr int kOneStageItems = 4096;
 constexpr int kGroupItems = 32;  // minimum items per first-stage group
 
 // Split statistic (one value per Gaussian and item): the items of a (scene, Gaussian chunk)

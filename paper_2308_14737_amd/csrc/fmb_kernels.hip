@@ -704,7 +704,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
     const int nt = min(T, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
 
-    __syncthreads();  // the previous item is done with the staged rays
+    const bool sparse = BIG && sr.n > BLOCK;
+    // entry q of the Gaussian tile from gb
+    auto stage = [&](int gb, int q) {
+        const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
+        make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[EW * q]);
+        if (COLOR) ents[EW * q + 5] = colour_entry(P.colors + 3 * gi);
+    };
+    // The last threads form the first Gaussian tile's entries beside the rays' prologue, so that their
+    // loads and FP64 chain share one wait (scenes in pre-culled rounds have no list yet).
+    if (!sparse && BLOCK - 1 - tid < min(TG, sr.n)) stage(0, BLOCK - 1 - tid);
     for (int q = tid; q < RAYS; q += BLOCK) {
         int row = 0, col = 0;
         const int local = (q >> 6) < nt ? tile_local(vr, item.ray0 + (q >> 6), q & 63, row, col) : -1;
@@ -759,7 +768,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     // Gaussian (masks) tells the finalize which of the item's records are.  Smaller scenes take one round of all
     // their Gaussians in order (and launches without kBig, whose scenes are all small, have no
     // such rounds).
-    const bool sparse = BIG && sr.n > BLOCK;
     TileBox ibox;
     if (BIG && !sparse && 64 * tid < sr.n) masks[item.moff + tid] = ~0ull;  // every record is written
     for (int rb = 0; rb < sr.n; rb += sparse ? BLOCK : sr.n) {
@@ -797,11 +805,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
       }
       for (int gb = 0; gb < total; gb += TG) {
         const int cnt = min(TG, total - gb);
-        __syncthreads();  // staged rays (and the list) visible; the previous tile's entries and sums are consumed
-        for (int q = tid; q < cnt; q += BLOCK) {
-            const int gi = sr.gauss_off + (sparse ? slist[gb + q] : gb + q);
-            make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[EW * q]);
-            if (COLOR) ents[EW * q + 5] = colour_entry(P.colors + 3 * gi);
+        if (gb > 0 || sparse) {
+            __syncthreads();  // the list visible; the previous tile's entries and sums are consumed
+            for (int q = tid; q < cnt; q += BLOCK) stage(gb, q);
         }
         __syncthreads();
         // The wave takes Gaussians i0, i0 + NW, ... and bounds GPB of them on the item's tiles in
@@ -954,7 +960,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
 }
 
 // ------------------------------------------------------------------------------------
-// Finalize, in two deterministic stages.
+// Finalize, deterministic, in one stage (fin_one_kernel) or two.
 //   stage 1: each group of <= kGroupItems consecutive items of a chunk is summed in item
 //            order in FP64 (all values of the chunk's partial record, and the betas);
 //   stage 2: each chunk sums its groups in order, maps the peak-depth adjoint to the means
@@ -963,22 +969,93 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
 //            reduces the scene's betas.
 // ------------------------------------------------------------------------------------
 
+// Gaussians per block of the one-stage reduction: their values leave two of 32 lanes for the betas.
+__host__ __device__ constexpr int fin_one_gauss(int rec) { return 30 / rec; }
+
 // Sum n strided values src[0], src[stride], ... in index order (FP64), issuing the loads
 // eight at a time so that they are in flight together; the association is fixed.
 template <typename T>
-__device__ __forceinline__ double ordered_sum(const T *__restrict__ src, int n, int stride)
+__device__ __forceinline__ double ordered_sum(const T *__restrict__ src, int n, size_t stride)
 {
     double s = 0.0;
     int i = 0;
     for (; i + 8 <= n; i += 8) {
         T x[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = src[(size_t)(i + k) * stride];
+        for (int k = 0; k < 8; ++k) x[k] = src[(i + k) * stride];
 #pragma unroll
         for (int k = 0; k < 8; ++k) s += (double)x[k];
     }
-    for (; i < n; ++i) s += (double)src[(size_t)i * stride];
+    for (; i < n; ++i) s += (double)src[i * stride];
     return s;
+}
+
+// Gradients of Gaussian gg from its summed record sm.
+__device__ __forceinline__ void fin_write(const Params &P, int gg, const double *sm, int rec, float *__restrict__ g_means,
+                                          float *__restrict__ g_prec, float *__restrict__ g_weights,
+                                          float *__restrict__ g_colors)
+{
+    const float *u = P.prec + 6 * gg;
+    float *gp = g_prec + 6 * gg;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) gp[c] = (float)sm[c];
+    const double r0 = sm[6], r1 = sm[7], r2 = sm[8];
+    g_means[3 * gg + 0] = (float)(-(double)u[0] * r0);
+    g_means[3 * gg + 1] = (float)(-((double)u[1] * r0 + (double)u[3] * r1));
+    g_means[3 * gg + 2] = (float)(-((double)u[2] * r0 + (double)u[4] * r1 + (double)u[5] * r2));
+    g_weights[gg] = (float)(sm[9] / (double)P.weights[gg]);
+    if (rec == kPartialColor && g_colors) {
+        // colour = sigmoid(q): dL/dq = dL/dc c (1 - c)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double col = 1.0 / (1.0 + exp(-(double)P.colors[3 * gg + c]));
+            g_colors[3 * gg + c] = (float)(sm[10 + c] * col * (1.0 - col));
+        }
+    }
+}
+
+// beta1_bar = sum z_bar d (d = d2 / log2 e); beta2_bar = -sum z_bar t / eta
+__device__ __forceinline__ void fin_write_beta(const Params &P, int scene, int k, double sb, float *__restrict__ g_betas)
+{
+    g_betas[2 * scene + k] = k == 0 ? (float)(sb / kLog2e) : (float)(-sb / (double)P.eta[scene]);
+}
+
+// One stage, for scenes of at most kOneStageItems items: block (task, slice) sums the records of a
+// few Gaussians (and, with the first, the betas) over all items.  Thread (k, v) of 32 x 32 adds value v of
+// items k, k + 32, ... in order, then a fixed tree adds the k: one launch with every load of a value
+// in flight, where the two stages below took two launches of 5 us each on small jobs (their reads of
+// a few items per thread leave nothing to hide the latency).
+__global__ __launch_bounds__(1024) void fin_one_kernel(Params P, const FinTask *__restrict__ tasks,
+                                                       const float *__restrict__ partial,
+                                                       const float *__restrict__ beta_partial, float *__restrict__ g_means,
+                                                       float *__restrict__ g_prec, float *__restrict__ g_weights,
+                                                       float *__restrict__ g_colors, float *__restrict__ g_betas)
+{
+    __shared__ double sums[32][32];
+    const FinTask task = tasks[blockIdx.x];
+    const int per = fin_one_gauss(task.rec), g_lo = blockIdx.y * per;
+    if (g_lo >= task.gc) return;
+    const int ng = min(per, task.gc - g_lo), nv = ng * task.rec;
+    const int v = threadIdx.x & 31, k = threadIdx.x >> 5;
+    const int nval = task.gc * task.rec, n = task.item_end - task.item_begin;
+    const int nk = n > k ? (n - k + 31) / 32 : 0;  // items k, k + 32, ...
+    const bool beta = v >= 30 && blockIdx.y == 0 && task.beta;
+    double s = 0.0;
+    if (v < nv)
+        s = ordered_sum(partial + task.poff + (size_t)k * nval + g_lo * task.rec + v, nk, (size_t)32 * nval);
+    else if (beta)
+        s = ordered_sum(beta_partial + 2 * (task.item_begin + k) + v - 30, nk, (size_t)64);
+    sums[k][v] = s;
+    __syncthreads();
+#pragma unroll
+    for (int h = 16; h > 0; h >>= 1) {
+        if (k < h) sums[k][v] += sums[k + h][v];
+        __syncthreads();
+    }
+    if (threadIdx.x < ng)
+        fin_write(P, P.scenes[task.scene].gauss_off + task.g0 + g_lo + threadIdx.x, &sums[0][task.rec * threadIdx.x], task.rec,
+                  g_means, g_prec, g_weights, g_colors);
+    if (k == 0 && beta) fin_write_beta(P, task.scene, v - 30, sums[0][v], g_betas);
 }
 
 // First stage: block (group, slice) sums the values slice * BLOCK + tid, + BLOCK * slices, ...
@@ -1102,31 +1179,10 @@ __global__ __launch_bounds__(BLOCK) void fin2_kernel(Params P, const FinTask *__
         sums[tv] = s;
     }
     __syncthreads();
-    if (tid < ng) {
-        const int gg = sr.gauss_off + task.g0 + g_lo + tid;
-        const double *sm = sums + rec * tid;
-        const float *u = P.prec + 6 * gg;
-        float *gp = g_prec + 6 * gg;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) gp[c] = (float)sm[c];
-        const double r0 = sm[6], r1 = sm[7], r2 = sm[8];
-        g_means[3 * gg + 0] = (float)(-(double)u[0] * r0);
-        g_means[3 * gg + 1] = (float)(-((double)u[1] * r0 + (double)u[3] * r1));
-        g_means[3 * gg + 2] = (float)(-((double)u[2] * r0 + (double)u[4] * r1 + (double)u[5] * r2));
-        g_weights[gg] = (float)(sm[9] / (double)P.weights[gg]);
-        if (rec == kPartialColor && g_colors) {
-            // colour = sigmoid(q): dL/dq = dL/dc c (1 - c)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double col = 1.0 / (1.0 + exp(-(double)P.colors[3 * gg + c]));
-                g_colors[3 * gg + c] = (float)(sm[10 + c] * col * (1.0 - col));
-            }
-        }
-    }
+    if (tid < ng) fin_write(P, sr.gauss_off + task.g0 + g_lo + tid, sums + rec * tid, rec, g_means, g_prec, g_weights, g_colors);
     if (task.beta && blockIdx.y == 0 && tid < 2) {
         const double sb = ordered_sum(stage_beta + 2 * task.sgroup_begin + tid, task.sgroup_end - task.sgroup_begin, 2);
-        // beta1_bar = sum z_bar d (d = d2 / log2 e); beta2_bar = -sum z_bar t / eta
-        g_betas[2 * task.scene + tid] = tid == 0 ? (float)(sb / kLog2e) : (float)(-sb / (double)P.eta[task.scene]);
+        fin_write_beta(P, task.scene, tid, sb, g_betas);
     }
 }
 
@@ -1167,6 +1223,12 @@ __global__ __launch_bounds__(BLOCK) void statt_kernel(Params P, const float *__r
     const bool b1_pos = bl.b1 >= 0.0f;  // the weight bounds need beta1 >= 0
     const int nt = min(T, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
 
+    auto stage = [&](int gb, int q) {
+        const int gi = sr.gauss_off + gb + q;
+        make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[5 * q]);
+    };
+    // (the first Gaussian tile beside the rays, as in the backward)
+    if (BLOCK - 1 - tid < min(TG, sr.n)) stage(0, BLOCK - 1 - tid);
     for (int q = tid; q < RAYS; q += BLOCK) {
         int row = 0, col = 0;
         const int local = (q >> 6) < nt ? tile_local(vr, item.ray0 + (q >> 6), q & 63, row, col) : -1;
@@ -1198,12 +1260,11 @@ __global__ __launch_bounds__(BLOCK) void statt_kernel(Params P, const float *__r
     float *__restrict__ out = partial + item.poff;
     for (int gb = 0; gb < sr.n; gb += TG) {
         const int cnt = min(TG, sr.n - gb);
-        __syncthreads();  // staged rays and boxes visible; the previous tile's entries are consumed
-        for (int q = tid; q < cnt; q += BLOCK) {
-            const int gi = sr.gauss_off + gb + q;
-            make_entry_est(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, &ents[5 * q]);
+        if (gb > 0) {
+            __syncthreads();  // the previous tile's entries are consumed
+            for (int q = tid; q < cnt; q += BLOCK) stage(gb, q);
         }
-        __syncthreads();
+        __syncthreads();  // staged rays, boxes and entries visible
         for (int i0 = wave; i0 < cnt; i0 += GPB * NW) {
             unsigned long long tmasks;  // bits [T k, T k + T): the tiles Gaussian i0 + k NW can weigh on
             {
@@ -1553,28 +1614,35 @@ hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Pa
     }
 }
 
+// The first n_one tasks (of at most one_gc Gaussians) are reduced in one stage, the others in two.
 // masks: the items' record masks (or NULL: every record is written), rec: floats per record.
 // max_gc: the largest chunk of any task (a whole scene for the ray-lane backward); max_nval: the
 // largest first-stage record of any group.
-hipError_t launch_fin(int n_tasks, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
+hipError_t launch_fin(int n_tasks, int n_one, int one_gc, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks, const FinGroup *groups, const float *partial, const float *bpart,
                       const unsigned long long *masks, int rec, double *stage, double *stage_beta, float *g_means, float *g_prec, float *g_weights,
                       float *g_colors, float *g_betas)
 {
     if (max_gc < 1 || max_nval < 1) return hipErrorInvalidValue;
-    const int slices = (max_nval + 255) / 256 < 65535 ? (max_nval + 255) / 256 : 65535;
-    if (masks)
-        hipLaunchKernelGGL((fin1s_kernel<256>), dim3(n_groups, (max_gc + 255) / 256 < 65535 ? (max_gc + 255) / 256 : 65535),
-                           dim3(256), 0, st, groups, partial, bpart, masks, rec, stage, stage_beta);
-    else
-        hipLaunchKernelGGL((fin1_kernel<256>), dim3(n_groups, slices), dim3(256), 0, st, groups, partial, bpart, stage,
-                           stage_beta);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int gslices = (max_gc + kFinSlice - 1) / kFinSlice;
-    if (gslices > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fin2_kernel<256>), dim3(n_tasks, gslices), dim3(256), 0, st, P, tasks, groups, stage,
-                       stage_beta, g_means, g_prec, g_weights, g_colors, g_betas);
+    if (n_one > 0) {
+        const int per = fin_one_gauss(rec);
+        if ((one_gc + per - 1) / per > 65535) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(fin_one_kernel, dim3(n_one, (one_gc + per - 1) / per), dim3(1024), 0, st, P, tasks, partial, bpart,
+                           g_means, g_prec, g_weights, g_colors, g_betas);
+    }
+    if (n_tasks > n_one) {
+        const int slices = (max_nval + 255) / 256 < 65535 ? (max_nval + 255) / 256 : 65535;
+        const int gslices = (max_gc + kFinSlice - 1) / kFinSlice;
+        if (gslices > 65535) return hipErrorInvalidValue;
+        if (masks)
+            hipLaunchKernelGGL((fin1s_kernel<256>), dim3(n_groups, (max_gc + 255) / 256 < 65535 ? (max_gc + 255) / 256 : 65535),
+                               dim3(256), 0, st, groups, partial, bpart, masks, rec, stage, stage_beta);
+        else
+            hipLaunchKernelGGL((fin1_kernel<256>), dim3(n_groups, slices), dim3(256), 0, st, groups, partial, bpart, stage,
+                               stage_beta);
+        hipLaunchKernelGGL((fin2_kernel<256>), dim3(n_tasks - n_one, gslices), dim3(256), 0, st, P, tasks + n_one, groups, stage,
+                           stage_beta, g_means, g_prec, g_weights, g_colors, g_betas);
+    }
     return hipGetLastError();
 }
 
