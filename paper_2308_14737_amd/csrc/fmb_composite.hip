@@ -12,7 +12,7 @@
 // Layout: one ray per lane, one 8 x 8 pixel tile (ViewRec's ray tiles) per wave; an item is a run of
 // consecutive tiles of one view.  A scene of at most kCompTG Gaussians is staged in LDS once per item
 // and block for four waves, which take the item's tiles in turn (one wave per block staged it for itself
-// and left a 20-view 128 x 128 job at 320 waves: 980 -> 197 us for its step).  Of a larger scene each
+// and left a 20-view 128 x 128 job at 320 waves: 980 -> 181 us for its step).  Of a larger scene each
 // wave first bounds every Gaussian on its tile and stages those that can matter there (about 10 of 1000 on
 // a clustered 480 x 270 view, 9.4 -> 0.9 ms); only a tile with more than kCompTG of them takes the
 // scene in staged tiles.
@@ -274,7 +274,8 @@ __device__ __forceinline__ void slots_z_plain(const CompList<NS> &L, CompZ &zs, 
         zs.z1[k - 32] = slot_z_plain(L, ns, w, M2, invS, tfb, kap, L.d1[k - 32], L.t1[k - 32]);
 }
 
-// z_bar of a slot's pair from its front sum F, density and depth (0 where the slot is empty).
+// z_bar of a slot's pair from its front sum F, density and depth (0 where the slot is empty); kap is
+// kappa less the pair's C_bar . c.
 __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, float invS, float tfb, float kap)
 {
     if (!(dl > 0.0f)) return 0.0f;
@@ -282,25 +283,26 @@ __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, 
     return exp2_(lw - M2) * invS * fmaf(tfb, ts * (1.0f / kDepthScale), -kap);
 }
 
-// The same z_bar for a tile of one window whose pairs are all slots' (no normal or colour
-// cotangent): first every slot's front sum F into zs, then every slot's z_bar into its density
-// register.  The adjoint of such a tile then takes a pair's front sum from zs and the sums of z_bar
-// behind it from the density registers: the slots' densities are needed only for the front sums,
-// and a second front sum per pair is saved.  The values are those slots_z_plain and comp_front
-// form, bit for bit.
-template <int NS>
+// The same z_bar for a tile of one window whose pairs are all slots' (no normal cotangent;
+// kap_of(k): kappa less C_bar . c of slot k's Gaussian): first every slot's front sum F into zs,
+// then every slot's z_bar into its density register.  The adjoint of such a tile then takes a
+// pair's front sum from zs and the sums of z_bar behind it from the density registers: the slots'
+// densities are needed only for the front sums, and a second front sum per pair is saved (the
+// kernel is bound by instruction issue: with a colour cotangent 141 -> 123 us for 20 views of
+// 128 x 128 and 64 Gaussians).
+template <int NS, class KapOf>
 __device__ __forceinline__ void slots_fz_plain(CompList<NS> &L, CompZ &zs, int ns, const CompWin &w, float M2,
-                                               float invS, float tfb, float kap)
+                                               float invS, float tfb, KapOf kap_of)
 {
 #pragma unroll 1
     for (int k = 0; k < min(ns, 32); ++k) zs.z0[k] = comp_front(L, ns, w, L.t0[k]);
 #pragma unroll 1
     for (int k = 32; k < ns; ++k) zs.z1[k - 32] = comp_front(L, ns, w, L.t1[k - 32]);
 #pragma unroll 1
-    for (int k = 0; k < min(ns, 32); ++k) L.d0[k] = slot_zf(zs.z0[k], L.d0[k], L.t0[k], M2, invS, tfb, kap);
+    for (int k = 0; k < min(ns, 32); ++k) L.d0[k] = slot_zf(zs.z0[k], L.d0[k], L.t0[k], M2, invS, tfb, kap_of(k));
 #pragma unroll 1
     for (int k = 32; k < ns; ++k)
-        L.d1[k - 32] = slot_zf(zs.z1[k - 32], L.d1[k - 32], L.t1[k - 32], M2, invS, tfb, kap);
+        L.d1[k - 32] = slot_zf(zs.z1[k - 32], L.d1[k - 32], L.t1[k - 32], M2, invS, tfb, kap_of(k));
 }
 
 // Entries of Gaussians [gb, gb + cnt) of the scene into LDS, EW float4 each: the entry, the terms
@@ -954,9 +956,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kBwdcWa
         float zthrough = 0.0f;
         for (;;) {
             // (a tile of one window whose pairs are all slots': the slots keep F and z_bar)
-            const bool fz = PLAIN && !COLOR && hit_tile;
+            const bool fz = PLAIN && hit_tile;
             if (fz) {
-                slots_fz_plain(L, zs, ns, w, M2, invS, tfb, kap);
+                slots_fz_plain(L, zs, ns, w, M2, invS, tfb, [&](int k) {
+                    if (!COLOR) return kap;
+                    const float4 cc = ents[EW * slot_g[k] + kCompCol];
+                    return kap - fmaf(cb0, cc.x, fmaf(cb1, cc.y, cb2 * cc.z));
+                });
             } else {
                 slots_z(ns);
                 zthrough += window_z(ns);

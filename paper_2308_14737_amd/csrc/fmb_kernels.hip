@@ -1468,7 +1468,7 @@ constexpr int kNumBwdRay = (int)(sizeof kBwdRay / sizeof kBwdRay[0]);
 // without a normal cotangent.  Calls with one run the form of it that takes them, numbered 9 (not a
 // variant to choose: eight waves share 8 tiles, whose rays are twice the size).  It passes over the
 // pairs that the Gaussian-lane variant 2, run before, evaluated: 12 views of 203 x 150 against 60
-// Gaussians 76 -> 45 us.
+// Gaussians 76 -> 49 us.
 // (256 threads per block for variants 6 and 7; variant 8 has eight waves share an item's 16 staged
 // tiles, 512 threads)
 static const int kBwdTiles[] = {8, 16, 16, 8};
