@@ -301,13 +301,15 @@ struct Job {
         prm.eta = d_eta.as<float>();
         // Untuned default of the forward: more rays per item amortise its staging and bounds, fewer fill
         // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 59 / 71 / 75,
-        // 330 000 rays 59.6 / 61.8 / 64.4, 1.1e6 103 / 103 / 105, 2.4e6 146 / 142 / 143, 12.6e6 832 / 808 / 786;
-        // with 10 000 Gaussians, whose items also pre-cull them, 2.1e6 rays 1909 / 1648 / 1554 and (4000)
-        // 0.5e6 rays 471 / 460 / 549.
+        // 330 000 rays 59.6 / 61.8 / 64.4, 1.1e6 103 / 103 / 105, 2.4e6 146 / 142 / 143, 12.6e6 832 / 808 / 786.
+        // Of clustered scenes beyond a block's count of Gaussians a few blocks take most of the pairs, and
+        // shorter ones leave less of a tail, at the price of a pre-cull each: 0.5e6 rays of 4000 Gaussians
+        // 411 / 438 / 548, 1.2e6 of 10 000 1410 / 1488 / 1575, 1.4e6 of 500 250 / 238 / 244, 2.1e6 of 10 000
+        // 1396 / 1288 / 1365, 2.1e6 of 1000 288 / 262 / 257.
         if (!launch_fixed) {
             const int64_t r = 256LL * n_cu;
-            const int64_t wide = max_scene_n() > block_size() ? 28 : 64;
-            fwd_variant = P < 6 * r ? 0 : P < wide * r ? 1 : 3;
+            const int64_t one = max_scene_n() > block_size() ? 24 : 6;
+            fwd_variant = P < one * r ? 0 : P < 64 * r ? 1 : 3;
         }
         return FMB_OK;
     }
