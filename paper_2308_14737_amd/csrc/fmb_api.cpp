@@ -33,8 +33,8 @@ int bwd_normal_variant();
 int block_size();
 hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const FwdOut &O,
                       const FwdItem *items, const int *order);
-hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, const int *order, float *partial, float *bpart,
+hipError_t launch_bwd(int variant, int flags, int n_small, int n_big, int big_tiles, hipStream_t st, const Params &P,
+                      const BwdIn &I, const BwdItem *items, const int *order, float *partial, float *bpart,
                       unsigned long long *masks);
 hipError_t launch_fin(int n_tasks, int n_one, int one_gc, int n_groups, int max_gc, int max_nval, hipStream_t st, const Params &P,
                       const FinTask *tasks,
@@ -252,7 +252,8 @@ struct Job {
     int n_cfitems[2] = {0, 0};
     DevBuf d_cfitems;
     // backward work
-    int n_bitems_small = 0;  // compositing: how many of the items in order are small scenes'
+    int n_bitems_small = 0;  // compositing and tiled kernels: how many of the items in order are small scenes'
+    int bwd_big_tiles = 0;   // tiled kernels: the most ray tiles of a large scene's item
     int bwd_variant = 8, bwd_built = -1, n_bitems = 0, n_tasks = 0, n_groups = 0;
     int n_one = 0, fin_one_gc = 1;         // leading tasks reduced in one stage, their largest chunk
     int fin_max_gc = 1, fin_max_nval = 1;  // largest chunk and first-stage record (finalize grid)
@@ -442,7 +443,8 @@ struct Job {
         int n_one = 0, one_gc = 1;
         int rec = kPartial;
         size_t mask_words = 0;
-        int n_small = 0;  // compositing: leading items of `order` that are small scenes'
+        int n_small = 0;  // leading items of `order` that are small scenes' (see plan_bwd)
+        int big_tiles = 0;  // tiled kernels: the most ray tiles of a large scene's item
     };
     BwdPlan na_plan;  // the plan of the last fmb_backward_noalloc call (host memory only)
 
@@ -473,6 +475,7 @@ struct Job {
         partial_floats = pl.poff;
         n_bitems = (int)pl.items.size();
         n_bitems_small = pl.n_small;
+        bwd_big_tiles = pl.big_tiles;
         n_tasks = (int)pl.tasks.size();
         bwd_built = key;
         return FMB_OK;
@@ -497,6 +500,31 @@ struct Job {
         const int64_t chunks = (scenes[s].n + gc - 1) / gc;
         while (chunks * scene_items(s, span, false) > 16384 && span < (1 << 22)) span *= 2;
         while (chunks * scene_items(s, span, false) < 2048 && span > least) span /= 2;
+        return span;
+    }
+
+    // Ray tiles per item of the tiled kernels for a scene of more than a block's count of Gaussians, from the
+    // scene alone.  Such scenes' work is uneven, and a view of few tiles leaves the GPU short of blocks:
+    // items are halved from 16 tiles down to 2 while there are fewer than kLargeItems of them; smaller
+    // ones pre-cull the scene more often.  A step (us) with items of 16 / 8 / 4 / 2 tiles: 1064 tiles of 700
+    // Gaussians 119 / 92 / 88 / 67, 1900 of 400 83 / 71 / 69 / 64, 8160 of 4000 400 / 303 / 268 / 319, 11 000 of
+    // 2000 276 / 293 / 333 / 381, 18 400 of 10 000 1351 / 1520 / 1641 / 1919.
+    // A record of each Gaussian per item bounds it too: items are no smaller than fits the workspace of
+    // fmb_backward_noalloc where those of 16 tiles fit there, else 2 GiB per scene.
+    static constexpr int kLargeItems = 1024;
+    int large_span(int s, int rec) const
+    {
+        const int64_t n = scenes[s].n, unit = n * rec * (int64_t)sizeof(float);
+        auto bytes = [&](int span) {  // records, reduction stages (48 items a group at least), items and masks
+            const int64_t items = scene_items(s, span, true);
+            return unit * (items + 2 * ((items + 47) / 48)) +
+                   items * (int64_t)(sizeof(BwdItem) + 2 * sizeof(float) + 8 * ((n + 63) / 64));
+        };
+        const int64_t noalloc = FMB_NOALLOC_SCRATCH_BYTES - (1 << 20);
+        const int64_t most = bytes(16) <= noalloc + (1 << 20) ? noalloc : 2LL << 30;
+        int span = 16;
+        while (span > 2 && scene_items(s, span, true) < kLargeItems) span /= 2;
+        while (span < 16 && bytes(span) > most) span *= 2;
         return span;
     }
 
@@ -540,8 +568,23 @@ struct Job {
         const int tiles = comp ? kCompTiles : bwd_variant_tiles(variant);
         const int B = block_size();
         std::vector<int> gcs(S), sls(S), spans(S);
+        auto large = [&](int s) { return !comp && tiles > 0 && scenes[s].n > B; };
+        // (a batch whose records would not fit with the scenes' own cuts takes 16 tiles for all of them)
+        int64_t floats = 0;
+        int big_tiles = 0;
+        if (variant != bwd_normal_variant())
+            for (int s = 0; s < S; ++s)
+                floats += scene_items(s, large(s) ? large_span(s, rec) : std::max(tiles, 1), true) * scenes[s].n * rec;
+        auto big_span = [&](int s) {
+            return variant == bwd_normal_variant() ? tiles : floats > INT32_MAX ? 16 : large_span(s, rec);
+        };
         for (int s = 0; s < S; ++s) {
-            if (tiles > 0) {
+            if (large(s)) {
+                gcs[s] = scenes[s].n;
+                sls[s] = 1;
+                spans[s] = big_span(s);
+                big_tiles = std::max(big_tiles, spans[s]);
+            } else if (tiles > 0) {
                 // tiled kernels: the whole scene per item, `tiles` ray tiles (ViewRec) per item
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
@@ -561,9 +604,9 @@ struct Job {
         std::vector<int> tasks_item_begin, tasks_item_end;
         std::vector<double> cost;
         size_t poff = 0, moff = 0;
-        // the tiled kernels' form for large scenes writes only the records that an item touched
-        const bool masked = !comp && tiles > 0 && max_scene_n() > block_size();
         for (int s = 0; s < S; ++s) {
+            // the tiled kernels' form for large scenes writes only the records that an item touched
+            const bool masked = large(s);
             const int gc = gcs[s], sl = sls[s], span = spans[s];
             const int n = scenes[s].n;
             for (int g0 = 0; g0 < n; g0 += gc) {
@@ -608,7 +651,7 @@ struct Job {
         std::vector<FinGroup> groups;
         // (a task that holds its whole scene, of few items whose records are all written, needs none)
         auto one_stage = [&](const FinTask &t) {
-            return !masked && t.gc == scenes[t.scene].n && t.item_end - t.item_begin <= kOneStageItems;
+            return !large(t.scene) && t.gc == scenes[t.scene].n && t.item_end - t.item_begin <= kOneStageItems;
         };
         size_t soff = 0;
         int scene_first_group = 0, cur_scene = -1;
@@ -629,7 +672,7 @@ struct Job {
             // take no more room than the groups saved.
             const double root = std::sqrt((double)(ie - ib));
             int gsz = std::max(kGroupItems, (int)std::ceil(root));
-            if (!comp && tiles > 0 && t.gc > block_size() &&
+            if (large(t.scene) &&
                 (double)(ie - ib) * t.gc * rec * sizeof(float) <= (double)FMB_NOALLOC_SCRATCH_BYTES)
                 gsz = std::max(48, (int)std::ceil(1.5 * root));
             for (int a = ib; a < ie; a += gsz) {
@@ -639,7 +682,7 @@ struct Job {
                 g.poff = items[a].poff;
                 g.nval = items[a].gc * rec;
                 g.moff = items[a].moff;
-                g.words = masked ? (items[a].gc + 63) / 64 : 0;
+                g.words = large(t.scene) ? (items[a].gc + 63) / 64 : 0;
                 g.soff = (int)soff;
                 soff += (size_t)g.nval;
                 groups.push_back(g);
@@ -655,14 +698,14 @@ struct Job {
         for (int i = 0; i < pl.n_one; ++i) pl.one_gc = std::max(pl.one_gc, (int)tasks[i].gc);
         std::vector<int> order(items.size());
         std::iota(order.begin(), order.end(), 0);
-        if (comp) {  // (the compositing kernels have a form for small scenes and one for the others)
-            auto big = [&](int i) { return items[i].gc > comp_resident_max(); };
-            std::stable_sort(order.begin(), order.end(),
-                             [&](int a, int b) { return big(a) != big(b) ? big(b) : cost[a] > cost[b]; });
-            pl.n_small = (int)std::count_if(order.begin(), order.end(), [&](int i) { return !big(i); });
-        } else {
-            std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-        }
+        // (the compositing and the tiled kernels have a form for small scenes and one for the others)
+        auto big = [&](int i) { return comp ? items[i].gc > comp_resident_max() : tiles > 0 && items[i].gc > B; };
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int a, int b) { return big(a) != big(b) ? big(b) : cost[a] > cost[b]; });
+        int n_small = 0;
+        for (int i = 0; i < (int)items.size(); ++i) n_small += !big(i);
+        pl.n_small = n_small;
+        pl.big_tiles = big_tiles;
         pl.key = key;
         pl.max_gc = 1;
         pl.max_nval = 1;
@@ -784,12 +827,6 @@ struct Job {
     {
         return fwd_flags(O) | (max_scene_n() > block_size() ? kFlagBig : 0);
     }
-    // The blend backward's flags for variant v: for the tiled variants with a scene of more than a
-    // block's count of Gaussians, the kernel form that takes such scenes in pre-culled rounds.
-    int blend_bwd_flags(const BwdIn &I, int v) const
-    {
-        return bwd_flags(I) | (bwd_variant_tiles(v) > 0 && max_scene_n() > block_size() ? kFlagBig : 0);
-    }
     static int bwd_flags(const BwdIn &I)
     {
         return (I.g_normal ? kFlagNrm : 0) | (I.g_flow ? kFlagFlw : 0) |
@@ -838,8 +875,10 @@ struct Job {
             tb.stop();
         } else {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwd(bv, blend_bwd_flags(I, bv), n_bitems, st, prm, I, d_bitems.as<BwdItem>(),
-                              ordered ? d_border.as<int>() : nullptr, d_partial.as<float>(), d_bpart.as<float>(),
+            const bool mixed = n_bitems_small > 0 && n_bitems_small < n_bitems;
+            HIPCHK(launch_bwd(bv, bwd_flags(I), n_bitems_small, n_bitems - n_bitems_small, bwd_big_tiles, st, prm, I,
+                              d_bitems.as<BwdItem>(), ordered || mixed ? d_border.as<int>() : nullptr,
+                              d_partial.as<float>(), d_bpart.as<float>(),
                               mask_words ? d_masks.as<unsigned long long>() : nullptr));
             tb.stop();
         }
@@ -916,7 +955,9 @@ struct Job {
             tb.stop();
         } else {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwd(bv, blend_bwd_flags(I, bv), n_items, st, prm, I, items, nullptr, part, bpart, masks));
+            // (one scene: its items are all of one form, in any order)
+            HIPCHK(launch_bwd(bv, bwd_flags(I), pl.n_small, n_items - pl.n_small, pl.big_tiles, st, prm, I, items,
+                              nullptr, part, bpart, masks));
             tb.stop();
         }
         TimedSpan tf(st, 2);

@@ -695,7 +695,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     __shared__ float4 ents[EW * TG];          // the Gaussian tile's entries (m estimate terms, colour)
     __shared__ float rec[LREC * TG];          // (H, Bv, L) [and the colour sums] of each Gaussian
     __shared__ float bsum[2 * NW];
-    // scenes beyond BLOCK Gaussians: the list of survivors (a ring), the waves' counts of two rounds
+    // large scenes (kBig): the list of survivors (a ring), the waves' counts of two rounds
     constexpr int LIST = 2 * BLOCK;
     static_assert(TG <= BLOCK, "a round is added to fewer than TG survivors");
     __shared__ int slist[BIG ? LIST : 1];
@@ -713,9 +713,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
     const Blend bl = blend_of(P, vr.scene);
     const bool b1_pos = bl.b1 >= 0.0f;  // the weight bound needs beta1 >= 0
-    const int nt = min(T, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
+    const int nt = min(item.span, vr.tiles - item.ray0);  // the item's tiles: ray0 is its first tile
 
-    const bool sparse = BIG && sr.n > BLOCK;
+    constexpr bool sparse = BIG;
     int rb = 0, head = 0, total = sparse ? 0 : sr.n;  // next round, ring position and count of the listed
     // entry q of the Gaussian tile
     auto stage = [&](int q) {
@@ -772,15 +772,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
         }
     }
     float aB1 = 0.0f, aB2 = 0.0f;
-    // Of a scene of more than BLOCK Gaussians each is first bounded on the whole item (tile_bounds on
-    // a box around all its tiles, against their least normaliser), BLOCK of them a round, and only
-    // those that can matter on some tile are listed, in scene order, and staged TG at a time; the
-    // others' records would be zero, as the per-tile bounds would have left them, and are not
-    // written: a bit per Gaussian (masks) tells the finalize which of the item's records are.
-    // Rounds go on until the list fills a staged tile.  Smaller scenes stage all their Gaussians in
-    // order (and launches without kBig, whose scenes are all small, have no list).
+    // Each Gaussian of a large scene is first bounded on the whole item (tile_bounds on a box around
+    // all its tiles, against their least normaliser), BLOCK of them a round, and only those that
+    // can matter on some tile are listed, in scene order, and staged TG at a time; the others'
+    // records would be zero, as the per-tile bounds would have left them, and are not written: a
+    // bit per Gaussian (masks) tells the finalize which of the item's records are.  Rounds go on
+    // until the list fills a staged tile.  Smaller scenes stage all their Gaussians in order.
     TileBox ibox;
-    if (BIG && !sparse && 64 * tid < sr.n) masks[item.moff + tid] = ~0ull;  // every record is written
     for (bool first = true; ; first = false) {
       if (sparse && rb < sr.n && total < TG) {
         if (first) __syncthreads();  // boxes visible
@@ -1150,7 +1148,11 @@ __global__ __launch_bounds__(BLOCK) void fin1s_kernel(const FinGroup *__restrict
 {
     __shared__ double sums[BLOCK / 64][64 * kPartialColor];
     const FinGroup gr = groups[blockIdx.x];
-    if (rec == kPartial)
+    if (gr.words == 0) {  // a small scene's: every record is written
+        const int n = gr.item_end - gr.item_begin;
+        for (int v = blockIdx.y * BLOCK + threadIdx.x; v < gr.nval; v += BLOCK * gridDim.y)
+            stage[gr.soff + v] = ordered_sum(partial + gr.poff + v, n, gr.nval);
+    } else if (rec == kPartial)
         fin1_sparse<BLOCK, kPartial>(gr, masks, partial, stage, sums[threadIdx.x >> 6]);
     else
         fin1_sparse<BLOCK, kPartialColor>(gr, masks, partial, stage, sums[threadIdx.x >> 6]);
@@ -1485,7 +1487,8 @@ constexpr int kNumBwdRay = (int)(sizeof kBwdRay / sizeof kBwdRay[0]);
 // pairs that the Gaussian-lane variant 2, run before, evaluated: 12 views of 203 x 150 against 60
 // Gaussians 76 -> 49 us.
 // (256 threads per block for variants 6 and 7; variant 8 has eight waves share an item's 16 staged
-// tiles, 512 threads)
+// tiles, 512 threads).  Items of scenes beyond a block's count of Gaussians are cut by the scene, 2 to 16
+// tiles, and run the form for large scenes of eight waves in all three.
 static const int kBwdTiles[] = {8, 16, 16, 8};
 constexpr int kNumBwdTiled = (int)(sizeof kBwdTiles / sizeof kBwdTiles[0]);  // the last: normal cotangents
 constexpr int kBwdTiledFirst = kNumBwdGauss + kNumBwdRay;
@@ -1547,7 +1550,7 @@ static hipError_t launch_bwd_v(int f, int grid, hipStream_t st, const Params &P,
     return hipGetLastError();
 }
 
-template <int BLK, int T>
+template <int BLK, int T, int BIG>
 static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P, const BwdIn &I,
                                 const BwdItem *items, const int *order, float *partial,
                                 float *bpart, unsigned long long *masks)
@@ -1555,15 +1558,12 @@ static hipError_t launch_bwdt_v(int f, int grid, hipStream_t st, const Params &P
 #define FMB_BWDT_CALL(F)                                                                                   \
     hipLaunchKernelGGL((bwdt_kernel<BLK, T, 64, F>), dim3(grid), dim3(BLK), 0, st, P, I, items, order,   \
                        partial, bpart, masks)
-    switch (f) {  // (no normal cotangent)
-    case 0: FMB_BWDT_CALL(0); break;
-    case kFlw: FMB_BWDT_CALL(kFlw); break;
-    case kCol: FMB_BWDT_CALL(kCol); break;
-    case kCol | kFlw: FMB_BWDT_CALL(kCol | kFlw); break;
-    case kBig: FMB_BWDT_CALL(kBig); break;
-    case kBig | kFlw: FMB_BWDT_CALL(kBig | kFlw); break;
-    case kBig | kCol: FMB_BWDT_CALL(kBig | kCol); break;
-    case kBig | kCol | kFlw: FMB_BWDT_CALL(kBig | kCol | kFlw); break;
+    if (grid == 0) return hipSuccess;
+    switch (f) {  // (no normal cotangent; BIG: kBig)
+    case 0: FMB_BWDT_CALL(BIG); break;
+    case kFlw: FMB_BWDT_CALL(BIG | kFlw); break;
+    case kCol: FMB_BWDT_CALL(BIG | kCol); break;
+    case kCol | kFlw: FMB_BWDT_CALL(BIG | kCol | kFlw); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1575,6 +1575,7 @@ static hipError_t launch_bwdt_normal(int f, int grid, hipStream_t st, const Para
                                      float *bpart, unsigned long long *masks)
 {
     constexpr int BLK = 512, T = 8;
+    if (grid == 0) return hipSuccess;
     switch (f) {
     case 1: FMB_BWDT_CALL(1); break;   case 3: FMB_BWDT_CALL(3); break;   case 5: FMB_BWDT_CALL(5); break;
     case 7: FMB_BWDT_CALL(7); break;   case 9: FMB_BWDT_CALL(9); break;   case 11: FMB_BWDT_CALL(11); break;
@@ -1610,10 +1611,26 @@ hipError_t launch_fwd(int variant, int flags, int grid, hipStream_t st, const Pa
     }
 }
 
-hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Params &P, const BwdIn &I,
-                      const BwdItem *items, const int *order, float *partial, float *bpart,
+// n_small, n_big: the items of scenes within and beyond a block's count of Gaussians, in this order (order
+// may be NULL where one of them is 0); big_tiles: the most ray tiles of the latter's items.  The variants
+// that are not tiled have no form for large scenes: all their items are n_small.
+hipError_t launch_bwd(int variant, int flags, int n_small, int n_big, int big_tiles, hipStream_t st, const Params &P,
+                      const BwdIn &I, const BwdItem *items, const int *order, float *partial, float *bpart,
                       unsigned long long *masks)
 {
+    const int grid = n_small;
+    if (n_big > 0) {
+        const int *big_order = order ? order + n_small : nullptr;
+        if (variant < kBwdTiledFirst || (!order && n_small > 0) || !masks || big_tiles > 16) return hipErrorInvalidValue;
+        hipError_t e;
+        if (variant == bwd_normal_variant())
+            e = launch_bwdt_normal(flags | kBig, n_big, st, P, I, items, big_order, partial, bpart, masks);
+        else if (big_tiles <= 8)
+            e = launch_bwdt_v<512, 8, kBig>(flags, n_big, st, P, I, items, big_order, partial, bpart, masks);
+        else
+            e = launch_bwdt_v<512, 16, kBig>(flags, n_big, st, P, I, items, big_order, partial, bpart, masks);
+        if (e != hipSuccess || n_small == 0) return e;
+    }
     switch (variant) {
     case 0: return launch_bwd_v<64>(flags, grid, st, P, I, items, order, partial, bpart);
     case 1: return launch_bwd_v<128>(flags, grid, st, P, I, items, order, partial, bpart);
@@ -1621,9 +1638,9 @@ hipError_t launch_bwd(int variant, int flags, int grid, hipStream_t st, const Pa
     case 3: return launch_bwdr_v<2, 64>(flags, grid, st, P, I, items, order, partial, bpart);
     case 4: return launch_bwdr_v<4, 64>(flags, grid, st, P, I, items, order, partial, bpart);
     case 5: return launch_bwdr_v<4, 128>(flags, grid, st, P, I, items, order, partial, bpart);
-    case 6: return launch_bwdt_v<256, 8>(flags, grid, st, P, I, items, order, partial, bpart, masks);
-    case 7: return launch_bwdt_v<256, 16>(flags, grid, st, P, I, items, order, partial, bpart, masks);
-    case 8: return launch_bwdt_v<512, 16>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 6: return launch_bwdt_v<256, 8, 0>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 7: return launch_bwdt_v<256, 16, 0>(flags, grid, st, P, I, items, order, partial, bpart, masks);
+    case 8: return launch_bwdt_v<512, 16, 0>(flags, grid, st, P, I, items, order, partial, bpart, masks);
     case 9: return launch_bwdt_normal(flags, grid, st, P, I, items, order, partial, bpart, masks);
     default: return hipErrorInvalidValue;
     }

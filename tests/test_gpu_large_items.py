@@ -1,0 +1,100 @@
+"""The blend backward of scenes beyond a block's count of Gaussians: items of 2 to 16 ray tiles, whose
+surviving Gaussians are listed over several rounds, alone, beside small scenes in one batch (bit for
+bit the same) and without an allocation -- against the FP64 oracle, or where that is too slow against
+the Gaussian-lane variant 2, which takes every pair.
+
+Tolerances: the gradients' of the other tests against the oracle; between the two variants, both of
+which are within it of the oracle, twice that."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from tests.gpu_util import TOL_GRAD, assert_grads, compare_grads, custom_scene, hit_mask_cot, make_scene, normwise, to_np
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+DEV = "cuda:0"
+BETAS = np.array([W.BETA1, W.BETA2], np.float32)
+
+
+def _t(a):
+    return None if a is None else torch.as_tensor(np.ascontiguousarray(a), device=DEV).contiguous()
+
+
+@pytest.mark.parametrize("colour", [False, True], ids=["plain", "colour"])
+def test_batch_of_small_and_large_scenes(colour):
+    """n = 257 ... 1100: one to three rounds, the last with one Gaussian; small ones before and after."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2308_14737_amd as fmb
+    sizes = [(20, [(24, 24)], (0.05, 0.2)), (257, [(24, 40), (7, 5)], (0.05, 0.2)), (1025, [(40, 24)], (0.01, 0.04)),
+             (256, [(16, 16)], (0.05, 0.2)), (1100, [(9, 70)], (0.005, 0.02))]
+    parts = [custom_scene(n, v, seed=700 + n, s_range=s) for n, v, s in sizes]
+    scenes, camsl = [p[0] for p in parts], [p[1] for p in parts]
+    g = np.random.Generator(np.random.PCG64(7))
+    cat = lambda k: _t(np.concatenate([getattr(s, k) for s in scenes]))  # noqa: E731
+    means, prec, weights, betas = cat("means"), cat("prec"), cat("weights"), _t(np.tile(BETAS, (len(scenes), 1)))
+    cams = [fmb.Cameras.from_numpy(c.w2c, c.intr, c.hw, device=DEV) for c in camsl]
+    b = fmb.Batch(means, prec, weights, betas, [1.0] * len(scenes), [s.n for s in scenes], cams)
+    q = (1.5 * g.standard_normal((means.shape[0], 3))).astype(np.float32) if colour else None
+    if colour:
+        qt = _t(q)
+        b.set_colors(qt)
+    outs = b.forward(b.alloc_outputs(color=colour))
+    qs = [q[b.gauss_off[i]:b.gauss_off[i + 1]] if colour else None for i in range(len(scenes))]
+    refs = [O.render_workload_view(s, c, BETAS, 1.0, colors=k)[0] for s, c, k in zip(scenes, camsl, qs)]
+    cot = W.random_cotangents(b.n_rays, 71, flow=False)
+    cot["normal"] = None
+    cot["color"] = g.standard_normal((b.n_rays, 3)).astype(np.float32) if colour else None
+    cot = hit_mask_cot(cot, np.concatenate([r["alpha"] for r in refs]))
+    grads = b.backward(outs, {k: _t(v) for k, v in cot.items()}, b.alloc_grads(colors=colour))
+    torch.cuda.synchronize()
+    for i, (sc, cm) in enumerate(zip(scenes, camsl)):
+        r0, r1, g0, g1 = b.ray_off[i], b.ray_off[i + 1], b.gauss_off[i], b.gauss_off[i + 1]
+        cut = {k: None if v is None else v[r0:r1] for k, v in cot.items()}
+        one = fmb.Scene(means[g0:g1], prec[g0:g1], weights[g0:g1], betas[i], 1.0, cams[i])
+        if colour:
+            one.set_colors(qt[g0:g1])
+        o = one.render()
+        args = (o, _t(cut["depth"]), _t(cut["alpha"]))
+        gi = one.backward(*args, g_color=_t(cut["color"]))
+        gn = one.backward(*args, g_color=_t(cut["color"]), noalloc=True)
+        torch.cuda.synchronize()
+        for k in ("means", "prec", "weights") + (("colors",) if colour else ()):
+            assert torch.equal(gi[k], grads[k][g0:g1]), (sc.n, k)
+            assert torch.equal(gi[k], gn[k]), (sc.n, k)
+        _, gref, _ = O.render_workload_view(sc, cm, BETAS, 1.0, cot=cut, colors=qs[i])
+        e = compare_grads(gi, gref)
+        if colour:
+            e["colors"] = normwise(to_np(gi["colors"]), gref["colors"])
+        assert_grads(e, f"N={sc.n}")
+
+
+# (Gaussians, view): items of 2, 4, 8 and 16 tiles; the last of 16 since the records of 8 would not fit the
+# workspace of a backward without allocation
+SPANS = [(300, (200, 260)), (300, (600, 640)), (300, (800, 800)), (2600, (360, 560))]
+
+
+@pytest.mark.parametrize("n,view", SPANS, ids=["2", "4", "8", "16"])
+def test_item_sizes(n, view):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2308_14737_amd as fmb
+    sc, cams = custom_scene(n, [view], seed=n + view[0], s_range=(0.01, 0.05))
+    scene, _ = make_scene(fmb, torch, sc, cams, BETAS, 1.0, DEV)
+    outs = scene.render()
+    cot = W.random_cotangents(cams.n_rays, 9, flow=False)
+    cot["normal"] = None
+    cot = hit_mask_cot(cot, to_np(outs["alpha"]))
+    args = (outs, _t(cot["depth"]), _t(cot["alpha"]))
+    got = scene.backward(*args)
+    na = scene.backward(*args, noalloc=True)
+    fmb.set_launch_config(scene=scene, bwd_variant=2)
+    ref = scene.backward(*args)
+    torch.cuda.synchronize()
+    for k in ("means", "prec", "weights", "betas"):
+        assert torch.equal(got[k], na[k]), k
+        assert normwise(to_np(got[k]), to_np(ref[k])) <= 2 * TOL_GRAD, k
