@@ -255,7 +255,9 @@ class _RenderFn(torch.autograd.Function):
         scene.set_colors(None if colors is None else colors.detach().contiguous())
         outs = scene.render(normals=normals, color=colors is not None)
         ctx.scene = scene
-        ctx.outs = outs
+        # aliases: ctx is the outputs' grad_fn, and holding the outputs themselves would be a cycle that
+        # keeps every step's buffers until the collector runs
+        ctx.outs = {k: None if v is None else v.detach() for k, v in outs.items()}
         ctx.has_colors = colors is not None
         ctx.save_for_backward(means, prec, weights, betas, colors)
         empty = outs["depth"].new_zeros(0)
