@@ -7,8 +7,8 @@ its scene, the loss cotangents (alpha-weighted L1 depth + BCE alpha against targ
 rendered from a perturbed copy of each scene), and the adjoint pass producing the
 gradients of means, precision factors, weights and both blend parameters.
 
-The timed value replays one HIP graph of the whole step (persistent forward kernel, loss
-cotangents, persistent backward + finalize kernels), captured from the stream the library
+The timed value replays one HIP graph of the whole step (forward kernel, loss
+cotangents, backward + finalize kernels), captured from the stream the library
 calls run on; the batch's own captured forward and backward graphs are timed too.  The same
 steps are also timed with one plain launch sequence per scene (`plain_value`).  Kernel
 durations for the roofline come from HIP events recorded around each kernel launch on its
@@ -68,10 +68,10 @@ def kernel_source_sha256():
 def bwd_kernel_name(variant):
     """The backward kernel a backward tile variant launches (the variant tables of the library)."""
     if variant < 3:
-        return "bwd_kernel (persistent, Gaussian lanes)"
+        return "bwd_kernel (Gaussian lanes)"
     if variant < 6:
-        return "bwdr_kernel (persistent, ray lanes)"
-    return "bwdt_kernel (persistent, 8x8 ray tiles per wave)"
+        return "bwdr_kernel (ray lanes)"
+    return "bwdt_kernel (8x8 ray tiles per wave)"
 
 
 def _profile_values(name, bwd_variant):
@@ -94,7 +94,7 @@ def _profile_values(name, bwd_variant):
 
 
 def measured_traffic(bwd_variant):
-    """HBM bytes per launch of the persistent backward kernel, from the committed rocprofv3
+    """HBM bytes per launch of the backward kernel, from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE summary, if it was taken of this variant's kernel as it is now."""
     try:
         return float(_profile_values("batch16_bwd_traffic.md", bwd_variant)["traffic_bytes_per_launch"])
@@ -243,7 +243,7 @@ def main():
         torch.cuda.synchronize()
         return (time.perf_counter() - t0) / k
 
-    # same steps, eager persistent launches, with HIP-event kernel timing
+    # same steps, eager launches, with HIP-event kernel timing
     def step_eager():
         # the forward writes the loss's depth and alpha cotangents in its per-ray epilogue (the
         # values the loss kernel would write), then the backward
@@ -535,7 +535,7 @@ def main():
 
     ms_step = ms_graph if ms_graph is not None else ms_eager
     value = pairs / (ms_step * 1e-3)
-    # dominant kernel: the persistent backward (adjoint with recompute) of the tuned variant
+    # dominant kernel: the backward (adjoint with recompute) of the tuned variant
     flops_bwd_launch = pairs * FLOPS_ADJ_PLAIN
     achieved = flops_bwd_launch / (bwd_ms * 1e-3)
     step_flops = pairs * (FLOPS_FWD_NORMALS + FLOPS_ADJ_PLAIN)
@@ -547,7 +547,7 @@ def main():
         "config": {"workload": "batch16: 16 uneven scenes, N~U{10..100}, V~U{4..32}, 64^2/128^2/256^2, "
                                "fwd (depth, alpha, normals) + bwd (L1 depth + BCE alpha), seed 3",
                    "scenes": S, "rays": P, "pairs_per_step": pairs, "global_batch": P,
-                   "parallelism": "single GPU, persistent batched kernels in HIP graphs"},
+                   "parallelism": "single GPU, batched kernels in HIP graphs"},
         "plain_value": (pairs / (plain_ms * 1e-3)) if plain_ms else None,
         "plain_ms_per_step": plain_ms,
         "plain_timed": ("replays of one graph of the 16 per-scene launch sequences"

@@ -503,29 +503,54 @@ struct Job {
         return span;
     }
 
-    // Ray tiles per item of the tiled kernels for a scene of more than a block's count of Gaussians, from the
-    // scene alone.  Such scenes' work is uneven, and a view of few tiles leaves the GPU short of blocks:
-    // items are halved from 16 tiles down to 2 while there are fewer than kLargeItems of them; smaller
-    // ones pre-cull the scene more often.  A step (us) with items of 16 / 8 / 4 / 2 tiles: 1064 tiles of 700
-    // Gaussians 119 / 92 / 88 / 67, 1900 of 400 83 / 71 / 69 / 64, 8160 of 4000 400 / 303 / 268 / 319, 11 000 of
-    // 2000 276 / 293 / 333 / 381, 18 400 of 10 000 1351 / 1520 / 1641 / 1919.
-    // A record of each Gaussian per item bounds it too: items are no smaller than fits the workspace of
-    // fmb_backward_noalloc where those of 16 tiles fit there, else 2 GiB per scene.
-    static constexpr int kLargeItems = 1024;
-    int large_span(int s, int rec) const
+    // Records per first-stage group: about sqrt(recs), so that both stages sum similar counts; more of a
+    // large scene whose records fit the fixed workspace of fmb_backward_noalloc, so that the items'
+    // masks take no more room than the groups saved.
+    static int group_size(int64_t recs, bool large, int64_t bytes)
+    {
+        const double root = std::sqrt((double)recs);
+        if (large && bytes <= (int64_t)FMB_NOALLOC_SCRATCH_BYTES) return std::max(48, (int)std::ceil(1.5 * root));
+        return std::max(kGroupItems, (int)std::ceil(root));
+    }
+
+    // How the tiled kernels cut a scene of more than a block's count of Gaussians, from the scene alone: ray
+    // tiles per record (span), and items that share a record, each taking a part of the Gaussians.  The work
+    // of such scenes is uneven (one 16-tile item of 10 000 clustered Gaussians holds 6 times the mean
+    // and is alone 2.4 times the whole launch's work per block slot), so items are cut until a part has at
+    // most kPartGauss Gaussians and there are kLargeItems of them.  A part repeats the rays' prologue, a
+    // smaller span the pre-cull, and takes more records.  A step (us) by span / parts: 10 000 Gaussians,
+    // 1080 x 1920, 16/1 1285, 16/2 1180, 16/4 1175, 8/1 1261, 8/4 1314; 10 000, 300 x 300, 16/1 1203, 16/8 435,
+    // 8/4 492, 2/1 479; 4000, 540 x 960, 16/1 414, 16/4 284, 8/2 241, 4/1 269; 1000, 1080 x 1920, 16/1 260,
+    // 16/2 283, 8/1 274; 400, 300 x 400, 16/1 85, 16/2 71, 2/1 64.
+    // Records and items stay within the workspace of fmb_backward_noalloc where those of 16/1 fit there,
+    // else 2 GiB a scene.
+    static constexpr int kLargeItems = 1024, kPartGauss = 2560, kMaxParts = 8;
+    struct LargeCut {
+        int span, parts;
+    };
+    LargeCut large_cut(int s, int rec) const
     {
         const int64_t n = scenes[s].n, unit = n * rec * (int64_t)sizeof(float);
-        auto bytes = [&](int span) {  // records, reduction stages (48 items a group at least), items and masks
-            const int64_t items = scene_items(s, span, true);
-            return unit * (items + 2 * ((items + 47) / 48)) +
-                   items * (int64_t)(sizeof(BwdItem) + 2 * sizeof(float) + 8 * ((n + 63) / 64));
+        auto bytes = [&](int span, int parts) {
+            const int64_t recs = scene_items(s, span, true), gsz = group_size(recs, true, unit * recs);
+            return unit * (recs + 2 * ((recs + gsz - 1) / gsz)) + recs * 8 * ((n + 63) / 64) +
+                   recs * parts * (int64_t)(sizeof(BwdItem) + 2 * sizeof(float));
         };
-        const int64_t noalloc = FMB_NOALLOC_SCRATCH_BYTES - (1 << 20);
-        const int64_t most = bytes(16) <= noalloc + (1 << 20) ? noalloc : 2LL << 30;
-        int span = 16;
-        while (span > 2 && scene_items(s, span, true) < kLargeItems) span /= 2;
-        while (span < 16 && bytes(span) > most) span *= 2;
-        return span;
+        const bool small = bytes(16, 1) <= (int64_t)FMB_NOALLOC_SCRATCH_BYTES;
+        const int64_t most = small ? (int64_t)FMB_NOALLOC_SCRATCH_BYTES - (1 << 20) : 2LL << 30;
+        auto fits = [&](int span, int parts) { return bytes(span, parts) <= most; };
+        int span = 16, parts = (int)std::min<int64_t>(kMaxParts, (n + kPartGauss - 1) / kPartGauss);
+        if (!fits(span, parts)) return {16, 1};
+        if (scene_items(s, 16, true) < kLargeItems / 2 && fits(8, parts)) span = 8;
+        while (scene_items(s, span, true) * parts < kLargeItems) {
+            if (2 * parts <= kMaxParts && n >= 512 * parts && fits(span, 2 * parts))
+                parts *= 2;
+            else if (span > 2 && fits(span / 2, parts))
+                span /= 2;
+            else
+                break;
+        }
+        return {span, parts};
     }
 
     // Whether calls with a normal cotangent run the tiled form: its items hold a record of every Gaussian
@@ -569,20 +594,25 @@ struct Job {
         const int B = block_size();
         std::vector<int> gcs(S), sls(S), spans(S);
         auto large = [&](int s) { return !comp && tiles > 0 && scenes[s].n > B; };
-        // (a batch whose records would not fit with the scenes' own cuts takes 16 tiles for all of them)
+        const bool normals = variant == bwd_normal_variant();
+        std::vector<int> parts(S, 1);
         int64_t floats = 0;
         int big_tiles = 0;
-        if (variant != bwd_normal_variant())
+        for (int s = 0; s < S; ++s) {
+            LargeCut cut{tiles, 1};
+            if (large(s) && !normals) cut = large_cut(s, rec);
+            spans[s] = cut.span;
+            parts[s] = cut.parts;
+            if (tiles > 0 && !comp) floats += scene_items(s, spans[s], true) * scenes[s].n * rec;
+        }
+        // (a batch whose records would not fit with the scenes' own cuts takes 16 tiles for all large ones)
+        if (floats > INT32_MAX && !normals)
             for (int s = 0; s < S; ++s)
-                floats += scene_items(s, large(s) ? large_span(s, rec) : std::max(tiles, 1), true) * scenes[s].n * rec;
-        auto big_span = [&](int s) {
-            return variant == bwd_normal_variant() ? tiles : floats > INT32_MAX ? 16 : large_span(s, rec);
-        };
+                if (large(s)) spans[s] = 16;
         for (int s = 0; s < S; ++s) {
             if (large(s)) {
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
-                spans[s] = big_span(s);
                 big_tiles = std::max(big_tiles, spans[s]);
             } else if (tiles > 0) {
                 // tiled kernels: the whole scene per item, `tiles` ray tiles (ViewRec) per item
@@ -630,15 +660,21 @@ struct Job {
                         if (poff > (size_t)INT32_MAX - (size_t)gc * rec)
                             return fail(FMB_ERR_SHAPE, "backward partial buffer exceeds 2^31 floats");
                         it.poff = (int)poff;
-                        it.seq = (int)items.size();
                         poff += (size_t)gc * rec;
                         if (masked) {
                             it.moff = (int)moff;  // (less than poff)
                             moff += (size_t)(gc + 63) / 64;
                         }
-                        items.push_back(it);
-                        cost.push_back((double)t.gc * (tiles > 0 ? std::min<int64_t>(64LL * span, hw - 64LL * r0)
-                                                                 : std::min(span, hw - r0)));
+                        for (int part = 0; part < parts[s]; ++part) {
+                            if (masked) {
+                                it.g0 = part;
+                                it.slots = parts[s];
+                            }
+                            it.seq = (int)items.size();
+                            items.push_back(it);
+                            cost.push_back((double)t.gc / parts[s] * (tiles > 0 ? std::min<int64_t>(64LL * span, hw - 64LL * r0)
+                                                                             : std::min(span, hw - r0)));
+                        }
                     }
                 }
                 tasks_item_end.push_back((int)items.size());
@@ -667,18 +703,13 @@ struct Job {
             }
             const int ib = t.item_begin, ie = t.item_end;
             t.group_begin = (int)groups.size();
-            // About sqrt(items) items per group so both stages sum similar counts; more of a large scene
-            // whose records fit the fixed workspace of fmb_backward_noalloc, so that the items' masks
-            // take no more room than the groups saved.
-            const double root = std::sqrt((double)(ie - ib));
-            int gsz = std::max(kGroupItems, (int)std::ceil(root));
-            if (large(t.scene) &&
-                (double)(ie - ib) * t.gc * rec * sizeof(float) <= (double)FMB_NOALLOC_SCRATCH_BYTES)
-                gsz = std::max(48, (int)std::ceil(1.5 * root));
-            for (int a = ib; a < ie; a += gsz) {
+            const int np = parts[t.scene], recs = (ie - ib) / np;
+            const int gsz = group_size(recs, large(t.scene), (int64_t)recs * t.gc * rec * (int64_t)sizeof(float));
+            for (int a = ib; a < ie; a += gsz * np) {
                 FinGroup g{};
                 g.item_begin = a;
-                g.item_end = std::min(ie, a + gsz);
+                g.item_end = std::min(ie, a + gsz * np);
+                g.parts = np;
                 g.poff = items[a].poff;
                 g.nval = items[a].gc * rec;
                 g.moff = items[a].moff;

@@ -68,6 +68,8 @@ struct BwdItem {       // 36 bytes
     int32_t g0;        // first Gaussian (scene-local) of the chunk
     int32_t gc;        // Gaussians in the chunk (<= block size)
     int32_t slots;     // ray slots: thread t works on Gaussian t % gc, rays t / gc mod slots
+                       // (tiled kernels with a large scene: the item is part g0 of slots of its record, every
+                       // slots-th 64 Gaussians)
     int32_t poff;      // offset (floats) of this item's partial record [gc][kPartial]
     int32_t seq;       // canonical item index (beta partials)
     int32_t moff;      // tiled kernels with a large scene: first 64-bit word of the item's mask of records
@@ -93,7 +95,7 @@ struct FinGroup {
     int32_t nval;      // gc * kPartial values per item (gc = item chunk size)
     int32_t soff;      // offset (doubles) of the group's sums in the stage buffer
     int32_t moff, words;  // the first item's mask and the words of each (items of a chunk are contiguous)
-    int32_t pad;
+    int32_t parts;     // items that share a record (large scenes' tiled items: each takes a part of the Gaussians)
 };
 // A chunk of at most this many items that holds its whole scene is reduced in one stage.
 constexpr int kOneStageItems = 4096;

@@ -717,6 +717,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
 
     constexpr bool sparse = BIG;
     int rb = 0, head = 0, total = sparse ? 0 : sr.n;  // next round, ring position and count of the listed
+    // large scenes: the item takes every slots-th 64 Gaussians of the scene, from the g0-th (words of masks)
+    const int words = (sr.n + 63) / 64, part_words = sparse ? (words - item.g0 + item.slots - 1) / item.slots : 0;
     // entry q of the Gaussian tile
     auto stage = [&](int q) {
         const int gi = sr.gauss_off + (sparse ? slist[(head + q) & (LIST - 1)] : head + q);
@@ -780,13 +782,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     // until the list fills a staged tile.  Smaller scenes stage all their Gaussians in order.
     TileBox ibox;
     for (bool first = true; ; first = false) {
-      if (sparse && rb < sr.n && total < TG) {
+      if (sparse && rb < part_words && total < TG) {
         if (first) __syncthreads();  // boxes visible
         float inorm = INFINITY;
         for (int t = 0; t < nt; ++t) inorm = fminf(inorm, tnorm[t]);
         if (first) ibox = wave_box_of(tbox, nt, lane, e);
         do {
-            const int gl = rb + tid, par = (rb / BLOCK) & 1;
+            const int word = item.g0 + item.slots * (rb + wave), gl = 64 * word + lane, par = (rb / NW) & 1;
             bool keep = false;
             if (gl < sr.n) {
                 const int gg = sr.gauss_off + gl;
@@ -800,7 +802,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
             const unsigned long long bal = wave_ballot(keep);
             if (lane == 0) {
                 wcnt[par][wave] = __popcll(bal);
-                if (rb + 64 * wave < sr.n) masks[item.moff + rb / 64 + wave] = bal;
+                if (word < words) masks[item.moff + word] = bal;
             }
             __syncthreads();
             int off = head + total;
@@ -810,8 +812,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
                 total += c;
             }
             if (keep) slist[(off + __popcll(bal & ((1ull << lane) - 1ull))) & (LIST - 1)] = gl;
-            rb += BLOCK;
-        } while (rb < sr.n && total < TG);
+            rb += NW;
+        } while (rb < part_words && total < TG);
       }
       if (total == 0) break;
       {
@@ -1100,7 +1102,7 @@ __device__ __forceinline__ void fin1_sparse(const FinGroup &gr, const unsigned l
     for (int base = blockIdx.y * BLOCK + (threadIdx.x & ~63); base < gc; base += BLOCK * gridDim.y) {
         const unsigned long long *mw = masks + gr.moff + base / 64;
         const float *rp = partial + gr.poff + REC * (base + lane);
-        const int n = gr.item_end - gr.item_begin;
+        const int n = (gr.item_end - gr.item_begin) / gr.parts;
         double s[REC];
 #pragma unroll
         for (int c = 0; c < REC; ++c) s[c] = 0.0;

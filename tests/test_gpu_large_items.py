@@ -73,12 +73,13 @@ def test_batch_of_small_and_large_scenes(colour):
         assert_grads(e, f"N={sc.n}")
 
 
-# (Gaussians, view): items of 2, 4, 8 and 16 tiles; the last of 16 since the records of 8 would not fit the
-# workspace of a backward without allocation
-SPANS = [(300, (200, 260)), (300, (600, 640)), (300, (800, 800)), (2600, (360, 560))]
+# (Gaussians, view): records of 2, 4, 8 and 16 tiles, the last shared by items that take parts of the Gaussians
+# (8 tiles would not fit the
+# workspace of a backward without allocation); few tiles and many parts
+SPANS = [(300, (200, 260)), (300, (600, 640)), (300, (800, 800)), (2600, (360, 560)), (5200, (64, 72))]
 
 
-@pytest.mark.parametrize("n,view", SPANS, ids=["2", "4", "8", "16"])
+@pytest.mark.parametrize("n,view", SPANS, ids=["2", "4", "8", "16_parts", "parts"])
 def test_item_sizes(n, view):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
