@@ -34,9 +34,8 @@ __device__ __forceinline__ Ent ent_from(const float4 a, const float4 b, const fl
 
 // Block-uniform, read-only metadata (work items, view and scene records, cameras, betas):
 // a load through the constant address space becomes a scalar load whose result stays in
-// SGPRs.  Inside a persistent loop the kernel's own stores would otherwise keep the compiler
-// from proving the records unchanged, and it would fall back to vector loads and VGPRs.  No
-// kernel writes these arrays.
+// SGPRs.  The kernel's own stores would otherwise keep the compiler from proving the records
+// unchanged, and it would fall back to vector loads and VGPRs.  No kernel writes these arrays.
 template <class T>
 __device__ __forceinline__ T ld_uniform(const T *p)
 {
@@ -122,7 +121,7 @@ __device__ __forceinline__ void cam_centre(const float *__restrict__ e, double o
 // (view, Gaussian) entry in double, rounded to float.  mu - o is split as hi + lo; the
 // pair loop forms U (t v - mu') as U (t v - hi) - U lo, so only U lo is stored.  log2 lambda
 // is the FP32 log2 (within an ulp of the rounded double): the FP64 routine's polynomial
-// constants would be hoisted out of a persistent loop and held in VGPRs for the whole kernel.
+// constants would be held in VGPRs around the staging loop.
 __device__ __forceinline__ void make_entry(const float *__restrict__ mu, const float *__restrict__ u,
                                            float lam, const double o[3], float4 out[4])
 {
@@ -145,7 +144,7 @@ __device__ __forceinline__ void make_entry(const float *__restrict__ mu, const f
 
 // The entry and, as a fifth float4, (|U mu'|^2, |Sigma^-1 mu'|_1, |U mu'|^2, 0): the terms of the
 // one-FMA estimate of the squared Mahalanobis distance m = |U mu'|^2 - (v.c) t and of its error bound
-// (pair_m_low, tile_bounds).
+// (tile_bounds).
 __device__ __forceinline__ void make_entry_est(const float *__restrict__ mu, const float *__restrict__ u,
                                                float lam, const double o[3], float4 out[5])
 {
@@ -293,16 +292,6 @@ __device__ __forceinline__ void pair_geo_resid(const Ent &g, float v0, float v1,
     q.z2 = fmaf(b1, q.d2, nc2 * q.t);
 }
 
-// A lower bound of the m that pair_geo_resid forms, from the entry's fifth float4 est and v.c:
-// m = |U mu'|^2 - (v.c)^2 / (a.a) estimated as est.x - (v.c) t in one FMA.  Its rounding error is a
-// few units of 2^-24 (|U mu'|^2 + |Sigma^-1 mu'|_1 |t|) (the terms that cancel; (v.c) t is at most
-// |U mu'|^2), and the residual form's own error is smaller still, so 2^-17 of that sum bounds both.
-__device__ __forceinline__ float pair_m_low(const float4 &est, float vc, float t)
-{
-    constexpr float kErr = 0x1p-17f;
-    return fmaf(-kErr, fmaf(est.y, fabsf(t), est.x), fmaf(-vc, t, est.x));
-}
-
 // The rays of a tile: unit centre direction c and an orthonormal basis (ex, ey, c) with the largest
 // |(v - c).ex|, |(v - c).ey|, |(v - c).c| over its unit ray directions v, as three float4
 // (c, Z) (ex, X) (ey, Y).  ex and ey follow the image axes, so that a pixel tile's box is tight.  A
@@ -385,8 +374,9 @@ __device__ __forceinline__ TileBox wave_box_of(const float4 *boxes, int n, int l
 // angle between them.  U v = U c + f with |f| <= F, F the largest |U (v - c)| over the box's corners,
 // so the line turns from the centre ray's by at most psi, sin(psi) = F / |U c|, and sqrt(m) lies within
 // |U mu'| sin(theta_c -+ psi) = sqrt(m_c) cos(psi) -+ |t_c| F (0 below theta_c = psi, |U mu'| above
-// theta_c + psi = pi/2; nothing is known where F >= |U c|).  m_c is the centre ray's m as pair_m_low
-// brackets it.  The depth is t = |U mu'| cos(theta) / |U v|, bounded the same way.  No inverse of U
+// theta_c + psi = pi/2; nothing is known where F >= |U c|).  m_c is the centre ray's m, estimated as
+// |U mu'|^2 - (v.c) t, whose rounding error is a few units of 2^-24 of the terms that cancel (|U mu'|^2 and
+// |Sigma^-1 mu'|_1 |t|); kErr of them covers it.  The depth is t = |U mu'| cos(theta) / |U v|, bounded the same way.  No inverse of U
 // enters, so needles and discs are bounded as tightly as balls: on scenes of scales 0.05 to 0.2 a
 // density cutoff of 2^-48 keeps 32 % of the (8 x 8 tile, Gaussian) pairs where some ray reaches it
 // on 31 %; the bound sqrt(m_c) - |U|_2 |U mu'| |U^-1|_2 rho over the tile's cone kept 40 %, and a

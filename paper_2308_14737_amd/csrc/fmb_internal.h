@@ -1,8 +1,7 @@
 // fmb_internal.h -- descriptors shared by the host library and the gfx950 kernels.
 //
 // A render job is always a "batch": S scenes, each with its own Gaussians, blend
-// parameters and views.  A single scene is the batch S = 1, so the plain and the
-// persistent kernels run the same per-item code.
+// parameters and views.  A single scene is the batch S = 1.
 //
 // Work is cut into items:
 //   forward item  = (view, first of BLOCK*RPT/64 consecutive ray tiles of that view, see ViewRec)
