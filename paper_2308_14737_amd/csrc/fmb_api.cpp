@@ -344,6 +344,21 @@ struct Job {
     // entries over 16 tiles, or over fewer where that leaves less than two blocks per compute unit
     // (20 views of 128 x 128: 4 tiles, 1280 blocks instead of 320); a larger scene's tiles stage their own
     // survivors, one tile an item.
+    // Into how many parts (4^cut waves) the compositing forward cuts the ray tiles of view k of a larger
+    // scene, from that scene alone: more where the Gaussians are many to a tile and while the waves
+    // are at most a few rounds of the GPU.  A render (us) with cut 0 / 1 / 2, clustered: 1000 Gaussians on
+    // 2040 tiles 304 / 165 / 351, on 256 1047 / 189 / 110; 1200 on 625 1288 / 327 / 226; 700 on 2040
+    // 112 / 102 / 335; 200 on 2040 30 / 63 / 199; 1000 on 8160 185 / 447 / 1669.  Spread over the whole image:
+    // 1000 on 256 84.5 / 77.9 / 75.5 ms, 900 on 950 64.0 / 59.7 / 83.4, 1000 on 2040 76.2 / 81.6 / 175.6.
+    int comp_cut(int k) const
+    {
+        const SceneRec &sc = scenes[views[k].scene];
+        int64_t tiles = 0;
+        for (int q = sc.view_off; q < sc.view_off + sc.n_views; ++q) tiles += views[q].tiles;
+        const double per_tile = (double)sc.n / views[k].tiles;
+        return tiles <= 320 && per_tile >= 1.5 ? 2 : tiles <= 2560 && per_tile >= 0.4 ? 1 : 0;
+    }
+
     int build_comp_fwd()
     {
         if (comp_fwd_built) return FMB_OK;
@@ -360,8 +375,11 @@ struct Job {
             const int big = n > comp_resident_max() ? 1 : 0;
             const int sp = big ? 1 : span;
             for (int t0 = 0; t0 < views[k].tiles; t0 += sp) {
-                items[big].push_back({k, t0, sp});
-                cost[big].push_back((double)n * std::min(sp, views[k].tiles - t0));
+                const int cut = big ? comp_cut(k) : 0;
+                for (int part = 0; part < 1 << (2 * cut); ++part) {
+                    items[big].push_back({k, t0, sp, part, cut});
+                    cost[big].push_back((double)n * std::min(sp, views[k].tiles - t0));
+                }
             }
         }
         std::vector<CompItem> all;
@@ -380,8 +398,10 @@ struct Job {
     // Ray tiles per item of the compositing backward of scene s, from that scene alone (its gradient
     // is then the same in any batch).  Small scenes: 16, or 8 or 4 where the scene has too few
     // tiles for 512 items.  Larger scenes, whose items are one wave each: as few as keep the partial
-    // records below 8 MiB.
-    int comp_bwd_span(int s, int rec) const
+    // records below 8 MiB or, with `more`, within the workspace of fmb_backward_noalloc where those fit it
+    // and else 256 MiB (items of one tile take 7.5 -> 3.9 ms for a step of 1200 clustered Gaussians at
+    // 270 x 480, 202 -> 114 us for one of 300).
+    int comp_bwd_span(int s, int rec, bool more) const
     {
         auto count = [&](int span) {
             int64_t c = 0;
@@ -394,6 +414,12 @@ struct Job {
             while (span > 4 && count(span) < 512) span /= 2;
         } else {
             while (span > 1 && count(span / 2) * scenes[s].n * rec * (int64_t)sizeof(float) <= (8 << 20)) span /= 2;
+            const int64_t unit = scenes[s].n * rec * (int64_t)sizeof(float);
+            // (at most kOneStageItems items a scene: one reduction stage)
+            auto bytes = [&](int sp) { return count(sp) * (unit + (int64_t)(sizeof(BwdItem) + 3 * sizeof(float))); };
+            const int64_t noalloc = FMB_NOALLOC_SCRATCH_BYTES - (64 << 10);
+            const int64_t most = bytes(span) <= (int64_t)FMB_NOALLOC_SCRATCH_BYTES ? noalloc : 256 << 20;
+            while (more && span > 1 && count(span - 1) <= kOneStageItems && bytes(span - 1) <= most) --span;
         }
         return span;
     }
@@ -603,10 +629,11 @@ struct Job {
             if (large(s) && !normals) cut = large_cut(s, rec);
             spans[s] = cut.span;
             parts[s] = cut.parts;
-            if (tiles > 0 && !comp) floats += scene_items(s, spans[s], true) * scenes[s].n * rec;
+            if (tiles > 0) floats += scene_items(s, comp ? comp_bwd_span(s, rec, true) : spans[s], true) * scenes[s].n * rec;
         }
-        // (a batch whose records would not fit with the scenes' own cuts takes 16 tiles for all large ones)
-        if (floats > INT32_MAX && !normals)
+        // (a batch whose records would not fit with the scenes' own cuts takes larger items for all large ones)
+        const bool own_cuts = floats <= INT32_MAX;
+        if (!own_cuts && !normals)
             for (int s = 0; s < S; ++s)
                 if (large(s)) spans[s] = 16;
         for (int s = 0; s < S; ++s) {
@@ -618,7 +645,7 @@ struct Job {
                 // tiled kernels: the whole scene per item, `tiles` ray tiles (ViewRec) per item
                 gcs[s] = scenes[s].n;
                 sls[s] = 1;
-                spans[s] = comp ? comp_bwd_span(s, rec) : tiles;
+                spans[s] = comp ? comp_bwd_span(s, rec, own_cuts) : tiles;
             } else if (ray_tile > 0) {
                 // ray-lane kernel: the whole scene per item, two ray tiles per item to start
                 gcs[s] = scenes[s].n;
@@ -770,7 +797,7 @@ struct Job {
         for (int s = 0; s < S; ++s) {
             const int n = scenes[s].n;
             const int gc = n, sl = 1;
-            const int span = comp ? comp_bwd_span(s, 1) : kStatTiles;  // ray tiles (ViewRec) per item
+            const int span = comp ? comp_bwd_span(s, 1, false) : kStatTiles;  // ray tiles (ViewRec) per item
             stat_max_gc = std::max(stat_max_gc, gc);
             for (int k = scenes[s].view_off; k < scenes[s].view_off + scenes[s].n_views; ++k)
                 rays[s] += (int64_t)views[k].h * views[k].w;

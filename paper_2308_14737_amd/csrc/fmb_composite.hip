@@ -305,6 +305,16 @@ __device__ __forceinline__ void slots_fz_plain(CompList<NS> &L, CompZ &zs, int n
         L.d1[k - 32] = slot_zf(zs.z1[k - 32], L.d1[k - 32], L.t1[k - 32], M2, invS, tfb, kap_of(k));
 }
 
+// The part of an 8 x 8 tile that the lane is in, of 4^cut square ones (cut 1 or 2).  The forward of a
+// larger scene gives a dense view's tiles to 4 or 16 waves: a part's rays share fewer Gaussians, so
+// that its wave takes fewer windows, and the slowest tile, which the launch waits for, is the sooner
+// done (1000 clustered Gaussians at 270 x 480: 304 -> 165 us; at 64 x 64: 2423 -> 196 us).
+__device__ __forceinline__ int comp_part(int lane, int cut)
+{
+    const int half = 3 - cut;
+    return ((lane >> (3 + half)) << cut) + ((lane & 7) >> half);
+}
+
 // Entries of Gaussians [gb, gb + cnt) of the scene into LDS, EW float4 each: the entry, the terms
 // of the m estimate (make_entry_est) and, with EW = 6, the colour.
 constexpr int kCompEst = 4, kCompCol = 5;  // float4 offsets within an LDS entry
@@ -542,7 +552,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
     for (int tt = wave; tt < nt; tt += NW) {
         int row, col;
         const int loc = tile_local(vr, item.tile0 + tt, lane, row, col);
-        const bool valid = loc >= 0;
+        const bool valid = loc >= 0 && (NW > 1 || item.cut == 0 || comp_part(lane, item.cut) == item.part);
+        if (NW == 1 && !wave_any(valid)) continue;  // a part past the edge
         float v0, v1, v2;
         tile_ray_dir(P, vr, e, kk, valid ? loc : 0, valid ? row : 0, valid ? col : 0, v0, v1, v2);
         float at = 0.0f, dt = 0.0f;  // loss targets, loaded ahead of the epilogue

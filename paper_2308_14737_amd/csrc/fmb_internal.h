@@ -58,6 +58,7 @@ struct FwdItem {       // 8 bytes
 struct CompItem {      // compositing forward: a run of ray tiles of one view
     int32_t view;
     int32_t tile0, span;
+    int32_t part, cut;  // cut > 0 (one tile of a larger scene): the block of (8 >> cut)^2 lanes it takes
 };
 
 struct BwdItem {       // 36 bytes
