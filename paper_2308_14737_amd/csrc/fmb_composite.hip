@@ -12,14 +12,14 @@
 // Layout: one ray per lane, one 8 x 8 pixel tile (ViewRec's ray tiles) per wave; an item is a run of
 // consecutive tiles of one view.  A scene of at most kCompTG Gaussians is staged in LDS once per item
 // and block for four waves, which take the item's tiles in turn (one wave per block staged it for itself
-// and left a 20-view 128 x 128 job at 320 waves: 980 -> 181 us for its step).  Of a larger scene each
+// and left a 20-view 128 x 128 job at 320 waves: 960 -> 196 us for its step).  Of a larger scene each
 // wave first bounds every Gaussian on its tile and stages those that can matter there (about 10 of 1000 on
 // a clustered 480 x 270 view, 9.4 -> 0.9 ms); only a tile with more than kCompTG of them takes the
 // scene in staged tiles.
 //
 // Front sums without a sort: F_i only needs the densities in front of t_i, and of those only the
-// significant ones (density above 2^sig: the rest total below 2^-27 in the forward,
-// comp_front_log2, and 2^-36 in the adjoint, comp_sig_log2, below FP32's rounding of T_i).  A lane keeps its ray's significant intersections, with their depths, in
+// significant ones (density above 2^sig, comp_sig_log2: the rest total below 2^-36, below FP32's
+// rounding of T_i).  A lane keeps its ray's significant intersections, with their depths, in
 // registers and forms F_i as a sum of exact 0/1 steps over them: per pair the cost is the count of
 // significant intersections around the tile (about ten on the benchmark scenes), not N.  Slots are
 // filled in Gaussian order at positions uniform over the wave -- a lane for which the slot's
@@ -50,17 +50,11 @@
 
 namespace fmb {
 
-// Significant intersections a lane holds per depth window: in the backward and the split statistic,
-// and in the forward, whose cutoff is higher (on the 16 benchmark scenes 2 % of the tiles have more than
-// 32 above it, 3.6 % above the backward's; larger scenes' tiles are denser, and one of 100 takes
-// a third of a millisecond in windows of 32).
-constexpr int kCompSlots = 48;
-__host__ __device__ constexpr int fwdc_slots(int nw) { return nw > 1 ? 32 : 48; }
+constexpr int kCompSlots = 48;  // significant intersections a lane holds per depth window
 constexpr int kCompTG = 128;    // Gaussians staged per LDS tile
 // Waves per SIMD the kernels are compiled for: the slots take 2 (forward) or 3 VGPRs each.  The
 // forward of small scenes is held to three waves (168 VGPRs, some values spilled to scratch, within
-// what the runtime keeps allocated); the others, with 48 slots so that their dense tiles take one window
-// instead of several, keep two and do not spill: spills above 267 bytes a lane make the runtime
+// what the runtime keeps allocated); the others keep two and do not spill: spills above 267 bytes a lane make the runtime
 // allocate scratch for every launch, which cost 0.5 ms.
 constexpr int kBwdcWaves = 2, kStatcWaves = 2;
 __host__ __device__ constexpr int fwdc_waves(int nw) { return nw > 1 ? 3 : 2; }
@@ -97,11 +91,6 @@ __device__ __forceinline__ float comp_sig_log2(int n)
     return fminf(-30.0f, -36.0f - (float)lg);
 }
 
-// The forward's cutoff of the log2 density: densities below 2^this (n of them) total less than 2^-27, of
-// a front sum, or, added to the log2 of a ray's density sum (at most 0), of its sum of weights, which
-// is at least 0.63 of that sum.
-__device__ __forceinline__ float comp_front_log2(int n) { return -27.0f - ceil_log2(n); }
-
 // A ray whose largest base-2 log weight is at least this takes only its significant pairs: the
 // others weigh less than n 2^sig <= 2^-36 together, below 2^-24 of its sum of weights.
 constexpr float kCompHitLog2 = -12.0f;
@@ -116,20 +105,25 @@ __device__ __forceinline__ float comp_skip_log2(int n)
     return fminf(-40.0f, -26.0f - (float)lg);
 }
 
-// A lane's NS slots (32 or 48): scaled depth and density of the significant intersection of the
-// slot's Gaussian (density 0 where that Gaussian is not significant for the lane, or not in its
-// window).  They are register vectors (slots 0..31 in the first, 32..47 in the second), read at
+// The same cutoff relative to a lower bound of a ray's largest log2 density (or 0 above it): a ray of
+// density sum D has a sum of weights of at least 1 - exp(-D) >= 0.63 min(1, D), so its largest weight
+// is at least 2^-0.67 / n of min(1, D).  Pairs below this on every ray of a tile are pairs that each ray's
+// own test against its running maximum would leave out, or whose terms a later, larger weight would
+// scale below the sums' rounding.
+__device__ __forceinline__ float comp_blend_log2(int n) { return comp_skip_log2(n) - 1.0f - ceil_log2(n); }
+
+// A lane's slots: scaled depth and density of the significant intersection of the slot's
+// Gaussian (density 0 where that Gaussian is not significant for the lane, or not in its window).
+// They are register vectors (slots 0..31 in the first, 32..47 in the second), read at
 // compile-time positions and written at the wave-uniform fill position by one indirect register
 // move; slot k holds the window's k-th Gaussian in staging order, and the slots from ns on hold
 // zeros.
 typedef float CompV32 __attribute__((ext_vector_type(32)));
 typedef float CompV16 __attribute__((ext_vector_type(16)));
-template <int NS>
+static_assert(kCompSlots == 48, "the slot vectors hold 32 + 16 slots");
 struct CompList {
-    static_assert(NS == 32 || NS == 48, "the slot vectors hold 32 + 16 slots");
-    static constexpr int N = NS;
     CompV32 t0, d0;
-    CompV16 t1, d1;  // (unused with 32 slots)
+    CompV16 t1, d1;
 };
 // a value per slot (the backward's z_bar of the slots' pairs)
 struct CompZ {
@@ -137,25 +131,21 @@ struct CompZ {
     CompV16 z1;
 };
 
-template <int NS>
-__device__ __forceinline__ float slot_t(const CompList<NS> &L, int k) { return NS == 32 || k < 32 ? L.t0[k] : L.t1[k - 32]; }
-template <int NS>
-__device__ __forceinline__ float slot_d(const CompList<NS> &L, int k) { return NS == 32 || k < 32 ? L.d0[k] : L.d1[k - 32]; }
+__device__ __forceinline__ float slot_t(const CompList &L, int k) { return k < 32 ? L.t0[k] : L.t1[k - 32]; }
+__device__ __forceinline__ float slot_d(const CompList &L, int k) { return k < 32 ? L.d0[k] : L.d1[k - 32]; }
 __device__ __forceinline__ float slot_z(const CompZ &z, int k) { return k < 32 ? z.z0[k] : z.z1[k - 32]; }
 
-template <int NS>
-__device__ __forceinline__ void slot_set_d(CompList<NS> &L, int k, float d)
+__device__ __forceinline__ void slot_set_d(CompList &L, int k, float d)
 {
-    if (NS == 32 || k < 32)
+    if (k < 32)
         L.d0[k] = d;
     else
         L.d1[k - 32] = d;
 }
 
-template <int NS>
-__device__ __forceinline__ void slot_set(CompList<NS> &L, int k, float t, float d)
+__device__ __forceinline__ void slot_set(CompList &L, int k, float t, float d)
 {
-    if (NS == 32 || k < 32) {
+    if (k < 32) {
         L.t0[k] = t;
         L.d0[k] = d;
     } else {
@@ -178,15 +168,12 @@ struct CompWin {
     float lo, hi, base, tie;
 };
 
-template <int NS>
-__device__ __forceinline__ void comp_clear(CompList<NS> &L)
+__device__ __forceinline__ void comp_clear(CompList &L)
 {
     L.t0 = (CompV32)(0.0f);
     L.d0 = (CompV32)(0.0f);
-    if (NS > 32) {
-        L.t1 = (CompV16)(0.0f);
-        L.d1 = (CompV16)(0.0f);
-    }
+    L.t1 = (CompV16)(0.0f);
+    L.d1 = (CompV16)(0.0f);
 }
 
 // Step sums over the slots in use, four slots at a time (template recursion, so that every slot
@@ -194,54 +181,52 @@ __device__ __forceinline__ void comp_clear(CompList<NS> &L)
 // and the unused slots of a group add zeros.  The even and the odd slots go to two sums (two
 // independent chains).
 constexpr int kSlotGroup = 4;
-template <int K, int NS>
+template <int K>
 struct SlotSums {
     // sum of the densities of the slots in front of ts
-    __device__ static __forceinline__ void front(const CompList<NS> &L, int ns, float ts, float &f, float &g)
+    __device__ static __forceinline__ void front(const CompList &L, int ns, float ts, float &f, float &g)
     {
-        if constexpr (K < NS) {
+        if constexpr (K < kCompSlots) {
             if (K >= ns) return;
 #pragma unroll
             for (int k = K; k < K + kSlotGroup; k += 2) {
                 f = fmaf(before(slot_t(L, k), ts), slot_d(L, k), f);
                 g = fmaf(before(slot_t(L, k + 1), ts), slot_d(L, k + 1), g);
             }
-            SlotSums<K + kSlotGroup, NS>::front(L, ns, ts, f, g);
+            SlotSums<K + kSlotGroup>::front(L, ns, ts, f, g);
         }
     }
     // sum of z over the slots behind ts
-    __device__ static __forceinline__ void behind(const CompList<NS> &L, const CompZ &z, int ns, float ts, float &b,
+    __device__ static __forceinline__ void behind(const CompList &L, const CompZ &z, int ns, float ts, float &b,
                                                   float &c)
     {
-        if constexpr (K < NS) {
+        if constexpr (K < kCompSlots) {
             if (K >= ns) return;
 #pragma unroll
             for (int k = K; k < K + kSlotGroup; k += 2) {
                 b = fmaf(before(ts, slot_t(L, k)), slot_z(z, k), b);
                 c = fmaf(before(ts, slot_t(L, k + 1)), slot_z(z, k + 1), c);
             }
-            SlotSums<K + kSlotGroup, NS>::behind(L, z, ns, ts, b, c);
+            SlotSums<K + kSlotGroup>::behind(L, z, ns, ts, b, c);
         }
     }
 };
-static_assert(32 % kSlotGroup == 0 && 48 % kSlotGroup == 0 && kSlotGroup % 2 == 0, "whole slot groups, of pairs");
+static_assert(kCompSlots % kSlotGroup == 0 && kSlotGroup % 2 == 0, "whole slot groups, of pairs");
 
 // F at scaled depth ts inside window w: base, the densities at lo (if ts > lo), and the slots
 // in front of ts.
-template <int NS>
-__device__ __forceinline__ float comp_front(const CompList<NS> &L, int ns, const CompWin &w, float ts)
+__device__ __forceinline__ float comp_front(const CompList &L, int ns, const CompWin &w, float ts)
 {
     float f = ts > w.lo ? w.base + w.tie : w.base, g = 0.0f;
-    SlotSums<0, NS>::front(L, ns, ts, f, g);
+    SlotSums<0>::front(L, ns, ts, f, g);
     return f + g;
 }
 
 // Sum of z over the slots behind ts.
-template <int NS>
-__device__ __forceinline__ float comp_behind(const CompList<NS> &L, const CompZ &z, int ns, float ts)
+__device__ __forceinline__ float comp_behind(const CompList &L, const CompZ &z, int ns, float ts)
 {
     float b = 0.0f, c = 0.0f;
-    SlotSums<0, NS>::behind(L, z, ns, ts, b, c);
+    SlotSums<0>::behind(L, z, ns, ts, b, c);
     return b + c;
 }
 
@@ -253,16 +238,14 @@ __device__ __forceinline__ float comp_behind(const CompList<NS> &L, const CompZ 
 // kernel's 118 KB of code (same speed on the benchmark scenes).
 __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, float invS, float tfb, float kap);
 
-template <int NS>
-__device__ __forceinline__ float slot_z_plain(const CompList<NS> &L, int ns, const CompWin &w, float M2, float invS,
+__device__ __forceinline__ float slot_z_plain(const CompList &L, int ns, const CompWin &w, float M2, float invS,
                                               float tfb, float kap, float dl, float ts)
 {
     if (!(dl > 0.0f)) return 0.0f;
     return slot_zf(comp_front(L, ns, w, ts), dl, ts, M2, invS, tfb, kap);
 }
 
-template <int NS>
-__device__ __forceinline__ void slots_z_plain(const CompList<NS> &L, CompZ &zs, int ns, const CompWin &w, float M2,
+__device__ __forceinline__ void slots_z_plain(const CompList &L, CompZ &zs, int ns, const CompWin &w, float M2,
                                               float invS, float tfb, float kap)
 {
     // (one loop per register vector, so that each writes a single vector in place)
@@ -290,8 +273,8 @@ __device__ __forceinline__ float slot_zf(float f, float dl, float ts, float M2, 
 // densities are needed only for the front sums, and a second front sum per pair is saved (the
 // kernel is bound by instruction issue: with a colour cotangent 141 -> 123 us for 20 views of
 // 128 x 128 and 64 Gaussians).
-template <int NS, class KapOf>
-__device__ __forceinline__ void slots_fz_plain(CompList<NS> &L, CompZ &zs, int ns, const CompWin &w, float M2,
+template <class KapOf>
+__device__ __forceinline__ void slots_fz_plain(CompList &L, CompZ &zs, int ns, const CompWin &w, float M2,
                                                float invS, float tfb, KapOf kap_of)
 {
 #pragma unroll 1
@@ -375,14 +358,14 @@ __device__ __forceinline__ void comp_masks(const CompBounds &cb, int cnt, int la
 
 // A scene of more than kCompTG Gaussians: those whose log2 density can reach the cutoff on a ray of the
 // tile, staged in scene order with their scene-local indices in gid.  The cutoff is `thr`, or with REL
-// (the forward) rel + min(0, the largest lower bound of the tile's log2 densities), bounded by the
-// Gaussians seen so far (a superset of the final cutoff's, which is returned in `low`).  The bounds are
+// (the forward) that or less, `rel` + min(0, the largest lower bound of the tile's log2 densities), bounded
+// by the Gaussians seen so far (a superset of the final cutoff's, whose bound is returned in `low`).  The bounds are
 // taken on FP32 entries (make_bound_entry); only the survivors' are formed in FP64.  Returns their
 // count, which may exceed kCompTG: then the first kCompTG are staged, and the tile takes the scene in
 // staged tiles.  One wave.
 template <int EW, bool REL>
 __device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &sr, const double o[3], float4 *__restrict__ ents,
-                                              int *__restrict__ gid, const TileBox &tb, float thr, int lane, float &low)
+                                              int *__restrict__ gid, const TileBox &tb, float thr, float rel, int lane, float &low)
 {
     int ne = 0;
     low = -INFINITY;
@@ -396,7 +379,7 @@ __device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &s
         make_bound_entry(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, g, est);
         const PairBounds pb = tile_bounds(g, est, tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
         if (REL) low = fmaxf(low, wave_max_u(in ? pb.d2_lo : -INFINITY));
-        const bool keep = in && !(pb.d2_hi < (REL ? fminf(low, 0.0f) + thr : thr));
+        const bool keep = in && !(pb.d2_hi < (REL ? fminf(thr, fminf(low, 0.0f) + rel) : thr));
         const unsigned long long bal = wave_ballot(keep);
         const int at = ne + __popcll(bal & ((1ull << lane) - 1ull));
         if (keep && at < kCompTG) gid[at] = gl;
@@ -413,10 +396,10 @@ __device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &s
 // go to w.tie (and each such pair, whose front sum is w.base, to on_tie(g, q, density, staged index)); a
 // lane that meets one more than the slots hold lowers w.hi to its depth.  gb: the scene-local index of
 // the first staged Gaussian; slot_g receives gb + the slots' staged indices.
-template <int EW, int NS, class OnTie>
+template <int EW, class OnTie>
 __device__ __forceinline__ void comp_collect_tile(const float4 *__restrict__ ents, int gb, const unsigned long long mask[2],
                                                   float v0, float v1, float v2, float hm, float sig2, int lane, CompWin &w,
-                                                  CompList<NS> &L, int &ns, bool &t_inf, int *__restrict__ slot_g, OnTie on_tie)
+                                                  CompList &L, int &ns, bool &t_inf, int *__restrict__ slot_g, OnTie on_tie)
 {
     // the pair's share of the window: tie, slot or (a full list) the end of the window
     auto take = [&](const Ent &g, const Geo &q, int i) {
@@ -432,7 +415,7 @@ __device__ __forceinline__ void comp_collect_tile(const float4 *__restrict__ ent
         }
         const bool cand = sig && ts > w.lo;
         if (!wave_any(cand)) return;
-        if (ns < NS) {
+        if (ns < kCompSlots) {
             slot_set(L, ns, ts, cand ? dl : 0.0f);
             t_inf = t_inf || (cand && ts == INFINITY);
             if (lane == 0) slot_g[ns] = gb + i;
@@ -464,11 +447,11 @@ __device__ __forceinline__ void comp_collect_tile(const float4 *__restrict__ ent
 // All slots of window w, from the staged Gaussians of `mask` (resident) or the scene's staged tiles;
 // slots at or behind w.hi are cleared (they belong to a later window).  Returns the slot count
 // (uniform).
-template <int EW, int NS, class OnTie>
+template <int EW, class OnTie>
 __device__ __forceinline__ int comp_collect(const Params &P, const SceneRec &sr, const double o[3],
                                             float4 *__restrict__ ents, bool resident, const unsigned long long rmask[2],
                                             float v0, float v1, float v2, float hm, float sig2, const TileBox &tb, int lane,
-                                            CompWin &w, CompList<NS> &L, int *__restrict__ slot_g, OnTie on_tie)
+                                            CompWin &w, CompList &L, int *__restrict__ slot_g, OnTie on_tie)
 {
     int ns = 0;
     bool t_inf = false;  // a slot of this lane holds an infinite scaled depth
@@ -485,14 +468,13 @@ __device__ __forceinline__ int comp_collect(const Params &P, const SceneRec &sr,
     // (where no lane's window was cut, only a slot at an infinite scaled depth can be at or behind hi)
     if (wave_any(w.hi != INFINITY || t_inf)) {
 #pragma unroll
-        for (int k = 0; k < NS; ++k) slot_set_d(L, k, slot_t(L, k) >= w.hi ? 0.0f : slot_d(L, k));
+        for (int k = 0; k < kCompSlots; ++k) slot_set_d(L, k, slot_t(L, k) >= w.hi ? 0.0f : slot_d(L, k));
     }
     return ns;
 }
 
 // Moves window w past hi (or marks the lane done); returns true while the lane has depths left.
-template <int NS>
-__device__ __forceinline__ bool comp_next(CompWin &w, const CompList<NS> &L, int ns)
+__device__ __forceinline__ bool comp_next(CompWin &w, const CompList &L, int ns)
 {
     if (w.hi == INFINITY) {
         w.lo = INFINITY;
@@ -500,7 +482,7 @@ __device__ __forceinline__ bool comp_next(CompWin &w, const CompList<NS> &L, int
     }
     float s = w.tie;
 #pragma unroll
-    for (int k = 0; k < NS; ++k) s += slot_d(L, k);
+    for (int k = 0; k < kCompSlots; ++k) s += slot_d(L, k);
     w.base += s;
     w.lo = w.hi;
     w.hi = INFINITY;
@@ -512,17 +494,6 @@ __device__ __forceinline__ bool comp_next(CompWin &w, const CompList<NS> &L, int
 // Forward
 // ------------------------------------------------------------------------------------
 
-// 1 - exp(-delta), relatively exact: the series below 1/4 (its next term is 5e-8 of it).
-__device__ __forceinline__ float opacity(float delta)
-{
-    float p = fmaf(delta, -1.0f / 720.0f, 1.0f / 120.0f);
-    p = fmaf(delta, p, -1.0f / 24.0f);
-    p = fmaf(delta, p, 1.0f / 6.0f);
-    p = fmaf(delta, p, -0.5f);
-    p = fmaf(delta, p, 1.0f);
-    return delta < 0.25f ? delta * p : 1.0f - exp2_(-(float)kLog2e * delta);
-}
-
 // NW waves per block: 4 for scenes of at most kCompTG Gaussians (staged once per item for all four, each
 // wave taking every fourth tile of it), 1 for larger ones (each wave stages its own tile's survivors).
 template <int F, int NW>
@@ -532,7 +503,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
     constexpr bool NORMALS = (F & kNrm) != 0, COLOR = (F & kCol) != 0;
     constexpr int EW = COLOR ? 6 : 5;
     __shared__ float4 ents[kCompTG * EW];
-    __shared__ int slot_gs[NW][fwdc_slots(NW)];
+    __shared__ int slot_gs[NW][kCompSlots];
     __shared__ int gid[NW == 1 ? kCompTG : 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int *const slot_g = slot_gs[wave];
@@ -545,7 +516,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
     cam_centre(e, o);
     const float o0 = (float)o[0], o1 = (float)o[1], o2 = (float)o[2];
     const float hm = (float)(-0.5 * kLog2e);
-    const float front2 = comp_front_log2(sr.n);
+    const float sig2 = comp_sig_log2(sr.n), skip2 = comp_skip_log2(sr.n), blend2 = comp_blend_log2(sr.n);
     if (NW > 1) comp_stage<EW, 64 * NW>(P, sr, 0, sr.n, o, ents);
     const int nt = min(item.span, vr.tiles - item.tile0);
 
@@ -565,26 +536,40 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
         // the tile's Gaussians: the whole scene, or its survivors, staged (ne of them)
         int ne = sr.n;
         float low = -INFINITY;
-        if (NW == 1) ne = comp_survivors<EW, true>(P, sr, o, ents, gid, tc, front2, lane, low);
+        if (NW == 1) ne = comp_survivors<EW, true>(P, sr, o, ents, gid, tc, sig2, blend2, lane, low);
         const bool resident = NW > 1 || ne <= kCompTG;
-        // Cutoffs of the log2 density: a tile whose every ray has a density sum of at least 2^low blends
-        // the pairs that can reach rel (the others total below 2^-26 of the ray's sum of weights); of
-        // the rest only those above front2 matter to a front sum.  On a tile with low above
-        // kCompHitLog2 every pair blended has a slot.
+        // the staged Gaussians that can be significant on the tile, and those that can reach the blend
         CompBounds cb{{0.0f, 0.0f}, low};
         if (resident) cb = comp_bounds<EW>(ents, ne, tc, lane);
-        const float rel = fminf(cb.low, 0.0f) + front2;
-        const bool hit = resident && cb.low >= kCompHitLog2;
-        const float sig2 = hit ? rel : front2;
+        const float rel = fminf(cb.low, 0.0f) + blend2;
         unsigned long long smask[2] = {0, 0};
         if (resident) comp_masks(cb, ne, lane, sig2, smask);
         float M, S, T, N0, N1, N2, C0, C1, C2, D;
-        auto reset = [&](float m) {
-            M = m;
+        auto reset = [&]() {
+            M = -INFINITY;
             S = T = N0 = N1 = N2 = C0 = C1 = C2 = D = 0.0f;
         };
-        // adds weight ew of pair (g, q); ci: the staged index of its colour
-        auto add = [&](const Ent &g, Geo &q, float ew, int ci) {
+        reset();
+        CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
+        CompList L;
+        // blends pair (g, q) of this lane at front sum fs; ci: the staged index of its colour
+        auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
+            const float delta = exp2_(q.d2);
+            D += delta;
+            const float lw = fmaf(-(float)kLog2e, fs, log2_opacity(delta, q.d2));
+            if (lw > M) {  // new running maximum: rescale the sums
+                const float sc = exp2_(M - lw);
+                S *= sc;
+                T *= sc;
+                N0 *= sc;
+                N1 *= sc;
+                N2 *= sc;
+                C0 *= sc;
+                C1 *= sc;
+                C2 *= sc;
+                M = lw;
+            }
+            const float ew = exp2_(lw - M);
             S += ew;
             T = fmaf(ew, q.t, T);
             if (NORMALS) {
@@ -601,33 +586,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
                 C2 = fmaf(ew, cc.z, C2);
             }
         };
-        // scales the sums, e.g. to a new largest weight
-        auto rescale = [&](float sc) {
-            S *= sc;
-            T *= sc;
-            N0 *= sc;
-            N1 *= sc;
-            N2 *= sc;
-            C0 *= sc;
-            C1 *= sc;
-            C2 *= sc;
-        };
-        CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
-        CompList<fwdc_slots(NW)> L;
         const auto no_tie = [](const Ent &, const Geo &, float, int) {};
         int ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
 
-        if (hit && !wave_any(w.hi != INFINITY)) {
-            // One window of a tile that every ray meets: the slots' pairs, with their weights themselves
-            // (the largest is far above FP32's smallest, so no logarithm is needed until the end).
-            reset(0.0f);
-            auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
-                const float delta = exp2_(q.d2);
-                D += delta;
-                const float ew = exp2_(-(float)kLog2e * fs) * opacity(delta);
-                M = fmaxf(M, ew);
-                add(g, q, ew, ci);
-            };
+        // A tile of one window whose rays all weigh at least 2^kCompHitLog2 somewhere blends only the
+        // significant pairs (the slots' Gaussians), each ray its own.  The weights are kept as logarithms and
+        // added in scene order in every tile, whatever the cut of the work: the sign of an L1 loss
+        // follows the last bit of a depth or colour.
+        bool done = false;
+        // (a ray whose densities are all below that cannot qualify: a weight is at most its density)
+        float most = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kCompSlots; ++k) most = fmaxf(most, slot_d(L, k));
+        if (resident && ns > 0 && !wave_any(w.hi != INFINITY) && wave_all(!valid || most > 0x1.fp-13f)) {
             for (int s = 0; s < ns; s += 2) {  // two slots a step (two independent chains)
                 const bool two = s + 1 < ns;
                 const int ia = slot_g[s], ib = two ? slot_g[s + 1] : ia;
@@ -638,58 +609,45 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(fwdc_wa
                 if (valid && qa.d2 > sig2) blend(ga, qa, comp_front(L, ns, w, qa.t * kDepthScale), ia);
                 if (two && valid && qb.d2 > sig2) blend(gb, qb, comp_front(L, ns, w, qb.t * kDepthScale), ib);
             }
-            rescale(1.0f / M);
-            M = __builtin_amdgcn_logf(M);
-        } else {
-            // A tile that sees background, or of several windows: every pair that can reach rel, with
-            // logarithms of the weights.
-            reset(-INFINITY);
-            auto blend = [&](const Ent &g, Geo &q, float fs, int ci) {
-                const float delta = exp2_(q.d2);
-                D += delta;
-                const float lw = fmaf(-(float)kLog2e, fs, log2_opacity(delta, q.d2));
-                if (lw > M) {  // new running maximum: rescale the sums
-                    rescale(exp2_(M - lw));
-                    M = lw;
+            done = wave_all(!valid || M >= kCompHitLog2);
+            if (!done) reset();
+        }
+        // Otherwise every pair of every window (a tile that sees background or several windows).
+        while (!done) {
+            for (int gb = 0; gb < (resident ? 1 : sr.n); gb += kCompTG) {
+                const int cnt = resident ? ne : min(kCompTG, sr.n - gb);
+                if (!resident) {
+                    comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
+                    cb = comp_bounds<EW>(ents, cnt, tc, lane);
                 }
-                add(g, q, exp2_(lw - M), ci);
-            };
-            for (;;) {
-                for (int gb = 0; gb < (resident ? 1 : sr.n); gb += kCompTG) {
-                    const int cnt = resident ? ne : min(kCompTG, sr.n - gb);
-                    if (!resident) {
-                        comp_stage<EW, 64>(P, sr, gb, cnt, o, ents);
-                        cb = comp_bounds<EW>(ents, cnt, tc, lane);
-                    }
-                    unsigned long long mask[2];
-                    comp_masks(cb, cnt, lane, rel, mask);
+                unsigned long long mask[2];
+                comp_masks(cb, cnt, lane, rel, mask);
 #pragma unroll 1
-                    for (int c = 0; c < 2; ++c) {
-                        unsigned long long mk = mask[c];
-                        while (mk) {  // two Gaussians a step (two independent chains)
-                            const int ia = 64 * c + __builtin_ctzll(mk);
-                            mk &= mk - 1;
-                            const bool two = mk != 0;
-                            const int ib = two ? 64 * c + __builtin_ctzll(mk) : ia;
-                            if (two) mk &= mk - 1;
-                            const Ent ga = comp_ent<EW>(ents, ia), gb2 = comp_ent<EW>(ents, ib);
-                            Geo qa, qb;
-                            pair_geo_coarse(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
-                            pair_geo_coarse(gb2, v0, v1, v2, hm, 0.0f, 0.0f, qb);
-                            // a pair of this window whose weight (at most its density) is not below
-                            // 2^front2 of the running maximum
-                            const float tsa = qa.t * kDepthScale, tsb = qb.t * kDepthScale;
-                            const bool la = tsa >= w.lo && tsa < w.hi && qa.d2 - M >= front2;
-                            if (wave_any(la) && la) blend(ga, qa, comp_front(L, ns, w, tsa), ia);
-                            const bool lb = two && tsb >= w.lo && tsb < w.hi && qb.d2 - M >= front2;
-                            if (wave_any(lb) && lb) blend(gb2, qb, comp_front(L, ns, w, tsb), ib);
-                        }
+                for (int c = 0; c < 2; ++c) {
+                    unsigned long long mk = mask[c];
+                    while (mk) {  // two Gaussians a step (two independent chains)
+                        const int ia = 64 * c + __builtin_ctzll(mk);
+                        mk &= mk - 1;
+                        const bool two = mk != 0;
+                        const int ib = two ? 64 * c + __builtin_ctzll(mk) : ia;
+                        if (two) mk &= mk - 1;
+                        const Ent ga = comp_ent<EW>(ents, ia), gb2 = comp_ent<EW>(ents, ib);
+                        Geo qa, qb;
+                        pair_geo_coarse(ga, v0, v1, v2, hm, 0.0f, 0.0f, qa);
+                        pair_geo_coarse(gb2, v0, v1, v2, hm, 0.0f, 0.0f, qb);
+                        // a pair of this window whose weight (at most its density) is not below
+                        // 2^skip2 of the running maximum
+                        const float tsa = qa.t * kDepthScale, tsb = qb.t * kDepthScale;
+                        const bool la = tsa >= w.lo && tsa < w.hi && qa.d2 - M >= skip2;
+                        if (wave_any(la) && la) blend(ga, qa, comp_front(L, ns, w, tsa), ia);
+                        const bool lb = two && tsb >= w.lo && tsb < w.hi && qb.d2 - M >= skip2;
+                        if (wave_any(lb) && lb) blend(gb2, qb, comp_front(L, ns, w, tsb), ib);
                     }
                 }
-                const bool more = comp_next(w, L, ns);
-                if (!wave_any(more)) break;
-                ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
             }
+            const bool more = comp_next(w, L, ns);
+            if (!wave_any(more)) break;
+            ns = comp_collect<EW>(P, sr, o, ents, resident, smask, v0, v1, v2, hm, sig2, tc, lane, w, L, slot_g, no_tie);
         }
         if (valid)
             write_ray<F>(P, O, item.view, vr.ray_off + loc, e, kk, o0, o1, o2, v0, v1, v2, M, S, T, N0, N1, N2, C0,
@@ -768,13 +726,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kBwdcWa
         const float lim = fminf(skip2, wskip), lim_min = wave_min_u(valid ? lim : INFINITY);
         const CompWin w0{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
         CompWin w = w0;
-        CompList<kCompSlots> L;
+        CompList L;
         CompZ zs;
         const TileBox tc = wave_box(v0, v1, v2, valid, e);
         // the tile's Gaussians: the whole scene, or its survivors, staged (ne of them)
         int ne = n;
         float low;
-        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), lane, low);
+        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), 0.0f, lane, low);
         const bool resident = NW > 1 || ne <= kCompTG;
         const bool mapped = NW == 1 && resident;  // the staged Gaussians' records are flushed per tile
         unsigned long long smask[2] = {0, 0}, fmask[2] = {0, 0};
@@ -1114,11 +1072,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kStatcW
         const float wskip = valid ? M2 - __builtin_amdgcn_logf(invS) + skip2 : INFINITY;
         const float lim_min = wave_min_u(wskip);
         CompWin w{valid ? -INFINITY : INFINITY, INFINITY, 0.0f, 0.0f};
-        CompList<kCompSlots> L;
+        CompList L;
         const TileBox tc = wave_box(v0, v1, v2, valid, e);
         int ne = n;
         float low;
-        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), lane, low);
+        if (NW == 1) ne = comp_survivors<EW, false>(P, sr, o, ents, gid, tc, fminf(sig2, lim_min), 0.0f, lane, low);
         const bool resident = NW > 1 || ne <= kCompTG;
         const bool mapped = NW == 1 && resident;
         unsigned long long smask[2] = {0, 0}, fmask[2] = {0, 0};
