@@ -507,6 +507,14 @@ struct Job {
         return FMB_OK;
     }
 
+    // Drops every plan and choice made from the cameras (or explicit rays): new ones were set.
+    void invalidate_plans()
+    {
+        fwd_built = bwd_built = stat_built = na_plan.key = -1;
+        comp_fwd_built = false;
+        normals_form[0] = normals_form[1] = -1;
+    }
+
     // Items of scene s whose view rays (or ray tiles) are cut in spans of `span`, for one Gaussian chunk.
     int64_t scene_items(int s, int span, bool tiled) const
     {
@@ -1147,9 +1155,7 @@ int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr
     j.prm.w2c_c = j.prm.intr_c = nullptr;
     j.prm.dirs = nullptr;
     j.has_flow = w2c_b != nullptr;
-    j.fwd_built = j.bwd_built = j.stat_built = -1;
-    j.comp_fwd_built = false;
-    j.normals_form[0] = j.normals_form[1] = -1;
+    j.invalidate_plans();
     j.cams_set = false;
     if ((rc = j.upload_descriptors())) return rc;
     j.cams_set = true;
@@ -1191,9 +1197,7 @@ int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, c
     j.prm.w2c_c = j.prm.intr_c = nullptr;
     j.prm.dirs = dirs;
     j.has_flow = w2c_b != nullptr;
-    j.fwd_built = j.bwd_built = j.stat_built = -1;
-    j.comp_fwd_built = false;
-    j.normals_form[0] = j.normals_form[1] = -1;
+    j.invalidate_plans();
     j.cams_set = false;
     int rc = j.upload_descriptors();
     if (rc) return rc;

@@ -1,0 +1,63 @@
+"""The host library's work plans, workspaces and uploads on a recording runtime, without a GPU: each check
+runs in a process of its own (tests/host_runtime.py)."""
+from __future__ import annotations
+
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+if __name__ == "__main__":
+    sys.path.insert(0, os.path.dirname(HERE))
+
+from tests.host_runtime import Runtime, Scene  # noqa: E402
+
+
+def _tiles(h, w):
+    return ((w + 7) // 8) * ((h + 7) // 8) if w >= 8 else (h * w + 63) // 64
+
+
+def _covered(items, tiles, lane_tiles=True):
+    """Per view, the ray tiles that the items of one backward launch take; fails on a view or tile past the end."""
+    got = [0] * len(tiles)
+    for view, ray0, span, *_ in items:
+        assert 0 <= view < len(tiles) and 0 <= ray0 < tiles[view], (view, ray0, tiles)
+        got[view] += min(span, tiles[view] - ray0)
+    return got
+
+
+def noalloc_plan_follows_the_cameras():
+    """fmb_backward_noalloc after other cameras or rays: fewer views, more views, explicit rays."""
+    rt = Runtime()
+    for composite in (False, True):
+        sc = Scene(rt, 40)
+        sc.set_model(composite)
+        steps = [("cams", [(64, 64)] * 3), ("cams", [(32, 24)]), ("cams", [(40, 64)] * 5), ("rays", [100, 0, 70]), ("cams", [(9, 5)])]
+        for kind, arg in steps:
+            if kind == "cams":
+                sc.set_cameras(arg)
+                tiles = [_tiles(h, w) for h, w in arg]
+            else:
+                sc.set_rays(arg)
+                tiles = [(c + 63) // 64 for c in arg]
+            sc.check(sc.render())
+            rt.launches()
+            sc.check(sc.backward(noalloc=True))
+            items = [i for name, _, i in rt.launches() if "bwd" in name][0]
+            assert _covered(items, tiles) == tiles, (composite, kind, arg)
+
+
+CHECKS = [noalloc_plan_follows_the_cameras]
+
+
+@pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
+def test_host(check):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), check], capture_output=True, text=True, timeout=300,
+                       cwd=os.path.dirname(HERE))
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[1]]()

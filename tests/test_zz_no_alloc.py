@@ -64,3 +64,29 @@ def test_noalloc_backward_equals_backward(fmb):
         scene.backward(outs, torch.zeros(p, device=DEV), torch.zeros(p, device=DEV), noalloc=True)
     assert ei.value.code == 2 and "FMB_NOALLOC_SCRATCH_BYTES" in str(ei.value), str(ei.value)
     _say(f"[noalloc] large1080 refused: {ei.value}")
+
+
+def test_noalloc_after_other_cameras(fmb):
+    """One scene, its cameras and rays changed between the calls (fewer views, more views, explicit rays)."""
+    betas = np.array([W.BETA1, W.BETA2], np.float32)
+    sc, cams = custom_scene(37, [(24, 40)] * 3, seed=5)
+    scene, _ = make_scene(fmb, torch, sc, cams, betas, 1.0, DEV)
+    g = np.random.Generator(np.random.PCG64(6))
+    for views, counts in (([(24, 40)] * 3, None), ([(16, 9)], None), ([(40, 33)] * 5, None), ([(24, 40)] * 3, [70, 0, 130])):
+        _, c = custom_scene(37, views, seed=5)
+        ct = fmb.Cameras.from_numpy(c.w2c, c.intr, c.hw, device=DEV)
+        if counts is None:
+            scene.set_cameras(ct)
+            p = c.n_rays
+        else:
+            p = int(sum(counts))
+            d = g.standard_normal((p, 3)) * 0.3 + np.array([0.0, 0.0, 1.0])
+            scene.set_rays(ct, np.array(counts, np.int32), _t(d.astype(np.float32)))
+        _say(f"[noalloc] other cameras: views={views} counts={counts}")
+        outs = scene.render()
+        args = (outs, _t(g.standard_normal(p).astype(np.float32) / p), _t(g.standard_normal(p).astype(np.float32) / p))
+        ref = scene.backward(*args)
+        got = scene.backward(*args, noalloc=True)
+        torch.cuda.synchronize()
+        for k in ("means", "prec", "weights", "betas"):
+            assert torch.equal(got[k], ref[k]), (views, counts, k)
