@@ -720,9 +720,12 @@ struct Job {
         }
         // first-stage reduction groups: runs of kGroupItems items inside each chunk
         std::vector<FinGroup> groups;
-        // (a task that holds its whole scene, of few items whose records are all written, needs none)
+        // (a task that holds its whole scene, of few items whose records are all written, needs none, up to the
+        // number of Gaussians that one launch's slices hold)
+        const int per = fin_one_gauss(rec);
         auto one_stage = [&](const FinTask &t) {
-            return !large(t.scene) && t.gc == scenes[t.scene].n && t.item_end - t.item_begin <= kOneStageItems;
+            return !large(t.scene) && t.gc == scenes[t.scene].n && t.item_end - t.item_begin <= kOneStageItems &&
+                   (t.gc + per - 1) / per <= kGridYMax;
         };
         size_t soff = 0;
         int scene_first_group = 0, cur_scene = -1;

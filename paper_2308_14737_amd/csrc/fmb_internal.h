@@ -100,6 +100,10 @@ struct FinGroup {
 // A chunk of at most this many items that holds its whole scene is reduced in one stage.
 constexpr int kOneStageItems = 4096;
 constexpr int kGroupItems = 32;  // minimum items per first-stage group
+// Gaussians per slice (a block of grid y) of the one-stage reduction: their values leave two of 32 lanes for
+// the betas.
+constexpr int fin_one_gauss(int rec) { return 30 / rec; }
+constexpr int kGridYMax = 65535;  // the largest grid y of a launch
 
 // Split statistic (one value per Gaussian and item): the items of a (scene, Gaussian chunk)
 // are consecutive, [item_begin, item_end), and their partial sums are added in that order.

@@ -984,9 +984,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
 //            reduces the scene's betas.
 // ------------------------------------------------------------------------------------
 
-// Gaussians per block of the one-stage reduction: their values leave two of 32 lanes for the betas.
-__host__ __device__ constexpr int fin_one_gauss(int rec) { return 30 / rec; }
-
 // Sum n strided values src[0], src[stride], ... in index order (FP64), issuing the loads
 // eight at a time so that they are in flight together; the association is fixed.
 template <typename T>
@@ -1654,16 +1651,16 @@ hipError_t launch_fin(int n_tasks, int n_one, int one_gc, int n_groups, int max_
     if (max_gc < 1 || max_nval < 1) return hipErrorInvalidValue;
     if (n_one > 0) {
         const int per = fin_one_gauss(rec);
-        if ((one_gc + per - 1) / per > 65535) return hipErrorInvalidValue;
+        if ((one_gc + per - 1) / per > kGridYMax) return hipErrorInvalidValue;
         hipLaunchKernelGGL(fin_one_kernel, dim3(n_one, (one_gc + per - 1) / per), dim3(1024), 0, st, P, tasks, partial, bpart,
                            g_means, g_prec, g_weights, g_colors, g_betas);
     }
     if (n_tasks > n_one) {
-        const int slices = (max_nval + 255) / 256 < 65535 ? (max_nval + 255) / 256 : 65535;
+        const int slices = (max_nval + 255) / 256 < kGridYMax ? (max_nval + 255) / 256 : kGridYMax;
         const int gslices = (max_gc + kFinSlice - 1) / kFinSlice;
-        if (gslices > 65535) return hipErrorInvalidValue;
+        if (gslices > kGridYMax) return hipErrorInvalidValue;
         if (masks)
-            hipLaunchKernelGGL((fin1s_kernel<256>), dim3(n_groups, (max_gc + 255) / 256 < 65535 ? (max_gc + 255) / 256 : 65535),
+            hipLaunchKernelGGL((fin1s_kernel<256>), dim3(n_groups, (max_gc + 255) / 256 < kGridYMax ? (max_gc + 255) / 256 : kGridYMax),
                                dim3(256), 0, st, groups, partial, bpart, masks, rec, stage, stage_beta);
         else
             hipLaunchKernelGGL((fin1_kernel<256>), dim3(n_groups, slices), dim3(256), 0, st, groups, partial, bpart, stage,

@@ -89,3 +89,7 @@ class Scene:
 
     def split(self):
         return self.rt.lib.fmb_split_statistic(self.h, None, PTR, PTR, PTR, self.stream)
+
+    def autotune(self):
+        return self.rt.lib.fmb_autotune(self.h, None, PTR, PTR, None, None, None, PTR, PTR, PTR, None, None, None,
+                                        PTR, PTR, PTR, None, PTR, None, self.stream)

@@ -49,7 +49,29 @@ def noalloc_plan_follows_the_cameras():
             assert _covered(items, tiles) == tiles, (composite, kind, arg)
 
 
-CHECKS = [noalloc_plan_follows_the_cameras]
+def reduction_of_many_gaussians():
+    """A chunk of a whole scene of few items is reduced in one stage up to 65535 slices of 3 Gaussians (2 with
+    colour), and in two above: none of them is refused, nor is an autotuner that meets one."""
+    rt = Runtime()
+    for n, colour, one in ((196605, False, True), (196606, False, False), (131070, True, True), (131071, True, False)):
+        for variant in (None, 3):  # the compositing model; the ray-lane variant of the blend
+            sc = Scene(rt, n)
+            sc.set_model(variant is None)
+            sc.set_cameras([(16, 16)])
+            sc.set_colors(colour)
+            if variant is not None:
+                sc.set_variants(0, variant)
+            rt.launches()
+            sc.check(sc.backward(color=colour))
+            names = [name for name, _, _ in rt.launches()]
+            assert any("fin_one" in k for k in names) == one and any("fin2" in k for k in names) != one, (n, colour, names)
+            sc.check(rt.lib.fmb_scene_destroy(sc.h))
+    sc = Scene(rt, 200000)
+    sc.set_cameras([(16, 16)])
+    sc.check(sc.autotune())
+
+
+CHECKS = [noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
