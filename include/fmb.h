@@ -119,6 +119,8 @@ int fmb_scene_destroy(fmb_scene *scene);
  * (H, W >= 1).  w2c_b / intr_b: device [v,3,4] / [v,4] second pose per view for the
  * flow output, or both NULL (no flow).  Borrowed like the scene parameters.  Sizes the
  * workspace (P = sum H W rays, at most FMB_MAX_RAYS).
+ * The library's own lists are replaced only once the scene's earlier passes are done: this call, and the
+ * first pass with other cotangents, model or variants, wait for the device if some may still run.
  * Errors: FMB_ERR_INVALID_ARG (NULL, v < 1, H or W < 1, only one of w2c_b/intr_b),
  * FMB_ERR_SHAPE (P > FMB_MAX_RAYS or v > FMB_MAX_VIEWS), FMB_ERR_OOM / FMB_ERR_HIP. */
 int fmb_set_cameras(fmb_scene *scene, int32_t v, const float *w2c, const float *intr,

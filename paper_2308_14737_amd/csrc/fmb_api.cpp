@@ -277,6 +277,26 @@ struct Job {
     }
     ~Job() { drop_graphs(); }
 
+    // The lists that launched kernels may still read (passes return before they finish).  They are
+    // replaced by copies on the null stream, which does not wait for a stream created non-blocking: settle
+    // waits for the device before one is overwritten.  A pass recorded into a caller's graph may be
+    // replayed at any time, so after one every replacement waits.
+    enum Uses : unsigned { kUseDescriptors = 1, kUseFwd = 2, kUseCompFwd = 4, kUseBwd = 8, kUseStat = 16 };
+    unsigned in_flight = 0;
+    bool recorded = false;
+    void launched(unsigned uses, hipStream_t st)
+    {
+        in_flight |= uses | kUseDescriptors;
+        recorded = recorded || stream_capturing(st);
+    }
+    int settle(unsigned uses)
+    {
+        if (!recorded && !(in_flight & uses)) return FMB_OK;
+        HIPCHK(hipDeviceSynchronize());
+        in_flight = 0;
+        return FMB_OK;
+    }
+
     int max_scene_n() const
     {
         int m = 0;
@@ -294,6 +314,8 @@ struct Job {
 
     int upload_descriptors()
     {
+        int rc = settle(kUseDescriptors);
+        if (rc) return rc;
         HIPCHK(d_scenes.upload(scenes));
         HIPCHK(d_views.upload(views));
         HIPCHK(d_eta.upload(eta));
@@ -318,6 +340,8 @@ struct Job {
     int build_fwd(int variant)
     {
         if (fwd_built == variant) return FMB_OK;
+        int rc = settle(kUseFwd);
+        if (rc) return rc;
         drop_graphs();  // the forward graph's items (and possibly their buffer) change
         const int R = fwd_variant_rays(variant);  // rays of an item: R / 64 tiles
         std::vector<FwdItem> items;
@@ -362,6 +386,8 @@ struct Job {
     int build_comp_fwd()
     {
         if (comp_fwd_built) return FMB_OK;
+        int rc = settle(kUseCompFwd);
+        if (rc) return rc;
         drop_graphs();
         std::vector<CompItem> items[2];
         std::vector<double> cost[2];
@@ -478,10 +504,11 @@ struct Job {
     {
         const int key = bwd_key(variant, colour);
         if (bwd_built == key) return FMB_OK;
-        drop_graphs();  // items, partial records and the finalize plan change (and may move)
         BwdPlan pl;
-        int rc = plan_bwd(variant, colour, pl);
+        int rc = settle(kUseBwd);
         if (rc) return rc;
+        drop_graphs();  // items, partial records and the finalize plan change (and may move)
+        if ((rc = plan_bwd(variant, colour, pl))) return rc;
         HIPCHK(d_bitems.upload(pl.items));
         HIPCHK(d_border.upload(pl.order));
         HIPCHK(d_tasks.upload(pl.tasks));
@@ -799,6 +826,8 @@ struct Job {
     int build_stat()
     {
         if (stat_built == model) return FMB_OK;
+        int rc = settle(kUseStat);
+        if (rc) return rc;
         const bool comp = model == FMB_MODEL_COMPOSITE;
         std::vector<BwdItem> items;
         std::vector<StatTask> tasks;
@@ -863,6 +892,7 @@ struct Job {
         CHECK_ARG(aligned(stash, 16), "stash must be 16-byte aligned");
         int rc = build_stat();
         if (rc) return rc;
+        launched(kUseStat, st);
         if (model == FMB_MODEL_COMPOSITE) {
             HIPCHK(launch_statc(n_sitems_small, n_sitems - n_sitems_small, st, prm, loss, stash, d_sitems.as<BwdItem>(),
                                 d_sorder.as<int>(), d_spartial.as<float>()));
@@ -912,6 +942,7 @@ struct Job {
         if (model == FMB_MODEL_COMPOSITE) {
             int rc = build_comp_fwd();
             if (rc) return rc;
+            launched(kUseCompFwd, st);
             TimedSpan ts(st, 0);
             HIPCHK(launch_fwdc(fwd_flags(O), n_cfitems[0], n_cfitems[1], st, prm, O, d_cfitems.as<CompItem>()));
             ts.stop();
@@ -919,6 +950,7 @@ struct Job {
         }
         int rc = build_fwd(fwd_variant);
         if (rc) return rc;
+        launched(kUseFwd, st);
         TimedSpan ts(st, 0);
         HIPCHK(launch_fwd(fwd_variant, blend_fwd_flags(O), n_fitems, st, prm, O, d_fitems.as<FwdItem>(),
                           ordered ? d_forder.as<int>() : nullptr));
@@ -937,6 +969,7 @@ struct Job {
         const int bv = bwd_run_variant(I);
         int rc = build_bwd(bv, I.g_color != nullptr);
         if (rc) return rc;
+        launched(kUseBwd, st);
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
             HIPCHK(launch_bwdc(bwd_flags(I), n_bitems_small, n_bitems - n_bitems_small, st, prm, I,
@@ -1006,6 +1039,7 @@ struct Job {
         void *base = nullptr;
         HIPCHK(scratch_base(&base));
         char *b = static_cast<char *>(base);
+        launched(0, st);
         HIPCHK(hipMemcpyAsync(b + o_items, pl.items.data(), pl.items.size() * sizeof(BwdItem), hipMemcpyHostToDevice, st));
         if (model == FMB_MODEL_COMPOSITE)
             HIPCHK(hipMemcpyAsync(b + o_order, pl.order.data(), pl.order.size() * sizeof(int), hipMemcpyHostToDevice, st));
@@ -1455,6 +1489,7 @@ int fmb_batch_graph_launch(fmb_batch *b, int32_t which, void *stream)
     Job &j = b->job;
     if (!j.gexec[0] || !j.gexec[1]) return fail(FMB_ERR_STATE, "no captured graph");
     hipStream_t st = (hipStream_t)stream;
+    j.launched(Job::kUseFwd | Job::kUseCompFwd | Job::kUseBwd, st);
     if (which != 1) {
         TimedSpan t(st, 0);
         HIPCHK(hipGraphLaunch(j.gexec[0], st));

@@ -71,7 +71,43 @@ def reduction_of_many_gaussians():
     sc.check(sc.autotune())
 
 
-CHECKS = [noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def lists_are_not_overwritten_under_a_kernel():
+    """On a stream of the caller's: a list that an earlier pass may still read is replaced only after a wait;
+    new rays cost one wait a step, and a repeated step none."""
+    rt = Runtime()
+    for composite in (False, True):
+        sc = Scene(rt, 300, stream=0x770)
+        sc.set_model(composite)
+        sc.set_colors()
+
+        def step(**kw):
+            sc.check(sc.render(normal=True, color=True))
+            sc.check(sc.backward(**kw))
+
+        sc.set_rays([200, 90])
+        step()
+        for kw in ({"normal": True}, {"color": True}, {"normal": True, "color": True}, {}):
+            step(**kw)  # other cotangents: another plan
+            sc.check(sc.split())
+        for counts in ([100, 190], [290, 0], [1, 2], [500, 900]):
+            before = rt.count("syncs")
+            sc.set_rays(counts)
+            step()
+            sc.check(sc.split())
+            assert rt.count("syncs") - before <= 1, (composite, counts)
+        before = rt.count("syncs")
+        step()
+        assert rt.count("syncs") == before
+        sc.set_cameras([(64, 64)])
+        step()
+        sc.set_variants(3, 2)
+        step()
+        sc.check(sc.backward(noalloc=True))
+        sc.set_cameras([(24, 24)])
+        assert rt.count("overwrites") == 0, (composite, rt.count("overwrites"))
+
+
+CHECKS = [lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
