@@ -136,7 +136,12 @@ struct DevBuf {
         if (n <= bytes && p) return hipSuccess;
         release();
         hipError_t e = hipMalloc(&p, n > 0 ? n : 16);
-        if (e == hipSuccess) bytes = n > 0 ? n : 16;
+        if (e == hipSuccess) {
+            bytes = n > 0 ? n : 16;
+        } else {
+            p = nullptr;
+            (void)hipGetLastError();  // (the launches check it: this failure is not theirs)
+        }
         return e;
     }
     template <class T>
@@ -342,6 +347,7 @@ struct Job {
         if (fwd_built == variant) return FMB_OK;
         int rc = settle(kUseFwd);
         if (rc) return rc;
+        fwd_built = -1;  // (until all of it is: a list may be replaced and the next fail)
         drop_graphs();  // the forward graph's items (and possibly their buffer) change
         const int R = fwd_variant_rays(variant);  // rays of an item: R / 64 tiles
         std::vector<FwdItem> items;
@@ -507,6 +513,7 @@ struct Job {
         BwdPlan pl;
         int rc = settle(kUseBwd);
         if (rc) return rc;
+        bwd_built = -1;
         drop_graphs();  // items, partial records and the finalize plan change (and may move)
         if ((rc = plan_bwd(variant, colour, pl))) return rc;
         HIPCHK(d_bitems.upload(pl.items));
@@ -828,6 +835,7 @@ struct Job {
         if (stat_built == model) return FMB_OK;
         int rc = settle(kUseStat);
         if (rc) return rc;
+        stat_built = -1;
         const bool comp = model == FMB_MODEL_COMPOSITE;
         std::vector<BwdItem> items;
         std::vector<StatTask> tasks;

@@ -141,7 +141,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3, void **args, size_t, hip
 hipError_t hipMalloc(void **p, size_t n)
 {
     if (capturing) return ++counts[3], hipErrorStreamCaptureUnsupported;
-    if (n > limit || in_use > limit - n) return hipErrorOutOfMemory;
+    if (n > limit || in_use > limit - n) return last_error = hipErrorOutOfMemory;
     ++counts[0];
     *p = calloc(n, 1);
     allocs[(uintptr_t)*p] = {n, nullptr, false};

@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 if __name__ == "__main__":
     sys.path.insert(0, os.path.dirname(HERE))
 
-from tests.host_runtime import Runtime, Scene  # noqa: E402
+from tests.host_runtime import OOM, Runtime, Scene  # noqa: E402
 
 
 def _tiles(h, w):
@@ -107,7 +107,30 @@ def lists_are_not_overwritten_under_a_kernel():
         assert rt.count("overwrites") == 0, (composite, rt.count("overwrites"))
 
 
-CHECKS = [lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def failed_build_is_not_taken_for_built():
+    """A backward that runs out of memory leaves no half-replaced lists behind: the earlier configuration
+    is built again, with its own items, once there is room."""
+    rt = Runtime()
+    sc = Scene(rt, 700)
+    sc.set_cameras([(200, 200)])
+    sc.set_variants(1, 8)
+    tiles = [_tiles(200, 200)]
+    sc.check(sc.render())
+    sc.check(sc.backward())
+    rt.rr.rr_set_limit(rt.rr.rr_in_use() + (1 << 10))
+    sc.set_variants(1, 0)  # Gaussian lanes: more records than the room left
+    assert sc.backward() == OOM
+    rt.rr.rr_set_limit(-1)
+    sc.set_variants(1, 8)
+    rt.launches()
+    sc.check(sc.render())
+    sc.check(sc.backward())
+    items = [i for name, _, i in rt.launches() if "bwdt" in name][0]
+    whole = [i for i in items if i[3] == 0]  # the first part of each record
+    assert _covered(whole, tiles) == tiles and all(i[4] == 700 for i in items)
+
+
+CHECKS = [failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
