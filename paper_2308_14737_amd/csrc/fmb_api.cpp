@@ -506,16 +506,28 @@ struct Job {
     };
     BwdPlan na_plan;  // the plan of the last fmb_backward_noalloc call (host memory only)
 
+    // Where the records of the finer cuts do not fit the memory that is left, those of 16 tiles are tried.
     int build_bwd(int variant, bool colour)
     {
         const int key = bwd_key(variant, colour);
         if (bwd_built == key) return FMB_OK;
-        BwdPlan pl;
         int rc = settle(kUseBwd);
         if (rc) return rc;
         bwd_built = -1;
         drop_graphs();  // items, partial records and the finalize plan change (and may move)
-        if ((rc = plan_bwd(variant, colour, pl))) return rc;
+        for (bool coarse : {false, true}) {
+            if ((rc = build_bwd_cut(variant, colour, coarse)) != FMB_ERR_OOM) break;
+            for (DevBuf *b : {&d_partial, &d_bpart, &d_masks, &d_stage, &d_stage_beta}) b->release();
+        }
+        if (rc == FMB_OK) bwd_built = key;
+        return rc;
+    }
+
+    int build_bwd_cut(int variant, bool colour, bool coarse)
+    {
+        BwdPlan pl;
+        int rc = plan_bwd(variant, colour, pl, coarse);
+        if (rc) return rc;
         HIPCHK(d_bitems.upload(pl.items));
         HIPCHK(d_border.upload(pl.order));
         HIPCHK(d_tasks.upload(pl.tasks));
@@ -537,7 +549,6 @@ struct Job {
         n_bitems_small = pl.n_small;
         bwd_big_tiles = pl.big_tiles;
         n_tasks = (int)pl.tasks.size();
-        bwd_built = key;
         return FMB_OK;
     }
 
@@ -650,7 +661,8 @@ struct Job {
         return all <= (8LL << 30) - (1 << 20);  // offsets of the records are 32-bit floats
     }
 
-    int plan_bwd(int variant, bool colour, BwdPlan &pl)
+    // coarse: records of 16 tiles for every scene beyond the small ones (the least workspace)
+    int plan_bwd(int variant, bool colour, BwdPlan &pl, bool coarse = false)
     {
         const int key = bwd_key(variant, colour);
         const bool comp = model == FMB_MODEL_COMPOSITE;
@@ -668,13 +680,13 @@ struct Job {
         int big_tiles = 0;
         for (int s = 0; s < S; ++s) {
             LargeCut cut{tiles, 1};
-            if (large(s) && !normals) cut = large_cut(s, rec);
+            if (large(s) && !normals && !coarse) cut = large_cut(s, rec);
             spans[s] = cut.span;
             parts[s] = cut.parts;
-            if (tiles > 0) floats += scene_items(s, comp ? comp_bwd_span(s, rec, true) : spans[s], true) * scenes[s].n * rec;
+            if (tiles > 0) floats += scene_items(s, comp ? comp_bwd_span(s, rec, !coarse) : spans[s], true) * scenes[s].n * rec;
         }
         // (a batch whose records would not fit with the scenes' own cuts takes larger items for all large ones)
-        const bool own_cuts = floats <= INT32_MAX;
+        const bool own_cuts = floats <= INT32_MAX && !coarse;
         if (!own_cuts && !normals)
             for (int s = 0; s < S; ++s)
                 if (large(s)) spans[s] = 16;
@@ -923,6 +935,17 @@ struct Job {
         return normals_tiled(I.g_color != nullptr) ? bwd_normal_variant() : 2;
     }
 
+    // Builds the backward of a call and says which variant it runs; where the tiled records of a normal
+    // cotangent do not fit the memory that is left, variant 2.
+    int build_bwd_run(const BwdIn &I, int &bv)
+    {
+        const bool colour = I.g_color != nullptr;
+        int rc = build_bwd(bv = bwd_run_variant(I), colour);
+        if (rc != FMB_ERR_OOM || bv != bwd_normal_variant()) return rc;
+        normals_form[colour] = 0;
+        return build_bwd(bv = bwd_run_variant(I), colour);
+    }
+
     static int fwd_flags(const FwdOut &O)
     {
         return (O.normal ? kFlagNrm : 0) | (O.flow ? kFlagFlw : 0) |
@@ -974,8 +997,8 @@ struct Job {
         CHECK_ARG(G.means && G.prec && G.weights && G.betas, "gradient outputs are required");
         CHECK_ARG(!I.g_flow || has_flow, "flow cotangent given but the cameras have no second pose");
         CHECK_ARG(!I.g_color || (prm.colors && I.color), "colour cotangent needs colours and the colour output");
-        const int bv = bwd_run_variant(I);
-        int rc = build_bwd(bv, I.g_color != nullptr);
+        int bv;
+        int rc = build_bwd_run(I, bv);
         if (rc) return rc;
         launched(kUseBwd, st);
         if (model == FMB_MODEL_COMPOSITE) {
@@ -1460,7 +1483,8 @@ int fmb_batch_capture(fmb_batch *b, float *depth, float *alpha, float *normal, f
     const BwdIn I{g_depth, g_alpha, g_normal, g_flow, g_color, depth, color, stash};
     const Grads G{g_means, g_prec, g_weights, g_colors, g_betas};
     // item lists are prepared outside the capture (they use synchronous copies)
-    int rc = j.build_bwd(j.bwd_run_variant(I), g_color != nullptr);
+    int bv;
+    int rc = j.build_bwd_run(I, bv);
     if (!rc && j.model == FMB_MODEL_COMPOSITE) rc = j.build_comp_fwd();
     if (!rc && j.model == FMB_MODEL_BLEND) rc = j.build_fwd(j.fwd_variant);
     if (rc) return rc;

@@ -130,7 +130,38 @@ def failed_build_is_not_taken_for_built():
     assert _covered(whole, tiles) == tiles and all(i[4] == 700 for i in items)
 
 
-CHECKS = [failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def coarser_cuts_where_memory_is_short():
+    """Records of the finer cuts that do not fit give way to 16-tile ones (the tiled form of a normal cotangent
+    to the Gaussian-lane variant), which fit; the whole view is still taken once."""
+    rt = Runtime()
+    for n, hw, composite, normal in ((20000, (400, 400), False, False), (5000, (480, 640), True, False), (10000, (1080, 1920), False, True)):
+        def passes(limit):
+            rt.rr.rr_set_limit(-1)
+            sc = Scene(rt, n)
+            sc.set_model(composite)
+            sc.set_cameras([hw])
+            sc.check(sc.render())
+            base = rt.rr.rr_in_use()
+            if limit is not None:
+                rt.rr.rr_set_limit(base + limit)
+            rt.launches()
+            rc = sc.backward(normal=normal)
+            items = [i for name, _, i in rt.launches() if "bwd" in name]
+            need = rt.rr.rr_in_use() - base
+            rt.lib.fmb_scene_destroy(sc.h)
+            return rc, need, items[0] if items else None
+
+        rc, fine, _ = passes(None)
+        assert rc == 0
+        rc, coarse, items = passes(fine - 1)
+        assert rc == 0 and coarse < fine, (n, rc, fine, coarse)
+        if not normal:
+            assert _covered([i for i in items if i[3] == 0], [_tiles(*hw)]) == [_tiles(*hw)] and (items[:, 2] == 16).all()
+        rc, _, _ = passes(coarse // 2)
+        assert rc == OOM, (n, rc)
+
+
+CHECKS = [coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
