@@ -890,11 +890,14 @@ struct Job {
                 tasks.push_back(t);
             }
         }
-        std::vector<int> order(items.size());  // small scenes' items first
-        std::iota(order.begin(), order.end(), 0);
-        auto small = [&](int i) { return items[i].gc <= comp_resident_max(); };
-        n_sitems_small = (int)(std::stable_partition(order.begin(), order.end(), small) - order.begin());
-        HIPCHK(d_sorder.upload(order));
+        n_sitems_small = (int)items.size();
+        if (comp) {  // (the blend kernel has one form and takes the items as they are)
+            std::vector<int> order(items.size());  // small scenes' items first
+            std::iota(order.begin(), order.end(), 0);
+            auto small = [&](int i) { return items[i].gc <= comp_resident_max(); };
+            n_sitems_small = (int)(std::stable_partition(order.begin(), order.end(), small) - order.begin());
+            HIPCHK(d_sorder.upload(order));
+        }
         HIPCHK(d_sitems.upload(items));
         HIPCHK(d_stasks.upload(tasks));
         HIPCHK(d_srays.upload(rays));

@@ -161,7 +161,21 @@ def coarser_cuts_where_memory_is_short():
         assert rc == OOM, (n, rc)
 
 
-CHECKS = [coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def split_statistic_uploads_what_its_kernel_reads():
+    """First split statistic on new cameras: items, tasks, ray counts and (compositing, whose kernel has two
+    forms) the items' order."""
+    rt = Runtime()
+    for composite, copies in ((False, 3), (True, 4)):
+        sc = Scene(rt, 40)
+        sc.set_model(composite)
+        sc.set_cameras([(64, 64)] * 4)
+        sc.check(sc.render())
+        before = rt.count("copies")
+        sc.check(sc.split())
+        assert rt.count("copies") - before == copies, (composite, rt.count("copies") - before)
+
+
+CHECKS = [split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
