@@ -1588,7 +1588,7 @@ int bwd_variant_tiles(int v) { return v >= kBwdTiledFirst && v <= num_bwd_varian
 // Gaussian-lane variants: rays staged per pass; others: 0.
 int bwd_variant_rt(int v) { return v < kNumBwdGauss ? kBwdRT[v] : 0; }
 // Ray-lane variants 3-5: rays per block tile (BLOCK * RPT); others: 0.
-int bwd_variant_ray_tile(int v) { return v >= kNumBwdGauss ? kBlock * kBwdRay[v - kNumBwdGauss].rpt : 0; }
+int bwd_variant_ray_tile(int v) { return v >= kNumBwdGauss && v < kBwdTiledFirst ? kBlock * kBwdRay[v - kNumBwdGauss].rpt : 0; }
 int block_size() { return kBlock; }
 
 // flags: bit 0 normals, 1 flow, 2 colour, 3 a scene beyond a block's count of Gaussians

@@ -175,7 +175,15 @@ def split_statistic_uploads_what_its_kernel_reads():
         assert rt.count("copies") - before == copies, (composite, rt.count("copies") - before)
 
 
-CHECKS = [split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def variant_tables():
+    """Each backward variant has one of the three sizes, the others are 0 (no table is read past its end)."""
+    rt = Runtime()
+    for v in range(10):  # 9: the tiled form of a normal cotangent
+        of = [getattr(rt.lib, "_ZN3fmb%d%sEi" % (len(f), f))(v) for f in ("bwd_variant_rt", "bwd_variant_ray_tile", "bwd_variant_tiles")]
+        assert [x > 0 for x in of] == [v < 3, 3 <= v < 6, v >= 6], (v, of)
+
+
+CHECKS = [variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
