@@ -448,7 +448,7 @@ struct Job {
             while (span > 1 && count(span / 2) * scenes[s].n * rec * (int64_t)sizeof(float) <= (8 << 20)) span /= 2;
             const int64_t unit = scenes[s].n * rec * (int64_t)sizeof(float);
             // (at most kOneStageItems items a scene: one reduction stage)
-            auto bytes = [&](int sp) { return count(sp) * (unit + (int64_t)(sizeof(BwdItem) + 3 * sizeof(float))); };
+            auto bytes = [&](int sp) { return count(sp) * (unit + (int64_t)(sizeof(BwdItem) + 2 * sizeof(float))); };
             const int64_t noalloc = FMB_NOALLOC_SCRATCH_BYTES - (64 << 10);
             const int64_t most = bytes(span) <= (int64_t)FMB_NOALLOC_SCRATCH_BYTES ? noalloc : 256 << 20;
             while (more && span > 1 && count(span - 1) <= kOneStageItems && bytes(span - 1) <= most) --span;
@@ -751,7 +751,6 @@ struct Job {
                                 it.g0 = part;
                                 it.slots = parts[s];
                             }
-                            it.seq = (int)items.size();
                             items.push_back(it);
                             cost.push_back((double)t.gc / parts[s] * (tiles > 0 ? std::min<int64_t>(64LL * span, hw - 64LL * r0)
                                                                              : std::min(span, hw - r0)));
@@ -881,7 +880,6 @@ struct Job {
                         if (poff > (size_t)INT32_MAX - (size_t)gc)
                             return fail(FMB_ERR_SHAPE, "split statistic partials exceed 2^31 floats");
                         it.poff = (int)poff;
-                        it.seq = (int)items.size();
                         poff += (size_t)gc;
                         items.push_back(it);
                     }
@@ -1053,7 +1051,6 @@ struct Job {
             return at;
         };
         const size_t o_items = take(pl.items.size() * sizeof(BwdItem));
-        const size_t o_order = model == FMB_MODEL_COMPOSITE ? take(pl.order.size() * sizeof(int)) : 0;
         const size_t o_tasks = take(pl.tasks.size() * sizeof(FinTask));
         const size_t o_groups = take(pl.groups.size() * sizeof(FinGroup));
         const size_t o_masks = pl.mask_words ? take(pl.mask_words * sizeof(unsigned long long)) : 0;
@@ -1075,8 +1072,6 @@ struct Job {
         char *b = static_cast<char *>(base);
         launched(0, st);
         HIPCHK(hipMemcpyAsync(b + o_items, pl.items.data(), pl.items.size() * sizeof(BwdItem), hipMemcpyHostToDevice, st));
-        if (model == FMB_MODEL_COMPOSITE)
-            HIPCHK(hipMemcpyAsync(b + o_order, pl.order.data(), pl.order.size() * sizeof(int), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(b + o_tasks, pl.tasks.data(), pl.tasks.size() * sizeof(FinTask), hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(b + o_groups, pl.groups.data(), pl.groups.size() * sizeof(FinGroup),
                               hipMemcpyHostToDevice, st));
@@ -1085,14 +1080,13 @@ struct Job {
         float *bpart = reinterpret_cast<float *>(b + o_bpart);
         unsigned long long *masks = pl.mask_words ? reinterpret_cast<unsigned long long *>(b + o_masks) : nullptr;
         const int n_items = (int)pl.items.size();
+        // (one scene: its items are all of one form, in any order)
         if (model == FMB_MODEL_COMPOSITE) {
             TimedSpan tb(st, 1);
-            HIPCHK(launch_bwdc(bwd_flags(I), pl.n_small, n_items - pl.n_small, st, prm, I, items,
-                               reinterpret_cast<const int *>(b + o_order), part, bpart));
+            HIPCHK(launch_bwdc(bwd_flags(I), pl.n_small, n_items - pl.n_small, st, prm, I, items, nullptr, part, bpart));
             tb.stop();
         } else {
             TimedSpan tb(st, 1);
-            // (one scene: its items are all of one form, in any order)
             HIPCHK(launch_bwd(bv, bwd_flags(I), pl.n_small, n_items - pl.n_small, pl.big_tiles, st, prm, I, items,
                               nullptr, part, bpart, masks));
             tb.stop();

@@ -686,7 +686,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kBwdcWa
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int *const slot_g = slot_gs[wave];
     float *const rec = recs[wave];
-    const BwdItem item = ld_uniform(items + ld_uniform(order + blockIdx.x));
+    const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
+    const BwdItem item = ld_uniform(items + it);
     const ViewRec vr = ld_uniform(P.views + item.view);
     const SceneRec sr = ld_uniform(P.scenes + vr.scene);
     const CamRec cam = cam_of(P, item.view);
@@ -1014,7 +1015,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kBwdcWa
                 write_partial(prec_out + REC * q, sum, REC, P.means + 3 * gg, o);
         }
     }
-    if (threadIdx.x < 2) beta_partial[2 * item.seq + threadIdx.x] = 0.0f;  // the model has no blend parameters
+    if (threadIdx.x < 2) beta_partial[2 * it + threadIdx.x] = 0.0f;  // the model has no blend parameters
 }
 
 // ------------------------------------------------------------------------------------
@@ -1181,7 +1182,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(kStatcW
 #define FMB_BWDC_SMALL(F_)                                                                                \
     hipLaunchKernelGGL((bwdc_kernel<F_, 4>), dim3(n_small), dim3(256), 0, st, P, I, items, order, partial, beta_partial)
 #define FMB_BWDC_BIG(F_)                                                                                  \
-    hipLaunchKernelGGL((bwdc_kernel<F_, 1>), dim3(n_big), dim3(64), dyn, st, P, I, items, order + n_small, partial, beta_partial)
+    hipLaunchKernelGGL((bwdc_kernel<F_, 1>), dim3(n_big), dim3(64), dyn, st, P, I, items, order ? order + n_small : nullptr, partial, beta_partial)
 
 int comp_resident_max() { return kCompTG; }
 
@@ -1195,11 +1196,12 @@ hipError_t launch_fwdc(int flags, int n_small, int n_big, hipStream_t st, const 
     return hipGetLastError();
 }
 
-// order: the items' indices, the n_small of small scenes first.
+// order: the items' indices, the n_small of small scenes first (or NULL where they are all of one kind).
 hipError_t launch_bwdc(int flags, int n_small, int n_big, hipStream_t st, const Params &P, const BwdIn &I,
                        const BwdItem *items, const int *order, float *partial, float *beta_partial)
 {
     const size_t dyn = (size_t)kCompSlots * 6 * sizeof(float4);
+    if (!order && n_small > 0 && n_big > 0) return hipErrorInvalidValue;
     if (n_small > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_SMALL)
     if (n_big > 0) FMB_COMP_DISPATCH(flags, FMB_BWDC_BIG)
     return hipGetLastError();

@@ -61,7 +61,7 @@ struct CompItem {      // compositing forward: a run of ray tiles of one view
     int32_t part, cut;  // cut > 0 (one tile of a larger scene): the block of (8 >> cut)^2 lanes it takes
 };
 
-struct BwdItem {       // 36 bytes
+struct BwdItem {       // 32 bytes; its index in the list is the index of its beta partials
     int32_t view;
     int32_t ray0;      // first local ray of the span
     int32_t span;      // rays in the span (clipped to the view by the kernel)
@@ -71,7 +71,6 @@ struct BwdItem {       // 36 bytes
                        // (tiled kernels with a large scene: the item is part g0 of slots of its record, every
                        // slots-th 64 Gaussians)
     int32_t poff;      // offset (floats) of this item's partial record [gc][kPartial]
-    int32_t seq;       // canonical item index (beta partials)
     int32_t moff;      // tiled kernels with a large scene: first 64-bit word of the item's mask of records
 };
 

@@ -471,8 +471,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(bwd_min_w
             s2 += __shfl_xor(s2, off, 64);
         }
         if (tid == 0) {
-            beta_partial[2 * item.seq] = s1;
-            beta_partial[2 * item.seq + 1] = s2;
+            beta_partial[2 * it] = s1;
+            beta_partial[2 * it + 1] = s2;
         }
     }
 }
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(BLOCK) void bwdr_kernel(Params P, BwdIn I, const Bw
     if (tid < 2) {
         float sb = 0.0f;
         for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
-        beta_partial[2 * item.seq + tid] = sb;
+        beta_partial[2 * it + tid] = sb;
     }
 }
 
@@ -970,7 +970,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
     if (tid < 2) {
         float sb = 0.0f;
         for (int w = 0; w < NW; ++w) sb += bsum[2 * w + tid];
-        beta_partial[2 * item.seq + tid] = sb;
+        beta_partial[2 * it + tid] = sb;
     }
 }
 

@@ -82,13 +82,13 @@ int rr_launches() { return (int)launches.size(); }
 void rr_clear() { launches.clear(); }
 const char *rr_name(int i) { return launches[i].name.c_str(); }
 void rr_grid(int i, unsigned *out) { memcpy(out, launches[i].grid, sizeof launches[i].grid); }
-// the items of launch i's blocks: (view, ray0, span, g0, gc, slots, poff, seq) each
+// the items of launch i's blocks: (view, ray0, span, g0, gc, slots, poff, moff) each
 int rr_items(int i, int *out, int cap)
 {
     int n = 0;
     for (const auto &it : launches[i].items) {
         if (n >= cap) break;
-        const int v[8] = {it.view, it.ray0, it.span, it.g0, it.gc, it.slots, it.poff, it.seq};
+        const int v[8] = {it.view, it.ray0, it.span, it.g0, it.gc, it.slots, it.poff, it.moff};
         memcpy(out + 8 * n++, v, sizeof v);
     }
     return (int)launches[i].items.size();

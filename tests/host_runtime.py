@@ -34,7 +34,7 @@ class Runtime:
         return self.rr.rr_count(COUNTS.index(what))
 
     def launches(self):
-        """[(kernel, grid, items or None)] since the last call; an item is (view, ray0, span, g0, gc, slots, poff, seq)."""
+        """[(kernel, grid, items or None)] since the last call; an item is (view, ray0, span, g0, gc, slots, poff, moff)."""
         res = []
         for i in range(self.rr.rr_launches()):
             grid = (ctypes.c_uint * 3)()

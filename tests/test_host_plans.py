@@ -183,7 +183,33 @@ def variant_tables():
         assert [x > 0 for x in of] == [v < 3, 3 <= v < 6, v >= 6], (v, of)
 
 
-CHECKS = [variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+# (composite, variant or None, colour, normal cotangent, views of H x W, Gaussians): the largest views of their
+# width whose backward fitted the fixed workspace when the items were 32 bytes and one stage of the reduction
+# more was needed
+NOALLOC_FITS = [
+    (False, None, False, False, 1, (322848, 64), 40), (False, None, False, True, 7, (2285, 203), 128),
+    (False, None, True, True, 1, (31728, 1000), 100), (False, 2, False, False, 1, (1536, 64), 2000),
+    (False, 2, True, False, 7, (4485, 1000), 200), (False, 3, False, False, 7, (920, 1000), 129),
+    (True, None, False, False, 1, (322848, 64), 40), (True, None, True, True, 7, (912, 1000), 100),
+    (True, None, False, True, 1, (100720, 64), 129),
+]
+
+
+def noalloc_takes_what_it_took():
+    """Views at the limit of fmb_backward_noalloc's workspace."""
+    rt = Runtime()
+    for composite, variant, colour, normal, v, hw, n in NOALLOC_FITS:
+        sc = Scene(rt, n)
+        sc.set_model(composite)
+        sc.set_cameras([hw] * v)
+        sc.set_colors(colour)
+        if variant is not None:
+            sc.set_variants(0, variant)
+        sc.check(sc.backward(normal=normal, color=colour, noalloc=True))
+        rt.launches()
+
+
+CHECKS = [noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
