@@ -287,16 +287,14 @@ struct Job {
     // waits for the device before one is overwritten.  A pass recorded into a caller's graph may be
     // replayed at any time, so after one every replacement waits.
     enum Uses : unsigned { kUseDescriptors = 1, kUseFwd = 2, kUseCompFwd = 4, kUseBwd = 8, kUseStat = 16 };
-    unsigned in_flight = 0;
-    bool recorded = false;
+    unsigned in_flight = 0, recorded = 0;
     void launched(unsigned uses, hipStream_t st)
     {
-        in_flight |= uses | kUseDescriptors;
-        recorded = recorded || stream_capturing(st);
+        (stream_capturing(st) ? recorded : in_flight) |= uses | kUseDescriptors;
     }
     int settle(unsigned uses)
     {
-        if (!recorded && !(in_flight & uses)) return FMB_OK;
+        if (!((recorded | in_flight) & uses)) return FMB_OK;
         HIPCHK(hipDeviceSynchronize());
         in_flight = 0;
         return FMB_OK;
@@ -974,6 +972,12 @@ struct Job {
         if (model == FMB_MODEL_COMPOSITE) {
             int rc = build_comp_fwd();
             if (rc) return rc;
+            // The backward of a forward that keeps its stash is planned here, so that a program may record both
+            // after one forward has run; where that does not fit, the backward's own call says so.
+            if (O.stash && bwd_built != bwd_key(0, false) && bwd_built != bwd_key(0, true) && !stream_capturing(st)) {
+                (void)build_bwd(bwd_variant, prm.colors != nullptr);
+                g_err.clear();
+            }
             launched(kUseCompFwd, st);
             TimedSpan ts(st, 0);
             HIPCHK(launch_fwdc(fwd_flags(O), n_cfitems[0], n_cfitems[1], st, prm, O, d_cfitems.as<CompItem>()));

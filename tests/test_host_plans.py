@@ -140,10 +140,10 @@ def coarser_cuts_where_memory_is_short():
             sc = Scene(rt, n)
             sc.set_model(composite)
             sc.set_cameras([hw])
-            sc.check(sc.render())
             base = rt.rr.rr_in_use()
             if limit is not None:
                 rt.rr.rr_set_limit(base + limit)
+            sc.check(sc.render())
             rt.launches()
             rc = sc.backward(normal=normal)
             items = [i for name, _, i in rt.launches() if "bwd" in name]
@@ -209,7 +209,24 @@ def noalloc_takes_what_it_took():
         rt.launches()
 
 
-CHECKS = [noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def compositing_step_is_recorded_after_one_forward():
+    """A capture allows no allocation and no synchronous copy: after one eager compositing forward with a
+    stash, a forward and a backward need neither (nor does a forward without one plan a backward)."""
+    rt = Runtime()
+    for colour in (False, True):
+        sc = Scene(rt, 40, stream=0x770)
+        sc.set_model(True)
+        sc.set_colors(colour)
+        sc.set_cameras([(64, 64)])
+        sc.check(sc.render(color=colour))
+        rt.rr.rr_set_capturing(1)
+        sc.check(sc.render(color=colour))
+        sc.check(sc.backward(color=colour))
+        rt.rr.rr_set_capturing(0)
+        assert rt.count("refused") == 0
+
+
+CHECKS = [compositing_step_is_recorded_after_one_forward, noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
