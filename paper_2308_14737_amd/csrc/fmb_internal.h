@@ -21,17 +21,12 @@ constexpr float kEpsN = 1e-30f;
 // kernels evaluate: 2^-150 is below half of FP32's smallest subnormal, so such a weight is
 // exactly zero and its terms are skipped.
 constexpr float kSkipLog2 = -150.0f;
-// Base-2 log of the smallest density whose alpha term D_bar delta the tiled backward evaluates
-// where a tile has no weight above zero: a pair below it adds at most 2^-48 |D_bar| to its
-// Gaussian's sums, so even 2^21 rays (a 1080p view) change a Gaussian's record by less than
-// 2^-27 |D_bar|, far below the terms of the rays that see it.
+// Base-2 log of the smallest density that is evaluated where a tile has no weight above zero: in the
+// forward a ray's density sum, and so its alpha, misses less than 2^-48 of each such pair (an absolute
+// bound: the alpha of a ray that sees nothing denser is 0); in the tiled backward a pair below it adds
+// at most 2^-48 |D_bar| to its Gaussian's sums, so even 2^21 rays (a 1080p view) change a Gaussian's
+// record by less than 2^-27 |D_bar|, far below the terms of the rays that see it.
 constexpr float kDensSkipLog2 = -48.0f;
-// The forward's cutoffs: in a scene of n Gaussians, densities below 2^-kDensRelLog2 / n of the least
-// density sum of a tile's rays together move no sum by more than 2^-kDensRelLog2 of it (FP32 rounds at
-// 2^-24), and weights below 2^kFwdSkipLog2 of the running maximum (2^-kDensRelLog2 / n of it for
-// n > 2^22), whose own weight adds at least 1 to the sum, likewise.
-constexpr float kDensRelLog2 = 26.0f;
-constexpr float kFwdSkipLog2 = -48.0f;
 
 struct ViewRec {       // one per view of the batch
     int32_t h, w;      // image size (explicit rays: h = ray count, w = 1)

@@ -38,15 +38,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
     constexpr bool COLOR = (F & kCol) != 0, BIG = (F & kBig) != 0;
     constexpr int EW = COLOR ? 6 : 5;  // float4 per LDS entry: the entry, the m estimate terms, colour
     __shared__ float4 tile[TG * EW];
-    // the upper bounds (log2 density, log2 weight) of each staged (Gaussian, ray tile): per wave, per
-    // group of 64 / RPT Gaussians, per lane
-    __shared__ float2 hisave[BLOCK / 64][TG * RPT];
+    // the upper bound of the log2 weight of each staged (Gaussian, ray tile), +inf where its density can
+    // reach the cutoff: per wave, per group of 64 / RPT Gaussians, per lane
+    __shared__ float hisave[BLOCK / 64][TG * RPT];
     __shared__ float4 tbox[BLOCK / 64 * RPT * 3];  // each ray tile's box (TileBox)
-    // scenes beyond BLOCK Gaussians: the waves' least running maxima and density sums, their counts
+    // scenes beyond BLOCK Gaussians: the waves' least running maxima, their counts
     // of survivors (of two rounds in turn), and the list of survivors (a ring)
     constexpr int LIST = 2 * BLOCK;
     static_assert(TG <= BLOCK, "a round is added to fewer than TG survivors");
-    __shared__ float2 wmin[BIG ? BLOCK / 64 : 1];
+    __shared__ float wmin[BIG ? BLOCK / 64 : 1];
     __shared__ int wcnt[2][BIG ? BLOCK / 64 : 1];
     __shared__ int slist[BIG ? LIST : 1];
     const int it = order ? ld_uniform(order + blockIdx.x) : (int)blockIdx.x;
@@ -95,18 +95,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             tbox[3 * (wave * RPT + j) + 2] = b.y;
         }
     }
-    const float g2n = ceil_log2(sr.n), wskip = fminf(kFwdSkipLog2, -kDensRelLog2 - g2n);
-    // lower bounds over lane's tile jl, from the Gaussians bounded so far: log2 of the density sum
-    // and the running maximum
-    float dlow = -INFINITY, mlow = -INFINITY;
+    // lower bound over lane's tile jl, from the Gaussians bounded so far, of the running maximum
+    float mlow = -INFINITY;
 
     // Of a scene of more than BLOCK Gaussians each is first bounded on a box around all the item's
     // tiles, BLOCK of them a round, and only those whose density can reach the cutoff there, or whose
-    // weight can be above 2^kFwdSkipLog2 against the least running maximum of the item's rays so
+    // weight can be above FP32's zero against the least running maximum of the item's rays so
     // far, are listed, in scene order; rounds go on until the list fills a staged tile (a round of
     // 10 000 clustered Gaussians leaves a handful: staged and bounded by themselves they took a third
     // of the kernel's instructions, 694 us against 593 for a 1920 x 1080 view).  The running
-    // maxima and density sums only grow, so a Gaussian left out is one that the tests below would
+    // maxima only grow, so a Gaussian left out is one that the tests below would
     // skip when its turn came.
     // Smaller scenes stage all their Gaussians (and launches without kBig, whose scenes are all
     // small, have no list).
@@ -115,23 +113,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
     int rb = 0, head = 0, total = sparse ? 0 : sr.n;  // next round, ring position and count of the listed
     for (bool first = true; ; first = false) {
       if (sparse && rb < sr.n && total < TG) {
-        float mm = INFINITY, dm = INFINITY;
+        float mm = INFINITY;
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
-            dm = loc[j] >= 0 ? fminf(dm, D[j]) : dm;
-        }
+        for (int j = 0; j < RPT; ++j) mm = loc[j] >= 0 ? fminf(mm, M[j]) : mm;
         mm = wave_min_u(mm);
-        dm = wave_min_u(dm);
-        if (lane == 0) wmin[wave] = make_float2(mm, dm);
+        if (lane == 0) wmin[wave] = mm;
         __syncthreads();  // tile boxes and least maxima visible
         if (first) ibox = wave_box_of(tbox, NW * RPT, lane, e);
-        float imin = INFINITY, idm = INFINITY;
-        for (int w = 0; w < NW; ++w) {
-            imin = fminf(imin, wmin[w].x);
-            idm = fminf(idm, wmin[w].y);
-        }
-        const float dcut = fmaxf(kDensSkipLog2, __builtin_amdgcn_logf(idm) - kDensRelLog2 - g2n);
+        float imin = INFINITY;
+        for (int w = 0; w < NW; ++w) imin = fminf(imin, wmin[w]);
         do {
             const int gl = rb + (int)threadIdx.x, par = (rb / BLOCK) & 1;
             bool keep = false;
@@ -142,7 +132,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
                 make_bound_entry(P.means + 3 * gg, P.prec + 6 * gg, P.weights[gg], o, ge, ee);
                 const PairBounds pb = tile_bounds(ge, ee, ibox, bl.hm, bl.b1, bl.nc2);
                 // (written so that a NaN bound keeps the Gaussian)
-                keep = !(b1_pos && pb.d2_hi < dcut && pb.z_hi - imin < wskip);
+                keep = !(b1_pos && pb.d2_hi < kDensSkipLog2 && pb.z_hi - imin < kSkipLog2);
             }
             const unsigned long long bal = wave_ballot(keep);
             if (lane == 0) wcnt[par][wave] = __popcll(bal);
@@ -168,11 +158,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
         }
         __syncthreads();
         // Every (Gaussian, ray tile) of the staged tile is bounded first, GP Gaussians at a time;
-        // the lower bounds give the least density sum and the least running maximum that the
-        // tile's rays end with.  A pair is taken if on some ray its density can reach the cutoff
-        // (2^kDensSkipLog2, or 2^-kDensRelLog2 / n of the least density sum) or its weight
-        // 2^kFwdSkipLog2 of the running maximum.  Without beta1 >= 0 the weight bounds do not
-        // hold and every pair is taken.
+        // the lower bounds give the least running maximum that the tile's rays end with.  A pair is
+        // taken if on some ray its density can reach 2^kDensSkipLog2 or its weight be above FP32's
+        // zero.  Without beta1 >= 0 the weight bounds do not hold and every pair is taken.
         constexpr int GP = 64 / RPT;
         const TileBox bj = TileBox{tbox[3 * (wave * RPT + jl)], tbox[3 * (wave * RPT + jl) + 1], tbox[3 * (wave * RPT + jl) + 2]};
         for (int ib = 0; ib < cnt; ib += GP) {
@@ -180,24 +168,18 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             if (il < cnt) {
                 const Ent gl = ent_from(tile[EW * il], tile[EW * il + 1], tile[EW * il + 2], tile[EW * il + 3]);
                 const PairBounds pb = tile_bounds(gl, tile[EW * il + 4], bj, bl.hm, bl.b1, bl.nc2);
-                hisave[wave][ib * RPT + lane] = make_float2(pb.d2_hi, pb.z_hi);
-                dlow = fmaxf(dlow, pb.d2_lo);
+                // (comparisons written so that a NaN bound keeps the pair)
+                hisave[wave][ib * RPT + lane] = pb.d2_hi < kDensSkipLog2 ? pb.z_hi : INFINITY;
                 mlow = fmaxf(mlow, pb.z_lo);
             }
         }
 #pragma unroll
-        for (int off = RPT; off < 64; off <<= 1) {
-            dlow = fmaxf(dlow, __shfl_xor(dlow, off, 64));
-            mlow = fmaxf(mlow, __shfl_xor(mlow, off, 64));
-        }
-        if (!first) {  // the sums of the Gaussians taken so far bound too
+        for (int off = RPT; off < 64; off <<= 1) mlow = fmaxf(mlow, __shfl_xor(mlow, off, 64));
+        if (!first) {  // the maxima of the Gaussians taken so far bound too
 #pragma unroll
             for (int j = 0; j < RPT; ++j) {
-                const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY), dm = wave_min_u(loc[j] >= 0 ? D[j] : INFINITY);
-                if (jl == j) {
-                    mlow = fmaxf(mlow, mm);
-                    dlow = fmaxf(dlow, __builtin_amdgcn_logf(dm));
-                }
+                const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY);
+                if (jl == j) mlow = fmaxf(mlow, mm);
             }
         } else if (b1_pos) {
             // the running maximum starts at its lower bound (a pair that reaches it is staged here),
@@ -206,14 +188,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             for (int j = 0; j < RPT; ++j)
                 M[j] = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mlow), j)), 1e30f);
         }
-        const float dcut = fmaxf(kDensSkipLog2, dlow - kDensRelLog2 - g2n), zcut = mlow + wskip;
+        const float zcut = mlow + kSkipLog2;
         for (int ib = 0; ib < cnt; ib += GP) {
             const int il = ib + lane / RPT;
             bool need = false;
             if (il < cnt && bj.c.w >= 0.0f) {
-                const float2 h = hisave[wave][ib * RPT + lane];
-                // (written so that a NaN bound keeps the pair)
-                need = !(b1_pos && h.x < dcut && h.y < zcut);
+                need = !(b1_pos && hisave[wave][ib * RPT + lane] < zcut);
             }
             unsigned long long nm = wave_ballot(need);
           while (nm != 0ull) {
@@ -233,9 +213,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
                 D[j] += delta;
                 // log2 of the weight relative to the running maximum, b1 d2 + (nc2 t - M)
                 float zr = fmaf(bl.b1, q.d2, fmaf(bl.nc2, q.t, -M[j]));
-                // A weight below 2^kFwdSkipLog2 of the running maximum does not change the sums:
-                // its terms are skipped (the branch is uniform over a wave for most Gaussians).
-                if (zr < wskip) continue;
+                // A weight below 2^-150 of the running maximum is zero in FP32: its terms are
+                // skipped (the branch is uniform over a wave for most distant Gaussians).
+                if (zr < kSkipLog2) continue;
                 pair_refine(q);
                 if (zr > 0.0f) {  // new running maximum: rescale the sums (rare)
                     const float sc = exp2_(M[j] - q.z2);
