@@ -368,25 +368,27 @@ struct Job {
         return FMB_OK;
     }
 
-    // Ray tiles per item of the compositing forward: blocks of four waves share a small scene's staged
-    // entries over 16 tiles, or over fewer where that leaves less than two blocks per compute unit
-    // (20 views of 128 x 128: 4 tiles, 1280 blocks instead of 320); a larger scene's tiles stage their own
-    // survivors, one tile an item.
     // Into how many parts (4^cut waves) the compositing forward cuts the ray tiles of view k of a larger
     // scene, from that scene alone: more where the Gaussians are many to a tile and while the waves
-    // are at most a few rounds of the GPU.  A render (us) with cut 0 / 1 / 2, clustered: 1000 Gaussians on
-    // 2040 tiles 304 / 165 / 351, on 256 1047 / 189 / 110; 1200 on 625 1288 / 327 / 226; 700 on 2040
-    // 112 / 102 / 335; 200 on 2040 30 / 63 / 199; 1000 on 8160 185 / 447 / 1669.  Spread over the whole image:
-    // 1000 on 256 84.5 / 77.9 / 75.5 ms, 900 on 950 64.0 / 59.7 / 83.4, 1000 on 2040 76.2 / 81.6 / 175.6.
+    // are at most a few rounds of the GPU.  A render (us) with cut 0 / 1 / 2 of clustered Gaussians:
+    // 1000 on 64 tiles 2863 / 1277 / 388, on 256 1637 / 730 / 306, on 2040 792 / 400 / 435, on 8160 436 / 474 / 1241;
+    // 1200 on 625 1260 / 479 / 309, on 722 1602 / 682 / 330; 700 on 2040 166 / 105 / 242; 600 on 625 135 / 69 / 91;
+    // 400 on 2040 39 / 54 / 173; 300 on 256 36 / 26 / 29; 150 on 64 31 / 20 / 16.  Spread over the whole image
+    // (ms): 1000 on 256 109 / 99 / 95, 900 on 950 89 / 85 / 116, and 1000 on 2040 99 / 109 / 232, where the rule's
+    // cut 1 loses a tenth: what decides is the Gaussians of the densest tile, which n / tiles only stands for.
     int comp_cut(int k) const
     {
         const SceneRec &sc = scenes[views[k].scene];
         int64_t tiles = 0;
         for (int q = sc.view_off; q < sc.view_off + sc.n_views; ++q) tiles += views[q].tiles;
         const double per_tile = (double)sc.n / views[k].tiles;
-        return tiles <= 320 && per_tile >= 1.5 ? 2 : tiles <= 2560 && per_tile >= 0.4 ? 1 : 0;
+        return tiles <= 768 && per_tile >= 1.5 ? 2 : tiles <= 2560 && per_tile >= 0.3 ? 1 : 0;
     }
 
+    // Ray tiles per item of the compositing forward: blocks of four waves share a small scene's staged
+    // entries over 16 tiles, or over fewer where that leaves less than two blocks per compute unit
+    // (20 views of 128 x 128: 4 tiles, 1280 blocks instead of 320); a larger scene's tiles stage their own
+    // survivors, one tile an item.
     int build_comp_fwd()
     {
         if (comp_fwd_built) return FMB_OK;

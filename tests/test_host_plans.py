@@ -226,7 +226,21 @@ def compositing_step_is_recorded_after_one_forward():
         assert rt.count("refused") == 0
 
 
-CHECKS = [compositing_step_is_recorded_after_one_forward, noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def compositing_parts_by_the_measured_rule():
+    """Blocks of the compositing forward: 16, 4 or 1 a tile of a larger scene, as measured best for these."""
+    rt = Runtime()
+    for n, hw, parts in ((1200, (200, 200), 16), (1200, (150, 300), 16), (1000, (128, 128), 16), (600, (200, 200), 4),
+                         (700, (270, 480), 4), (1000, (270, 480), 4), (400, (270, 480), 1), (1000, (540, 960), 1)):
+        sc = Scene(rt, n)
+        sc.set_model(True)
+        sc.set_cameras([hw])
+        rt.launches()
+        sc.check(sc.render())
+        grid = [g for name, g, _ in rt.launches() if "fwdc" in name][0]
+        assert grid[0] == parts * _tiles(*hw), (n, hw, grid)
+
+
+CHECKS = [compositing_parts_by_the_measured_rule, compositing_step_is_recorded_after_one_forward, noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
