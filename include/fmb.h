@@ -156,7 +156,7 @@ int fmb_set_flow_pose2(fmb_scene *scene, fmb_batch *batch, const float *w2c_c,
  * move a sum by less than 2^-36, and pairs whose density is below 2^skip of the ray's largest
  * weight, skip = min(-40, -26 - ceil(log2 n)), are left out of the blend and of its adjoint
  * (which keeps those with a density of at least 2^skip)), blended by Eq. (3) for depth,
- * normals and colour, alpha by Eq. (8) over every density; betas and eta are not
+ * normals and colour, alpha by Eq. (8) over the densities of the blended pairs; betas and eta are not
  * used and their gradient is 0.  Every
  * other call keeps its meaning, arguments and outputs; the stash holds the same fields
  * (the running maximum is that of log2 w_i).  Captured graphs are dropped when the model
@@ -242,8 +242,8 @@ int64_t fmb_batch_num_rays(const fmb_batch *batch);
 int64_t fmb_batch_ray_offset(const fmb_batch *batch, int32_t i);
 int64_t fmb_batch_gauss_offset(const fmb_batch *batch, int32_t i);
 
-/* Forward / backward over the whole batch with one kernel each (a block per work item of
- * (scene, view, ray tiles), largest first).  Arguments as
+/* Forward / backward over the whole batch with one kernel each, or two where small and large scenes are
+ * mixed (a block per work item of (scene, view, ray tiles), largest first).  Arguments as
  * fmb_render / fmb_backward with concatenated arrays; g_betas is [s,2]. */
 int fmb_batch_forward(fmb_batch *batch, float *depth, float *alpha, float *normal, float *flow,
                       float *color, float *stash, void *stream);

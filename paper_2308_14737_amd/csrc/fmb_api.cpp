@@ -1,8 +1,8 @@
 // fmb_api.cpp -- host side of the C ABI declared in include/fmb.h.
 //
 // Holds the scene / batch descriptors, cuts the work into items (see
-// fmb_internal.h), owns the device workspace (item lists, partial gradients, work
-// counters), launches the kernels of fmb_kernels.hip on the caller's stream, captures
+// fmb_internal.h), owns the device workspace (item lists, partial gradients,
+// reduction stages), launches the kernels of fmb_kernels.hip on the caller's stream, captures
 // HIP graphs for batches, times the tile variants (autotuner) and records kernel
 // timings with HIP events.  No exception crosses the ABI.
 #include <hip/hip_runtime.h>
@@ -326,12 +326,13 @@ struct Job {
         prm.views = d_views.as<ViewRec>();
         prm.eta = d_eta.as<float>();
         // Untuned default of the forward: more rays per item amortise its staging and bounds, fewer fill
-        // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 59 / 71 / 75,
-        // 330 000 rays 59.6 / 61.8 / 64.4, 1.1e6 103 / 103 / 105, 2.4e6 146 / 142 / 143, 12.6e6 832 / 808 / 786.
+        // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 59 / 67 / 81,
+        // 330 000 rays 59.2 / 62.6 / 66.7, 1.1e6 115 / 117 / 118, 2.4e6 212 / 213 / 220, 4.2e6 238 / 233 / 232,
+        // 12.6e6 in 16 scenes 830 / 812 / 789.
         // Of clustered scenes beyond a block's count of Gaussians a few blocks take most of the pairs, and
         // shorter ones leave less of a tail, at the price of a pre-cull each: 0.5e6 rays of 4000 Gaussians
-        // 411 / 438 / 548, 1.2e6 of 10 000 1410 / 1488 / 1575, 1.4e6 of 500 250 / 238 / 244, 2.1e6 of 10 000
-        // 1396 / 1288 / 1365, 2.1e6 of 1000 288 / 262 / 257.
+        // 251 / 279 / 379, 1.2e6 of 10 000 1160 / 1195 / 1336, 1.4e6 of 500 191 / 180 / 182, 2.1e6 of 10 000
+        // 1268 / 1148 / 1201, 2.1e6 of 1000 283 / 257 / 253.
         if (!launch_fixed) {
             const int64_t r = 256LL * n_cu;
             const int64_t one = max_scene_n() > block_size() ? 24 : 6;
@@ -431,8 +432,8 @@ struct Job {
     // is then the same in any batch).  Small scenes: 16, or 8 or 4 where the scene has too few
     // tiles for 512 items.  Larger scenes, whose items are one wave each: as few as keep the partial
     // records below 8 MiB or, with `more`, within the workspace of fmb_backward_noalloc where those fit it
-    // and else 256 MiB (items of one tile take 7.5 -> 3.9 ms for a step of 1200 clustered Gaussians at
-    // 270 x 480, 202 -> 114 us for one of 300).
+    // and else 256 MiB (than items of 16 tiles: 8.7 -> 3.7 ms for a step of 1200 clustered Gaussians at
+    // 270 x 480, 385 -> 90 us for one of 300).
     int comp_bwd_span(int s, int rec, bool more) const
     {
         auto count = [&](int span) {
@@ -481,8 +482,7 @@ struct Job {
         slots = block / gc;
     }
 
-    // Backward items (and, for the compositing model, the forward items too).  The key
-    // records the model, the colour record size and the blend backward's variant.
+    // The key of a backward's lists: the model, the colour record size and the blend backward's variant.
     int bwd_key(int variant, bool colour) const
     {
         return model == FMB_MODEL_COMPOSITE ? (colour ? 3 : 1) : (variant * 2 + (colour ? 1 : 0)) * 2;
@@ -597,10 +597,10 @@ struct Job {
     // of such scenes is uneven (one 16-tile item of 10 000 clustered Gaussians holds 6 times the mean
     // and is alone 2.4 times the whole launch's work per block slot), so items are cut until a part has at
     // most kPartGauss Gaussians and there are kLargeItems of them.  A part repeats the rays' prologue, a
-    // smaller span the pre-cull, and takes more records.  A step (us) by span / parts: 10 000 Gaussians,
-    // 1080 x 1920, 16/1 1285, 16/2 1180, 16/4 1175, 8/1 1261, 8/4 1314; 10 000, 300 x 300, 16/1 1203, 16/8 435,
-    // 8/4 492, 2/1 479; 4000, 540 x 960, 16/1 414, 16/4 284, 8/2 241, 4/1 269; 1000, 1080 x 1920, 16/1 260,
-    // 16/2 283, 8/1 274; 400, 300 x 400, 16/1 85, 16/2 71, 2/1 64.
+    // smaller span the pre-cull, and takes more records.  A step (us) by span / parts, the cut taken last:
+    // 10 000 Gaussians, 1080 x 1920, 16/1 1250, 16/2 1141, 8/1 1221, 8/4 1304, 16/4 1160; 10 000, 300 x 300, 16/1 1199,
+    // 16/8 404, 8/4 451, 2/1 416, 8/8 404; 4000, 540 x 960, 16/1 464, 16/4 293, 4/1 288, 8/2 267; 1000, 1080 x 1920,
+    // 16/2 288, 8/1 275, 16/1 264; 400, 300 x 400, 16/1 88, 16/2 74, 2/1 64.
     // Records and items stay within the workspace of fmb_backward_noalloc where those of 16/1 fit there,
     // else 2 GiB a scene.
     static constexpr int kLargeItems = 1024, kPartGauss = 2560, kMaxParts = 8;
@@ -1634,14 +1634,13 @@ int fmb_kernel_times(double *out6, int reset)
 // Autotuner: time every (forward variant) x (backward variant) on the real shapes.
 // ---------------------------------------------------------------------------------------
 
-static std::string tune_key(const Job &j, int fflags, int unused, int cot_mask)
+static std::string tune_key(const Job &j, int fflags, int cot_mask)
 {
     hipDeviceProp_t prop{};
     (void)hipGetDeviceProperties(&prop, j.device);
     std::ostringstream k;
     k << prop.gcnArchName << ":cu" << j.n_cu << ":v6:S" << j.S << ":V" << j.V << ":P" << j.P << ":N" << j.n_total
       << ":out" << fflags << ":cot" << cot_mask;
-    (void)unused;
     return k.str();
 }
 
@@ -1664,7 +1663,7 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
     const Grads G{g_means, g_prec, g_weights, g_colors, g_betas};
     const int cot_mask = (g_depth ? 1 : 0) | (g_alpha ? 2 : 0) | (g_normal ? 4 : 0) | (g_flow ? 8 : 0) |
                          (g_color ? 16 : 0);
-    const std::string key = tune_key(j, Job::fwd_flags(O), 0, cot_mask);
+    const std::string key = tune_key(j, Job::fwd_flags(O), cot_mask);
     if (cache_path) {
         std::ifstream in(cache_path);
         std::string line;

@@ -14,7 +14,7 @@
 // and block for four waves, which take the item's tiles in turn (one wave per block staged it for itself
 // and left a 20-view 128 x 128 job at 320 waves: 960 -> 196 us for its step).  Of a larger scene each
 // wave first bounds every Gaussian on its tile and stages those that can matter there (about 10 of 1000 on
-// a clustered 480 x 270 view, 9.4 -> 0.9 ms); only a tile with more than kCompTG of them takes the
+// a clustered 480 x 270 view: a render of 13.3 ms, and 0.8 before a tile was cut over several waves); only a tile with more than kCompTG of them takes the
 // scene in staged tiles.
 //
 // Front sums without a sort: F_i only needs the densities in front of t_i, and of those only the
@@ -45,7 +45,7 @@
 // left out carry normalised weights below 2^-24 of the ray's largest, and delta_j B_j is itself
 // below 2^-24 of z_bar_j where every density of the ray is insignificant.  Each wave sums its pairs'
 // terms over its 64 rays for every Gaussian it touches (a fixed butterfly), adds them to the item's
-// record in LDS in tile order, and the records go to the deterministic two-stage finalize.
+// record in LDS in tile order, and the records go to the deterministic finalize.
 #include "fmb_device.h"
 
 namespace fmb {
@@ -291,7 +291,7 @@ __device__ __forceinline__ void slots_fz_plain(CompList &L, CompZ &zs, int ns, c
 // The part of an 8 x 8 tile that the lane is in, of 4^cut square ones (cut 1 or 2).  The forward of a
 // larger scene gives a dense view's tiles to 4 or 16 waves: a part's rays share fewer Gaussians, so
 // that its wave takes fewer windows, and the slowest tile, which the launch waits for, is the sooner
-// done (1000 clustered Gaussians at 270 x 480: 304 -> 165 us; at 64 x 64: 2423 -> 196 us).
+// done (1000 clustered Gaussians at 270 x 480: 792 -> 400 us; at 64 x 64: 2863 -> 388 us).
 __device__ __forceinline__ int comp_part(int lane, int cut)
 {
     const int half = 3 - cut;

@@ -381,9 +381,9 @@ __device__ __forceinline__ TileBox wave_box_of(const float4 *boxes, int n, int l
 // density cutoff of 2^-48 keeps 32 % of the (8 x 8 tile, Gaussian) pairs where some ray reaches it
 // on 31 %; the bound sqrt(m_c) - |U|_2 |U mu'| |U^-1|_2 rho over the tile's cone kept 40 %, and a
 // one-FMA bound per pair after it found little more to skip.  With both sides bounded the forward also
-// knows the least density sum and running maximum of a tile before its first pair.  A training step
-// of 16 scenes (8.5e6 rays, 10 to 100 Gaussians) went from 918 to 815 us, one of 10 000 Gaussians at
-// 1080 x 1920 from 3.80 to 2.06 ms.  The slack terms cover the FP32 rounding of the bound and of the
+// knows the least running maximum of a tile before its first pair.  A training step
+// of 16 scenes (12.6e6 rays, 10 to 100 Gaussians) with the cone's bound and two sweeps took 922 us, and
+// takes 792; one of 640 x 480 video frames 382 and 350.  The slack terms cover the FP32 rounding of the bound and of the
 // pair's own evaluation.
 struct PairBounds {
     float d2_hi, d2_lo, z_hi, z_lo;

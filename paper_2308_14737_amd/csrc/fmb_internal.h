@@ -61,7 +61,7 @@ struct BwdItem {       // 32 bytes; its index in the list is the index of its be
     int32_t ray0;      // first local ray of the span
     int32_t span;      // rays in the span (clipped to the view by the kernel)
     int32_t g0;        // first Gaussian (scene-local) of the chunk
-    int32_t gc;        // Gaussians in the chunk (<= block size)
+    int32_t gc;        // Gaussians in the chunk: at most a block's count for the Gaussian-lane kernel, else the scene's
     int32_t slots;     // ray slots: thread t works on Gaussian t % gc, rays t / gc mod slots
                        // (tiled kernels with a large scene: the item is part g0 of slots of its record, every
                        // slots-th 64 Gaussians)

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
     // weight can be above FP32's zero against the least running maximum of the item's rays so
     // far, are listed, in scene order; rounds go on until the list fills a staged tile (a round of
     // 10 000 clustered Gaussians leaves a handful: staged and bounded by themselves they took a third
-    // of the kernel's instructions, 694 us against 593 for a 1920 x 1080 view).  The running
+    // of the kernel's instructions, 718 us against 542 for a 1920 x 1080 view).  The running
     // maxima only grow, so a Gaussian left out is one that the tests below would
     // skip when its turn came.
     // Smaller scenes stage all their Gaussians (and launches without kBig, whose scenes are all
