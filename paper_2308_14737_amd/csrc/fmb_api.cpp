@@ -13,6 +13,7 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <numeric>
 #include <sstream>
@@ -82,13 +83,29 @@ int fail(int code, const std::string &msg)
     return code;
 }
 
+// (an error is cleared where it is reported: the launches of later calls check for one of their own)
 #define HIPCHK(x)                                                                                 \
     do {                                                                                          \
         hipError_t e_ = (x);                                                                      \
-        if (e_ != hipSuccess)                                                                     \
+        if (e_ != hipSuccess) {                                                                   \
+            (void)hipGetLastError();                                                              \
             return fail(e_ == hipErrorOutOfMemory ? FMB_ERR_OOM : FMB_ERR_HIP,                    \
                         std::string(#x) + ": " + hipGetErrorString(e_));                          \
+        }                                                                                         \
     } while (0)
+
+// Ends an entry point whose work may allocate host memory: its exceptions become a status.
+int caught() noexcept
+{
+    try {
+        throw;
+    } catch (const std::bad_alloc &) {
+        return fail(FMB_ERR_OOM, "host memory");
+    } catch (...) {
+        return fail(FMB_ERR_STATE, "exception");
+    }
+}
+#define FMB_CAUGHT catch (...) { return caught(); }
 
 #define CHECK_ARG(cond, msg)                                                                      \
     do {                                                                                          \
@@ -136,12 +153,10 @@ struct DevBuf {
         if (n <= bytes && p) return hipSuccess;
         release();
         hipError_t e = hipMalloc(&p, n > 0 ? n : 16);
-        if (e == hipSuccess) {
+        if (e == hipSuccess)
             bytes = n > 0 ? n : 16;
-        } else {
+        else
             p = nullptr;
-            (void)hipGetLastError();  // (the launches check it: this failure is not theirs)
-        }
         return e;
     }
     template <class T>
@@ -201,7 +216,10 @@ Timing g_timing;
 bool stream_capturing(hipStream_t st)
 {
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &s) != hipSuccess) return false;
+    if (hipStreamIsCapturing(st, &s) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     return s != hipStreamCaptureStatusNone;
 }
 
@@ -1149,7 +1167,7 @@ const char *fmb_last_error(void) { return g_err.c_str(); }
 
 int fmb_scene_create(fmb_scene **out, int32_t n, const float *means, const float *prec, const float *weights,
                      const float *betas, float eta)
-{
+try {
     g_err.clear();
     CHECK_ARG(out, "out must be non-NULL");
     *out = nullptr;
@@ -1158,8 +1176,7 @@ int fmb_scene_create(fmb_scene **out, int32_t n, const float *means, const float
     int rc = check_params(means, prec, weights, betas);
     if (rc) return rc;
     if (n > kMaxGaussians) return fail(FMB_ERR_SHAPE, "more than FMB_MAX_GAUSSIANS Gaussians");
-    fmb_scene *s = new (std::nothrow) fmb_scene();
-    if (!s) return fail(FMB_ERR_OOM, "host allocation failed");
+    std::unique_ptr<fmb_scene> s(new fmb_scene());
     s->n = n;
     Job &j = s->job;
     j.S = 1;
@@ -1170,13 +1187,10 @@ int fmb_scene_create(fmb_scene **out, int32_t n, const float *means, const float
     j.prm.prec = prec;
     j.prm.weights = weights;
     j.prm.betas = betas;
-    if ((rc = j.init_device()) || (rc = j.upload_descriptors())) {
-        delete s;
-        return rc;
-    }
-    *out = s;
+    if ((rc = j.init_device()) || (rc = j.upload_descriptors())) return rc;
+    *out = s.release();
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int fmb_scene_rebind(fmb_scene *s, const float *means, const float *prec, const float *weights,
                      const float *betas)
@@ -1201,7 +1215,7 @@ int fmb_scene_destroy(fmb_scene *s)
 
 int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr, const int32_t *hw,
                     const float *w2c_b, const float *intr_b)
-{
+try {
     g_err.clear();
     CHECK_ARG(s, "scene must be non-NULL");
     CHECK_ARG(v >= 1, "v must be >= 1");
@@ -1209,6 +1223,8 @@ int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr
     int rc = check_cams(w2c, intr, hw, v, w2c_b, intr_b, p);
     if (rc) return rc;
     Job &j = s->job;
+    j.cams_set = false;  // (until all of it is)
+    j.invalidate_plans();
     j.V = v;
     j.P = p;
     j.views.clear();
@@ -1226,16 +1242,14 @@ int fmb_set_cameras(fmb_scene *s, int32_t v, const float *w2c, const float *intr
     j.prm.w2c_c = j.prm.intr_c = nullptr;
     j.prm.dirs = nullptr;
     j.has_flow = w2c_b != nullptr;
-    j.invalidate_plans();
-    j.cams_set = false;
     if ((rc = j.upload_descriptors())) return rc;
     j.cams_set = true;
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, const int32_t *counts,
                  const float *dirs, const float *w2c_b, const float *intr_b)
-{
+try {
     g_err.clear();
     CHECK_ARG(s, "scene must be non-NULL");
     CHECK_ARG(v >= 1, "v must be >= 1");
@@ -1251,6 +1265,8 @@ int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, c
     }
     CHECK_ARG(p >= 1, "at least one ray is needed");
     Job &j = s->job;
+    j.cams_set = false;  // (until all of it is)
+    j.invalidate_plans();
     j.V = v;
     j.P = p;
     j.views.clear();
@@ -1268,13 +1284,11 @@ int fmb_set_rays(fmb_scene *s, int32_t v, const float *w2c, const float *intr, c
     j.prm.w2c_c = j.prm.intr_c = nullptr;
     j.prm.dirs = dirs;
     j.has_flow = w2c_b != nullptr;
-    j.invalidate_plans();
-    j.cams_set = false;
     int rc = j.upload_descriptors();
     if (rc) return rc;
     j.cams_set = true;
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int64_t fmb_num_rays(const fmb_scene *s) { return (s && s->job.cams_set) ? s->job.P : 0; }
 
@@ -1321,39 +1335,39 @@ int fmb_set_colors(fmb_scene *s, fmb_batch *b, const float *colors)
 
 int fmb_render(fmb_scene *s, float *depth, float *alpha, float *normal, float *flow, float *color, float *stash,
                void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(s, "scene must be non-NULL");
     return s->job.forward(FwdOut{depth, alpha, normal, flow, color, stash}, false, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_backward(fmb_scene *s, const float *g_depth, const float *g_alpha, const float *g_normal,
                  const float *g_flow, const float *g_color, const float *depth, const float *color,
                  const float *stash, float *g_means, float *g_prec, float *g_weights, float *g_colors,
                  float *g_betas, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(s, "scene must be non-NULL");
     return s->job.backward(BwdIn{g_depth, g_alpha, g_normal, g_flow, g_color, depth, color, stash},
                            Grads{g_means, g_prec, g_weights, g_colors, g_betas}, false, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_backward_noalloc(fmb_scene *s, const float *g_depth, const float *g_alpha, const float *g_normal,
                          const float *g_flow, const float *g_color, const float *depth, const float *color,
                          const float *stash, float *g_means, float *g_prec, float *g_weights, float *g_colors,
                          float *g_betas, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(s, "scene must be non-NULL");
     return s->job.backward_noalloc(BwdIn{g_depth, g_alpha, g_normal, g_flow, g_color, depth, color, stash},
                                    Grads{g_means, g_prec, g_weights, g_colors, g_betas}, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_batch_create(fmb_batch **out, int32_t s, const int32_t *n_host, const int32_t *v_host, const float *means,
                      const float *prec, const float *weights, const float *betas, const float *eta,
                      const float *w2c, const float *intr, const int32_t *hw, const float *w2c_b,
                      const float *intr_b)
-{
+try {
     g_err.clear();
     CHECK_ARG(out, "out must be non-NULL");
     *out = nullptr;
@@ -1372,8 +1386,7 @@ int fmb_batch_create(fmb_batch **out, int32_t s, const int32_t *n_host, const in
     if (v_total > kMaxViews) return fail(FMB_ERR_SHAPE, "more than FMB_MAX_VIEWS views in the batch");
     int64_t p = 0;
     if ((rc = check_cams(w2c, intr, hw, (int)v_total, w2c_b, intr_b, p))) return rc;
-    fmb_batch *b = new (std::nothrow) fmb_batch();
-    if (!b) return fail(FMB_ERR_OOM, "host allocation failed");
+    std::unique_ptr<fmb_batch> b(new fmb_batch());
     Job &j = b->job;
     j.S = s;
     j.V = (int)v_total;
@@ -1403,14 +1416,11 @@ int fmb_batch_create(fmb_batch **out, int32_t s, const int32_t *n_host, const in
     j.prm.w2c_b = w2c_b;
     j.prm.intr_b = intr_b;
     j.has_flow = w2c_b != nullptr;
-    if ((rc = j.init_device()) || (rc = j.upload_descriptors())) {
-        delete b;
-        return rc;
-    }
+    if ((rc = j.init_device()) || (rc = j.upload_descriptors())) return rc;
     j.cams_set = true;
-    *out = b;
+    *out = b.release();
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int fmb_batch_destroy(fmb_batch *b)
 {
@@ -1435,16 +1445,16 @@ int64_t fmb_batch_gauss_offset(const fmb_batch *b, int32_t i)
 
 int fmb_batch_forward(fmb_batch *b, float *depth, float *alpha, float *normal, float *flow, float *color,
                       float *stash, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(b, "batch must be non-NULL");
     return b->job.forward(FwdOut{depth, alpha, normal, flow, color, stash}, true, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_batch_forward_loss(fmb_batch *b, float *depth, float *alpha, float *normal, float *flow, float *color,
                            float *stash, const float *depth_t, const float *alpha_t, float w_depth,
                            float *g_depth, float *g_alpha, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(b, "batch must be non-NULL");
     CHECK_ARG(depth_t && alpha_t && g_depth && g_alpha, "targets and cotangent outputs must be non-NULL");
@@ -1457,24 +1467,24 @@ int fmb_batch_forward_loss(fmb_batch *b, float *depth, float *alpha, float *norm
     O.w_depth = w_depth;
     O.inv_p = 1.0f / (float)b->job.P;  // as the loss kernel forms it
     return b->job.forward(O, true, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_batch_backward(fmb_batch *b, const float *g_depth, const float *g_alpha, const float *g_normal,
                        const float *g_flow, const float *g_color, const float *depth, const float *color,
                        const float *stash, float *g_means, float *g_prec, float *g_weights, float *g_colors,
                        float *g_betas, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(b, "batch must be non-NULL");
     return b->job.backward(BwdIn{g_depth, g_alpha, g_normal, g_flow, g_color, depth, color, stash},
                            Grads{g_means, g_prec, g_weights, g_colors, g_betas}, true, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_batch_capture(fmb_batch *b, float *depth, float *alpha, float *normal, float *flow, float *color,
                       float *stash, const float *g_depth, const float *g_alpha, const float *g_normal,
                       const float *g_flow, const float *g_color, float *g_means, float *g_prec, float *g_weights,
                       float *g_colors, float *g_betas, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG(b, "batch must be non-NULL");
     CHECK_ARG(stash, "capture needs the stash buffer");
@@ -1514,7 +1524,7 @@ int fmb_batch_capture(fmb_batch *b, float *depth, float *alpha, float *normal, f
         }
     }
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int fmb_batch_graph_launch(fmb_batch *b, int32_t which, void *stream)
 {
@@ -1556,11 +1566,11 @@ int fmb_validate(fmb_scene *s, int32_t *bad_host, void *stream)
 
 int fmb_split_statistic(fmb_scene *s, fmb_batch *b, const float *loss, const float *stash, float *lbar,
                         void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG((s != nullptr) != (b != nullptr), "exactly one of scene and batch must be given");
     return (s ? s->job : b->job).split_statistic(loss, stash, lbar, (hipStream_t)stream);
-}
+} FMB_CAUGHT
 
 int fmb_set_config(fmb_scene *s, fmb_batch *b, int32_t fwd_variant, int32_t bwd_variant, int32_t fwd_grid_mult,
                    int32_t bwd_grid_mult)
@@ -1648,7 +1658,7 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
                  float *stash, const float *g_depth, const float *g_alpha, const float *g_normal,
                  const float *g_flow, const float *g_color, float *g_means, float *g_prec, float *g_weights,
                  float *g_colors, float *g_betas, const char *cache_path, void *stream)
-{
+try {
     g_err.clear();
     CHECK_ARG((s != nullptr) != (b != nullptr), "exactly one of scene and batch must be given");
     CHECK_ARG(depth && alpha && stash && g_means && g_prec && g_weights && g_betas, "buffers are required");
@@ -1732,7 +1742,7 @@ int fmb_autotune(fmb_scene *s, fmb_batch *b, float *depth, float *alpha, float *
         if (outf) outf << key << " " << bf << " " << bb << " 1 1\n";
     }
     return FMB_OK;
-}
+} FMB_CAUGHT
 
 int fmb_loss_grad(int64_t p, const float *depth, const float *alpha, const float *flow, const float *color,
                   const float *depth_t, const float *alpha_t, const float *flow_t, const float *color_t,

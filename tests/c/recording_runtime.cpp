@@ -142,8 +142,10 @@ hipError_t hipMalloc(void **p, size_t n)
 {
     if (capturing) return ++counts[3], hipErrorStreamCaptureUnsupported;
     if (n > limit || in_use > limit - n) return last_error = hipErrorOutOfMemory;
+    void *mem = calloc(n, 1);
+    if (!mem) return last_error = hipErrorOutOfMemory;
     ++counts[0];
-    *p = calloc(n, 1);
+    *p = mem;
     allocs[(uintptr_t)*p] = {n, nullptr, false};
     in_use += n;
     return hipSuccess;

@@ -240,7 +240,41 @@ def compositing_parts_by_the_measured_rule():
         assert grid[0] == parts * _tiles(*hw), (n, hw, grid)
 
 
-CHECKS = [compositing_parts_by_the_measured_rule, compositing_step_is_recorded_after_one_forward, noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
+def host_memory_exhausted_is_a_status():
+    """A plan that the host cannot hold ends in FMB_ERR_OOM, not in an exception through the C interface, and
+    the scene works again once there is room."""
+    import resource
+    rt = Runtime()
+    sc = Scene(rt, 40)
+    big, small = [(16384, 16384)] * 4, [(64, 64)]  # 1.7e7 ray tiles
+
+    def limited(f):
+        with open("/proc/self/statm") as st:
+            now = int(st.read().split()[0]) * resource.getpagesize()
+        old = resource.getrlimit(resource.RLIMIT_AS)
+        resource.setrlimit(resource.RLIMIT_AS, (now + (16 << 20), old[1]))
+        try:
+            return f()
+        finally:
+            resource.setrlimit(resource.RLIMIT_AS, old)
+
+    for composite in (False, True):
+        sc.set_model(composite)
+        sc.set_cameras(big)
+        assert limited(sc.render) == OOM
+        assert limited(sc.backward) == OOM
+        assert limited(sc.split) == OOM
+        assert limited(lambda: sc.backward(noalloc=True)) == OOM
+        sc.set_cameras(small)
+        rt.launches()
+        sc.check(sc.render())
+        sc.check(sc.backward())
+        sc.check(sc.backward(noalloc=True))
+        for name, _, items in rt.launches():
+            assert len(items) == 0 or _covered(items, [64]) == [64], name
+
+
+CHECKS = [host_memory_exhausted_is_a_status, compositing_parts_by_the_measured_rule, compositing_step_is_recorded_after_one_forward, noalloc_takes_what_it_took, variant_tables, split_statistic_uploads_what_its_kernel_reads, coarser_cuts_where_memory_is_short, failed_build_is_not_taken_for_built, lists_are_not_overwritten_under_a_kernel, noalloc_plan_follows_the_cameras, reduction_of_many_gaussians]
 
 
 @pytest.mark.parametrize("check", [c.__name__ for c in CHECKS])
