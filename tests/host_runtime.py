@@ -2,8 +2,10 @@
 copies and launches without a GPU.  For a process of its own, in which nothing else has loaded libfmb.so."""
 from __future__ import annotations
 
+import atexit
 import ctypes
 import os
+import shutil
 import subprocess
 import tempfile
 
@@ -18,7 +20,9 @@ COUNTS = ("allocations", "copies", "overwrites", "refused", "syncs")
 
 class Runtime:
     def __init__(self, root=ROOT):
-        out = os.path.join(tempfile.mkdtemp(prefix="fmb_rr_"), "rr.so")
+        tmp = tempfile.mkdtemp(prefix="fmb_rr_")
+        atexit.register(shutil.rmtree, tmp, True)
+        out = os.path.join(tmp, "rr.so")
         subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include",
                         "-I" + os.path.join(root, "paper_2308_14737_amd", "csrc"),
                         os.path.join(HERE, "c", "recording_runtime.cpp"), "-o", out], check=True)
