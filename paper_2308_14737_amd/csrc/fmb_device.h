@@ -421,7 +421,8 @@ __device__ __forceinline__ PairBounds tile_bounds(const Ent &g, const float4 &es
     const float hi = (sh * s < gl && s < 0.999f ? fmaf(sh, co, gs) : nb) * kUp;
     PairBounds r;
     r.d2_hi = fmaf(hm, lo * lo, g.l2l) + 1e-3f;
-    r.d2_lo = fmaf(hm, hi * hi, g.l2l) - 1e-3f;
+    // (a U that takes the centre ray to 0 gives |U c| = NaN, and no lower bound: the pair's density is NaN)
+    r.d2_lo = fmaf(hm, hi * hi, g.l2l) + fmaf(0.0f, na, -1e-3f);
     // |t| in [(gc - sh s) / (|U c| + F), (gc + sh s) / (|U c| - F)], of the centre ray's sign unless the
     // lower end is negative; the upper numerator is |U mu'| where some ray's theta can be 0
     const float nlo = fmaf(-sh, s, gl), rm = rcp_(na - f);

@@ -172,6 +172,22 @@ def test_bounds_hold(lib, kind):
     assert 0 < taken < total, (taken, total)  # (the cutoff decides both ways over these inputs)
 
 
+def test_no_lower_bound_where_no_density(lib):
+    """A zero precision factor has no peak on a ray (0 / 0): the kernels' density is NaN and the Gaussian is
+    passed over, so it may not promise a density to the cutoffs that are relative to one."""
+    g = np.random.Generator(np.random.PCG64(4))
+    e, o = _camera(g)
+    v, ok = _tiles(g, "pixels", e, 1)[0]
+    box = _box(lib, v, ok, e)
+    means, prec, weights = _gaussians(g, 4, o, v, False)
+    prec[:] = 0.0
+    out = np.zeros((4, 2, 4), np.float32)
+    c = ctypes.c_float
+    for b1, nc2 in ((0.0, 0.0), (21.4, -4.5)):
+        lib.db_bounds(4, _p(means), _p(prec), _p(weights), _p(o), _p(box), c(b1), c(nc2), _p(out))
+        assert not (out[:, :, 1] > -np.inf).any() and not (out[:, :, 3] > -np.inf).any(), out
+
+
 def test_unusable_camera_axes_bound_nothing(lib):
     """A rank-deficient camera matrix has no frame: nothing may be skipped by its boxes."""
     g = np.random.Generator(np.random.PCG64(3))

@@ -1,0 +1,52 @@
+"""Degenerate parameters among sound ones: what a kernel cannot evaluate neither spreads to the rays and
+gradients of the others nor is passed over in silence."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.gpu_util import custom_scene
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def fmb():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2308_14737_amd as m
+    return m
+
+
+def _t(a):
+    return torch.as_tensor(np.ascontiguousarray(a), device=DEV).contiguous()
+
+
+def _scene(fmb, sc, cams, model, **change):
+    p = {"means": sc.means, "prec": sc.prec, "weights": sc.weights, "betas": np.array([W.BETA1, W.BETA2], np.float32)}
+    p.update(change)
+    s = fmb.Scene(*(_t(p[k]) for k in ("means", "prec", "weights", "betas")), 1.0,
+                  fmb.Cameras.from_numpy(cams.w2c, cams.intr, cams.hw, device=DEV))
+    s.set_model(model)
+    return s
+
+
+@pytest.mark.parametrize("n", [40, 140])
+def test_zero_precision_is_passed_over(fmb, n):
+    """Compositing: a Gaussian with a zero precision factor has no peak (its density is 0 / 0) and takes no
+    part; the others render as without it.  Tolerance: its absence moves the last bits of the sums."""
+    sc, cams = custom_scene(n, [(24, 40)], seed=n, s_range=(0.02, 0.08))
+    k = n // 2
+    prec = sc.prec.copy()
+    prec[k] = 0.0
+    keep = np.arange(n) != k
+    out = _scene(fmb, sc, cams, "composite", prec=prec).render(normals=True)
+    ref = _scene(fmb, sc, cams, "composite", means=sc.means[keep], prec=sc.prec[keep], weights=sc.weights[keep]).render(normals=True)
+    torch.cuda.synchronize()
+    for q in ("depth", "alpha", "normal"):
+        a, b = out[q].double(), ref[q].double()
+        assert bool(torch.isfinite(a).all()), q
+        assert float((a - b).norm() / b.norm()) <= 1e-5, q
