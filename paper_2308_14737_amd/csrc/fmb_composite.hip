@@ -349,14 +349,15 @@ __device__ __forceinline__ CompBounds comp_bounds(const float4 *__restrict__ ent
     return cb;
 }
 
-// Those whose log2 density can reach thr, as 64-bit masks (a NaN bound keeps the Gaussian).
+// Those whose log2 density can exceed thr, as 64-bit masks (a NaN bound keeps the Gaussian; one of weight 0,
+// with a bound of -inf, is dropped also where a ray without any density makes thr -inf).
 __device__ __forceinline__ void comp_masks(const CompBounds &cb, int cnt, int lane, float thr, unsigned long long mask[2])
 {
 #pragma unroll
-    for (int c = 0; c < 2; ++c) mask[c] = wave_ballot(64 * c + lane < cnt && !(cb.hi[c] < thr));
+    for (int c = 0; c < 2; ++c) mask[c] = wave_ballot(64 * c + lane < cnt && !(cb.hi[c] <= thr));
 }
 
-// A scene of more than kCompTG Gaussians: those whose log2 density can reach the cutoff on a ray of the
+// A scene of more than kCompTG Gaussians: those whose log2 density can exceed the cutoff on a ray of the
 // tile, staged in scene order with their scene-local indices in gid.  The cutoff is `thr`, or with REL
 // (the forward) that or less, `rel` + min(0, the largest lower bound of the tile's log2 densities), bounded
 // by the Gaussians seen so far (a superset of the final cutoff's, whose bound is returned in `low`).  The bounds are
@@ -379,7 +380,7 @@ __device__ __forceinline__ int comp_survivors(const Params &P, const SceneRec &s
         make_bound_entry(P.means + 3 * gi, P.prec + 6 * gi, P.weights[gi], o, g, est);
         const PairBounds pb = tile_bounds(g, est, tb, (float)(-0.5 * kLog2e), 0.0f, 0.0f);
         if (REL) low = fmaxf(low, wave_max_u(in ? pb.d2_lo : -INFINITY));
-        const bool keep = in && !(pb.d2_hi < (REL ? fminf(thr, fminf(low, 0.0f) + rel) : thr));
+        const bool keep = in && !(pb.d2_hi <= (REL ? fminf(thr, fminf(low, 0.0f) + rel) : thr));
         const unsigned long long bal = wave_ballot(keep);
         const int at = ne + __popcll(bal & ((1ull << lane) - 1ull));
         if (keep && at < kCompTG) gid[at] = gl;

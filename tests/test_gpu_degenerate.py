@@ -50,3 +50,17 @@ def test_zero_precision_is_passed_over(fmb, n):
         a, b = out[q].double(), ref[q].double()
         assert bool(torch.isfinite(a).all()), q
         assert float((a - b).norm() / b.norm()) <= 1e-5, q
+
+
+@pytest.mark.parametrize("n", [5, 140])
+def test_zero_weights_have_zero_gradients(fmb, n):
+    """Compositing with every weight 0: nothing is rendered, and the gradients of means and precision are 0."""
+    sc, cams = custom_scene(n, [(24, 40)], seed=n, s_range=(0.02, 0.2))
+    s = _scene(fmb, sc, cams, "composite", weights=np.zeros(n, np.float32))
+    out = s.render(normals=True)
+    p = out["depth"].numel()
+    ones = torch.full((p,), 1.0 / p, device=DEV)
+    for normal in (None, torch.full((p, 3), 1.0 / p, device=DEV)):
+        g = s.backward(out, ones, ones, normal)
+        torch.cuda.synchronize()
+        assert float(g["means"].abs().max()) == 0.0 and float(g["prec"].abs().max()) == 0.0, normal is not None
