@@ -847,7 +847,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((F & kNrm
                     const float4 x2 = rays[RW * (64 * t + lane) + 2];
                     const float delta = exp2_(q.d2), dd = x2.z * delta;
                     const float zr = q.z2 - x0.w;
-                    if (wave_any(zr >= kSkipLog2)) {
+                    if (wave_any(!(zr < kSkipLog2))) {  // (a NaN weight shows in the sums)
                         const float4 x3 = rays[RW * (64 * t + lane) + 3];
                         const float wt = exp2_(zr) * x1.x;  // normalised blend weight
                         const float tfb = x1.y;

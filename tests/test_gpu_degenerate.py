@@ -64,3 +64,17 @@ def test_zero_weights_have_zero_gradients(fmb, n):
         g = s.backward(out, ones, ones, normal)
         torch.cuda.synchronize()
         assert float(g["means"].abs().max()) == 0.0 and float(g["prec"].abs().max()) == 0.0, normal is not None
+
+
+@pytest.mark.parametrize("n", [5, 300])
+def test_nan_blend_parameter_shows_in_the_gradients(fmb, n):
+    """A NaN beta makes every output NaN; the gradients with a normal cotangent are NaN too, not 0."""
+    sc, cams = custom_scene(n, [(24, 40)], seed=n, s_range=(0.02, 0.2))
+    s = _scene(fmb, sc, cams, "blend", betas=np.array([np.nan, W.BETA2], np.float32))
+    out = s.render(normals=True)
+    p = out["depth"].numel()
+    g = s.backward(out, torch.full((p,), 1.0 / p, device=DEV), None, torch.full((p, 3), 1.0 / p, device=DEV))
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(out["depth"]).all())
+    for q in ("means", "prec", "betas"):
+        assert bool(torch.isnan(g[q]).all()), q
