@@ -181,13 +181,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
                 const float mm = wave_min_u(loc[j] >= 0 ? M[j] : INFINITY);
                 if (jl == j) mlow = fmaxf(mlow, mm);
             }
-        } else if (b1_pos) {
-            // the running maximum starts at its lower bound (a pair that reaches it is staged here),
-            // so that lesser weights are skipped from the start
-#pragma unroll
-            for (int j = 0; j < RPT; ++j)
-                M[j] = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(mlow), j)), 1e30f);
         }
+        // (The running maximum itself starts at -inf, not at that bound: sums scaled to a bound round
+        // otherwise than sums scaled to weights, and the sign of an L1 loss follows the last bit of a depth.
+        // Starting at the bound saved 0.4 % of a step, of 16 scenes 1.6 %.)
         const float zcut = mlow + kSkipLog2;
         for (int ib = 0; ib < cnt; ib += GP) {
             const int il = ib + lane / RPT;
