@@ -190,7 +190,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(TG > 128 
             const int il = ib + lane / RPT;
             bool need = false;
             if (il < cnt && bj.c.w >= 0.0f) {
-                need = !(b1_pos && hisave[wave][ib * RPT + lane] < zcut);
+                // (a weight of 0, with a bound of -inf, is passed over also where zcut is -inf)
+                const float h = hisave[wave][ib * RPT + lane];
+                need = !(b1_pos && (h < zcut || h == -INFINITY));
             }
             unsigned long long nm = wave_ballot(need);
           while (nm != 0ull) {

@@ -78,3 +78,18 @@ def test_nan_blend_parameter_shows_in_the_gradients(fmb, n):
     assert bool(torch.isnan(out["depth"]).all())
     for q in ("means", "prec", "betas"):
         assert bool(torch.isnan(g[q]).all()), q
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_zero_weight_where_no_weight_is_bounded(fmb, seed):
+    """Blend: one 8 x 8 view that is a wide tile of thin discs, on which no Gaussian's weight has a lower bound; the
+    first Gaussian's weight is 0 and takes no part.  Tolerance: the others' sums are the same."""
+    sc, cams = custom_scene(3, [(8, 8)], seed=seed, s_range=(0.001, 0.5))
+    cams.intr[0] = [3.0, 3.0, 4.0, 4.0]
+    weights = sc.weights.copy()
+    weights[0] = 0.0
+    out = _scene(fmb, sc, cams, "blend", weights=weights).render(normals=True)
+    ref = _scene(fmb, sc, cams, "blend", means=sc.means[1:], prec=sc.prec[1:], weights=sc.weights[1:]).render(normals=True)
+    torch.cuda.synchronize()
+    for q in ("depth", "alpha", "normal"):
+        assert torch.equal(out[q], ref[q]), q
