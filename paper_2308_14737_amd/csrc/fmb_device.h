@@ -3,6 +3,7 @@
 // (ray, Gaussian) pair, the per-ray adjoint prologue and the per-pair adjoint that maps
 // (dL/dt_i, dL/dd_i, dL/dn_i) to the Gaussian's parameters.
 #pragma once
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>

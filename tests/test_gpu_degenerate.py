@@ -93,3 +93,18 @@ def test_zero_weight_where_no_weight_is_bounded(fmb, seed):
     torch.cuda.synchronize()
     for q in ("depth", "alpha", "normal"):
         assert torch.equal(out[q], ref[q]), q
+
+
+@pytest.mark.parametrize("n", [5, 40, 300])
+def test_mean_out_of_range_is_passed_over(fmb, n):
+    """Blend: a mean so far that its distance overflows has a density and weight of 0 on every ray and takes no
+    part.  Tolerance: the others' sums are the same; only densities below 2^-48 may be left out elsewhere."""
+    sc, cams = custom_scene(n, [(24, 40)], seed=n, s_range=(0.05, 0.2) if n < 100 else (0.02, 0.08))
+    means = sc.means.copy()
+    means[n // 2] = 1e30
+    keep = np.arange(n) != n // 2
+    out = _scene(fmb, sc, cams, "blend", means=means).render(normals=True)
+    ref = _scene(fmb, sc, cams, "blend", means=sc.means[keep], prec=sc.prec[keep], weights=sc.weights[keep]).render(normals=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out["depth"], ref["depth"]) and torch.equal(out["normal"], ref["normal"])
+    assert float((out["alpha"] - ref["alpha"]).abs().max()) <= n * 2.0 ** -48
