@@ -344,13 +344,13 @@ struct Job {
         prm.views = d_views.as<ViewRec>();
         prm.eta = d_eta.as<float>();
         // Untuned default of the forward: more rays per item amortise its staging and bounds, fewer fill
-        // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 59 / 67 / 81,
-        // 330 000 rays 59.2 / 62.6 / 66.7, 1.1e6 115 / 117 / 118, 2.4e6 212 / 213 / 220, 4.2e6 238 / 233 / 232,
-        // 12.6e6 in 16 scenes 830 / 812 / 789.
+        // the GPU.  A step (us) with 256 / 512 / 1024 rays per item: 85 000 rays in 5 scenes 60 / 67 / 81,
+        // 330 000 rays 60.1 / 63.2 / 68.0, 1.1e6 117 / 119 / 119, 2.4e6 215 / 218 / 225, 4.2e6 239 / 236 / 233,
+        // 12.6e6 in 16 scenes 845 / 828 / 802.
         // Of clustered scenes beyond a block's count of Gaussians a few blocks take most of the pairs, and
         // shorter ones leave less of a tail, at the price of a pre-cull each: 0.5e6 rays of 4000 Gaussians
-        // 251 / 279 / 379, 1.2e6 of 10 000 1160 / 1195 / 1336, 1.4e6 of 500 191 / 180 / 182, 2.1e6 of 10 000
-        // 1268 / 1148 / 1201, 2.1e6 of 1000 283 / 257 / 253.
+        // 253 / 282 / 373, 1.2e6 of 10 000 1162 / 1169 / 1336, 1.4e6 of 500 192 / 181 / 182, 2.1e6 of 10 000
+        // 1270 / 1154 / 1188, 2.1e6 of 1000 285 / 260 / 255.
         if (!launch_fixed) {
             const int64_t r = 256LL * n_cu;
             const int64_t one = max_scene_n() > block_size() ? 24 : 6;

@@ -383,8 +383,8 @@ __device__ __forceinline__ TileBox wave_box_of(const float4 *boxes, int n, int l
 // on 31 %; the bound sqrt(m_c) - |U|_2 |U mu'| |U^-1|_2 rho over the tile's cone kept 40 %, and a
 // one-FMA bound per pair after it found little more to skip.  With both sides bounded the forward also
 // knows the least running maximum of a tile before its first pair.  A training step
-// of 16 scenes (12.6e6 rays, 10 to 100 Gaussians) with the cone's bound and two sweeps took 922 us, and
-// takes 792; one of 640 x 480 video frames 382 and 350.  The slack terms cover the FP32 rounding of the bound and of the
+// of 16 scenes (12.6e6 rays, 10 to 100 Gaussians) with the cone's bound and two sweeps took 924 us, and
+// takes 806; one of 640 x 480 video frames 377 and 345.  The slack terms cover the FP32 rounding of the bound and of the
 // pair's own evaluation.
 struct PairBounds {
     float d2_hi, d2_lo, z_hi, z_lo;
